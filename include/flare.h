@@ -217,6 +217,17 @@ int flare_backward(const flare_shape *shape, const void *q_lat, const void *k, c
                    void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * flare_backward with dq_lat in the storage type: every sum is rounded once from fp32 where it is formed, which is
+ * what an optimiser that keeps 16-bit gradients beside 16-bit latents wants (and saves it a conversion kernel).
+ *   dq_lat [H][M][d] dtype (summed over the batch)                                                      (out)
+ * Everything else as for flare_backward.
+ */
+int flare_backward_cast(const flare_shape *shape, const void *q_lat, const void *k, const void *v,
+                        const void *y, const float *lse_dec, const void *dy, const float *z,
+                        const float *lse_enc, void *dq_lat, void *dk, void *dv, float scale,
+                        void *workspace, size_t workspace_bytes, void *stream);
+
+/*
  * Eigenpairs of the mixing matrix W = W_decode W_encode (N x N, rank <= M) of every (b,h) without
  * forming it (Appendix C.1 "Eigenanalysis procedure", Algorithm 1): with A = exp(S),
  * L_M = 1 / row sums, L_N = 1 / column sums and J = L_M^(1/2) A L_N^(1/2), the nonzero eigenvalues

@@ -1,8 +1,9 @@
 """Thin Python binding of libflare.so (see include/flare.h).
 
 Argument marshalling only: every step of the operator runs in the library's HIP kernels.
-torch is used for device memory and for the current stream, nothing else.  There is no
-fallback: if the library is missing or a call fails, an exception is raised.
+torch is used for device memory and for the current stream, nothing else.  The calls of the hot path are
+marshalled in native code (csrc/torch_binding.cpp, built as _native.so), the others here with ctypes.
+There is no fallback: if a library is missing or a call fails, an exception is raised.
 """
 import ctypes
 import os
@@ -21,7 +22,8 @@ VARIANT_SEPARATE_DQ = 2
 
 EXPORTS = [
     "flare_version", "flare_strerror", "flare_workspace_bytes", "flare_encode", "flare_decode",
-    "flare_forward", "flare_forward_static", "flare_decode_project", "flare_forward_project", "flare_backward", "flare_profile_enable", "flare_profile_kernels",
+    "flare_forward", "flare_forward_static", "flare_decode_project", "flare_forward_project", "flare_backward",
+    "flare_backward_cast", "flare_profile_enable", "flare_profile_kernels",
     "flare_profile_name", "flare_profile_read", "flare_spectral_workspace_bytes", "flare_spectral",
 ]
 
@@ -65,6 +67,7 @@ def load():
     lib.flare_forward_project.restype = ctypes.c_int
     lib.flare_backward.argtypes = [sp, vp, vp, vp, vp, fp, vp, fp, fp, fp, vp, vp, ctypes.c_float, vp,
                                    ctypes.c_size_t, vp]
+    lib.flare_backward_cast.argtypes = lib.flare_backward.argtypes
     lib.flare_spectral_workspace_bytes.argtypes = [sp, ctypes.POINTER(ctypes.c_size_t)]
     lib.flare_spectral.argtypes = [sp, vp, vp, fp, fp, ctypes.c_float, ctypes.c_int, fp, fp, fp, vp, ctypes.c_size_t, vp]
     lib.flare_profile_enable.argtypes = [ctypes.c_int]
@@ -72,7 +75,7 @@ def load():
     lib.flare_profile_name.argtypes = [ctypes.c_int]
     lib.flare_profile_read.argtypes = [ctypes.c_int, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int)]
     for name in ("flare_spectral_workspace_bytes", "flare_spectral", "flare_workspace_bytes", "flare_encode", "flare_decode", "flare_forward", "flare_backward",
-                 "flare_profile_enable", "flare_profile_kernels", "flare_profile_read"):
+                 "flare_backward_cast", "flare_profile_enable", "flare_profile_kernels", "flare_profile_read"):
         getattr(lib, name).restype = ctypes.c_int
     _lib = lib
     return lib
@@ -124,12 +127,6 @@ def _shape_of(q, k, layout="bhnd", y_f32=False):
     return FlareShape(B, H, N, M, d, _dtype_code(k), LAYOUTS[layout], 1 if shared else 0, 1 if y_f32 else 0)
 
 
-def _wants_f32_y(y, k, y_f32):
-    """flare_shape.y_f32: asked for, or implied by an fp32 y next to 16-bit token tensors."""
-    torch = _torch()
-    return bool(y_f32) or (y is not None and y.dtype == torch.float32 and k.dtype != torch.float32)
-
-
 def _dev(t, name, dtype=None, shape=None):
     if not t.is_cuda or not t.is_contiguous():
         raise FlareError("%s must be a contiguous device tensor" % name)
@@ -158,62 +155,40 @@ def _shape_workspace_bytes(shp):
     return int(f.value), int(b.value)
 
 
-def _workspace(shp, which, workspace, device, stream=None):
-    torch = _torch()
-    f, b = _shape_workspace_bytes(shp)
-    need = f if which == "fwd" else b
-    if workspace is None:
-        # A temporary block: the kernels are only enqueued when the call returns, so the caching allocator must
-        # learn on which stream they run, or it could hand the block to other work on the allocating stream
-        # while kernels on `stream` still use it.
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
-        if stream is not None and stream != torch.cuda.current_stream():
-            workspace.record_stream(stream)
-    if workspace.dtype != torch.uint8:
-        raise FlareError("workspace must be a uint8 tensor")
-    return workspace, ctypes.c_void_p(workspace.data_ptr()), ctypes.c_size_t(workspace.numel())
+_ext = None
+
+
+def _native():
+    """The native half of this binding (_native.so, built by paper_2508_12594_amd.build beside libflare.so)."""
+    global _ext
+    if _ext is None:
+        load()
+        try:
+            from . import _native as ext
+        except ImportError as e:
+            raise FlareError("_native.so not found or not loadable (%s): run `python -m paper_2508_12594_amd.build`" % e)
+        ext.set_error_class(FlareError)
+        ext.load_library(LIB_PATH)
+        _ext = ext
+    return _ext
+
+
+def _layout(layout):
+    try:
+        return LAYOUTS[layout]
+    except KeyError:
+        raise FlareError("layout must be 'bhnd' or 'bnhd'") from None
 
 
 def encode(q_lat, k, v, scale, z=None, lse_enc=None, workspace=None, stream=None, layout="bhnd"):
     """flare_encode: returns (z[B,H,M,d] fp32, lse_enc[B,H,M] fp32)."""
-    torch = _torch()
-    shp = _shape_of(q_lat, k, layout)
-    if z is None:
-        z = torch.empty((shp.B, shp.H, shp.M, shp.d), dtype=torch.float32, device=k.device)
-    if lse_enc is None:
-        lse_enc = torch.empty((shp.B, shp.H, shp.M), dtype=torch.float32, device=k.device)
-    ws, ws_p, ws_n = _workspace(shp, "fwd", workspace, k.device, stream)
-    _check(load().flare_encode(ctypes.byref(shp), _dev(q_lat, "q_lat"), _dev(k, "k"),
-                               _dev(v, "v", k.dtype, k.shape),
-                               _dev(z, "z", torch.float32, (shp.B, shp.H, shp.M, shp.d)),
-                               _dev(lse_enc, "lse_enc", torch.float32, (shp.B, shp.H, shp.M)),
-                               ctypes.c_float(scale), ws_p, ws_n, _stream(stream)), "flare_encode")
-    return z, lse_enc
-
-
-def _opt_lse_dec(lse_dec, shp):
-    torch = _torch()
-    if lse_dec is None:
-        return None
-    return _dev(lse_dec, "lse_dec", torch.float32, (shp.B, shp.H, shp.N))
+    return (_ext or _native()).encode(q_lat, k, v, scale, z, lse_enc, workspace, stream, _layout(layout))
 
 
 def decode(q_lat, k, z, scale, y=None, lse_dec=None, workspace=None, stream=None, layout="bhnd", y_f32=False):
     """flare_decode: returns y (k's shape; k's dtype, or fp32 with y_f32 / when an fp32 y is passed);
     fills lse_dec[B,H,N] (fp32) when given."""
-    torch = _torch()
-    f32y = _wants_f32_y(y, k, y_f32)
-    shp = _shape_of(q_lat, k, layout, f32y)
-    ydt = torch.float32 if f32y else k.dtype
-    if y is None:
-        y = torch.empty(k.shape, dtype=ydt, device=k.device)
-    ws, ws_p, ws_n = _workspace(shp, "fwd", workspace, k.device, stream)
-    _check(load().flare_decode(ctypes.byref(shp), _dev(q_lat, "q_lat"), _dev(k, "k"),
-                               _dev(z, "z", torch.float32, (shp.B, shp.H, shp.M, shp.d)),
-                               _dev(y, "y", ydt, k.shape), _opt_lse_dec(lse_dec, shp),
-                               ctypes.c_float(scale), ws_p, ws_n, _stream(stream)),
-           "flare_decode")
-    return y
+    return (_ext or _native()).decode(q_lat, k, z, scale, y, lse_dec, workspace, stream, _layout(layout), bool(y_f32))
 
 
 def forward(q_lat, k, v, scale, y=None, z=None, lse_enc=None, lse_dec=None, workspace=None, stream=None,
@@ -222,24 +197,8 @@ def forward(q_lat, k, v, scale, y=None, z=None, lse_enc=None, lse_dec=None, work
 
     layout 'bhnd': k, v, y are [B,H,N,d]; 'bnhd': they are [B,N,H,d].  y_f32 (or an fp32 y next to 16-bit
     inputs): y is written in fp32, for a backward that takes delta from it (flare_shape.y_f32)."""
-    torch = _torch()
-    f32y = _wants_f32_y(y, k, y_f32)
-    shp = _shape_of(q_lat, k, layout, f32y)
-    ydt = torch.float32 if f32y else k.dtype
-    if y is None:
-        y = torch.empty(k.shape, dtype=ydt, device=k.device)
-    if z is None:
-        z = torch.empty((shp.B, shp.H, shp.M, shp.d), dtype=torch.float32, device=k.device)
-    if lse_enc is None:
-        lse_enc = torch.empty((shp.B, shp.H, shp.M), dtype=torch.float32, device=k.device)
-    ws, ws_p, ws_n = _workspace(shp, "fwd", workspace, k.device, stream)
-    _check(load().flare_forward(ctypes.byref(shp), _dev(q_lat, "q_lat"), _dev(k, "k"),
-                                _dev(v, "v", k.dtype, k.shape), _dev(y, "y", ydt, k.shape),
-                                _dev(z, "z", torch.float32, (shp.B, shp.H, shp.M, shp.d)),
-                                _dev(lse_enc, "lse_enc", torch.float32, (shp.B, shp.H, shp.M)),
-                                _opt_lse_dec(lse_dec, shp),
-                                ctypes.c_float(scale), ws_p, ws_n, _stream(stream)), "flare_forward")
-    return y, z, lse_enc
+    return (_ext or _native()).forward(q_lat, k, v, scale, y, z, lse_enc, lse_dec, workspace, stream, _layout(layout),
+                                       bool(y_f32))
 
 
 def forward_project(q_lat, k, v, w_out, scale, bias=None, out=None, y=None, z=None, lse_enc=None, lse_dec=None,
@@ -247,28 +206,8 @@ def forward_project(q_lat, k, v, w_out, scale, bias=None, out=None, y=None, z=No
     """flare_forward_project: the forward with the output projection fused into the decode.  Token tensors are
     [B,N,H,d] (layout 'bnhd'), w_out [C,C] in their dtype, bias [C] fp32 or None.  Returns (out[B,N,C], z, lse_enc);
     y (the mixer's own output, for a backward) is written only when given or when keep_y is set."""
-    torch = _torch()
-    shp = _shape_of(q_lat, k, "bnhd", False)
-    C = shp.H * shp.d
-    if out is None:
-        out = torch.empty((shp.B, shp.N, C), dtype=k.dtype, device=k.device)
-    if y is None and keep_y:
-        y = torch.empty_like(k)
-    if z is None:
-        z = torch.empty((shp.B, shp.H, shp.M, shp.d), dtype=torch.float32, device=k.device)
-    if lse_enc is None:
-        lse_enc = torch.empty((shp.B, shp.H, shp.M), dtype=torch.float32, device=k.device)
-    ws, ws_p, ws_n = _workspace(shp, "fwd", workspace, k.device, stream)
-    _check(load().flare_forward_project(ctypes.byref(shp), _dev(q_lat, "q_lat"), _dev(k, "k"),
-                                        _dev(v, "v", k.dtype, k.shape), _dev(w_out, "w_out", k.dtype, (C, C)),
-                                        None if bias is None else _dev(bias, "bias", torch.float32, (C,)),
-                                        _dev(out, "out", k.dtype, (shp.B, shp.N, C)),
-                                        None if y is None else _dev(y, "y", k.dtype, k.shape),
-                                        _dev(z, "z", torch.float32, (shp.B, shp.H, shp.M, shp.d)),
-                                        _dev(lse_enc, "lse_enc", torch.float32, (shp.B, shp.H, shp.M)),
-                                        _opt_lse_dec(lse_dec, shp), ctypes.c_float(scale), ws_p, ws_n,
-                                        _stream(stream)), "flare_forward_project")
-    return out, z, lse_enc
+    return (_ext or _native()).forward_project(q_lat, k, v, w_out, scale, bias, out, y, z, lse_enc, lse_dec, workspace,
+                                               stream, bool(keep_y))
 
 
 STATIC_SCRATCH_BYTES = 32 << 20   # FLARE_STATIC_SCRATCH_BYTES of include/flare.h
@@ -276,16 +215,7 @@ STATIC_SCRATCH_BYTES = 32 << 20   # FLARE_STATIC_SCRATCH_BYTES of include/flare.
 
 def forward_static(q_lat, k, v, scale, y, z, lse_enc, lse_dec=None, stream=None, layout="bhnd"):
     """flare_forward_static: the forward with the library's own static scratch; every output is the caller's."""
-    torch = _torch()
-    f32y = _wants_f32_y(y, k, False)
-    shp = _shape_of(q_lat, k, layout, f32y)
-    ydt = torch.float32 if f32y else k.dtype
-    _check(load().flare_forward_static(ctypes.byref(shp), _dev(q_lat, "q_lat"), _dev(k, "k"),
-                                       _dev(v, "v", k.dtype, k.shape), _dev(y, "y", ydt, k.shape),
-                                       _dev(z, "z", torch.float32, (shp.B, shp.H, shp.M, shp.d)),
-                                       _dev(lse_enc, "lse_enc", torch.float32, (shp.B, shp.H, shp.M)),
-                                       _opt_lse_dec(lse_dec, shp), ctypes.c_float(scale), _stream(stream)),
-           "flare_forward_static")
+    (_ext or _native()).forward_static(q_lat, k, v, scale, y, z, lse_enc, lse_dec, stream, _layout(layout))
     return y, z, lse_enc
 
 
@@ -294,28 +224,9 @@ def backward(q_lat, k, v, dy, z, lse_enc, scale, y=None, lse_dec=None, dq_lat=No
     """flare_backward: returns (dq_lat[H,M,d] fp32, dk, dv in k's dtype).
 
     Pass the forward's y and lse_dec to reuse them; without both, they are recomputed from z.  An fp32 y next
-    to 16-bit inputs is the forward's y_f32 output."""
-    torch = _torch()
-    f32y = _wants_f32_y(y, k, False)
-    shp = _shape_of(q_lat, k, layout, f32y)
-    shp.variant = int(variant)     # flare_variant bits: force a kernel variant (tests, measurements)
-    if dq_lat is None:
-        dq_lat = torch.empty(tuple(q_lat.shape), dtype=torch.float32, device=k.device)
-    if dk is None:
-        dk = torch.empty_like(k)
-    if dv is None:
-        dv = torch.empty_like(k)
-    ws, ws_p, ws_n = _workspace(shp, "bwd", workspace, k.device, stream)
-    _check(load().flare_backward(ctypes.byref(shp), _dev(q_lat, "q_lat"), _dev(k, "k"),
-                                 _dev(v, "v", k.dtype, k.shape),
-                                 None if y is None else _dev(y, "y", torch.float32 if f32y else k.dtype, k.shape),
-                                 _opt_lse_dec(lse_dec, shp), _dev(dy, "dy", k.dtype, k.shape),
-                                 _dev(z, "z", torch.float32, (shp.B, shp.H, shp.M, shp.d)),
-                                 _dev(lse_enc, "lse_enc", torch.float32, (shp.B, shp.H, shp.M)),
-                                 _dev(dq_lat, "dq_lat", torch.float32, tuple(q_lat.shape)),
-                                 _dev(dk, "dk", k.dtype, k.shape), _dev(dv, "dv", k.dtype, k.shape),
-                                 ctypes.c_float(scale), ws_p, ws_n, _stream(stream)), "flare_backward")
-    return dq_lat, dk, dv
+    to 16-bit inputs is the forward's y_f32 output.  variant: flare_variant bits (tests, measurements)."""
+    return (_ext or _native()).backward(q_lat, k, v, dy, z, lse_enc, scale, y, lse_dec, dq_lat, dk, dv, workspace,
+                                        stream, _layout(layout), int(variant))
 
 
 def spectral(q_lat, k, lse_enc, lse_dec, scale, first=0, want_gram=False, stream=None, layout="bhnd"):

@@ -1,4 +1,5 @@
-"""Compile libflare.so and libflare_rates.so (HIP, gfx950 only) in-tree with hipcc.
+"""Compile libflare.so and libflare_rates.so (HIP, gfx950 only) in-tree with hipcc, and _native.so (the native half
+of the torch binding) with g++.
 
     python -m paper_2508_12594_amd.build
 
@@ -10,12 +11,14 @@ operator does not link.
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libflare.so")
 RATES_LIB = os.path.join(HERE, "libflare_rates.so")
+NATIVE = os.path.join(HERE, "_native.so")
 RATES_SOURCES = {"machine_rates.hip": []}
 # source -> extra flags.  The matrix-core files never produce NaNs (masked scores are -inf and
 # are only ever compared, exponentiated or shifted by finite values), so they are compiled with
@@ -33,9 +36,30 @@ FLAGS = [
 
 
 def build_library(verbose=True, extra_flags=()):
-    """Both libraries; returns the path of libflare.so."""
+    """Both libraries and the torch binding; returns the path of libflare.so."""
+    native = _start_native(verbose)
     _build(RATES_LIB, RATES_SOURCES, verbose, extra_flags)
-    return _build(LIB, SOURCES, verbose, extra_flags)
+    lib = _build(LIB, SOURCES, verbose, extra_flags)
+    cmd, proc, tmp = native
+    if proc.wait() != 0:
+        raise subprocess.CalledProcessError(proc.returncode, cmd)
+    os.replace(tmp, NATIVE)
+    return lib
+
+
+def _start_native(verbose):
+    """The torch binding holds no GPU code: plain C++ against torch's headers (libflare.so is opened at run time)."""
+    import torch
+    home = os.path.dirname(torch.__file__)
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-I", os.path.join(home, "include"), "-I", os.path.join(home, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+           "-o", tmp, os.path.join(CSRC, "torch_binding.cpp"), "-L", os.path.join(home, "lib"), "-lc10", "-lc10_hip",
+           "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    return cmd, subprocess.Popen(cmd), tmp
 
 
 def _build(lib, sources, verbose, extra_flags):

@@ -103,7 +103,7 @@ using namespace flare;
 
 extern "C" {
 
-int flare_version(void) { return 400; }   // 0.4.0: flare_shape grew by variant; flare_forward_static
+int flare_version(void) { return 500; }   // 0.5.0: flare_backward_cast
 
 const char *flare_strerror(int status)
 {
@@ -223,10 +223,10 @@ int flare_forward_project(const flare_shape *shape, const void *q_lat, const voi
     return flare_decode_project(shape, q_lat, k, z, w_out, bias, out, y, lse_dec, scale, stream);
 }
 
-int flare_backward(const flare_shape *shape, const void *q_lat, const void *k, const void *v,
-                   const void *y, const float *lse_dec, const void *dy, const float *z,
-                   const float *lse_enc, float *dq_lat, void *dk, void *dv, float scale, void *workspace,
-                   size_t workspace_bytes, void *stream)
+static int backward(const flare_shape *shape, const void *q_lat, const void *k, const void *v, const void *y,
+                    const float *lse_dec, const void *dy, const float *z, const float *lse_enc, void *dq_lat,
+                    bool dq_cast, void *dk, void *dv, float scale, void *workspace, size_t workspace_bytes,
+                    void *stream)
 {
     int rc = check_shape(shape);
     if (rc != FLARE_OK) return rc;
@@ -238,8 +238,26 @@ int flare_backward(const flare_shape *shape, const void *q_lat, const void *k, c
     size_t need = 0;
     flare_workspace_bytes(shape, nullptr, &need);
     if (!workspace || workspace_bytes < need) return FLARE_EWORKSPACE;
-    return valu_backward(*shape, q_lat, k, v, y, lse_dec, dy, z, lse_enc, dq_lat, dk, dv, scale, workspace,
+    return valu_backward(*shape, q_lat, k, v, y, lse_dec, dy, z, lse_enc, dq_lat, dq_cast, dk, dv, scale, workspace,
                          static_cast<hipStream_t>(stream));
+}
+
+int flare_backward(const flare_shape *shape, const void *q_lat, const void *k, const void *v,
+                   const void *y, const float *lse_dec, const void *dy, const float *z,
+                   const float *lse_enc, float *dq_lat, void *dk, void *dv, float scale, void *workspace,
+                   size_t workspace_bytes, void *stream)
+{
+    return backward(shape, q_lat, k, v, y, lse_dec, dy, z, lse_enc, dq_lat, false, dk, dv, scale, workspace,
+                    workspace_bytes, stream);
+}
+
+int flare_backward_cast(const flare_shape *shape, const void *q_lat, const void *k, const void *v,
+                        const void *y, const float *lse_dec, const void *dy, const float *z,
+                        const float *lse_enc, void *dq_lat, void *dk, void *dv, float scale, void *workspace,
+                        size_t workspace_bytes, void *stream)
+{
+    return backward(shape, q_lat, k, v, y, lse_dec, dy, z, lse_enc, dq_lat, true, dk, dv, scale, workspace,
+                    workspace_bytes, stream);
 }
 
 int flare_spectral_workspace_bytes(const flare_shape *shape, size_t *bytes)

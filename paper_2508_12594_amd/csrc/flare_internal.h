@@ -96,10 +96,10 @@ int valu_encode(const flare_shape &s, const void *q, const void *k, const void *
 int valu_decode(const flare_shape &s, const void *q, const void *k, const float *z, void *y,
                 float *lse_dec, float scale, hipStream_t stream);
 // The whole backward; uses the matrix-core kernels where the shape allows.  y and lse_dec may be
-// NULL (then the token statistics are recomputed).
+// NULL (then the token statistics are recomputed).  dq is fp32, or of the storage type with dq_cast.
 int valu_backward(const flare_shape &s, const void *q, const void *k, const void *v, const void *y,
-                  const float *lse_dec, const void *dy, const float *z, const float *lse_enc, float *dq,
-                  void *dk, void *dv, float scale, void *ws, hipStream_t stream);
+                  const float *lse_dec, const void *dy, const float *z, const float *lse_enc, void *dq,
+                  bool dq_cast, void *dk, void *dv, float scale, void *ws, hipStream_t stream);
 
 // ---- bf16 matrix-core path (d in {16,32}; M = 32 or a multiple of 64 up to 256) --------------
 struct MfmaPlan {

@@ -15,6 +15,8 @@
 // per-token forms.  The backward follows the formulas in include/flare.h.
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "flare_internal.h"
 
 namespace flare {
@@ -105,6 +107,23 @@ __device__ __forceinline__ void store_row(bf16_t *__restrict__ p, const float (&
 #pragma unroll
         for (int i = 0; i < D / 8; ++i) p4[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
     }
+}
+// two neighbouring elements of a row
+__device__ __forceinline__ void store_pair(float *p, float a, float b)
+{
+    *reinterpret_cast<float2 *>(p) = make_float2(a, b);
+}
+__device__ __forceinline__ void store_pair(bf16_t *p, float a, float b)
+{
+    *reinterpret_cast<uint32_t *>(p) = f32_to_bf16_rne(a) | (f32_to_bf16_rne(b) << 16);
+}
+__device__ __forceinline__ void store_pair(f16_t *p, float a, float b)
+{
+    typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+    half2_t t;
+    t[0] = (_Float16)a;
+    t[1] = (_Float16)b;
+    *reinterpret_cast<half2_t *>(p) = t;
 }
 template <int D>
 __device__ __forceinline__ float dot(const float (&a)[D], const float (&b)[D])
@@ -650,9 +669,10 @@ __global__ __launch_bounds__(256) void dz_merge_few_kernel(
     if (j == 0) eps[idx] = e;
 }
 
-template <int D>
+// dq_lat in fp32, or (T: the storage type) rounded once as it is stored.
+template <typename T, int D>
 __global__ __launch_bounds__(256) void dq_reduce_few_kernel(
-    const float *__restrict__ dq_part, float *__restrict__ dq, int B, int H, int M, int parts, float scale)
+    const float *__restrict__ dq_part, T *__restrict__ dq, int B, int H, int M, int parts, float scale)
 {
     constexpr int L = D / 2, ROWS = 256 / L;
     const int j = threadIdx.x % L;
@@ -660,7 +680,7 @@ __global__ __launch_bounds__(256) void dq_reduce_few_kernel(
     const int h = blockIdx.y;
     if (m >= M) return;
     const float2 a = sum_slots_few<D>(dq_part, h, H, B, parts, M, m, j);
-    *reinterpret_cast<float2 *>(dq + ((size_t)h * M + m) * D + 2 * j) = make_float2(a.x * scale, a.y * scale);
+    store_pair(dq + ((size_t)h * M + m) * D + 2 * j, a.x * scale, a.y * scale);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -717,9 +737,9 @@ __global__ __launch_bounds__(kLatentBlock) void dq_partial_kernel(
 }
 
 // dq_lat[h][m] = scale * sum over batch items and partial slots (fixed order, see sum_slots).
-template <int D>
+template <typename T, int D>
 __global__ __launch_bounds__(256) void dq_reduce_kernel(
-    const float *__restrict__ dq_part, float *__restrict__ dq, int B, int H, int M, int parts, float scale)
+    const float *__restrict__ dq_part, T *__restrict__ dq, int B, int H, int M, int parts, float scale)
 {
     const int j = threadIdx.x & 15;
     const int m = blockIdx.x * 16 + (threadIdx.x >> 4);
@@ -865,8 +885,8 @@ int decode_impl(const flare_shape &s, const T *q, const T *k, const float *z, T 
 
 template <typename T, int D>
 int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, const T *y, const float *lse_dec,
-                  const T *dy, const float *z, const float *lse_enc, float *dq, T *dk, T *dv, float scale, void *ws,
-                  hipStream_t stream)
+                  const T *dy, const float *z, const float *lse_enc, void *dq, bool dq_cast, T *dk, T *dv, float scale,
+                  void *ws, hipStream_t stream)
 {
     const ValuPlan plan = valu_plan(s);
     const bool mf = mfma_supported(s);          // matrix-core kernels where they exist
@@ -968,12 +988,17 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
         LaunchTimer t(KID_BWD_DQ_REDUCE, stream);
         // shared latents: one gradient for all heads, summed over (b, h) in that fixed order
         const int groups = s.shared_latents ? BH : s.B, outers = s.shared_latents ? 1 : s.H;
-        if ((long long)groups * dq_parts <= kFewSlots)
-            dq_reduce_few_kernel<D><<<dim3((s.M + kFewRows - 1) / kFewRows, outers), 256, 0, stream>>>(
-                w.part, dq, groups, outers, s.M, dq_parts, scale);
-        else
-            dq_reduce_kernel<D><<<dim3((s.M + 15) / 16, outers), 256, 0, stream>>>(w.part, dq, groups, outers, s.M,
-                                                                                 dq_parts, scale);
+        auto launch = [&](auto *out) {
+            typedef std::remove_reference_t<decltype(*out)> O;
+            if ((long long)groups * dq_parts <= kFewSlots)
+                dq_reduce_few_kernel<O, D><<<dim3((s.M + kFewRows - 1) / kFewRows, outers), 256, 0, stream>>>(
+                    w.part, out, groups, outers, s.M, dq_parts, scale);
+            else
+                dq_reduce_kernel<O, D><<<dim3((s.M + 15) / 16, outers), 256, 0, stream>>>(
+                    w.part, out, groups, outers, s.M, dq_parts, scale);
+        };
+        if (dq_cast) launch(static_cast<T *>(dq));
+        else launch(static_cast<float *>(dq));
         return check_launch();
     };
     if (!dq_fused) {
@@ -1105,11 +1130,11 @@ int valu_decode(const flare_shape &s, const void *q, const void *k, const float 
     FLARE_DISPATCH(s, (decode_impl<T, D>(s, (const T *)q, (const T *)k, z, (T *)y, lse_dec, scale, stream)));
 }
 int valu_backward(const flare_shape &s, const void *q, const void *k, const void *v, const void *y,
-                  const float *lse_dec, const void *dy, const float *z, const float *lse_enc, float *dq, void *dk,
-                  void *dv, float scale, void *ws, hipStream_t stream)
+                  const float *lse_dec, const void *dy, const float *z, const float *lse_enc, void *dq,
+                  bool dq_cast, void *dk, void *dv, float scale, void *ws, hipStream_t stream)
 {
     FLARE_DISPATCH(s, (backward_impl<T, D>(s, (const T *)q, (const T *)k, (const T *)v, (const T *)y, lse_dec,
-                                           (const T *)dy, z, lse_enc, dq, (T *)dk, (T *)dv, scale, ws, stream)));
+                                           (const T *)dy, z, lse_enc, dq, dq_cast, (T *)dk, (T *)dv, scale, ws, stream)));
 }
 
 }  // namespace flare
