@@ -32,11 +32,12 @@
  *     Shapes with dtype bf16 or f16, M <= 2048 and N >= 16 run on the matrix-core kernels (d < 16 with the
  *     contraction padded to 16; M in tiles of 32 on the geometry of the next of 32, 64, 128, 256
  *     or a multiple of 256, the latents beyond M being padding that is masked; M > 256 in chunks
- *     of 256 latents); everything else runs on the fp32 vector kernels.  On the matrix
- *     cores the scores come from exact products of the stored 16-bit values, the softmax weights
- *     and dS are rounded to bf16 whatever the storage type (with f16 storage v and dy are rounded
- *     to bf16 as they are read), sums are fp32, and outputs are rounded once from fp32.  With f16
- *     storage scale*log2(e)*q_lat and the scaled scores must stay below 65504 in magnitude.
+ *     of 256 latents); dtype f32 runs on matrix-core kernels of its own (every fp32 operand as the exact sum
+ *     of three bf16 terms, products good to 2^-26, fp32 sums); everything else runs on the fp32 vector kernels.
+ *     With 16-bit storage on the matrix cores the scores come from exact products of the stored 16-bit
+ *     values, the softmax weights and dS are rounded to bf16 whatever the storage type (with f16 storage v
+ *     and dy are rounded to bf16 as they are read), sums are fp32, and outputs are rounded once from fp32.
+ *     With f16 storage scale*log2(e)*q_lat and the scaled scores must stay below 65504 in magnitude.
  *   - Results are bit-identical from run to run for the same inputs and shape (no float atomics;
  *     every cross-block reduction is done in a fixed order).
  *   - Non-finite inputs give undefined results.

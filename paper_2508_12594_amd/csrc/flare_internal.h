@@ -74,7 +74,7 @@ __device__ __forceinline__ size_t tok_off(const TokStride &t, int n)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// ---- fp32 vector-ALU path (any M, d in {4,8,16,32}, f32 or bf16 storage) -------------------
+// ---- fp32 vector-ALU path (any M, d in {4,8,16,32}, 16-bit storage), launch sequences of fp32 storage ---
 struct ValuPlan {
     Split enc;          // split used by the encode partials
     Split bwd;          // split used by the dZ and dQ partials
@@ -193,6 +193,26 @@ __device__ __forceinline__ bool bwd_one_exp_ok(const float *__restrict__ ld_rang
     for (int i = 0; i < 16; ++i) worst = fmaxf(worst, red[i]);
     return worst <= kPlanSpan && !force_two;
 }
+
+// ---- fp32 storage on the matrix cores (flare_mfma_f32.hip) ------------------------------------
+// Partial slots per (b,h) of the latent-major kernels (encode, dZ, dQ) = chunks of this split.
+Split mfma32_split(const flare_shape &s);
+int mfma32_encode(const flare_shape &s, const float *q, const float *k, const float *v, float *m_part, float *l_part,
+                  float *o_part, float scale, hipStream_t stream);
+int mfma32_decode(const flare_shape &s, const float *q, const float *k, const float *z, float *y, float *lse_dec,
+                  float scale, hipStream_t stream);
+int mfma32_token_stats(const flare_shape &s, const float *q, const float *k, const float *z, const float *dy,
+                       float *lse_dec2, float *delta, float scale, hipStream_t stream);
+// y, delta_out, ld_mul, ld_range, plan: as for the 16-bit launchers above
+int mfma32_dz_partial(const flare_shape &s, const float *q, const float *k, const float *dy, const float *lse_dec,
+                      float ld_mul, const float *y, float *delta_out, float *ld_range, float *dz_part, float scale,
+                      hipStream_t stream);
+int mfma32_dq_partial(const flare_shape &s, const float *q, const float *k, const float *v, const float *dy,
+                      const float *z, const float *lse_enc, const float *dz, const float *eps, const float *lse_dec,
+                      const float *delta, float ld_mul, const int *plan, float *dq_part, float scale, hipStream_t stream);
+int mfma32_dkdv(const flare_shape &s, const float *q, const float *k, const float *v, const float *dy, const float *z,
+                const float *lse_enc, const float *dz, const float *eps, const float *lse_dec, const float *delta,
+                float ld_mul, const int *plan, float *dk, float *dv, float scale, hipStream_t stream);
 
 // ---- spectral analysis (Appendix C.1, Algorithm 1) ---------------------------------------------
 bool mfma_gram_supported(const flare_shape &s);

@@ -1,0 +1,1007 @@
+// Matrix-core kernels of the FLARE mixer for fp32 storage on gfx950.
+//
+// An fp32 number is the exact sum of three bf16 numbers x0 + x1 + x2 (8 significant bits each, rounded to nearest,
+// so |x1| <= 2^-9 |x| and |x2| <= 2^-18 |x|).  A product a.b is taken as the six matrix products
+//     a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1 + a0 b0        (small terms first, fp32 accumulation)
+// of v_mfma_f32_32x32x16_bf16; what is left out (a1 b2, a2 b1, a2 b2) is below 2^-26 |a||b|, a quarter of the rounding
+// an fp32 multiplication makes.  Exponentials, normalisers, dS and every sum stay fp32; a weight enters its value
+// product as three planes as well, so nothing is rounded to 16 bits anywhere.  The range is fp32's own (bf16 has its
+// exponent field).
+//
+// Why: the vector ALU does an fp32 multiply-add for a wave in about 4.5 clocks, 145 clocks for one score with its value
+// product at d = 16; a 32 x 32 tile of scores took 2800 clocks per SIMD in the vector kernels this file replaces.  On
+// the matrix cores it is 14 instructions of 33 ... 41 clocks beside 16 exponentials and the splitting of 16 weights
+// (about 15 clocks each), which run on the other pipe.
+//
+// Planes lie in LDS as rows [x0 | x1 | x2 | zeros] of one token or latent each.  The same rows serve as an operand whose
+// contraction runs along the row (scores; plain 16-byte reads) and, through the transposing LDS read, as one whose
+// contraction runs over the rows (value products).  At d <= 8 the three planes of a row fill the 32 rows of one
+// transposed operand; at d = 16 two planes do ([x0 | x1], then [x2 | 0]); the halves of the result are added at the end.
+// In the score product of d <= 8 the two lane halves of the 16-slot contraction hold different planes: three products
+// instead of six.
+//
+// Equations: Section 3.1, Eq. flare_encode / Eq. flare_decode; Appendix F; backward as in include/flare.h.
+#include <type_traits>
+#include <utility>
+
+#include "flare_mfma_common.h"
+
+namespace flare {
+namespace {
+
+template <int DR>
+struct F32Geo {
+    static constexpr int PD = DR <= 8 ? 8 : DR;              // width of one plane
+    static constexpr int KS = DR == 32 ? 2 : 1;              // k-steps of a score product
+    static constexpr int NP = 3 * KS;                        // operands of one row set in a score product
+    static constexpr int PIECES = PD / 8;                    // pieces of eight elements per row
+    static constexpr int NV = DR <= 8 ? 1 : DR == 16 ? 2 : 3;   // transposed operands per 16 rows
+    // uint16 per LDS row: planes (and, for the transposed reads, the zeros that complete the last operand) plus 8, which
+    // keeps rows 16-byte aligned and 16 of them on distinct banks
+    static constexpr int RT = (DR <= 8 ? 32 : DR == 16 ? 64 : 96) + 8;
+    static constexpr int RD = (DR <= 8 ? 32 : 3 * PD) + 8;
+    static constexpr int OUT = DR == 32 ? 16 : DR == 16 ? 8 : 4;   // result values per lane of a 32-column tile
+};
+
+__device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// eight fp32 -> three planes of eight bf16
+__device__ __forceinline__ void split3(const float (&x)[8], u32x4 (&p)[3])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = x[2 * i], b = x[2 * i + 1];
+        const uint32_t w0 = cvt_pk_bf16(a, b);
+        const float a1 = a - bf_lo(w0), b1 = b - bf_hi(w0);
+        const uint32_t w1 = cvt_pk_bf16(a1, b1);
+        p[0][i] = w0;
+        p[1][i] = w1;
+        p[2][i] = cvt_pk_bf16(a1 - bf_lo(w1), b1 - bf_hi(w1));
+    }
+}
+// 16 accumulator values -> the three planes of the two k-steps of a value product
+__device__ __forceinline__ void split_tile(const f32x16 &t, bf16x8 (&p)[2][3])
+{
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        float x[8];
+        u32x4 w[3];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = t[8 * s + i];
+        split3(x, w);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) p[s][j] = as_bf16x8(w[j]);
+    }
+}
+
+// one piece of a row: its planes to LDS
+template <int DR>
+__device__ __forceinline__ void store_planes(uint16_t *row, int piece, const float (&x)[8])
+{
+    u32x4 p[3];
+    split3(x, p);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) *reinterpret_cast<u32x4 *>(row + j * F32Geo<DR>::PD + 8 * piece) = p[j];
+}
+template <int DR>
+__device__ __forceinline__ void load_piece(const float *__restrict__ p, float (&x)[8])
+{
+    const float4 a = *reinterpret_cast<const float4 *>(p);
+    float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
+    if constexpr (DR > 4) b = *reinterpret_cast<const float4 *>(p + 4);
+    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+}
+
+// Operands of a score product from LDS rows (row = this lane's token or latent).
+__device__ __forceinline__ bf16x8 lds_op(const uint16_t *p) { return as_bf16x8(*reinterpret_cast<const u32x4 *>(p)); }
+template <int DR, bool LATENT>
+__device__ __forceinline__ void row_ops(const uint16_t *row, int hh, bf16x8 (&p)[F32Geo<DR>::NP])
+{
+    if constexpr (DR <= 8) {
+        if constexpr (LATENT) {
+            p[0] = lds_op(row + 8 * hh);                 // x0 | x1
+            p[1] = lds_op(row + (hh ? 0 : 16));          // x2 | x0
+            p[2] = p[0];
+        } else {
+            p[0] = lds_op(row);                          // x0 | x0
+            p[1] = lds_op(row + 8);                      // x1 | x1
+            p[2] = lds_op(row + (hh ? 16 : 0));          // x0 | x2
+        }
+    } else {
+        constexpr int KS = F32Geo<DR>::KS;
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) p[KS * j + s] = lds_op(row + j * DR + 8 * KS * hh + 8 * s);
+    }
+}
+// The same for a row of the lane's own in registers: x holds the elements 8 KS hh ... of the row (all of it at d <= 8).
+template <int DR, bool LATENT>
+__device__ __forceinline__ void reg_ops(const float (&x)[F32Geo<DR>::KS][8], int hh, bf16x8 (&p)[F32Geo<DR>::NP])
+{
+    constexpr int KS = F32Geo<DR>::KS;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        u32x4 w[3];
+        split3(x[s], w);
+        if constexpr (DR <= 8) {
+            if constexpr (LATENT) {
+                p[0] = as_bf16x8(hh ? w[1] : w[0]);
+                p[1] = as_bf16x8(hh ? w[0] : w[2]);
+                p[2] = p[0];
+            } else {
+                p[0] = as_bf16x8(w[0]);
+                p[1] = as_bf16x8(w[1]);
+                p[2] = as_bf16x8(hh ? w[2] : w[0]);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) p[KS * j + s] = as_bf16x8(w[j]);
+        }
+    }
+}
+template <int DR>
+__device__ __forceinline__ void load_row_half(const float *__restrict__ row, int hh, float (&x)[F32Geo<DR>::KS][8])
+{
+#pragma unroll
+    for (int s = 0; s < F32Geo<DR>::KS; ++s) load_piece<DR>(row + (DR <= 8 ? 0 : 8 * F32Geo<DR>::KS * hh + 8 * s), x[s]);
+}
+
+// c + <latent, token>.  TOK_ROWS: the tile's rows are tokens and its columns latents, else the other way round.
+template <int DR, bool TOK_ROWS>
+__device__ __forceinline__ f32x16 row_dot(const bf16x8 (&lat)[F32Geo<DR>::NP], const bf16x8 (&tok)[F32Geo<DR>::NP],
+                                          f32x16 c)
+{
+    auto mm = [&](int l, int t) { c = TOK_ROWS ? mfma(tok[t], lat[l], c) : mfma(lat[l], tok[t], c); };
+    if constexpr (DR <= 8) {
+        mm(1, 2);
+        mm(0, 1);
+        mm(0, 0);
+    } else {
+        constexpr int KS = F32Geo<DR>::KS;
+        constexpr int L[6] = {2, 1, 0, 1, 0, 0}, T[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) mm(KS * L[i] + s, KS * T[i] + s);
+    }
+    return c;
+}
+
+// Transposed operands of 32 LDS rows: v[k-step][operand].  Lane mapping of the transposing read: lds_read_tr16.
+struct TrLane {
+    int row, col;
+    __device__ __forceinline__ explicit TrLane(int lane)
+        : row(4 * (lane >> 5) + (lane & 15) / 4), col(((lane & 16) ? 16 : 0) + 4 * (lane & 3)) {}
+};
+template <int DR>
+__device__ __forceinline__ void tr_ops(const uint16_t *rows, const TrLane &tl, int s2, bf16x8 (&v)[F32Geo<DR>::NV])
+{
+    constexpr int RS = F32Geo<DR>::RT;
+#pragma unroll
+    for (int j = 0; j < F32Geo<DR>::NV; ++j) {
+        const uint16_t *src = rows + (16 * s2 + tl.row) * RS + 32 * j + tl.col;
+        const u32x2 a = lds_read_tr16(src);
+        const u32x2 b = lds_read_tr16(src + 8 * RS);
+        u32x4 w;
+        w[0] = a[0]; w[1] = a[1]; w[2] = b[0]; w[3] = b[1];
+        v[j] = as_bf16x8(w);
+    }
+}
+// acc[column of the value rows][lane's column] += value rows (transposed) . weights, one k-step of 16 rows
+template <int DR>
+__device__ __forceinline__ f32x16 value_step(const bf16x8 (&v)[F32Geo<DR>::NV], const bf16x8 (&p)[3], f32x16 acc)
+{
+    if constexpr (DR <= 8) {
+        acc = mfma(v[0], p[2], acc);
+        acc = mfma(v[0], p[1], acc);
+        acc = mfma(v[0], p[0], acc);
+    } else if constexpr (DR == 16) {
+        acc = mfma(v[0], p[2], acc);
+        acc = mfma(v[1], p[0], acc);
+        acc = mfma(v[0], p[1], acc);
+        acc = mfma(v[0], p[0], acc);
+    } else {
+        acc = mfma(v[2], p[0], acc);
+        acc = mfma(v[1], p[1], acc);
+        acc = mfma(v[0], p[2], acc);
+        acc = mfma(v[1], p[0], acc);
+        acc = mfma(v[0], p[1], acc);
+        acc = mfma(v[0], p[0], acc);
+    }
+    return acc;
+}
+// The planes' rows added up: out[i] is column out_col(i, hh) of the value rows.
+template <int DR>
+__device__ __forceinline__ void fold_planes(const f32x16 &acc, float (&out)[F32Geo<DR>::OUT])
+{
+#pragma unroll
+    for (int i = 0; i < F32Geo<DR>::OUT; ++i) {
+        if constexpr (DR <= 8) out[i] = (acc[8 + i] + acc[4 + i]) + acc[i];
+        else if constexpr (DR == 16) out[i] = acc[8 + i] + acc[i];
+        else out[i] = acc[i];
+    }
+}
+// Quartet i of a lane's result columns starts at column 8 i + 4 hh.
+template <int DR>
+__device__ __forceinline__ void store_quartets(float *__restrict__ row, int hh, const float (&x)[F32Geo<DR>::OUT])
+{
+#pragma unroll
+    for (int i = 0; i < F32Geo<DR>::OUT / 4; ++i)
+        if (8 * i + 4 * hh < DR)
+            *reinterpret_cast<float4 *>(row + 8 * i + 4 * hh) = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
+}
+// 16 per-row values of a tile: register r holds row 8 (r / 4) + 4 hh + r % 4
+__device__ __forceinline__ f32x16 tile_rows(const float *p, int hh)
+{
+    f32x16 t;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float4 x = *reinterpret_cast<const float4 *>(p + 8 * i + 4 * hh);
+        t[4 * i] = x.x; t[4 * i + 1] = x.y; t[4 * i + 2] = x.z; t[4 * i + 3] = x.w;
+    }
+    return t;
+}
+__device__ __forceinline__ int tile_row(int r, int hh) { return 8 * (r / 4) + 4 * hh + r % 4; }
+__device__ __forceinline__ float sum16(const f32x16 &t)
+{
+    float a[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = (t[4 * i] + t[4 * i + 1]) + (t[4 * i + 2] + t[4 * i + 3]);
+    return (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+// Log-sum-exps within this many log2 units of zero need no normaliser inside an exponential: 2^S and 2^-lse are then
+// normal numbers wherever they matter (as kPlanSpan for the variants of the backward).
+constexpr float kSpan = 60.f;
+
+// ============================================================================================
+// Latent-major pass over a chunk of tokens: encode partials (MODE 0), dZ partials (1), dQ partials (2).
+// A workgroup has G x TG waves; wave w owns the 32 latents of tile blockIdx.z G + w % G and every TG-th 32-token tile
+// of the chunk.  The workgroup stages TG token tiles at a time: every thread loads pieces of eight elements, splits them
+// into planes and puts them into one of two LDS buffers, a stage ahead of their use; one barrier per stage.  (Split by
+// every wave for itself, the rows of a tile would cost each of the G waves 125 clocks per tensor and tile.)
+//   MODE 0: weights 2^S as they come; when a latent's sum leaves [2^-80, 2^100] the workgroup does the chunk again with
+//           a running maximum.  Writes (c, l, O) of the chunk.
+//   MODE 1: weights 2^S, values 2^-lse_dec2[n] dY_n (|lse_dec2| beyond kSpan: what is beyond goes into the exponent).
+//           Also delta[n] = <dY_n, Y_n> when y is given, and the range of lse_dec2 for bwd_one_exp_ok.
+//   MODE 2: dS = 2^S (<dZ'_m, V_n> - eps'_m + 2^-lse_dec2[n] (<Z_m, dY_n> - delta_n)) with dZ', eps' carrying
+//           2^-lse_enc2[m] (plan 1), or with both exponentials (plan 0); values K.
+// ============================================================================================
+struct LatentArgs {
+    const float *q, *k, *v, *dy, *z, *lse_enc, *dz, *eps, *lse_dec, *delta, *y;
+    const int *plan;
+    float *m_part, *l_part, *o_part, *delta_out, *ld_range;
+    TokStride ts;
+    int H, N, M, chunk_len, G, TG;
+    float c2, ld_mul;
+};
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose index is a constant in every pass
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+template <int DR, int MODE>
+struct LatentLds {   // in uint16 units, per token tile
+    using Geo = F32Geo<DR>;
+    static constexpr int K = 0, KR = MODE == 2 ? Geo::RT : Geo::RD;           // rows of K: also values in MODE 2
+    static constexpr int V = K + 32 * KR, VR = MODE == 2 ? Geo::RD : Geo::RT;   // V, or dY in MODE 1
+    static constexpr int Y = V + 32 * VR;                                     // dY in MODE 2
+    static constexpr int ST = Y + (MODE == 2 ? 32 * Geo::RD : 0);             // 2 x 32 floats: per-token statistics
+    static constexpr int TILE = ST + 128;
+};
+
+template <int DR, int MODE, int IT>
+__global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArgs A)
+{
+    using Geo = F32Geo<DR>;
+    using L = LatentLds<DR, MODE>;
+    constexpr int NA = MODE == 2 ? 3 : 2;
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int G = A.G, TG = A.TG, g = wave % G, tg = wave / G;
+    const int nt = 64 * G * TG;
+    const GridPos gp = grid_pos(A.ts, A.H, DR * 4);
+    const int bh = gp.y, h = bh % A.H, chunk = gp.x, chunks = gridDim.x;
+    const int n0 = chunk * A.chunk_len, n1 = min(A.N, n0 + A.chunk_len);
+    const int stage_tok = 32 * TG, stages = (n1 - n0 + stage_tok - 1) / stage_tok;
+    const int M = A.M, m = 32 * (G * (int)blockIdx.z + g) + l32, mc = min(m, M - 1);
+    const size_t base = tok_base(A.ts, bh, A.H);
+    const TrLane tl(lane);
+
+    // the zeros that complete the last transposed operand, in both buffers
+    if constexpr (Geo::RT - 8 > 3 * Geo::PD) {
+        constexpr int ROWS0 = MODE == 2 ? L::K : L::V, Z0 = 3 * Geo::PD, ZN = (Geo::RT - 8 - Z0) / 8;
+        const u32x4 zero{0u, 0u, 0u, 0u};
+        for (int i = threadIdx.x; i < 2 * TG * 32 * ZN; i += nt) {
+            const int row = i / ZN;
+            *reinterpret_cast<u32x4 *>(smem + (row >> 5) * L::TILE + ROWS0 + (row & 31) * Geo::RT + Z0 + 8 * (i % ZN)) = zero;
+        }
+    }
+
+    // this wave's latents
+    bf16x8 qp[Geo::NP], zp[MODE == 2 ? Geo::NP : 1], dzp[MODE == 2 ? Geo::NP : 1];
+    float le2 = 0.f, ep = 0.f;
+    {
+        float x[Geo::KS][8];
+        load_row_half<DR>(A.q + (size_t)h * A.ts.sq + (size_t)mc * DR, hh, x);
+#pragma unroll
+        for (int s = 0; s < Geo::KS; ++s)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[s][i] *= A.c2;
+        reg_ops<DR, true>(x, hh, qp);
+        if constexpr (MODE == 2) {
+            const size_t row = (size_t)bh * M + mc;
+            load_row_half<DR>(A.z + row * DR, hh, x);
+            reg_ops<DR, true>(x, hh, zp);
+            load_row_half<DR>(A.dz + row * DR, hh, x);
+            reg_ops<DR, true>(x, hh, dzp);
+            le2 = A.lse_enc[row] * kLog2e;
+            ep = A.eps[row];
+        }
+    }
+    const bool one_exp = MODE == 2 && A.plan[bh] != 0;
+
+    // ---- staging ----
+    const int span = stage_tok * Geo::PIECES;       // items per tensor and stage
+    float x[IT][8], yv[MODE == 1 ? IT : 1][8], st0[IT], st1[IT];
+    float ld_min = INFINITY, ld_max = -INFINITY;
+    const bool do_delta = MODE == 1 && A.y != nullptr && blockIdx.z == 0;
+    auto item = [&](int it, int &a, int &tok, int &piece) __attribute__((always_inline)) {   // thread's it-th item of a stage; false: none
+        const int e = it * nt + (int)threadIdx.x;
+        a = e >= 2 * span ? 2 : e >= span ? 1 : 0;
+        const int r = e - a * span;
+        tok = r / Geo::PIECES;
+        piece = r % Geo::PIECES;
+        return e < NA * span;
+    };
+    auto load = [&](int st) __attribute__((always_inline)) {
+        unrolled([&](auto index) __attribute__((always_inline)) {
+            constexpr int it = decltype(index)::value;
+            int a, tok, piece;
+            if (!item(it, a, tok, piece)) return;
+            const int n = n0 + st * stage_tok + tok, nc = min(n, A.N - 1);
+            const float *t = a == 0 ? A.k : a == 1 ? (MODE == 1 ? A.dy : A.v) : A.dy;
+            const size_t off = base + tok_off(A.ts, nc) + 8 * piece, row = (size_t)bh * A.N + nc;
+            load_piece<DR>(t + off, x[it]);
+            if (MODE == 1 && a == 1) {
+                st0[it] = A.lse_dec[row];
+                if (do_delta) load_piece<DR>(A.y + off, yv[MODE == 1 ? it : 0]);
+            }
+            if (MODE == 2 && a == 0 && piece == 0) {
+                st0[it] = A.lse_dec[row];
+                st1[it] = A.delta[row];
+            }
+        }, std::make_integer_sequence<int, IT>{});
+    };
+    auto stage = [&](int st) __attribute__((always_inline)) {
+        unrolled([&](auto index) __attribute__((always_inline)) {
+            constexpr int it = decltype(index)::value;
+            int a, tok, piece;
+            if (!item(it, a, tok, piece)) return;
+            const int n = n0 + st * stage_tok + tok, t32 = tok & 31;
+            const bool in = n < n1;
+            uint16_t *tile = smem + ((st & 1) * TG + (tok >> 5)) * L::TILE;
+            float *stat = reinterpret_cast<float *>(tile + L::ST);
+            if (MODE == 1 && a == 1) {
+                const float ld = st0[it] * A.ld_mul;
+                if (do_delta) {
+                    float d = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) d = fmaf(x[it][i], yv[MODE == 1 ? it : 0][i], d);
+#pragma unroll
+                    for (int off = 1; off < Geo::PIECES; off <<= 1) d += __shfl_xor(d, off);
+                    if (piece == 0 && in) A.delta_out[(size_t)bh * A.N + n] = d;
+                }
+                if (in) {
+                    ld_min = fminf(ld_min, ld);
+                    ld_max = fmaxf(ld_max, ld);
+                }
+                const float lc = fminf(fmaxf(ld, -kSpan), kSpan), w = fast_exp2(-lc);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[it][i] *= w;
+                if (piece == 0) stat[t32] = in ? ld - lc : 0.f;
+            }
+            if (MODE == 2 && a == 0 && piece == 0) {
+                const float ld = in ? st0[it] * A.ld_mul : 0.f;
+                stat[t32] = one_exp ? fast_exp2(-ld) : ld;
+                stat[32 + t32] = in ? -st1[it] : 0.f;
+            }
+            if (!in) {                            // behind the chunk's end: rows of zeros
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[it][i] = 0.f;
+            }
+            uint16_t *row = tile + (a == 0 ? L::K + t32 * L::KR : a == 1 ? L::V + t32 * L::VR : L::Y + t32 * Geo::RD);
+            store_planes<DR>(row, piece, x[it]);
+        }, std::make_integer_sequence<int, IT>{});
+    };
+
+    // ---- one sweep over the chunk ----
+    f32x16 o = splat16(0.f);
+    float l = 0.f, c = 0.f;
+    auto values = [&](const f32x16 &w, const uint16_t *rows) {
+        bf16x8 p[2][3];
+        split_tile(w, p);
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+            bf16x8 v[Geo::NV];
+            tr_ops<DR>(rows, tl, s2, v);
+            o = value_step<DR>(v, p[s2], o);
+        }
+    };
+    auto compute = [&](int st, auto online_tag) {
+        constexpr bool ONLINE = decltype(online_tag)::value;
+        const int tok0 = n0 + st * stage_tok + 32 * tg;
+        if (tok0 >= n1) return;
+        const uint16_t *tile = smem + ((st & 1) * TG + tg) * L::TILE;
+        const float *stat = reinterpret_cast<const float *>(tile + L::ST);
+        bf16x8 tok[Geo::NP];
+        row_ops<DR, false>(tile + L::K + l32 * L::KR, hh, tok);
+        f32x16 s = row_dot<DR, true>(qp, tok, splat16(0.f));
+        if constexpr (MODE == 0) {
+            if (tok0 + 32 > n1) {     // the chunk's last tile: no weight for the tokens behind its end
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[i] = tok0 + tile_row(i, hh) < n1 ? s[i] : -INFINITY;
+            }
+            if constexpr (ONLINE) {
+                float mx = max16(s, -INFINITY);
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                if (__any(mx > c)) {
+                    const float cn = fmaxf(c, mx), f = fast_exp2(c - cn);
+                    l *= f;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) o[i] *= f;
+                    c = cn;
+                }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[i] -= c;
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = fast_exp2(s[i]);
+            l += sum16(s);
+            values(s, tile + L::V);
+        } else if constexpr (MODE == 1) {
+            if (__any(stat[l32] != 0.f)) {
+                const f32x16 ex = tile_rows(stat, hh);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[i] -= ex[i];
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = fast_exp2(s[i]);
+            values(s, tile + L::V);
+        } else {
+            row_ops<DR, false>(tile + L::V + l32 * L::VR, hh, tok);
+            f32x16 a = row_dot<DR, true>(dzp, tok, splat16(-ep));
+            row_ops<DR, false>(tile + L::Y + l32 * Geo::RD, hh, tok);
+            f32x16 cc = row_dot<DR, true>(zp, tok, tile_rows(stat + 32, hh));
+            const f32x16 w = tile_rows(stat, hh);
+            if (one_exp) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[i] = fast_exp2(s[i]) * fmaf(w[i], cc[i], a[i]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    s[i] = fmaf(fast_exp2(s[i] - le2), a[i], fast_exp2(s[i] - w[i]) * cc[i]);
+            }
+            values(s, tile + L::K);
+        }
+    };
+    auto sweep = [&](auto online_tag) __attribute__((always_inline)) {
+        load(0);
+        stage(0);
+        for (int st = 0; st < stages; ++st) {
+            __syncthreads();
+            if (st + 1 < stages) load(st + 1);
+            compute(st, online_tag);
+            if (st + 1 < stages) stage(st + 1);
+        }
+    };
+    sweep(PlainTag<false>{});
+    if constexpr (MODE == 0) {
+        l += __shfl_xor(l, 32);
+        // waves without a tile in this chunk (l = 0) and padding latents have nothing to say
+        const uint32_t lb = __float_as_uint(l);
+        const bool bad = m < M && 32 * tg < n1 - n0 && (lb < ((127u - 80u) << 23) || lb > ((127u + 100u) << 23));
+        if (__syncthreads_or(bad)) {
+            o = splat16(0.f);
+            l = 0.f;
+            c = -INFINITY;
+            sweep(PlainTag<true>{});
+            l += __shfl_xor(l, 32);
+        }
+    }
+
+    // ---- the TG waves of a latent tile, added in order ----
+    float out[Geo::OUT];
+    fold_planes<DR>(o, out);
+    float *red = reinterpret_cast<float *>(smem);
+    if (TG > 1) {
+        __syncthreads();                         // the staging buffers are free now
+        if constexpr (MODE == 0) {               // to a common stabiliser first (all zero after the plain sweep)
+            if (hh == 0) red[wave * 32 + l32] = c;
+            __syncthreads();
+            float cm = -INFINITY;
+            for (int t = 0; t < TG; ++t) cm = fmaxf(cm, red[(t * G + g) * 32 + l32]);
+            const float f = c == -INFINITY ? 0.f : fast_exp2(c - cm);
+            l *= f;
+#pragma unroll
+            for (int i = 0; i < Geo::OUT; ++i) out[i] *= f;
+            c = cm;
+            __syncthreads();
+        }
+        if (tg > 0) {
+#pragma unroll
+            for (int i = 0; i < Geo::OUT; ++i) red[(wave * (Geo::OUT + 1) + i) * 64 + lane] = out[i];
+            red[(wave * (Geo::OUT + 1) + Geo::OUT) * 64 + lane] = l;
+        }
+        __syncthreads();
+        if (tg == 0) {
+            for (int t = 1; t < TG; ++t) {
+                const float *r = red + (size_t)(t * G + g) * (Geo::OUT + 1) * 64 + lane;
+#pragma unroll
+                for (int i = 0; i < Geo::OUT; ++i) out[i] += r[i * 64];
+                l += r[Geo::OUT * 64];
+            }
+        }
+    }
+    if (tg == 0 && m < M) {
+        const size_t slot = ((size_t)bh * chunks + chunk) * M + m;
+        store_quartets<DR>(A.o_part + slot * DR, hh, out);
+        if (MODE == 0 && hh == 0) {
+            A.m_part[slot] = c;
+            A.l_part[slot] = l;
+        }
+    }
+    if constexpr (MODE == 1) {                   // range of lse_dec2 in this chunk
+        if (blockIdx.z == 0) {
+            __syncthreads();
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                ld_min = fminf(ld_min, __shfl_xor(ld_min, off));
+                ld_max = fmaxf(ld_max, __shfl_xor(ld_max, off));
+            }
+            if (lane == 0) { red[2 * wave] = ld_min; red[2 * wave + 1] = ld_max; }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                for (int w = 1; w < G * TG; ++w) {
+                    ld_min = fminf(ld_min, red[2 * w]);
+                    ld_max = fmaxf(ld_max, red[2 * w + 1]);
+                }
+                A.ld_range[2 * ((size_t)bh * chunks + chunk)] = ld_min;
+                A.ld_range[2 * ((size_t)bh * chunks + chunk) + 1] = ld_max;
+            }
+        }
+    }
+}
+
+// ============================================================================================
+// Token-major pass: a wave owns 32 tokens (columns) and goes over the latents (rows).
+//   MODE 0: decode, y and lse_dec (natural log).  MODE 1: lse_dec2 (log2) and delta = <dY, Y>.
+//   MODE 2: dK and dV.
+// The planes of up to CT latent tiles lie in LDS (built by the workgroup).  With more latents than that (T = 4) a wave
+// keeps the sums of T token tiles in registers while the workgroup goes over the chunks of latents.
+// Weights are 2^S as they come; a token whose denominator leaves [2^-80, 2^100] is done again from its exact maximum.
+// MODE 2 has a one- and a two-exponential form (plan) as the latent-major kernel.
+// ============================================================================================
+struct TokenArgs {
+    const float *q, *k, *v, *dy, *z, *lse_enc, *dz, *eps, *lse_dec, *delta;
+    const int *plan;
+    float *out0, *out1;      // y, lse_dec | lse_dec2, delta | dk, dv
+    TokStride ts;
+    int H, N, M, CT;
+    float c2, ld_mul, scale;
+};
+template <int DR, int MODE>
+struct TokenLds {   // in uint16 units, per latent tile
+    using Geo = F32Geo<DR>;
+    static constexpr int Q = 0, QR = MODE == 2 ? Geo::RT : Geo::RD;
+    static constexpr int Z = Q + 32 * QR, ZR = MODE == 2 ? Geo::RD : Geo::RT;
+    static constexpr int D = Z + 32 * ZR;                                  // dZ (MODE 2)
+    static constexpr int ST = D + (MODE == 2 ? 32 * Geo::RT : 0);          // per latent: bias of the scores, -eps, lse_enc2
+    static constexpr int TILE = ST + 192;
+};
+
+template <int DR, int MODE, int T>
+__global__ __launch_bounds__(512, 2) void token_pass_f32_kernel(const TokenArgs A)
+{
+    using Geo = F32Geo<DR>;
+    using L = TokenLds<DR, MODE>;
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int waves = blockDim.x >> 6;
+    const GridPos gp = grid_pos(A.ts, A.H, DR * 4);
+    const int bh = gp.y, h = bh % A.H;
+    const size_t base = tok_base(A.ts, bh, A.H), rows = (size_t)bh * A.N;
+    const int M = A.M, MT = (M + 31) / 32, CT = A.CT, chunks = (MT + CT - 1) / CT;
+    const TrLane tl(lane);
+    const bool one_exp = MODE == 2 && A.plan[bh] != 0;
+
+    // planes of the latent tiles of one chunk
+    auto fill = [&](int chunk) {
+        constexpr int NA = MODE == 2 ? 3 : 2;
+        const int t0 = chunk * CT, nrow = 32 * min(CT, MT - t0);
+        for (int e = threadIdx.x; e < NA * nrow * Geo::PIECES; e += blockDim.x) {
+            const int a = e / (nrow * Geo::PIECES), r = e - a * nrow * Geo::PIECES;
+            const int row = r / Geo::PIECES, piece = r % Geo::PIECES, mm = 32 * t0 + row;
+            const int mc = min(mm, M - 1);
+            float x[8];
+            const float *src = a == 0 ? A.q + (size_t)h * A.ts.sq + (size_t)mc * DR
+                                      : (a == 1 ? A.z : A.dz) + ((size_t)bh * M + mc) * DR;
+            load_piece<DR>(src + 8 * piece, x);
+            const float f = mm >= M ? 0.f : a == 0 ? A.c2 : 1.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] *= f;
+            uint16_t *tile = smem + (row >> 5) * L::TILE;
+            uint16_t *dst = a == 0 ? tile + L::Q + (row & 31) * L::QR
+                                   : a == 1 ? tile + L::Z + (row & 31) * L::ZR : tile + L::D + (row & 31) * Geo::RT;
+            store_planes<DR>(dst, piece, x);
+            const bool transposed = MODE == 2 ? a != 1 : a == 1;
+            if (Geo::RT - 8 > 3 * Geo::PD && transposed && piece == 0) {
+                const u32x4 zero{0u, 0u, 0u, 0u};
+                for (int i = 3 * Geo::PD; i < Geo::RT - 8; i += 8) *reinterpret_cast<u32x4 *>(dst + i) = zero;
+            }
+            if (piece == 0) {
+                float *stat = reinterpret_cast<float *>(tile + L::ST);
+                if (a == 0) stat[row & 31] = mm < M ? 0.f : -1e30f;   // no weight for the padding latents
+                if constexpr (MODE == 2) {
+                    if (a == 1) stat[32 + (row & 31)] = mm < M ? -A.eps[(size_t)bh * M + mc] : 0.f;
+                    if (a == 2) stat[64 + (row & 31)] = A.lse_enc[(size_t)bh * M + mc] * kLog2e;
+                }
+            }
+        }
+    };
+    if (T == 1) {            // all latents fit: once for the whole kernel
+        fill(0);
+        __syncthreads();
+    }
+
+    const int tiles = (A.N + 31) / 32;
+    const int batch = waves * T, batches = (tiles + batch - 1) / batch;
+    auto tile_of = [&](int b, int t) { return b * batch + t * waves + wave; };
+    auto tok_of = [&](int tile) { return min(tile * 32 + l32, A.N - 1); };
+    float kx[Geo::KS][8];
+    for (int b = gp.x; b < batches; b += gridDim.x) {
+        f32x16 acc[T], acc2[MODE == 2 ? T : 1];
+        float l[T], bias[T];
+        if constexpr (MODE == 2) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                acc[t] = splat16(0.f);
+                acc2[t] = splat16(0.f);
+            }
+            for (int ch = 0; ch < chunks; ++ch) {
+                if (T > 1) {
+                    __syncthreads();
+                    fill(ch);
+                    __syncthreads();
+                }
+                const int nlt = min(CT, MT - ch * CT);
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const int tile = tile_of(b, t), n = tok_of(tile);
+                    if (tile >= tiles) continue;
+                    bf16x8 kp[Geo::NP], vp[Geo::NP], gq[Geo::NP];
+                    const size_t off = base + tok_off(A.ts, n);
+                    load_row_half<DR>(A.k + off, hh, kx);
+                    reg_ops<DR, false>(kx, hh, kp);
+                    load_row_half<DR>(A.v + off, hh, kx);
+                    reg_ops<DR, false>(kx, hh, vp);
+                    load_row_half<DR>(A.dy + off, hh, kx);
+                    reg_ops<DR, false>(kx, hh, gq);
+                    const float ld = A.lse_dec[rows + n] * A.ld_mul, w = fast_exp2(-ld), dl = A.delta[rows + n];
+                    for (int lt = 0; lt < nlt; ++lt) {
+                        const uint16_t *im = smem + lt * L::TILE;
+                        const float *stat = reinterpret_cast<const float *>(im + L::ST);
+                        bf16x8 lat[Geo::NP];
+                        row_ops<DR, true>(im + L::Q + l32 * L::QR, hh, lat);
+                        f32x16 s = row_dot<DR, false>(lat, kp, tile_rows(stat, hh));
+                        row_ops<DR, true>(im + L::D + l32 * Geo::RT, hh, lat);
+                        f32x16 a = row_dot<DR, false>(lat, vp, tile_rows(stat + 32, hh));
+                        row_ops<DR, true>(im + L::Z + l32 * L::ZR, hh, lat);
+                        f32x16 c = row_dot<DR, false>(lat, gq, splat16(-dl));
+                        if (one_exp) {
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) {
+                                s[i] = fast_exp2(s[i]);
+                                a[i] = s[i] * fmaf(w, c[i], a[i]);
+                            }
+                        } else {
+                            const f32x16 le = tile_rows(stat + 64, hh);
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) {
+                                const float r = fast_exp2(s[i] - ld);
+                                s[i] = fast_exp2(s[i] - le[i]);
+                                a[i] = fmaf(s[i], a[i], r * c[i]);
+                            }
+                        }
+                        bf16x8 p[2][3], v[Geo::NV];
+                        split_tile(s, p);
+#pragma unroll
+                        for (int s2 = 0; s2 < 2; ++s2) {
+                            tr_ops<DR>(im + L::D, tl, s2, v);
+                            acc2[t] = value_step<DR>(v, p[s2], acc2[t]);
+                        }
+                        split_tile(a, p);
+#pragma unroll
+                        for (int s2 = 0; s2 < 2; ++s2) {
+                            tr_ops<DR>(im + L::Q, tl, s2, v);
+                            acc[t] = value_step<DR>(v, p[s2], acc[t]);
+                        }
+                    }
+                }
+            }
+            // the rows of Q carry c2 = scale log2 e; dK wants scale
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int tile = tile_of(b, t), n = tile * 32 + l32;
+                if (tile >= tiles || n >= A.N) continue;
+                float out[Geo::OUT];
+                fold_planes<DR>(acc[t], out);
+#pragma unroll
+                for (int i = 0; i < Geo::OUT; ++i) out[i] *= kLn2;
+                store_quartets<DR>(A.out0 + base + tok_off(A.ts, n), hh, out);
+                fold_planes<DR>(acc2[t], out);
+                store_quartets<DR>(A.out1 + base + tok_off(A.ts, n), hh, out);
+            }
+        } else {
+            // WHAT 0: weights as they come; 1: only the maximum of the scores; 2: weights behind that maximum
+            auto sweep = [&](auto what_tag) {
+                constexpr int WHAT = decltype(what_tag)::value;
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    acc[t] = splat16(0.f);
+                    l[t] = 0.f;
+                    if (WHAT == 0) bias[t] = 0.f;
+                    if (WHAT == 1) bias[t] = -INFINITY;
+                }
+                for (int ch = 0; ch < chunks; ++ch) {
+                    if (T > 1) {
+                        __syncthreads();
+                        fill(ch);
+                        __syncthreads();
+                    }
+                    const int nlt = min(CT, MT - ch * CT);
+#pragma unroll
+                    for (int t = 0; t < T; ++t) {
+                        const int tile = tile_of(b, t);
+                        if (tile >= tiles) continue;
+                        bf16x8 kp[Geo::NP];
+                        load_row_half<DR>(A.k + base + tok_off(A.ts, tok_of(tile)), hh, kx);
+                        reg_ops<DR, false>(kx, hh, kp);
+                        for (int lt = 0; lt < nlt; ++lt) {
+                            const uint16_t *im = smem + lt * L::TILE;
+                            bf16x8 lat[Geo::NP];
+                            row_ops<DR, true>(im + L::Q + l32 * L::QR, hh, lat);
+                            f32x16 s = row_dot<DR, false>(lat, kp, tile_rows(reinterpret_cast<const float *>(im + L::ST), hh));
+                            if constexpr (WHAT == 1) {
+                                bias[t] = max16(s, bias[t]);
+                            } else {
+#pragma unroll
+                                for (int i = 0; i < 16; ++i) s[i] = fast_exp2(WHAT == 2 ? s[i] - bias[t] : s[i]);
+                                l[t] += sum16(s);
+                                bf16x8 p[2][3], v[Geo::NV];
+                                split_tile(s, p);
+#pragma unroll
+                                for (int s2 = 0; s2 < 2; ++s2) {
+                                    tr_ops<DR>(im + L::Z, tl, s2, v);
+                                    acc[t] = value_step<DR>(v, p[s2], acc[t]);
+                                }
+                            }
+                        }
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    if (WHAT == 1) bias[t] = fmaxf(bias[t], __shfl_xor(bias[t], 32));
+                    else l[t] += __shfl_xor(l[t], 32);
+                }
+            };
+            sweep(std::integral_constant<int, 0>{});
+            bool bad = false;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const uint32_t lb = __float_as_uint(l[t]);
+                bad |= tile_of(b, t) < tiles && (lb < ((127u - 80u) << 23) || lb > ((127u + 100u) << 23));
+            }
+            if (T > 1 ? __syncthreads_or(bad) : __any(bad)) {
+                sweep(std::integral_constant<int, 1>{});
+                sweep(std::integral_constant<int, 2>{});
+            }
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int tile = tile_of(b, t), n = tile * 32 + l32;
+                if (tile >= tiles) continue;
+                const float inv = 1.f / l[t], lse2 = bias[t] + log2f(l[t]);
+                float out[Geo::OUT];
+                fold_planes<DR>(acc[t], out);
+#pragma unroll
+                for (int i = 0; i < Geo::OUT; ++i) out[i] *= inv;
+                const size_t off = base + tok_off(A.ts, min(n, A.N - 1));
+                if constexpr (MODE == 0) {
+                    if (n < A.N) {
+                        store_quartets<DR>(A.out0 + off, hh, out);
+                        if (A.out1 && hh == 0) A.out1[rows + n] = lse2 * kLn2;
+                    }
+                } else {
+                    float d = 0.f;
+#pragma unroll
+                    for (int i = 0; i < Geo::OUT / 4; ++i)
+                        if (8 * i + 4 * hh < DR) {
+                            const float4 gr = *reinterpret_cast<const float4 *>(A.dy + off + 8 * i + 4 * hh);
+                            d = fmaf(out[4 * i], gr.x, d);
+                            d = fmaf(out[4 * i + 1], gr.y, d);
+                            d = fmaf(out[4 * i + 2], gr.z, d);
+                            d = fmaf(out[4 * i + 3], gr.w, d);
+                        }
+                    d += __shfl_xor(d, 32);
+                    if (n < A.N && hh == 0) {
+                        A.out0[rows + n] = lse2;
+                        A.out1[rows + n] = d;
+                    }
+                }
+            }
+        }
+    }
+}
+
+// ---- launches -------------------------------------------------------------------------------
+// Latent-major: up to 8 waves per workgroup; one 32-latent tile per wave, what is left of the 8 waves splits the
+// tokens as far as two staging buffers of kStageLds hold a tile for each.
+constexpr int kStageLds = 48 * 1024;
+constexpr int kWaves = 4096;        // waves a launch aims at: 16 per CU
+constexpr int kWorkgroups = 512;    // and workgroups of the token-major kernels
+struct LatentGeom { int G, TG, zdim; };
+inline LatentGeom latent_geom(int M, int tile_bytes)
+{
+    const int MT = (M + 31) / 32;
+    LatentGeom g;
+    g.zdim = (MT + 7) / 8;
+    g.G = (MT + g.zdim - 1) / g.zdim;
+    g.TG = g.G == 1 ? 8 : g.G == 2 ? 4 : g.G <= 4 ? 2 : 1;
+    while (g.TG > 1 && 2 * g.TG * tile_bytes > kStageLds) g.TG >>= 1;
+    return g;
+}
+
+template <int DR, int MODE>
+int launch_latent(const flare_shape &s, const LatentArgs &a, int kid, hipStream_t stream)
+{
+    using Geo = F32Geo<DR>;
+    using L = LatentLds<DR, MODE>;
+    const LatentGeom g = latent_geom(s.M, L::TILE * 2);
+    const Split sp = mfma32_split(s);
+    LatentArgs A = a;
+    A.G = g.G;
+    A.TG = g.TG;
+    A.chunk_len = sp.chunk_len;
+    const dim3 grid(sp.chunks, s.B * s.H, g.zdim);
+    const int threads = 64 * g.G * g.TG;
+    size_t lds = (size_t)2 * g.TG * L::TILE * 2;
+    const size_t red = (size_t)g.G * g.TG * (Geo::OUT + 1) * 64 * 4;
+    if (red > lds) lds = red;
+    constexpr int NA = MODE == 2 ? 3 : 2;
+    const int it = (Geo::PIECES * NA + 2 * g.G - 1) / (2 * g.G);
+    LaunchTimer t(kid, stream);
+#define FLARE_LATENT(I) latent_pass_f32_kernel<DR, MODE, I><<<grid, threads, lds, stream>>>(A)
+    if (it <= 1) FLARE_LATENT(1);
+    else if (it <= 2) FLARE_LATENT(2);
+    else if constexpr (Geo::PIECES * NA > 4) {
+        if (it <= 3) FLARE_LATENT(3);
+        else if constexpr (Geo::PIECES * NA > 6) FLARE_LATENT((Geo::PIECES * NA / 2));
+    }
+#undef FLARE_LATENT
+    return check_launch();
+}
+
+template <int DR, int MODE>
+int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t stream)
+{
+    using L = TokenLds<DR, MODE>;
+    constexpr int kLds = 160 * 1024 - 512;   // (the workgroup's votes take a little of the 160 KiB)
+    constexpr int CTMAX = kLds / (L::TILE * 2) < 8 ? kLds / (L::TILE * 2) : 8;
+    const int MT = (s.M + 31) / 32, tiles = (s.N + 31) / 32, BH = s.B * s.H;
+    TokenArgs A = a;
+    const bool fits = MT <= CTMAX;
+    A.CT = fits ? MT : CTMAX;
+    const size_t lds = (size_t)A.CT * L::TILE * 2;
+    const int waves = 8, batch = waves * (fits ? 1 : MODE == 2 ? 2 : 4);
+    int blocks = (tiles + batch - 1) / batch;
+    const int most = (kWorkgroups + BH - 1) / BH;
+    if (blocks > most) blocks = most;
+    LaunchTimer t(kid, stream);
+    if (fits) token_pass_f32_kernel<DR, MODE, 1><<<dim3(blocks, BH), 64 * waves, lds, stream>>>(A);
+    else token_pass_f32_kernel<DR, MODE, MODE == 2 ? 2 : 4><<<dim3(blocks, BH), 64 * waves, lds, stream>>>(A);
+    return check_launch();
+}
+
+#define FLARE_D(s, CALL)                                        \
+    do {                                                        \
+        switch ((s).d) {                                        \
+            case 4: { constexpr int D = 4; return CALL; }       \
+            case 8: { constexpr int D = 8; return CALL; }       \
+            case 16: { constexpr int D = 16; return CALL; }     \
+            case 32: { constexpr int D = 32; return CALL; }     \
+        }                                                       \
+        return FLARE_EUNSUPPORTED;                              \
+    } while (0)
+
+}  // namespace
+
+// Chunks of tokens of the latent-major kernels: enough for kWaves waves, at least one stage of the encode and at most
+// 8192 tokens long (a chunk's sums are taken one after the other in fp32).
+Split mfma32_split(const flare_shape &s)
+{
+    const int tile = s.d <= 8 ? LatentLds<8, 0>::TILE : s.d == 16 ? LatentLds<16, 0>::TILE : LatentLds<32, 0>::TILE;
+    const LatentGeom g = latent_geom(s.M, tile * 2);
+    const int stage = 32 * g.TG, per = s.B * s.H * g.zdim * g.G * g.TG;
+    const int stages = (s.N + stage - 1) / stage;
+    int want = (kWaves + per - 1) / per;
+    if (want > stages) want = stages;
+    int len = (stages + want - 1) / want * stage;
+    if (len > 8192) len = 8192;
+    return Split{(s.N + len - 1) / len, len};
+}
+
+int mfma32_encode(const flare_shape &s, const float *q, const float *k, const float *v, float *m_part, float *l_part,
+                  float *o_part, float scale, hipStream_t stream)
+{
+    LatentArgs a{};
+    a.q = q; a.k = k; a.v = v;
+    a.m_part = m_part; a.l_part = l_part; a.o_part = o_part;
+    a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e;
+    FLARE_D(s, (launch_latent<D, 0>(s, a, KID_ENCODE_PARTIAL, stream)));
+}
+int mfma32_dz_partial(const flare_shape &s, const float *q, const float *k, const float *dy, const float *lse_dec,
+                      float ld_mul, const float *y, float *delta_out, float *ld_range, float *dz_part, float scale,
+                      hipStream_t stream)
+{
+    LatentArgs a{};
+    a.q = q; a.k = k; a.dy = dy; a.lse_dec = lse_dec; a.ld_mul = ld_mul; a.y = y;
+    a.delta_out = delta_out; a.ld_range = ld_range; a.o_part = dz_part;
+    a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e;
+    FLARE_D(s, (launch_latent<D, 1>(s, a, KID_BWD_DZ_PARTIAL, stream)));
+}
+int mfma32_dq_partial(const flare_shape &s, const float *q, const float *k, const float *v, const float *dy,
+                      const float *z, const float *lse_enc, const float *dz, const float *eps, const float *lse_dec,
+                      const float *delta, float ld_mul, const int *plan, float *dq_part, float scale, hipStream_t stream)
+{
+    LatentArgs a{};
+    a.q = q; a.k = k; a.v = v; a.dy = dy; a.z = z; a.lse_enc = lse_enc; a.dz = dz; a.eps = eps;
+    a.lse_dec = lse_dec; a.delta = delta; a.ld_mul = ld_mul; a.plan = plan; a.o_part = dq_part;
+    a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e;
+    FLARE_D(s, (launch_latent<D, 2>(s, a, KID_BWD_DQ_PARTIAL, stream)));
+}
+int mfma32_decode(const flare_shape &s, const float *q, const float *k, const float *z, float *y, float *lse_dec,
+                  float scale, hipStream_t stream)
+{
+    TokenArgs a{};
+    a.q = q; a.k = k; a.z = z; a.out0 = y; a.out1 = lse_dec;
+    a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e;
+    FLARE_D(s, (launch_token<D, 0>(s, a, KID_DECODE, stream)));
+}
+int mfma32_token_stats(const flare_shape &s, const float *q, const float *k, const float *z, const float *dy,
+                       float *lse_dec2, float *delta, float scale, hipStream_t stream)
+{
+    TokenArgs a{};
+    a.q = q; a.k = k; a.z = z; a.dy = dy; a.out0 = lse_dec2; a.out1 = delta;
+    a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e;
+    FLARE_D(s, (launch_token<D, 1>(s, a, KID_BWD_TOKEN_STATS, stream)));
+}
+int mfma32_dkdv(const flare_shape &s, const float *q, const float *k, const float *v, const float *dy, const float *z,
+                const float *lse_enc, const float *dz, const float *eps, const float *lse_dec, const float *delta,
+                float ld_mul, const int *plan, float *dk, float *dv, float scale, hipStream_t stream)
+{
+    TokenArgs a{};
+    a.q = q; a.k = k; a.v = v; a.dy = dy; a.z = z; a.lse_enc = lse_enc; a.dz = dz; a.eps = eps;
+    a.lse_dec = lse_dec; a.delta = delta; a.ld_mul = ld_mul; a.plan = plan; a.out0 = dk; a.out1 = dv;
+    a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e; a.scale = scale;
+    FLARE_D(s, (launch_token<D, 2>(s, a, KID_BWD_DKDV, stream)));
+}
+
+}  // namespace flare

@@ -1,7 +1,8 @@
-// fp32 vector-ALU kernels of the FLARE mixer: the fp32 path, and the general path for
-// shapes the matrix-core kernels do not take (any M, d in {4,8,16,32}, f32 or bf16 storage).
+// fp32 vector-ALU kernels of the FLARE mixer for the 16-bit shapes that the matrix-core kernels do not take (more than
+// 2048 latents, fewer than 16 tokens), the kernels that merge partial sums for every path, and the backward's sequence
+// of launches.
 //
-// Two kernel shapes cover every step:
+// Two kernel shapes cover every step of the vector path:
 //   * one thread per LATENT, streaming tokens (encode partials, dZ partials, dQ partials):
 //     the token rows k_n, v_n, dy_n have wave-uniform addresses, so they arrive through the
 //     scalar data path (reads only) and cost no vector memory traffic or LDS;
@@ -863,7 +864,10 @@ int encode_impl(const flare_shape &s, const T *q, const T *k, const T *v, float 
     valu_fwd_layout(s, plan.enc, ws, &m_part, &l_part, &o_part);
     const int BH = s.B * s.H;
     const int lat_blocks = (s.M + kLatentBlock - 1) / kLatentBlock;
-    {
+    if constexpr (std::is_same_v<T, float>) {
+        const int rc = mfma32_encode(s, q, k, v, m_part, l_part, o_part, scale, stream);
+        if (rc != FLARE_OK) return rc;
+    } else {
         LaunchTimer t(KID_ENCODE_PARTIAL, stream);
         encode_partial_kernel<T, D><<<dim3(plan.enc.chunks, BH, lat_blocks), kLatentBlock, 0, stream>>>(
             q, k, v, m_part, l_part, o_part, tok_stride(s), s.H, s.N, s.M, plan.enc.chunk_len, plan.enc.chunks, scale * kLog2e,
@@ -877,10 +881,14 @@ template <typename T, int D>
 int decode_impl(const flare_shape &s, const T *q, const T *k, const float *z, T *y, float *lse_dec, float scale,
                 hipStream_t stream)
 {
-    LaunchTimer t(KID_DECODE, stream);
-    token_pass_kernel<T, D, 0><<<dim3((s.N + kTokenBlock - 1) / kTokenBlock, s.B * s.H), kTokenBlock, 0, stream>>>(
-        q, k, z, y, nullptr, lse_dec, nullptr, tok_stride(s), s.H, s.N, s.M, scale * kLog2e, s.y_f32);
-    return check_launch();
+    if constexpr (std::is_same_v<T, float>) {
+        return mfma32_decode(s, q, k, z, y, lse_dec, scale, stream);
+    } else {
+        LaunchTimer t(KID_DECODE, stream);
+        token_pass_kernel<T, D, 0><<<dim3((s.N + kTokenBlock - 1) / kTokenBlock, s.B * s.H), kTokenBlock, 0, stream>>>(
+            q, k, z, y, nullptr, lse_dec, nullptr, tok_stride(s), s.H, s.N, s.M, scale * kLog2e, s.y_f32);
+        return check_launch();
+    }
 }
 
 template <typename T, int D>
@@ -889,7 +897,9 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
                   void *ws, hipStream_t stream)
 {
     const ValuPlan plan = valu_plan(s);
-    const bool mf = mfma_supported(s);          // matrix-core kernels where they exist
+    constexpr bool F32 = std::is_same_v<T, float>;   // matrix-core kernels of their own, for every shape
+    const bool mf = mfma_supported(s);               // 16-bit storage: matrix-core kernels where they exist
+    const bool planned = F32 || mf;                  // their kernels choose between one and two exponentials by (b,h)
     const int dz_parts = mf ? mfma_plan(s).parts : plan.bwd.chunks;
     BwdWs w;
     bwd_layout(s, bwd_slots(s, plan), ws, &w);
@@ -916,12 +926,17 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
                           !(s.y_f32 && mf);   // an fp32 y is not coarse (the fp32 kernels, which take the
                                               // 16-bit shapes of fewer than 16 tokens, never read it: they recompute)
     const bool saved = y && lse_dec && !coarse_y;
-    const bool fused = saved && mf && mfma_dkdv_supported(s);   // every later kernel is a matrix-core one
+    const bool fused = saved && (F32 || (mf && mfma_dkdv_supported(s)));   // every later kernel is a matrix-core one
     const float *ld = fused ? lse_dec : w.lse_dec2;
     const float ld_mul = fused ? kLog2e : 1.f;
     // delta from the fp32 y: at d <= 8 inside the dZ kernel like from a 16-bit y, else by a pass of its own
-    const bool y32 = fused && s.y_f32 && s.d > 8;
-    if (y32) {
+    const bool y32 = fused && !F32 && s.y_f32 && s.d > 8;
+    if constexpr (F32) {
+        if (!saved) {
+            const int rc = mfma32_token_stats(s, q, k, z, dy, w.lse_dec2, w.delta, scale, stream);
+            if (rc != FLARE_OK) return rc;
+        }
+    } else if (y32) {
         LaunchTimer t(KID_BWD_PREP, stream);
         const size_t rows = (size_t)BH * s.N;
         bwd_prep_y32_kernel<T, D><<<(unsigned)((rows + 255) / 256), 256, 0, stream>>>(
@@ -941,7 +956,11 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
                                                                          ts, s.H, s.N, s.M, c2, 0);
     }
     if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
-    if (mf) {
+    if constexpr (F32) {
+        const int rc = mfma32_dz_partial(s, q, k, dy, ld, ld_mul, fused ? y : nullptr, w.delta, w.ld_range, w.part, scale,
+                                         stream);
+        if (rc != FLARE_OK) return rc;
+    } else if (mf) {
         int rc = mfma_dz_partial(s, q, k, dy, ld, ld_mul, (fused && !y32) ? y : nullptr,
                                  (fused && !y32) ? w.delta : nullptr, w.ld_range, w.part, scale, stream);
         if (rc != FLARE_OK) return rc;
@@ -958,12 +977,12 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
     {
         LaunchTimer t(KID_BWD_DZ_MERGE, stream);
         if (dz_parts <= kFewSlots)
-            dz_merge_few_kernel<D><<<dim3((s.M + kFewRows - 1) / kFewRows + (mf ? 1 : 0), BH), 256, 0, stream>>>(
-                w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, mf ? w.plan : nullptr,
+            dz_merge_few_kernel<D><<<dim3((s.M + kFewRows - 1) / kFewRows + (planned ? 1 : 0), BH), 256, 0, stream>>>(
+                w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, planned ? w.plan : nullptr,
                 (s.variant & FLARE_VARIANT_TWO_EXP) ? 1 : 0);
         else
-            dz_merge_kernel<D><<<dim3((s.M + 15) / 16 + (mf ? 1 : 0), BH), 256, 0, stream>>>(
-                w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, mf ? w.plan : nullptr,
+            dz_merge_kernel<D><<<dim3((s.M + 15) / 16 + (planned ? 1 : 0), BH), 256, 0, stream>>>(
+                w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, planned ? w.plan : nullptr,
                 (s.variant & FLARE_VARIANT_TWO_EXP) ? 1 : 0);
     }
     if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
@@ -971,6 +990,10 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
     const bool dq_fused = mf && mfma_dkdv_supported(s) && mfma_dq_fused(s);   // dQ comes out of the dK/dV kernel
     if (dq_fused) {
         dq_parts = mfma_dkdv_blocks(s);
+    } else if constexpr (F32) {
+        const int rc = mfma32_dq_partial(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, w.part,
+                                         scale, stream);
+        if (rc != FLARE_OK) return rc;
     } else if (mf) {
         dq_parts = mfma_dq_parts(s);
         const int rc = mfma_dq_partial(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, w.part,
@@ -1014,7 +1037,9 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
         }
         return dq_fused ? reduce_dq() : FLARE_OK;
     }
-    {
+    if constexpr (F32) {
+        return mfma32_dkdv(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, dk, dv, scale, stream);
+    } else {
         LaunchTimer t(KID_BWD_DKDV, stream);
         dkdv_kernel<T, D><<<tok_grid, kTokenBlock, 0, stream>>>(q, k, v, dy, z, lse_enc, w.dz, w.eps, w.lse_dec2,
                                                                 w.delta, dk, dv, ts, s.H, s.N, s.M, scale);
@@ -1113,6 +1138,7 @@ ValuPlan valu_plan(const flare_shape &s)
         p.enc.chunk_len = kMaxChunk;
         p.enc.chunks = (s.N + kMaxChunk - 1) / kMaxChunk;
     }
+    if (s.dtype == FLARE_F32) p.enc = mfma32_split(s);
     p.bwd = p.enc;
     p.fwd_bytes = valu_fwd_layout(s, p.enc, nullptr, nullptr, nullptr, nullptr);
     p.bwd_bytes = bwd_layout(s, bwd_slots(s, p), nullptr, nullptr);
