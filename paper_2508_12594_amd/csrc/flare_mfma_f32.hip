@@ -60,20 +60,6 @@ __device__ __forceinline__ void split3(const float (&x)[8], u32x4 (&p)[3])
         p[2][i] = cvt_pk_bf16(a1 - bf_lo(w1), b1 - bf_hi(w1));
     }
 }
-// 16 accumulator values -> the three planes of the two k-steps of a value product
-__device__ __forceinline__ void split_tile(const f32x16 &t, bf16x8 (&p)[2][3])
-{
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        float x[8];
-        u32x4 w[3];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = t[8 * s + i];
-        split3(x, w);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) p[s][j] = as_bf16x8(w[j]);
-    }
-}
 
 // one piece of a row: its planes to LDS
 template <int DR>
@@ -210,6 +196,26 @@ __device__ __forceinline__ f32x16 value_step(const bf16x8 (&v)[F32Geo<DR>::NV], 
         acc = mfma(v[1], p[0], acc);
         acc = mfma(v[0], p[1], acc);
         acc = mfma(v[0], p[0], acc);
+    }
+    return acc;
+}
+// acc[column of the value rows][lane's column] += 32 value rows (transposed) . the 32 x 32 tile w of weights, whose
+// accumulator layout is the operand's: k-step s2 takes registers 8 s2 ... 8 s2 + 7
+template <int DR>
+__device__ __forceinline__ f32x16 value_product(const uint16_t *rows, const TrLane &tl, const f32x16 &w, f32x16 acc)
+{
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+        float x[8];
+        u32x4 wp[3];
+        bf16x8 p[3], v[F32Geo<DR>::NV];
+        tr_ops<DR>(rows, tl, s2, v);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = w[8 * s2 + i];
+        split3(x, wp);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) p[j] = as_bf16x8(wp[j]);
+        acc = value_step<DR>(v, p, acc);
     }
     return acc;
 }
@@ -425,16 +431,6 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
     // ---- one sweep over the chunk ----
     f32x16 o = splat16(0.f);
     float l = 0.f, c = 0.f;
-    auto values = [&](const f32x16 &w, const uint16_t *rows) {
-        bf16x8 p[2][3];
-        split_tile(w, p);
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-            bf16x8 v[Geo::NV];
-            tr_ops<DR>(rows, tl, s2, v);
-            o = value_step<DR>(v, p[s2], o);
-        }
-    };
     auto compute = [&](int st, auto online_tag) {
         constexpr bool ONLINE = decltype(online_tag)::value;
         const int tok0 = n0 + st * stage_tok + 32 * tg;
@@ -465,7 +461,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[i] = fast_exp2(s[i]);
             l += sum16(s);
-            values(s, tile + L::V);
+            o = value_product<DR>(tile + L::V, tl, s, o);
         } else if constexpr (MODE == 1) {
             if (__any(stat[l32] != 0.f)) {
                 const f32x16 ex = tile_rows(stat, hh);
@@ -474,7 +470,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
             }
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[i] = fast_exp2(s[i]);
-            values(s, tile + L::V);
+            o = value_product<DR>(tile + L::V, tl, s, o);
         } else {
             row_ops<DR, false>(tile + L::V + l32 * L::VR, hh, tok);
             f32x16 a = row_dot<DR, true>(dzp, tok, splat16(-ep));
@@ -489,7 +485,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
                 for (int i = 0; i < 16; ++i)
                     s[i] = fmaf(fast_exp2(s[i] - le2), a[i], fast_exp2(s[i] - w[i]) * cc[i]);
             }
-            values(s, tile + L::K);
+            o = value_product<DR>(tile + L::K, tl, s, o);
         }
     };
     auto sweep = [&](auto online_tag) __attribute__((always_inline)) {
@@ -607,8 +603,9 @@ struct TokenLds {   // in uint16 units, per latent tile
     static constexpr int TILE = ST + 192;
 };
 
+constexpr int kTokenWaves = 8;
 template <int DR, int MODE, int T>
-__global__ __launch_bounds__(512, 2) void token_pass_f32_kernel(const TokenArgs A)
+__global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(const TokenArgs A)
 {
     using Geo = F32Geo<DR>;
     using L = TokenLds<DR, MODE>;
@@ -721,19 +718,8 @@ __global__ __launch_bounds__(512, 2) void token_pass_f32_kernel(const TokenArgs 
                                 a[i] = fmaf(s[i], a[i], r * c[i]);
                             }
                         }
-                        bf16x8 p[2][3], v[Geo::NV];
-                        split_tile(s, p);
-#pragma unroll
-                        for (int s2 = 0; s2 < 2; ++s2) {
-                            tr_ops<DR>(im + L::D, tl, s2, v);
-                            acc2[t] = value_step<DR>(v, p[s2], acc2[t]);
-                        }
-                        split_tile(a, p);
-#pragma unroll
-                        for (int s2 = 0; s2 < 2; ++s2) {
-                            tr_ops<DR>(im + L::Q, tl, s2, v);
-                            acc[t] = value_step<DR>(v, p[s2], acc[t]);
-                        }
+                        acc2[t] = value_product<DR>(im + L::D, tl, s, acc2[t]);
+                        acc[t] = value_product<DR>(im + L::Q, tl, a, acc[t]);
                     }
                 }
             }
@@ -786,13 +772,7 @@ __global__ __launch_bounds__(512, 2) void token_pass_f32_kernel(const TokenArgs 
 #pragma unroll
                                 for (int i = 0; i < 16; ++i) s[i] = fast_exp2(WHAT == 2 ? s[i] - bias[t] : s[i]);
                                 l[t] += sum16(s);
-                                bf16x8 p[2][3], v[Geo::NV];
-                                split_tile(s, p);
-#pragma unroll
-                                for (int s2 = 0; s2 < 2; ++s2) {
-                                    tr_ops<DR>(im + L::Z, tl, s2, v);
-                                    acc[t] = value_step<DR>(v, p[s2], acc[t]);
-                                }
+                                acc[t] = value_product<DR>(im + L::Z, tl, s, acc[t]);
                             }
                         }
                     }
@@ -910,7 +890,7 @@ int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t 
     const bool fits = MT <= CTMAX;
     A.CT = fits ? MT : CTMAX;
     const size_t lds = (size_t)A.CT * L::TILE * 2;
-    const int waves = 8, batch = waves * (fits ? 1 : MODE == 2 ? 2 : 4);
+    const int waves = kTokenWaves, batch = waves * (fits ? 1 : MODE == 2 ? 2 : 4);
     int blocks = (tiles + batch - 1) / batch;
     const int most = (kWorkgroups + BH - 1) / BH;
     if (blocks > most) blocks = most;
