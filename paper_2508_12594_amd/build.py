@@ -57,7 +57,7 @@ def _start_native(verbose):
            "-I", os.path.join(home, "include"), "-I", os.path.join(home, "include", "torch", "csrc", "api", "include"),
            "-I", sysconfig.get_paths()["include"], "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
            "-o", tmp, os.path.join(CSRC, "torch_binding.cpp"), "-L", os.path.join(home, "lib"), "-lc10", "-lc10_hip",
-           "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+           "-ltorch_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
     if verbose:
         print(" ".join(cmd), flush=True)
     return cmd, subprocess.Popen(cmd), tmp

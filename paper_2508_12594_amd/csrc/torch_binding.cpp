@@ -4,10 +4,14 @@
 // Why native: with argument checks, allocations and the C call marshalled in Python (ctypes) a forward cost the host
 // 27 us and a training step through torch.autograd 215-230 us, while the kernels of four meshes of 16384 tokens
 // (H = 8, d = 16, M = 64, bf16) need 31 and 84 us: every small or medium call was bound by the interpreter.
-#include <torch/csrc/autograd/custom_function.h>
+#include <torch/csrc/autograd/function.h>
+#include <torch/csrc/autograd/functions/utils.h>
+#include <torch/csrc/autograd/saved_variable.h>
 #include <torch/csrc/utils/pybind.h>
 
 #include <ATen/ATen.h>
+#include <ATen/core/LegacyTypeDispatch.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <c10/core/impl/VirtualGuardImpl.h>
 #include <c10/hip/HIPStream.h>
 #include <dlfcn.h>
@@ -128,16 +132,17 @@ void *dev(const OptTensor &t, const char *name, at::ScalarType dt, at::IntArrayR
 {
     return t ? dev(*t, name, dt, shape) : nullptr;
 }
-template <typename T = float>
-T *f32(void *p)
-{
-    return static_cast<T *>(p);
-}
+float *f32(void *p) { return static_cast<float *>(p); }
 
+// A new device tensor, from the caching allocator (without the dispatcher: 0.7 instead of 1.7 us)
+Tensor new_empty(at::IntArrayRef shape, at::ScalarType dt, const Tensor &like)
+{
+    return at::detail::empty_cuda(shape, dt, like.device(), std::nullopt);
+}
 // An output the caller brought, or a new one.
 Tensor out_or_new(const OptTensor &t, at::IntArrayRef shape, at::ScalarType dt, const Tensor &like)
 {
-    return t ? *t : at::empty(shape, like.options().dtype(dt));
+    return t ? *t : new_empty(shape, dt, like);
 }
 
 // Where a call is enqueued: torch's current stream, or the one that was handed in (a torch.cuda.Stream).
@@ -172,7 +177,7 @@ Workspace workspace_for(size_t need, const OptTensor &given, const Tensor &like,
         // A temporary block: the kernels are only enqueued when the call returns, so the caching allocator must
         // learn on which stream they run, or it could hand the block to other work on the allocating stream
         // while kernels on `stream` still use it.
-        t = at::empty({(int64_t)(need < 256 ? 256 : need)}, like.options().dtype(at::kByte));
+        t = new_empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte, like);
         if (to.other) t.record_stream(*to.other);
     }
     return Workspace{t, t.data_ptr(), (size_t)t.numel()};
@@ -285,7 +290,7 @@ std::tuple<Tensor, Tensor, Tensor> forward_project(const Tensor &q, const Tensor
     Tensor out = out_or_new(out_in, out_dim, dt, k), z = out_or_new(z_in, dim.z, at::kFloat, k),
            le = out_or_new(le_in, dim.lse_enc, at::kFloat, k);
     OptTensor y = y_in;
-    if (!y && keep_y) y = at::empty_like(k);
+    if (!y && keep_y) y = new_empty(k.sizes(), dt, k);
     const Workspace ws = workspace_for(fwd_bytes(s), ws_in, k, to);
     check(lib.forward_project(&s, dev(q, "q_lat"), dev(k, "k"), dev(v, "v", dt, k.sizes()), dev(w, "w_out", dt, w_dim),
                               f32(dev(bias, "bias", at::kFloat, b_dim)), dev(out, "out", dt, out_dim),
@@ -336,55 +341,72 @@ struct Saved {
     }
 };
 
-struct Mixer : torch::autograd::Function<Mixer> {
-    static Tensor forward(torch::autograd::AutogradContext *ctx, const Tensor &q_in, const Tensor &k_in,
-                          const Tensor &v_in, double scale, int64_t layout, bool y_f32)
-    {
-        const Tensor q = q_in.contiguous(), k = k_in.contiguous(), v = v_in.contiguous();
-        const flare_shape s = shape_of(q, k, (int)layout, y_f32);
-        const Saved at_(s);
-        const Target to{c10::hip::getCurrentHIPStream().stream(), std::nullopt};
-        Tensor y = at::empty(k.sizes(), k.options().dtype(y_f32 ? at::kFloat : k.scalar_type()));
-        Tensor stats = at::empty({(int64_t)at_.bytes}, k.options().dtype(at::kByte));
-        const Workspace ws = workspace_for(fwd_bytes(s), std::nullopt, k, to);
-        char *const st = static_cast<char *>(dev(stats, "k"));
-        check(lib.forward(&s, dev(q, "q_lat"), dev(k, "k"), dev(v, "v", k.scalar_type(), k.sizes()), y.data_ptr(),
-                          reinterpret_cast<float *>(st), reinterpret_cast<float *>(st + at_.lse_enc),
-                          reinterpret_cast<float *>(st + at_.lse_dec), (float)scale, ws.ptr, ws.bytes, to.stream),
-              "flare_forward");
-        ctx->save_for_backward({q, k, v, y, stats});
-        ctx->saved_data["scale"] = scale;
-        ctx->saved_data["layout"] = layout;
-        return y;
-    }
+// The autograd node, written out (a torch::autograd::Function costs several microseconds more in both directions).
+struct MixerBackward : torch::autograd::Node {
+    torch::autograd::SavedVariable q, k, v, y, stats;
+    flare_shape shape{};
+    float scale = 0.f;
 
-    static torch::autograd::variable_list backward(torch::autograd::AutogradContext *ctx,
-                                                   torch::autograd::variable_list grads)
+    std::string name() const override { return "FlareMixerBackward"; }
+    void release_variables() override
     {
-        const auto saved = ctx->get_saved_variables();
-        const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &y = saved[3], &stats = saved[4];
-        const at::ScalarType dt = k.scalar_type();
+        std::lock_guard<std::mutex> lock(mutex_);
+        for (auto *t : {&q, &k, &v, &y, &stats}) t->reset_data();
+    }
+    torch::autograd::variable_list apply(torch::autograd::variable_list &&grads) override
+    {
+        std::lock_guard<std::mutex> lock(mutex_);
+        if (!grads[0].defined()) return {Tensor(), Tensor(), Tensor()};
+        const Tensor tq = q.unpack(), tk = k.unpack(), tv = v.unpack(), ty = y.unpack(shared_from_this()),
+                     ts = stats.unpack();
+        const at::ScalarType dt = tk.scalar_type();
         // (with an fp32 y autograd hands over an fp32 dY: the library takes it in the storage type)
-        const Tensor dy = grads[0].to(dt).contiguous();
-        const flare_shape s = shape_of(q, k, (int)ctx->saved_data["layout"].toInt(), y.scalar_type() != dt);
-        const Saved at_(s);
+        Tensor dy = std::move(grads[0]);
+        if (dy.scalar_type() != dt) dy = dy.to(dt);
+        dy = dy.contiguous();
+        const Saved off(shape);
         const Target to{c10::hip::getCurrentHIPStream().stream(), std::nullopt};
-        Tensor dq = at::empty_like(q), dk = at::empty_like(k), dv = at::empty_like(k);
-        const Workspace ws = workspace_for(bwd_bytes(s), std::nullopt, k, to);
-        char *const st = static_cast<char *>(stats.data_ptr());
-        check(lib.backward_cast(&s, q.data_ptr(), k.data_ptr(), v.data_ptr(), y.data_ptr(),
-                                reinterpret_cast<float *>(st + at_.lse_dec), dev(dy, "dy", dt, k.sizes()),
-                                reinterpret_cast<float *>(st), reinterpret_cast<float *>(st + at_.lse_enc),
-                                dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
-                                (float)ctx->saved_data["scale"].toDouble(), ws.ptr, ws.bytes, to.stream),
+        Tensor dq = new_empty(tq.sizes(), dt, tk), dk = new_empty(tk.sizes(), dt, tk), dv = new_empty(tk.sizes(), dt, tk);
+        const Workspace ws = workspace_for(bwd_bytes(shape), std::nullopt, tk, to);
+        char *const st = static_cast<char *>(ts.data_ptr());
+        check(lib.backward_cast(&shape, dev(tq, "q_lat"), dev(tk, "k"), dev(tv, "v"), dev(ty, "y"),
+                                f32(st + off.lse_dec), dev(dy, "dy", dt, tk.sizes()), f32(st), f32(st + off.lse_enc),
+                                dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), scale, ws.ptr, ws.bytes, to.stream),
               "flare_backward_cast");
-        return {dq, dk, dv, Tensor(), Tensor(), Tensor()};
+        return {dq, dk, dv};
     }
 };
 
-Tensor mixer(const Tensor &q, const Tensor &k, const Tensor &v, double scale, int64_t layout, bool y_f32)
+Tensor mixer(const Tensor &q_in, const Tensor &k_in, const Tensor &v_in, double scale, int layout, bool y_f32)
 {
-    return Mixer::apply(q, k, v, scale, layout, y_f32);
+    std::shared_ptr<MixerBackward> node;
+    if (at::GradMode::is_enabled() && (q_in.requires_grad() || k_in.requires_grad() || v_in.requires_grad())) {
+        node = std::shared_ptr<MixerBackward>(new MixerBackward(), torch::autograd::deleteNode);
+        node->set_next_edges(torch::autograd::collect_next_edges(q_in, k_in, v_in));
+    }
+    at::AutoDispatchBelowADInplaceOrView below;
+    const Tensor q = q_in.contiguous(), k = k_in.contiguous(), v = v_in.contiguous();
+    const flare_shape s = shape_of(q, k, layout, y_f32);
+    const Saved off(s);
+    const Target to{c10::hip::getCurrentHIPStream().stream(), std::nullopt};
+    Tensor y = new_empty(k.sizes(), y_f32 ? at::kFloat : k.scalar_type(), k);
+    Tensor stats = new_empty({(int64_t)off.bytes}, at::kByte, k);
+    const Workspace ws = workspace_for(fwd_bytes(s), std::nullopt, k, to);
+    char *const st = static_cast<char *>(stats.data_ptr());
+    check(lib.forward(&s, dev(q, "q_lat"), dev(k, "k"), dev(v, "v", k.scalar_type(), k.sizes()), y.data_ptr(), f32(st),
+                      f32(st + off.lse_enc), f32(st + off.lse_dec), (float)scale, ws.ptr, ws.bytes, to.stream),
+          "flare_forward");
+    if (node) {
+        node->shape = s;
+        node->scale = (float)scale;
+        node->q = torch::autograd::SavedVariable(q, false);
+        node->k = torch::autograd::SavedVariable(k, false);
+        node->v = torch::autograd::SavedVariable(v, false);
+        node->stats = torch::autograd::SavedVariable(stats, false);
+        torch::autograd::set_history(y, node);
+        node->y = torch::autograd::SavedVariable(y, true);
+    }
+    return y;
 }
 
 }  // namespace
