@@ -135,10 +135,10 @@ int flare_workspace_bytes(const flare_shape *shape, size_t *fwd_bytes, size_t *b
     return FLARE_OK;
 }
 
-int flare_encode(const flare_shape *shape, const void *q_lat, const void *k, const void *v, float *z,
-                 float *lse_enc, float scale, void *workspace, size_t workspace_bytes, void *stream)
+static int check_encode(const flare_shape *shape, const void *q_lat, const void *k, const void *v, const float *z,
+                        const float *lse_enc, const void *workspace, size_t workspace_bytes)
 {
-    int rc = check_shape(shape);
+    const int rc = check_shape(shape);
     if (rc != FLARE_OK) return rc;
     if (!q_lat || !k || !v || !z || !lse_enc) return FLARE_EINVAL;
     if (!aligned16(q_lat) || !aligned16(k) || !aligned16(v) || !aligned16(z) || !aligned16(lse_enc) ||
@@ -147,6 +147,14 @@ int flare_encode(const flare_shape *shape, const void *q_lat, const void *k, con
     size_t need = 0;
     flare_workspace_bytes(shape, &need, nullptr);
     if (!workspace || workspace_bytes < need) return FLARE_EWORKSPACE;
+    return FLARE_OK;
+}
+
+int flare_encode(const flare_shape *shape, const void *q_lat, const void *k, const void *v, float *z,
+                 float *lse_enc, float scale, void *workspace, size_t workspace_bytes, void *stream)
+{
+    const int rc = check_encode(shape, q_lat, k, v, z, lse_enc, workspace, workspace_bytes);
+    if (rc != FLARE_OK) return rc;
     if (mfma_supported(*shape))
         return mfma_encode(*shape, q_lat, k, v, z, lse_enc, scale, workspace, static_cast<hipStream_t>(stream));
     return valu_encode(*shape, q_lat, k, v, z, lse_enc, scale, workspace, static_cast<hipStream_t>(stream));
@@ -175,9 +183,11 @@ int flare_forward(const flare_shape *shape, const void *q_lat, const void *k, co
 {
     if (!y) return FLARE_EINVAL;
     if (!aligned16(y) || !aligned16(lse_dec)) return FLARE_EALIGN;
-    int rc = flare_encode(shape, q_lat, k, v, z, lse_enc, scale, workspace, workspace_bytes, stream);
+    const int rc = check_encode(shape, q_lat, k, v, z, lse_enc, workspace, workspace_bytes);
     if (rc != FLARE_OK) return rc;
-    return flare_decode(shape, q_lat, k, z, y, lse_dec, scale, workspace, workspace_bytes, stream);
+    hipStream_t const st = static_cast<hipStream_t>(stream);
+    if (mfma_supported(*shape)) return mfma_forward(*shape, q_lat, k, v, y, z, lse_enc, lse_dec, scale, workspace, st);
+    return valu_forward(*shape, q_lat, k, v, y, z, lse_enc, lse_dec, scale, workspace, st);
 }
 
 int flare_forward_static(const flare_shape *shape, const void *q_lat, const void *k, const void *v, void *y,

@@ -9,6 +9,9 @@
 
 namespace flare {
 
+struct MergeZ;    // flare_merge.h
+struct MergeDz;
+
 // ---- kernel ids for the per-kernel timing hooks ------------------------------------------
 enum KernelId {
     KID_ENCODE_PARTIAL = 0,
@@ -93,6 +96,8 @@ int launch_encode_merge(const flare_shape &s, const float *m_part, const float *
 
 int valu_encode(const flare_shape &s, const void *q, const void *k, const void *v, float *z,
                 float *lse_enc, float scale, void *ws, hipStream_t stream);
+int valu_forward(const flare_shape &s, const void *q, const void *k, const void *v, void *y, float *z, float *lse_enc,
+                 float *lse_dec, float scale, void *ws, hipStream_t stream);
 int valu_decode(const flare_shape &s, const void *q, const void *k, const float *z, void *y,
                 float *lse_dec, float scale, hipStream_t stream);
 // The whole backward; uses the matrix-core kernels where the shape allows.  y and lse_dec may be
@@ -104,13 +109,19 @@ int valu_backward(const flare_shape &s, const void *q, const void *k, const void
 // ---- bf16 matrix-core path (d in {16,32}; M = 32 or a multiple of 64 up to 256) --------------
 struct MfmaPlan {
     Split enc;   // token chunks of the encode (one workgroup each)
-    int parts;   // partial slots per (b,h) = chunks * token groups per workgroup
+    int parts;   // partial slots per (b,h) of the encode and dZ kernels: one per chunk
 };
 bool mfma_supported(const flare_shape &s);
 MfmaPlan mfma_plan(const flare_shape &s);
 size_t mfma_fwd_bytes(const flare_shape &s);
 int mfma_encode(const flare_shape &s, const void *q, const void *k, const void *v, float *z,
                 float *lse_enc, float scale, void *ws, hipStream_t stream);
+// encode and decode; where the encode's slots are few the decode merges them itself
+int mfma_forward(const flare_shape &s, const void *q, const void *k, const void *v, void *y, float *z, float *lse_enc,
+                 float *lse_dec, float scale, void *ws, hipStream_t stream);
+// The encode's partial slots only; *g says where they are, for a consumer to merge.
+int mfma_encode_partial(const flare_shape &s, const void *q, const void *k, const void *v, float *z, float *lse_enc,
+                        float scale, void *ws, MergeZ *g, hipStream_t stream);
 // Shapes with M > 256 run the token-major kernels once per chunk of 256 latents.  The decode and the
 // token statistics then need mfma_tok_part_bytes(s) of scratch (`ws`; unused and may be NULL
 // otherwise), the dK/dV step mfma_dkdv_acc_bytes(s) for its fp32 sums.
@@ -129,9 +140,8 @@ bool mfma_dkdv_supported(const flare_shape &s);
 // ld_mul * lse_dec2[n]: pass the workspace array with ld_mul = 1, or the forward's natural-log
 // lse_dec with ld_mul = log2(e).
 int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v, const void *dy, const float *z,
-              const float *lse_enc, const float *dz, const float *eps, const float *lse_dec2, const float *delta,
-              float ld_mul, const int *plan, void *dk, void *dv, float *acc32, float *dq_part, int m0, float scale,
-              hipStream_t stream);
+              const float *lse_enc, const float *lse_dec2, const float *delta, float ld_mul, void *dk, void *dv,
+              float *acc32, float *dq_part, int m0, float scale, const MergeDz &g, hipStream_t stream);
 int mfma_dkdv_blocks(const flare_shape &s);
 bool mfma_dq_fused(const flare_shape &s);
 int mfma_dq_parts(const flare_shape &s);
@@ -139,68 +149,19 @@ int mfma_dq_partial(const flare_shape &s, const void *q, const void *k, const vo
                     const float *z, const float *lse_enc, const float *dz, const float *eps,
                     const float *lse_dec2, const float *delta, float ld_mul, const int *plan, float *dq_part,
                     float scale, hipStream_t stream);
+// May the dK/dV kernel merge the dZ slots itself?
+bool mfma_dz_inline(const flare_shape &s);
 // y and delta_out may be NULL; when given, delta_out[b][h][n] = <dY_n, Y_n> is written as a by-product.
 int mfma_dz_partial(const flare_shape &s, const void *q, const void *k, const void *dy, const float *lse_dec2,
                     float ld_mul, const void *y, float *delta_out, float *ld_range, float *dz_part, float scale,
                     hipStream_t stream);
-// The dQ and dK/dV kernels exist in two variants, one and two exponentials per score.  Both are
-// launched; each leaves at once the (b,h) slices that plan[b*h] (1 = one exponential) gives to the
-// other.  ld_range[b*h][part] = (min, max) of lse_dec2 as mfma_dz_partial recorded it.
-// One exponential: P~ = 2^S2 as it comes, without a normaliser (S2 <= lse_enc2[m] and S2 <= lse_dec2[n], so with
-// both log-sum-exps of a (b,h) within +-kPlanSpan nothing overflows and every weight that matters is a normal
-// number), P = P~ e_m with e_m = 2^-lse_enc2[m] and R = P~ w_n with w_n = 2^-lse_dec2[n]:
-//   dS = P (a - eps) + R (c - delta) = P~ (e_m (a - eps_m) + w_n (c - delta_n)),   dV += (e_m dZ_m) P~.
-// e_m is folded into dZ where its partials are merged, BEFORE dZ is rounded to bf16 and eps = <dZ, Z> is formed
-// (bwd_one_exp_ok decides there, and the kernels that follow take dZ and eps as they find them), so that a and
-// eps still see the same rounded values and the score products need no correction k-step; w_n is a per-token
-// scalar.  Anything else (log-sum-exps beyond +-kPlanSpan, non-finite statistics) takes the two-exponential
-// kernels with dZ as it is.
-// Called by a whole workgroup of 256 threads (of the kernel that merges the dZ partials: everything it reads is
-// complete by then), all of whose threads take part in the reads (one memory latency, not one per 64 values);
-// one barrier inside; every thread returns the same answer.  red: 16 floats of LDS.
-constexpr float kPlanSpan = 60.f;
-__device__ __forceinline__ bool bwd_one_exp_ok(const float *__restrict__ ld_range, const float *__restrict__ lse_enc,
-                                               int bh, int parts, int M, int force_two, float *red)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // extremes of lse_enc2, as (max, -min), and of lse_dec2 likewise: one maximum each
-    float le_hi = -INFINITY, le_lo = -INFINITY, ld_hi = -INFINITY, ld_lo = -INFINITY;
-    bool nan = false;
-    for (int m = tid; m < M; m += 256) {
-        const float v = lse_enc[(size_t)bh * M + m] * 1.4426950408889634f;
-        nan |= v != v;
-        le_hi = fmaxf(le_hi, v);
-        le_lo = fmaxf(le_lo, -v);
-    }
-    for (int p = tid; p < parts; p += 256) {
-        const float a = ld_range[2 * ((size_t)bh * parts + p)], b = ld_range[2 * ((size_t)bh * parts + p) + 1];
-        nan |= a != a || b != b;
-        ld_lo = fmaxf(ld_lo, -a);
-        ld_hi = fmaxf(ld_hi, b);
-    }
-    if (nan) le_hi = INFINITY;                       // a NaN anywhere makes the test fail
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        le_hi = fmaxf(le_hi, __shfl_xor(le_hi, off));
-        le_lo = fmaxf(le_lo, __shfl_xor(le_lo, off));
-        ld_hi = fmaxf(ld_hi, __shfl_xor(ld_hi, off));
-        ld_lo = fmaxf(ld_lo, __shfl_xor(ld_lo, off));
-    }
-    if (lane == 0) { red[4 * wave] = le_hi; red[4 * wave + 1] = le_lo; red[4 * wave + 2] = ld_hi; red[4 * wave + 3] = ld_lo; }
-    __syncthreads();
-    float worst = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) worst = fmaxf(worst, red[i]);
-    return worst <= kPlanSpan && !force_two;
-}
-
 // ---- fp32 storage on the matrix cores (flare_mfma_f32.hip) ------------------------------------
 // Partial slots per (b,h) of the latent-major kernels (encode, dZ, dQ) = chunks of this split.
 Split mfma32_split(const flare_shape &s);
 int mfma32_encode(const flare_shape &s, const float *q, const float *k, const float *v, float *m_part, float *l_part,
                   float *o_part, float scale, hipStream_t stream);
 int mfma32_decode(const flare_shape &s, const float *q, const float *k, const float *z, float *y, float *lse_dec,
-                  float scale, hipStream_t stream);
+                  float scale, const MergeZ &g, hipStream_t stream);
 int mfma32_token_stats(const flare_shape &s, const float *q, const float *k, const float *z, const float *dy,
                        float *lse_dec2, float *delta, float scale, hipStream_t stream);
 // y, delta_out, ld_mul, ld_range, plan: as for the 16-bit launchers above
@@ -211,8 +172,9 @@ int mfma32_dq_partial(const flare_shape &s, const float *q, const float *k, cons
                       const float *z, const float *lse_enc, const float *dz, const float *eps, const float *lse_dec,
                       const float *delta, float ld_mul, const int *plan, float *dq_part, float scale, hipStream_t stream);
 int mfma32_dkdv(const flare_shape &s, const float *q, const float *k, const float *v, const float *dy, const float *z,
-                const float *lse_enc, const float *dz, const float *eps, const float *lse_dec, const float *delta,
-                float ld_mul, const int *plan, float *dk, float *dv, float scale, hipStream_t stream);
+                const float *lse_enc, const float *lse_dec, const float *delta, float ld_mul, float *dk, float *dv,
+                float scale, const MergeDz &g, hipStream_t stream);
+bool mfma32_inline(const flare_shape &s);   // do the decode and dK/dV kernels merge the slots?
 
 // ---- spectral analysis (Appendix C.1, Algorithm 1) ---------------------------------------------
 bool mfma_gram_supported(const flare_shape &s);

@@ -1,0 +1,239 @@
+// Fixed-order merges of partial slots, as device functions: the merge kernels call them, and where the slots of a
+// (b,h) are few the kernels that consume the merged rows call them themselves (every workgroup for itself, into LDS),
+// which saves a launch.  A merge kernel of this size costs 5 ... 9 us on the device (launch, two or three dependent
+// memory latencies) and about 2.5 us on the host; reading the slots again in every workgroup 1 ... 2 us.
+#ifndef FLARE_MERGE_H
+#define FLARE_MERGE_H
+
+#include "flare_internal.h"
+
+namespace flare {
+
+struct f16_t { uint16_t bits; };   // raw IEEE fp16 bits (a type of its own so that the row helpers can overload)
+
+// Slots that a consumer merges itself: few enough to be walked over in order, and no more bytes per (b,h) than a
+// workgroup reads in a microsecond or two from its L2.  (With more, the slot-parallel merge kernels are faster.)
+constexpr int kInlineSlots = 16;
+constexpr size_t kInlineBytes = 80 * 1024;
+inline bool merge_inline(const flare_shape &s, int parts)
+{
+    return parts <= kInlineSlots && (size_t)parts * s.M * (s.d + 2) * 4 <= kInlineBytes;
+}
+
+// ---- encode: z and lse_enc of one (b,h) -------------------------------------------------------
+struct MergeZ {
+    const float *m_part, *l_part, *o_part;   // slot p of latent m at [(b*h) * parts + p][M]
+    float *z, *lse_enc;                      // [b*h][M][d], [b*h][M]
+    int parts;                               // 0: z is complete, there is nothing to merge
+};
+
+// D / 4 threads per latent own four columns each; the slots are folded in order behind one maximum (exact in any order),
+// so the bits depend on the slot count only.  A slot with m = -inf is empty.  P >= g.parts: everything a thread needs of P
+// slots is requested before anything is used (one memory latency).
+template <int D, int P>
+__device__ __forceinline__ void merge_z_row(const MergeZ &g, int bh, int M, int m, int j, float *z_lds, bool write)
+{
+    const size_t s0 = (size_t)bh * g.parts * M + m;   // slot p of this latent: s0 + p * M
+    float mp[P], lp[P];
+    float4 oc[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const size_t slot = s0 + (size_t)min(p, g.parts - 1) * M;
+        mp[p] = g.m_part[slot];
+        lp[p] = g.l_part[slot];
+        oc[p] = *reinterpret_cast<const float4 *>(g.o_part + slot * D + 4 * j);
+    }
+    float gm = -INFINITY;
+#pragma unroll
+    for (int p = 0; p < P; ++p) gm = fmaxf(gm, mp[p]);
+    float l = 0.f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const float w = (p >= g.parts || mp[p] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mp[p] - gm);
+        l = fmaf(lp[p], w, l);
+        o.x = fmaf(oc[p].x, w, o.x);
+        o.y = fmaf(oc[p].y, w, o.y);
+        o.z = fmaf(oc[p].z, w, o.z);
+        o.w = fmaf(oc[p].w, w, o.w);
+    }
+    const float inv = 1.f / l;
+    const size_t idx = (size_t)bh * M + m;
+    o = make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
+    if (z_lds) *reinterpret_cast<float4 *>(z_lds + (size_t)m * D + 4 * j) = o;
+    if (write) {
+        *reinterpret_cast<float4 *>(g.z + idx * D + 4 * j) = o;
+        if (j == 0) g.lse_enc[idx] = (gm + log2f(l)) * kLn2;
+    }
+}
+// Rows m0 .. m1 by the nt threads of a workgroup; z_lds (when given) gets them, and with `write` they go to global memory.
+template <int D>
+__device__ __forceinline__ void merge_z_rows(const MergeZ &g, int bh, int M, int m0, int m1, int tid, int nt,
+                                             float *z_lds, bool write)
+{
+    constexpr int L = D / 4;
+    for (int m = m0 + tid / L; m < m1; m += nt / L) {
+        if (g.parts <= 4) merge_z_row<D, 4>(g, bh, M, m, tid % L, z_lds, write);
+        else if (g.parts <= 8) merge_z_row<D, 8>(g, bh, M, m, tid % L, z_lds, write);
+        else merge_z_row<D, kInlineSlots>(g, bh, M, m, tid % L, z_lds, write);
+    }
+}
+// ---- the variant of the last backward kernels ---------------------------------------------------
+// They exist with one and with two exponentials per score.
+// One exponential: P~ = 2^S2 as it comes, without a normaliser (S2 <= lse_enc2[m] and S2 <= lse_dec2[n], so with
+// both log-sum-exps of a (b,h) within +-kPlanSpan nothing overflows and every weight that matters is a normal
+// number), P = P~ e_m with e_m = 2^-lse_enc2[m] and R = P~ w_n with w_n = 2^-lse_dec2[n]:
+//   dS = P (a - eps) + R (c - delta) = P~ (e_m (a - eps_m) + w_n (c - delta_n)),   dV += (e_m dZ_m) P~.
+// e_m is folded into dZ where its partials are merged, BEFORE dZ is rounded to bf16 and eps = <dZ, Z> is formed
+// (bwd_one_exp_ok decides there, and the kernels that follow take dZ and eps as they find them), so that a and
+// eps still see the same rounded values and the score products need no correction k-step; w_n is a per-token
+// scalar.  Anything else (log-sum-exps beyond +-kPlanSpan, non-finite statistics) takes the two-exponential
+// form with dZ as it is.
+// ld_range[b*h][part] = (min, max) of lse_dec2 as the dZ kernels recorded it.
+// Called by a whole workgroup of at most 16 waves, all of whose threads take part in the reads (one memory latency, not
+// one per 64 values); one barrier inside; every thread returns the same answer.  red: 64 floats of LDS.
+constexpr float kPlanSpan = 60.f;
+__device__ __forceinline__ bool is_nan(float x) { return (__float_as_uint(x) & 0x7fffffffu) > 0x7f800000u; }
+__device__ __forceinline__ bool bwd_one_exp_ok(const float *__restrict__ ld_range, const float *__restrict__ lse_enc,
+                                               int bh, int parts, int M, int force_two, float *red)
+{
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
+    // the largest of lse_enc2, -lse_enc2, lse_dec2, -lse_dec2
+    float worst = -INFINITY;
+    bool nan = false;
+    for (int m = tid; m < M; m += nt) {
+        const float v = lse_enc[(size_t)bh * M + m] * kLog2e;
+        nan |= is_nan(v);
+        worst = fmaxf(worst, fabsf(v));
+    }
+    for (int p = tid; p < parts; p += nt) {
+        const float a = ld_range[2 * ((size_t)bh * parts + p)], b = ld_range[2 * ((size_t)bh * parts + p) + 1];
+        nan |= is_nan(a) || is_nan(b);
+        worst = fmaxf(worst, fmaxf(-a, b));
+    }
+    if (nan) worst = INFINITY;                       // a NaN anywhere makes the test fail
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) worst = fmaxf(worst, __shfl_xor(worst, off));
+    if (lane == 0) red[wave] = worst;
+    __syncthreads();
+    for (int i = 0; i < nt / 64; ++i) worst = fmaxf(worst, red[i]);
+    return worst <= kPlanSpan && !force_two;
+}
+
+// ---- dZ and eps of one (b,h) ------------------------------------------------------------------
+struct MergeDz {
+    const float *part, *ld_range;   // slots as above; ranges of lse_dec2
+    float *dz, *eps;                // [b*h][M][d], [b*h][M]
+    int *plan;                      // [b*h]: 1 = one exponential
+    int parts;                      // 0: dz, eps and plan are complete
+    int force_two;
+    unsigned lds;                   // byte offset of the merged rows in the workgroup's dynamic LDS
+};
+
+__device__ __forceinline__ float bf16_rounded(float x)
+{
+    uint32_t u = __float_as_uint(x);
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return __uint_as_float(u & 0xffff0000u);
+}
+__device__ __forceinline__ void add4(float4 &a, const float4 &b)
+{
+    a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+}
+// Four columns of a row summed over at most P slots in slot order, all of them requested first; slot p at p + i * stride.
+template <int P>
+__device__ __forceinline__ float4 sum_slots_upto(const float *__restrict__ p, size_t stride, int n)
+{
+    float4 t[P], a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < P; ++i) t[i] = *reinterpret_cast<const float4 *>(p + (size_t)min(i, n - 1) * stride);
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+        if (i < n) add4(a, t[i]);
+    return a;
+}
+// Row m (four columns, D / 4 lanes per row, called together) of dZ, scaled and rounded as its consumers want it, and eps_m
+// (in every lane of the row).
+template <int D>
+__device__ __forceinline__ float4 merge_dz_row(const float *__restrict__ part, const float *__restrict__ z,
+                                               const float *__restrict__ lse_enc, int bh, int M, int parts, int m,
+                                               int j, bool one_exp, bool round_bf16, float &eps)
+{
+    constexpr int L = D / 4;
+    const size_t idx = (size_t)bh * M + m, stride = (size_t)M * D;
+    const float *p = part + ((size_t)bh * parts * M + m) * D + 4 * j;
+    const float4 zr = *reinterpret_cast<const float4 *>(z + idx * D + 4 * j);
+    const float le = lse_enc[idx];
+    float4 a = parts <= 4 ? sum_slots_upto<4>(p, stride, parts) : parts <= 8 ? sum_slots_upto<8>(p, stride, parts)
+                                                                : sum_slots_upto<kInlineSlots>(p, stride, parts);
+    if (one_exp) {                                   // the one-exponential kernels take dZ scaled by 2^-lse_enc2[m]
+        const float em = exp2f(-le * kLog2e);
+        a = make_float4(a.x * em, a.y * em, a.z * em, a.w * em);
+    }
+    // The 16-bit kernels take dZ as a bf16 operand.  Rounding it here, before eps is formed, keeps
+    // a[m][n] = <dZ_m, V_n - Z_m> an exact expression in the rounded dZ (eps and the products see the same
+    // values), instead of leaving <V_n, rounding error> uncancelled in every score.
+    if (round_bf16) a = make_float4(bf16_rounded(a.x), bf16_rounded(a.y), bf16_rounded(a.z), bf16_rounded(a.w));
+    float e = fmaf(a.w, zr.w, fmaf(a.z, zr.z, fmaf(a.y, zr.y, a.x * zr.x)));
+#pragma unroll
+    for (int off = 1; off < L; off <<= 1) {          // fixed tree over the row's lanes (L is a power of two)
+        const float o = __shfl_xor(e, off);
+        e = ((j & off) == 0) ? (e + o) : (o + e);
+    }
+    eps = e;
+    return a;
+}
+// What a consuming workgroup needs of one (b,h): the variant, and rows of dZ and eps: merged into `lds` (M * D, then M
+// floats; with `write` they and the plan also go to global memory, for a later kernel) or in global memory.  Ends with
+// a barrier when it merges.  red: 64 floats of LDS.
+template <int D>
+__device__ __forceinline__ bool merged_dz(const MergeDz &g, const float *z, const float *lse_enc, int bh, int M,
+                                          bool round_bf16, bool write, float *lds, float *red, const float *&dz,
+                                          const float *&eps)
+{
+    dz = g.dz + (size_t)bh * M * D;
+    eps = g.eps + (size_t)bh * M;
+    if (g.parts == 0) return g.plan[bh] != 0;
+    constexpr int L = D / 4;
+    const bool one = bwd_one_exp_ok(g.ld_range, lse_enc, bh, g.parts, M, g.force_two, red);
+    const int j = threadIdx.x % L, rows = blockDim.x / L;
+    for (int m0 = 0; m0 < M; m0 += rows) {           // whole rows of lanes stay together (shuffles)
+        const int m = m0 + threadIdx.x / L;
+        float e;
+        const float4 a = merge_dz_row<D>(g.part, z, lse_enc, bh, M, g.parts, min(m, M - 1), j, one, round_bf16, e);
+        if (m < M) {
+            *reinterpret_cast<float4 *>(lds + (size_t)m * D + 4 * j) = a;
+            if (j == 0) lds[(size_t)M * D + m] = e;
+            if (write) {
+                *reinterpret_cast<float4 *>(g.dz + ((size_t)bh * M + m) * D + 4 * j) = a;
+                if (j == 0) g.eps[(size_t)bh * M + m] = e;
+            }
+        }
+    }
+    if (write && threadIdx.x == 0) g.plan[bh] = one ? 1 : 0;
+    __syncthreads();
+    dz = lds;
+    eps = lds + (size_t)M * D;
+    return one;
+}
+
+// ---- dQ ---------------------------------------------------------------------------------------
+// four neighbouring elements of a row
+__device__ __forceinline__ void store_four(float *p, const float4 &a) { *reinterpret_cast<float4 *>(p) = a; }
+__device__ __forceinline__ void store_four(uint16_t *p, const float4 &a)   // bf16
+{
+    *reinterpret_cast<uint2 *>(p) =
+        make_uint2((__float_as_uint(bf16_rounded(a.x)) >> 16) | __float_as_uint(bf16_rounded(a.y)),
+                   (__float_as_uint(bf16_rounded(a.z)) >> 16) | __float_as_uint(bf16_rounded(a.w)));
+}
+__device__ __forceinline__ void store_four(f16_t *p, const float4 &a)
+{
+    typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+    half4_t t;
+    t[0] = (_Float16)a.x; t[1] = (_Float16)a.y; t[2] = (_Float16)a.z; t[3] = (_Float16)a.w;
+    *reinterpret_cast<half4_t *>(p) = t;
+}
+
+}  // namespace flare
+
+#endif  // FLARE_MERGE_H

@@ -34,9 +34,10 @@ __device__ __forceinline__ void dq_body(
     const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
     const bf16_t *__restrict__ dy, const float *__restrict__ z, const float *__restrict__ lse_enc,
     const float *__restrict__ dz, const float *__restrict__ eps, const float *__restrict__ lse_dec2,
-    const float *__restrict__ delta, float ld_mul, const int *__restrict__ plan, float *__restrict__ dq_part,
+    const float *__restrict__ delta, float ld_mul, float *__restrict__ dq_part,
     TokStride ts, int H, int N, int M, int chunk_len, int parts, int G, int TG, float c2)
 {
+    // dz, eps: the rows of this (b,h)
     constexpr int D = padded_dim(DR);
     constexpr int KS = D / 16;
     // Row blocks of the dQ accumulation.  d <= 16: one 32x32 product per 16 columns (rows 16-31 of the K^T
@@ -60,7 +61,6 @@ __device__ __forceinline__ void dq_body(
     const int g = wave % G, tg = wave / G;
     const GridPos gp = grid_pos(ts, H, DR * 2);
     const int bh = gp.y, h = bh % H, chunk = gp.x;
-    if ((plan[bh] != 0) != ONE) return;         // the other variant owns this (b,h)
     const bool lower = hh == 0;
     uint16_t *lds = kt_all[wave];
     float (*wl)[32] = wl_all[ONE ? wave : 0];
@@ -101,7 +101,7 @@ __device__ __forceinline__ void dq_body(
             wu[1] = lower ? (us >> 16) : 0u;
             // slots 4,5 := -eps (hi + lo): with one exponential the a chain's correction rides in the same
             // product as the c chain's (against ones in the token operand), see the tile loop
-            wu[2] = (!PACK && lower) ? split_bf16_pair(real ? -eps[(size_t)bh * M + m] : 0.f) : 0u;
+            wu[2] = (!PACK && lower) ? split_bf16_pair(real ? -eps[m] : 0.f) : 0u;
             wu[3] = 0u;
             u_aug[b] = as_bf16x8(wu);
         }
@@ -114,7 +114,7 @@ __device__ __forceinline__ void dq_body(
         for (int s = 0; s < KS; ++s) {
             float zr[8], dr[8];
             row8_f32<DR>(z + ((size_t)bh * M + m) * DR, PACK ? 0 : (D / 2) * hh + 8 * s, zr);
-            row8_f32<DR>(dz + ((size_t)bh * M + m) * DR, (D / 2) * hh + 8 * s, dr);
+            row8_f32<DR>(dz + (size_t)m * DR, (D / 2) * hh + 8 * s, dr);
             if (!real) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) { zr[i] = 0.f; dr[i] = 0.f; }
@@ -135,7 +135,7 @@ __device__ __forceinline__ void dq_body(
             zl[b][s] = as_bf16x8(wzl);
         }
         u32x4 we;
-        we[0] = (lower != PACK) ? split_bf16_pair(real ? -eps[(size_t)bh * M + m] : 0.f) : 0u;
+        we[0] = (lower != PACK) ? split_bf16_pair(real ? -eps[m] : 0.f) : 0u;
         we[1] = 0u; we[2] = 0u; we[3] = 0u;
         dz_aug[b] = as_bf16x8(we);
         if constexpr (PACK) {   // slots 8,9 of the dZ operand := -eps (the rest of its upper half is zero)
@@ -400,12 +400,13 @@ __global__ __launch_bounds__(256, MINB) void bwd_dq_mfma_kernel(
     TokStride ts, int H, int N, int M, int chunk_len, int parts, int G, int TG, float c2)
 {
     const int bh = grid_pos(ts, H, DR * 2).y;
+    const float *dz_bh = dz + (size_t)bh * M * DR, *eps_bh = eps + (size_t)bh * M;
     if (plan[bh] != 0)
-        dq_body<DR, NB, MINB, true, F>(q, k, v, dy, z, lse_enc, dz, eps, lse_dec2, delta, ld_mul, plan, dq_part, ts, H, N,
-                                       M, chunk_len, parts, G, TG, c2);
+        dq_body<DR, NB, MINB, true, F>(q, k, v, dy, z, lse_enc, dz_bh, eps_bh, lse_dec2, delta, ld_mul, dq_part, ts, H, N, M,
+                                       chunk_len, parts, G, TG, c2);
     else
-        dq_body<DR, NB, MINB, false, F>(q, k, v, dy, z, lse_enc, dz, eps, lse_dec2, delta, ld_mul, plan, dq_part, ts, H, N,
-                                        M, chunk_len, parts, G, TG, c2);
+        dq_body<DR, NB, MINB, false, F>(q, k, v, dy, z, lse_enc, dz_bh, eps_bh, lse_dec2, delta, ld_mul, dq_part, ts, H, N, M,
+                                        chunk_len, parts, G, TG, c2);
 }
 
 // ============================================================================================
@@ -447,7 +448,7 @@ __device__ __forceinline__ void dkdv_body(
     const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
     const bf16_t *__restrict__ dy, const float *__restrict__ z, const float *__restrict__ lse_enc,
     const float *__restrict__ dz, const float *__restrict__ eps, const float *__restrict__ lse_dec2,
-    const float *__restrict__ delta, float ld_mul, const int *__restrict__ plan, bf16_t *__restrict__ dk,
+    const float *__restrict__ delta, float ld_mul, bf16_t *__restrict__ dk,
     bf16_t *__restrict__ dv, float *__restrict__ acc32, float *__restrict__ dq_part, TokStride ts, int H, int N,
     int Mtot, int m0, float c2, float scale)
 {
@@ -503,18 +504,17 @@ __device__ __forceinline__ void dkdv_body(
     const int tid = threadIdx.x;
     const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // known to be wave-uniform: scalar unit
-    const GridPos gp = grid_pos(ts, H, DR * 2);
+    const GridPos gp = grid_pos_latents(ts, H, DR * 2);
     const int bh = gp.y, h = bh % H;
     const bool lower = hh == 0;
-    if ((plan[bh] != 0) != ONE) return;         // the other variant owns this (b,h); uniform over the workgroup
     constexpr float kap = 0.f;                  // w[n] = 2^(kap - lse_dec2[n])
 
     // ---- build the operand images ----
     {
         const bf16_t *qh_ = q + (size_t)h * ts.sq + (size_t)m0 * DR;
         const float *zb = z + ((size_t)bh * Mtot + m0) * DR;
-        const float *dzb = dz + ((size_t)bh * Mtot + m0) * DR;
-        const float *eb = eps + (size_t)bh * Mtot + m0;
+        const float *dzb = dz + (size_t)m0 * DR;   // (dz, eps: the rows of this (b,h), in global memory or merged into LDS)
+        const float *eb = eps + m0;
         const float *leb = lse_enc + (size_t)bh * Mtot + m0;
         // Padding latents (at or beyond Mtot; mleft = real ones from m0 on): loads are clamped to the last
         // real latent and every value that could reach dK or dV is zero -- q, Z, dZ, eps, u and the ones
@@ -966,17 +966,19 @@ __device__ __forceinline__ void dkdv_body(
 #define FLARE_DKDV_PARAMS                                                                                        \
     const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,                    \
         const bf16_t *__restrict__ dy, const float *__restrict__ z, const float *__restrict__ lse_enc,           \
-        const float *__restrict__ dz, const float *__restrict__ eps, const float *__restrict__ lse_dec2,         \
-        const float *__restrict__ delta, float ld_mul, const int *__restrict__ plan, bf16_t *__restrict__ dk,    \
+        const float *__restrict__ lse_dec2, const float *__restrict__ delta, float ld_mul, bf16_t *__restrict__ dk, \
         bf16_t *__restrict__ dv, float *__restrict__ acc32, float *__restrict__ dq_part, TokStride ts, int H,    \
-        int N, int Mtot, int m0, float c2, float scale
+        int N, int Mtot, int m0, float c2, float scale, MergeDz merge
 #define FLARE_DKDV_PASS \
-    q, k, v, dy, z, lse_enc, dz, eps, lse_dec2, delta, ld_mul, plan, dk, dv, acc32, dq_part, ts, H, N, Mtot, m0, c2, scale
+    q, k, v, dy, z, lse_enc, dz_bh, eps_bh, lse_dec2, delta, ld_mul, dk, dv, acc32, dq_part, ts, H, N, Mtot, m0, c2, scale
 
 // One variant per launch (the workgroups of a (b,h) that the plan gives to the other variant leave at once) ...
 template <int DR, int MT, bool DQ, bool ONE, bool F, int WV = 8>
 __global__ __launch_bounds__(64 * WV, 1) void bwd_dkdv_mfma_kernel(FLARE_DKDV_PARAMS)
 {
+    const int bh = grid_pos_latents(ts, H, DR * 2).y;
+    if ((merge.plan[bh] != 0) != ONE) return;   // the other variant owns this (b,h); uniform over the workgroup
+    const float *dz_bh = merge.dz + (size_t)bh * Mtot * DR, *eps_bh = merge.eps + (size_t)bh * Mtot;
     dkdv_body<DR, MT, DQ, ONE, F, WV>(FLARE_DKDV_PASS);
 }
 
@@ -986,9 +988,16 @@ __global__ __launch_bounds__(64 * WV, 1) void bwd_dkdv_mfma_kernel(FLARE_DKDV_PA
 template <int DR, int MT, bool DQ, bool F, bool ZL = false>
 __global__ __launch_bounds__(512, 1) void bwd_dkdv_planned_kernel(FLARE_DKDV_PARAMS)
 {
-    const int bh = grid_pos(ts, H, DR * 2).y;
-    if (plan[bh] != 0) dkdv_body<DR, MT, DQ, true, F, 8, ZL>(FLARE_DKDV_PASS);
-    else dkdv_body<DR, MT, DQ, false, F, 8, ZL>(FLARE_DKDV_PASS);
+    extern __shared__ __attribute__((aligned(16))) u32x4 img[];
+    __shared__ float red[64];
+    const GridPos gp = grid_pos_latents(ts, H, DR * 2);
+    float *rows = reinterpret_cast<float *>(reinterpret_cast<char *>(img) + merge.lds);
+    const float *dz_bh, *eps_bh;
+    // (a dQ kernel of its own runs behind this one and reads what workgroup 0 writes)
+    if (merged_dz<DR>(merge, z, lse_enc, gp.y, Mtot, true, !DQ && gp.x == 0, rows, red, dz_bh, eps_bh))
+        dkdv_body<DR, MT, DQ, true, F, 8, ZL>(FLARE_DKDV_PASS);
+    else
+        dkdv_body<DR, MT, DQ, false, F, 8, ZL>(FLARE_DKDV_PASS);
 }
 #undef FLARE_DKDV_PASS
 #undef FLARE_DKDV_PARAMS
@@ -1067,9 +1076,9 @@ bool mfma_dq_fused(const flare_shape &s)
 }
 
 int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v, const void *dy, const float *z,
-              const float *lse_enc, const float *dz, const float *eps, const float *lse_dec2, const float *delta,
-              float ld_mul, const int *plan, void *dk, void *dv, float *acc32, float *dq_part, int m0, float scale,
-              hipStream_t stream)
+              const float *lse_enc, const float *lse_dec2, const float *delta,
+              float ld_mul, void *dk, void *dv, float *acc32, float *dq_part, int m0, float scale,
+              const MergeDz &merge_in, hipStream_t stream)
 {
     // Both variants (one or two exponentials per score, whichever the plan names for a (b,h)) for the latent chunk
     // that starts at m0.  dq_part != NULL: also write the dQ partials (mfma_dq_fused(s) must hold), slot layout
@@ -1085,18 +1094,18 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
     // dQ from this kernel at d = 16 with fewer tokens than latents: one more image, the lo term of Z (see the kernel)
     const bool zlo = fuse && s.d == 16 && s.N < s.M;
     const int na = (zlo ? 5 : 4) * KS + 1;
-    const size_t lds = (size_t)MT * (na + 4 * HV) * 1024 + (fuse ? 8 * kFusedWaveLds * 2 : 0);
+    size_t lds = (size_t)MT * (na + 4 * HV) * 1024 + (fuse ? 8 * kFusedWaveLds * 2 : 0);
+    MergeDz merge = merge_in;
+    merge.lds = (unsigned)lds;
+    if (merge.parts) lds += (size_t)s.M * (s.d + 1) * 4;
     const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *vv = (const bf16_t *)v, *gg = (const bf16_t *)dy;
     const bool f16 = s.dtype == FLARE_F16;
 #define FLARE_DKDV_LAUNCH(KERN, THREADS)                                                                         \
     do {                                                                                                         \
         auto kern = KERN;                                                                                        \
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                (int)lds) != hipSuccess)                                                         \
-            return FLARE_ELAUNCH;                                                                                \
-        kern<<<grid, THREADS, lds, stream>>>(qq, kk, vv, gg, z, lse_enc, dz, eps, lse_dec2, delta, ld_mul, plan, \
+        kern<<<grid, THREADS, lds, stream>>>(qq, kk, vv, gg, z, lse_enc, lse_dec2, delta, ld_mul, \
                                              (bf16_t *)dk, (bf16_t *)dv, acc32, dq_part, tok_stride(s), s.H,     \
-                                             s.N, s.M, m0, c2, scale);                                           \
+                                             s.N, s.M, m0, c2, scale, merge);                                    \
     } while (0)
     if (s.d == 32 && MT == 8) {
         // d = 32, 256 latents: the one-exponential variant fits 168 registers, so twelve waves (three per SIMD) share
@@ -1170,6 +1179,14 @@ size_t mfma_dkdv_acc_bytes(const flare_shape &s)
 {
     if (s.M <= kLatChunk) return 0;
     return ((size_t)s.B * s.H * s.N * s.d * 4 * 2 + 255) & ~(size_t)255;
+}
+
+// With few dZ slots the dK/dV kernel merges them.  Not with more than 256 latents, whose chunks are launches of
+// their own, nor at d = 32 with 256, where dK/dV is one launch per variant.
+bool mfma_dz_inline(const flare_shape &s)
+{
+    const int Me = lat_eff(s.M);
+    return s.M <= kLatChunk && !(s.d == 32 && (Me == 192 || Me == 256)) && merge_inline(s, mfma_plan(s).parts);
 }
 
 // partial slots per (b,h) that mfma_dq_partial writes

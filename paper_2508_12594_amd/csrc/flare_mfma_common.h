@@ -33,6 +33,7 @@
 #define FLARE_MFMA_COMMON_H
 
 #include "flare_internal.h"
+#include "flare_merge.h"
 
 namespace flare {
 namespace {
@@ -435,6 +436,19 @@ __device__ __forceinline__ GridPos grid_pos(const TokStride &ts, int H, int row_
     const int yg = g / gx;                                  // b * hgroups + group of heads
     p.x = g % gx;
     p.y = (yg / hgroups) * H + (yg % hgroups) * hg + hs;
+    return p;
+}
+
+// The same for the token-major kernels, all of whose workgroups of one (b,h) read the same latent-side rows (and, where
+// they merge them, partial slots): with whole rounds of the eight XCDs a (b,h) stays on one of them.
+__device__ __forceinline__ GridPos grid_pos_latents(const TokStride &ts, int H, int row_bytes)
+{
+    GridPos p = grid_pos(ts, H, row_bytes);
+    if (ts.sh >= ts.sn && gridDim.y % 8 == 0) {
+        const int L = p.x + (int)gridDim.x * p.y, slot = L >> 3;
+        p.y = (slot / (int)gridDim.x) * 8 + (L & 7);
+        p.x = slot % (int)gridDim.x;
+    }
     return p;
 }
 

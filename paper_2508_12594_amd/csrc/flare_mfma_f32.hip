@@ -586,8 +586,9 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
 // MODE 2 has a one- and a two-exponential form (plan) as the latent-major kernel.
 // ============================================================================================
 struct TokenArgs {
-    const float *q, *k, *v, *dy, *z, *lse_enc, *dz, *eps, *lse_dec, *delta;
-    const int *plan;
+    const float *q, *k, *v, *dy, *z, *lse_enc, *lse_dec, *delta;
+    MergeZ mz;               // MODE 0
+    MergeDz mdz;             // MODE 2
     float *out0, *out1;      // y, lse_dec | lse_dec2, delta | dk, dv
     TokStride ts;
     int H, N, M, CT;
@@ -604,7 +605,7 @@ struct TokenLds {   // in uint16 units, per latent tile
 };
 
 constexpr int kTokenWaves = 8;
-template <int DR, int MODE, int T>
+template <int DR, int MODE, int T, bool MERGE>
 __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(const TokenArgs A)
 {
     using Geo = F32Geo<DR>;
@@ -613,12 +614,29 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
     const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int waves = blockDim.x >> 6;
-    const GridPos gp = grid_pos(A.ts, A.H, DR * 4);
+    const GridPos gp = grid_pos_latents(A.ts, A.H, DR * 4);
     const int bh = gp.y, h = bh % A.H;
     const size_t base = tok_base(A.ts, bh, A.H), rows = (size_t)bh * A.N;
     const int M = A.M, MT = (M + 31) / 32, CT = A.CT, chunks = (MT + CT - 1) / CT;
     const TrLane tl(lane);
-    const bool one_exp = MODE == 2 && A.plan[bh] != 0;
+
+    // rows of z, dZ and eps: in global memory, or (few partial slots, T == 1) merged by this workgroup into LDS behind
+    // the planes
+    const float *zr = A.z + (size_t)bh * M * DR, *dzr = nullptr, *epr = nullptr;
+    bool one_exp = false;
+    float *const merged = reinterpret_cast<float *>(smem + A.CT * L::TILE);
+    if constexpr (MERGE && MODE == 0) {
+        merge_z_rows<DR>(A.mz, bh, M, 0, M, threadIdx.x, blockDim.x, merged, gp.x == 0);
+        __syncthreads();
+        zr = merged;
+    } else if constexpr (MERGE && MODE == 2) {
+        __shared__ float red[64];
+        one_exp = merged_dz<DR>(A.mdz, A.z, A.lse_enc, bh, M, false, gp.x == 0, merged, red, dzr, epr);
+    } else if constexpr (MODE == 2) {
+        dzr = A.mdz.dz + (size_t)bh * M * DR;
+        epr = A.mdz.eps + (size_t)bh * M;
+        one_exp = A.mdz.plan[bh] != 0;
+    }
 
     // planes of the latent tiles of one chunk
     auto fill = [&](int chunk) {
@@ -630,7 +648,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
             const int mc = min(mm, M - 1);
             float x[8];
             const float *src = a == 0 ? A.q + (size_t)h * A.ts.sq + (size_t)mc * DR
-                                      : (a == 1 ? A.z : A.dz) + ((size_t)bh * M + mc) * DR;
+                                      : (a == 1 ? zr : dzr) + (size_t)mc * DR;
             load_piece<DR>(src + 8 * piece, x);
             const float f = mm >= M ? 0.f : a == 0 ? A.c2 : 1.f;
 #pragma unroll
@@ -648,7 +666,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
                 float *stat = reinterpret_cast<float *>(tile + L::ST);
                 if (a == 0) stat[row & 31] = mm < M ? 0.f : -1e30f;   // no weight for the padding latents
                 if constexpr (MODE == 2) {
-                    if (a == 1) stat[32 + (row & 31)] = mm < M ? -A.eps[(size_t)bh * M + mc] : 0.f;
+                    if (a == 1) stat[32 + (row & 31)] = mm < M ? -epr[mc] : 0.f;
                     if (a == 2) stat[64 + (row & 31)] = A.lse_enc[(size_t)bh * M + mc] * kLog2e;
                 }
             }
@@ -834,7 +852,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
 // ---- launches -------------------------------------------------------------------------------
 // Latent-major: up to 8 waves per workgroup; one 32-latent tile per wave, what is left of the 8 waves splits the
 // tokens as far as two staging buffers of kStageLds hold a tile for each.
-constexpr int kStageLds = 48 * 1024;
+constexpr int kStageLds = 80 * 1024;   // (two workgroups per CU)
 constexpr int kWaves = 4096;        // waves a launch aims at: 16 per CU
 constexpr int kWorkgroups = 512;    // and workgroups of the token-major kernels
 struct LatentGeom { int G, TG, zdim; };
@@ -889,14 +907,26 @@ int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t 
     TokenArgs A = a;
     const bool fits = MT <= CTMAX;
     A.CT = fits ? MT : CTMAX;
-    const size_t lds = (size_t)A.CT * L::TILE * 2;
-    const int waves = kTokenWaves, batch = waves * (fits ? 1 : MODE == 2 ? 2 : 4);
+    size_t lds = (size_t)A.CT * L::TILE * 2;
+    if (fits && (MODE == 0 ? A.mz.parts : A.mdz.parts) != 0) lds += (size_t)s.M * (s.d + 1) * 4;
+    const bool merge = fits && (MODE == 0 ? A.mz.parts : A.mdz.parts) != 0;
+    // eight waves share a workgroup's planes; with less than half of the CUs busy that way, four (1024 tokens, 4 heads:
+    // dK/dV 17 -> 15.5 us)
+    const int waves = (tiles + kTokenWaves - 1) / kTokenWaves * BH <= 128 ? kTokenWaves / 2 : kTokenWaves;
+    const int batch = waves * (fits ? 1 : MODE == 2 ? 2 : 4);
     int blocks = (tiles + batch - 1) / batch;
     const int most = (kWorkgroups + BH - 1) / BH;
     if (blocks > most) blocks = most;
     LaunchTimer t(kid, stream);
-    if (fits) token_pass_f32_kernel<DR, MODE, 1><<<dim3(blocks, BH), 64 * waves, lds, stream>>>(A);
-    else token_pass_f32_kernel<DR, MODE, MODE == 2 ? 2 : 4><<<dim3(blocks, BH), 64 * waves, lds, stream>>>(A);
+    const dim3 grid(blocks, BH);
+    if constexpr (MODE != 1) {
+        if (merge) {
+            token_pass_f32_kernel<DR, MODE, 1, true><<<grid, 64 * waves, lds, stream>>>(A);
+            return check_launch();
+        }
+    }
+    if (fits) token_pass_f32_kernel<DR, MODE, 1, false><<<grid, 64 * waves, lds, stream>>>(A);
+    else token_pass_f32_kernel<DR, MODE, MODE == 2 ? 2 : 4, false><<<grid, 64 * waves, lds, stream>>>(A);
     return check_launch();
 }
 
@@ -913,19 +943,28 @@ int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t 
 
 }  // namespace
 
-// Chunks of tokens of the latent-major kernels: enough for kWaves waves, at least one stage of the encode and at most
-// 8192 tokens long (a chunk's sums are taken one after the other in fp32).
+// Chunks of tokens of the latent-major kernels: enough for kWaves waves, at least one stage of the encode and kMinChunk
+// tokens (shorter ones would cost more in slots to merge than they gain) and at most 8192 tokens long (a chunk's sums are taken one after the other in fp32).
 Split mfma32_split(const flare_shape &s)
 {
+    constexpr int kMinChunk = 128;
     const int tile = s.d <= 8 ? LatentLds<8, 0>::TILE : s.d == 16 ? LatentLds<16, 0>::TILE : LatentLds<32, 0>::TILE;
     const LatentGeom g = latent_geom(s.M, tile * 2);
     const int stage = 32 * g.TG, per = s.B * s.H * g.zdim * g.G * g.TG;
     const int stages = (s.N + stage - 1) / stage;
     int want = (kWaves + per - 1) / per;
+    const int most = (s.N + kMinChunk - 1) / kMinChunk;
+    if (want > most) want = most;
     if (want > stages) want = stages;
     int len = (stages + want - 1) / want * stage;
     if (len > 8192) len = 8192;
     return Split{(s.N + len - 1) / len, len};
+}
+
+// The decode and dK/dV kernels merge the slots where these are few and the merged rows fit beside all latents' planes.
+bool mfma32_inline(const flare_shape &s)
+{
+    return s.M <= (s.d == 32 ? 128 : 256) && merge_inline(s, mfma32_split(s).chunks);
 }
 
 int mfma32_encode(const flare_shape &s, const float *q, const float *k, const float *v, float *m_part, float *l_part,
@@ -958,9 +997,10 @@ int mfma32_dq_partial(const flare_shape &s, const float *q, const float *k, cons
     FLARE_D(s, (launch_latent<D, 2>(s, a, KID_BWD_DQ_PARTIAL, stream)));
 }
 int mfma32_decode(const flare_shape &s, const float *q, const float *k, const float *z, float *y, float *lse_dec,
-                  float scale, hipStream_t stream)
+                  float scale, const MergeZ &g, hipStream_t stream)
 {
     TokenArgs a{};
+    a.mz = g;
     a.q = q; a.k = k; a.z = z; a.out0 = y; a.out1 = lse_dec;
     a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e;
     FLARE_D(s, (launch_token<D, 0>(s, a, KID_DECODE, stream)));
@@ -974,12 +1014,13 @@ int mfma32_token_stats(const flare_shape &s, const float *q, const float *k, con
     FLARE_D(s, (launch_token<D, 1>(s, a, KID_BWD_TOKEN_STATS, stream)));
 }
 int mfma32_dkdv(const flare_shape &s, const float *q, const float *k, const float *v, const float *dy, const float *z,
-                const float *lse_enc, const float *dz, const float *eps, const float *lse_dec, const float *delta,
-                float ld_mul, const int *plan, float *dk, float *dv, float scale, hipStream_t stream)
+                const float *lse_enc, const float *lse_dec, const float *delta, float ld_mul, float *dk, float *dv,
+                float scale, const MergeDz &g, hipStream_t stream)
 {
     TokenArgs a{};
-    a.q = q; a.k = k; a.v = v; a.dy = dy; a.z = z; a.lse_enc = lse_enc; a.dz = dz; a.eps = eps;
-    a.lse_dec = lse_dec; a.delta = delta; a.ld_mul = ld_mul; a.plan = plan; a.out0 = dk; a.out1 = dv;
+    a.mdz = g;
+    a.q = q; a.k = k; a.v = v; a.dy = dy; a.z = z; a.lse_enc = lse_enc;
+    a.lse_dec = lse_dec; a.delta = delta; a.ld_mul = ld_mul; a.out0 = dk; a.out1 = dv;
     a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e; a.scale = scale;
     FLARE_D(s, (launch_token<D, 2>(s, a, KID_BWD_DKDV, stream)));
 }

@@ -26,11 +26,12 @@ namespace {
 // MODE 0 writes y and, when lse_dec2 is not NULL, log sum_m exp(S[m][n]) (natural log) there.
 // MODE 1 (first step of the backward when nothing was saved) writes per token
 //   lse_dec2[n] = log2 sum_m 2^S2[m][n]   and   delta[n] = <dY_n, Y_n>   (Y_n kept in fp32).
-template <int DR, int MT, bool PRE, int MINB, int MODE, bool F>
+template <int DR, int MT, bool PRE, int MINB, int MODE, bool F, bool MERGE>
 __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
     const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const float *__restrict__ z,
     bf16_t *__restrict__ y, const bf16_t *__restrict__ dy, float *__restrict__ lse_dec2,
-    float *__restrict__ delta, TokStride ts, TokStride ts_y, int H, int N, int Mtot, int m0, float c2, int flags)
+    float *__restrict__ delta, TokStride ts, TokStride ts_y, int H, int N, int Mtot, int m0, float c2, int flags,
+    MergeZ merge)
 {
     // flags: bit 0 (d <= 8): Z enters the value product as a hi + lo pair (see the Zaug operand below);
     // bit 1 (MODE 0): y is an fp32 tensor of the same layout (flare_shape.y_f32)
@@ -48,7 +49,7 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
     constexpr bool PACK = PRE && pack_dim(DR);   // q' hi | lo in one operand, keys repeated in both lane halves
     const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // known to be wave-uniform: scalar unit
-    const GridPos gp = grid_pos(ts, H, DR * 2);
+    const GridPos gp = grid_pos_latents(ts, H, DR * 2);
     const int bh = gp.y, h = bh % H;
     const bool flip = c2 < 0.f;
     const float ac2 = PRE ? c2 : fabsf(c2);
@@ -70,6 +71,12 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
     bf16x8 zt[ZLDS ? 1 : HV][ZLDS ? 1 : 2 * MT];
     {
         const float *zb = z + ((size_t)bh * Mtot + m0) * DR;
+        if constexpr (MERGE) {   // few encode slots: every workgroup merges them for itself, into dynamic LDS
+            extern __shared__ __attribute__((aligned(16))) float z_rows[];
+            merge_z_rows<DR>(merge, bh, Mtot, 0, Mtot, threadIdx.x, 256, z_rows, gp.x == 0);   // (one also writes them)
+            __syncthreads();
+            zb = z_rows;
+        }
 #pragma unroll
         for (int hv = 0; hv < HV; ++hv)
 #pragma unroll
@@ -420,7 +427,7 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
 // ahead; the value rows of consecutive tiles alternate between two sets of registers (a copy of
 // a load in flight would be waited for in the tile that issued it).  The MFMAs of the next
 // latent tile (or of the next token tile) are issued before the vector work on the current one.
-// Output per wave: (c, row sums, unnormalised O) for its latents = one partial slot.
+// Output per chunk: (c, row sums, unnormalised O) of its latents = one partial slot.
 // ============================================================================================
 // MODE 1 (second step of the backward) reuses the same machinery for dZ = R^T dY: the values are
 // dY, the weights are R^T[n][m] = 2^(S2 - lse_dec2[n]) with the per-token -lse_dec2 as the value the score
@@ -429,7 +436,7 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
 // (ld_mul = log2 e when the array holds the forward's natural-log statistic).  When y_tok is given,
 // every wave also forms delta[n] = <dY_n, Y_n> from the rows it streams anyway (no branch in the
 // loop), and the waves of latent group 0 store it to delta_out for the two kernels that follow.
-// Those waves also record the smallest and largest lse_dec2 they met, ld_range[part] = (min, max),
+// The smallest and largest lse_dec2 of a chunk are recorded, ld_range[part] = (min, max),
 // from which bwd_one_exp_ok decides which variant of the next two kernels may run.
 template <int DR, int NB, int MINB, int MODE, bool F, bool Y32 = false>
 __global__ __launch_bounds__(256, MINB) void encode_mfma_kernel(
@@ -921,26 +928,77 @@ __global__ __launch_bounds__(256, MINB) void encode_mfma_kernel(
 #pragma unroll
         for (int b = 0; b < NB; ++b) l[b] += __shfl_xor(l[b], 32);
     }
-    // partial slot of this wave: (bh, chunk*TG + tg), latents lat0 .. lat0 + 32*NB
-    if (tg >= TG) return;
-    const size_t part = (size_t)bh * parts + (size_t)chunk * TG + tg;
-    if (MODE == 1 && ld_range != nullptr && g == 0 && blockIdx.z == 0) {
+    // One slot per chunk: the TG waves that share latents are folded in order, one latent tile at a time, through the
+    // value tiles' LDS (every wave is done with its own).  Waves without a tile have nothing to add.
+    if (TG > 1) {
+        constexpr int VALS = WIDE ? 16 : 9;       // accumulator registers that hold results (d <= 16: the denominator too)
+        const int active = min(TG, tiles);
+        float *mine = reinterpret_cast<float *>(vt_all[wave]);
+        static_assert((VALS + 2) * 64 * 4 <= 2 * BUF * 2, "a wave's share of a slot fits its value tiles");
 #pragma unroll
-        for (int off = 1; off < 32; off <<= 1) {   // both lane halves hold the same tokens
+        for (int b = 0; b < NB; ++b) {
+            if (b > 0) __syncthreads();
+            if (tg > 0 && tg < active) {
+#pragma unroll
+                for (int i = 0; i < VALS; ++i) mine[i * 64 + lane] = o[b][0][i];
+                if constexpr (MODE == 0) {
+                    mine[VALS * 64 + lane] = c[b];
+                    mine[(VALS + 1) * 64 + lane] = l[b];
+                }
+            }
+            __syncthreads();
+            if (tg == 0) {
+                for (int t = 1; t < active; ++t) {
+                    const float *r = reinterpret_cast<const float *>(vt_all[t * G + g]);
+                    float wa = 1.f, wb = 1.f;
+                    if constexpr (MODE == 0) {     // (both zero, and so no exponentials, after the plain sweep)
+                        const float ct = r[VALS * 64 + lane], cn = fmaxf(c[b], ct);
+                        if (__any(c[b] != ct)) {
+                            wa = fast_exp2(c[b] - cn);
+                            wb = fast_exp2(ct - cn);
+                            c[b] = cn;
+                        }
+                        l[b] = l[b] * wa + r[(VALS + 1) * 64 + lane] * wb;
+                    }
+#pragma unroll
+                    for (int i = 0; i < VALS; ++i) o[b][0][i] = o[b][0][i] * wa + r[i * 64 + lane] * wb;
+                }
+            }
+        }
+        if constexpr (MODE == 1) {
+            float *range = ld_all[wave];          // (its last values were read a tile ago)
+#pragma unroll
+            for (int off = 1; off < 32; off <<= 1) {   // both lane halves hold the same tokens
+                nl_min = fminf(nl_min, __shfl_xor(nl_min, off));
+                nl_max = fmaxf(nl_max, __shfl_xor(nl_max, off));
+            }
+            if (lane == 0) { range[0] = nl_min; range[1] = nl_max; }
+            __syncthreads();
+            if (tg == 0)
+                for (int t = 1; t < active; ++t) {
+                    nl_min = fminf(nl_min, ld_all[t * G + g][0]);
+                    nl_max = fmaxf(nl_max, ld_all[t * G + g][1]);
+                }
+        }
+    } else if constexpr (MODE == 1) {
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) {
             nl_min = fminf(nl_min, __shfl_xor(nl_min, off));
             nl_max = fmaxf(nl_max, __shfl_xor(nl_max, off));
         }
-        if (lane == 0) {   // a wave without tiles leaves (+inf, -inf): neutral
-            ld_range[2 * part] = -nl_max;
-            ld_range[2 * part + 1] = -nl_min;
-        }
+    }
+    if (tg > 0) return;
+    const size_t part = (size_t)bh * parts + chunk;
+    if (MODE == 1 && ld_range != nullptr && g == 0 && blockIdx.z == 0 && lane == 0) {
+        ld_range[2 * part] = -nl_max;
+        ld_range[2 * part + 1] = -nl_min;
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         if (lat0 + 32 * b + l32 >= M) continue;
         const size_t slot = part * M + lat0 + 32 * b + l32;
         if (MODE == 0 && hh == 0) {
-            m_part[slot] = (cnt > 0) ? c[b] : -INFINITY;
+            m_part[slot] = c[b];
             l_part[slot] = ROWSUM ? l[b] : o[b][0][8];
         }
 #pragma unroll
@@ -1077,7 +1135,7 @@ MfmaPlan mfma_plan(const flare_shape &s)
     const int BH = s.B * s.H;
     // each chunk gives every token group at least 8 tiles of 32 tokens
     p.enc = plan_split(s.N, BH, 256 * e.TG, kEncodeTargetBlocks);
-    p.parts = p.enc.chunks * e.TG;
+    p.parts = p.enc.chunks;
     return p;
 }
 
@@ -1090,8 +1148,8 @@ size_t mfma_fwd_bytes(const flare_shape &s)
     return valu_fwd_layout(s, sp, nullptr, nullptr, nullptr, nullptr);
 }
 
-int mfma_encode(const flare_shape &s, const void *q, const void *k, const void *v, float *z, float *lse_enc,
-                float scale, void *ws, hipStream_t stream)
+int mfma_encode_partial(const flare_shape &s, const void *q, const void *k, const void *v, float *z, float *lse_enc,
+                        float scale, void *ws, MergeZ *g, hipStream_t stream)
 {
     const MfmaPlan p = mfma_plan(s);
     const EncGeom e = enc_geom(lat_eff(s.M), padded_dim(s.d));
@@ -1135,8 +1193,17 @@ int mfma_encode(const flare_shape &s, const void *q, const void *k, const void *
 #undef FLARE_ENC_NB
 #undef FLARE_ENC
     }
-    if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
-    return launch_encode_merge(s, m_part, l_part, o_part, z, lse_enc, p.parts, stream);
+    *g = MergeZ{m_part, l_part, o_part, z, lse_enc, p.parts};
+    return check_launch();
+}
+
+int mfma_encode(const flare_shape &s, const void *q, const void *k, const void *v, float *z, float *lse_enc,
+                float scale, void *ws, hipStream_t stream)
+{
+    MergeZ g;
+    const int rc = mfma_encode_partial(s, q, k, v, z, lse_enc, scale, ws, &g, stream);
+    if (rc != FLARE_OK) return rc;
+    return launch_encode_merge(s, g.m_part, g.l_part, g.o_part, z, lse_enc, g.parts, stream);
 }
 
 // dZ partials of the backward (the encode machinery with values dY and weights R^T)
@@ -1196,8 +1263,9 @@ int mfma_dz_partial(const flare_shape &s, const void *q, const void *k, const vo
 template <int MODE>
 static int launch_decode_family(const flare_shape &s, const void *q, const void *k, const float *z, void *y,
                                 TokStride ts_y, const void *dy, float *lse_dec2, float *delta, int m0, int Mc,
-                                float scale, hipStream_t stream, int flags = 0)
+                                float scale, const MergeZ &merge, hipStream_t stream, int flags = 0)
 {
+    const size_t lds = merge.parts ? (size_t)s.M * s.d * 4 : 0;
     const int BH = s.B * s.H;
     const int tiles = (s.N + 31) / 32;
     // d = 32 with 192 or 256 latents (Z in LDS, 168 registers): three workgroups fit a CU
@@ -1210,13 +1278,23 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
     bf16_t *yy = (bf16_t *)y;
     LaunchTimer t(MODE == 0 ? KID_DECODE : KID_BWD_TOKEN_STATS, stream);
     const bool f16 = s.dtype == FLARE_F16;
-#define FLARE_DEC_ARGS qq, kk, z, yy, gg, lse_dec2, delta, tok_stride(s), ts_y, s.H, s.N, s.M, m0, c2, flags
+#define FLARE_DEC_ARGS qq, kk, z, yy, gg, lse_dec2, delta, tok_stride(s), ts_y, s.H, s.N, s.M, m0, c2, flags, merge
+#define FLARE_DEC_F(DD, MTT, PREE, MINB, FF)                                                                       \
+    do {                                                                                                           \
+        if constexpr (MODE == 0) {                                                                                 \
+            if (merge.parts) {                                                                                     \
+                decode_mfma_kernel<DD, MTT, PREE, MINB, 0, FF, true><<<grid, 256, lds, stream>>>(FLARE_DEC_ARGS);  \
+                break;                                                                                             \
+            }                                                                                                      \
+        }                                                                                                          \
+        decode_mfma_kernel<DD, MTT, PREE, MINB, MODE, FF, false><<<grid, 256, 0, stream>>>(FLARE_DEC_ARGS);        \
+    } while (0)
 #define FLARE_DEC(DD, MTT, PREE, MINB)                                                                          \
     do {                                                                                                        \
         if (f16)                                                                                                \
-            decode_mfma_kernel<DD, MTT, PREE, MINB, MODE, true><<<grid, 256, 0, stream>>>(FLARE_DEC_ARGS);      \
+            FLARE_DEC_F(DD, MTT, PREE, MINB, true);                                                             \
         else                                                                                                    \
-            decode_mfma_kernel<DD, MTT, PREE, MINB, MODE, false><<<grid, 256, 0, stream>>>(FLARE_DEC_ARGS);     \
+            FLARE_DEC_F(DD, MTT, PREE, MINB, false);                                                            \
     } while (0)
     const int MT = Mc / 32;
 #define FLARE_DEC_MT(DD)                               \
@@ -1246,6 +1324,7 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
     }
 #undef FLARE_DEC_MT
 #undef FLARE_DEC
+#undef FLARE_DEC_F
 #undef FLARE_DEC_ARGS
     return check_launch();
 }
@@ -1367,11 +1446,12 @@ size_t mfma_tok_part_bytes(const flare_shape &s)
 // decode (MODE 0) or token statistics (MODE 1) over all latents, in chunks of 256 when there are more
 template <int MODE>
 static int decode_all(const flare_shape &s, const void *q, const void *k, const float *z, void *y, const void *dy,
-                      float *lse_out, float *delta, float scale, void *ws, hipStream_t stream, int flags = 0)
+                      float *lse_out, float *delta, float scale, void *ws, const MergeZ &merge, hipStream_t stream,
+                      int flags = 0)
 {
     if (s.M <= kLatChunk)
         return launch_decode_family<MODE>(s, q, k, z, y, tok_stride(s), dy, lse_out, delta, 0, lat_eff(s.M), scale,
-                                          stream, flags);
+                                          merge, stream, flags);
     const int C = lat_chunks(s.M);
     const size_t rows = (size_t)s.B * s.H * s.N;
     const size_t es = s.y_f32 ? 4 : 2;          // bytes per element of the partial rows
@@ -1382,7 +1462,7 @@ static int decode_all(const flare_shape &s, const void *q, const void *k, const 
         for (int c = 0; c < C; ++c) {
             const int rc = launch_decode_family<1>(s, q, k, z, nullptr, tok_stride(s), dy, lse_part + (size_t)c * rows,
                                                    delta_part + (size_t)c * rows, c * kLatChunk, kLatChunk, scale,
-                                                   stream, flags);
+                                                   merge, stream, flags);
             if (rc != FLARE_OK) return rc;
         }
         LaunchTimer t(KID_DECODE_MERGE, stream);
@@ -1395,7 +1475,7 @@ static int decode_all(const flare_shape &s, const void *q, const void *k, const 
         for (int c = 0; c < C; ++c) {
             void *part_c = static_cast<char *>(ws) + (size_t)c * rows * s.d * es;
             const int rc = launch_decode_family<0>(s, q, k, z, part_c, tp, nullptr, lse_part + (size_t)c * rows, nullptr,
-                                                   c * kLatChunk, kLatChunk, scale, stream, flags);
+                                                   c * kLatChunk, kLatChunk, scale, merge, stream, flags);
             if (rc != FLARE_OK) return rc;
         }
         const dim3 grid((s.N + 255) / 256, s.B * s.H);
@@ -1465,13 +1545,33 @@ int mfma_gram_partial(const flare_shape &s, const Split &sp, const void *q, cons
     return check_launch();
 }
 
-int mfma_decode(const flare_shape &s, const void *q, const void *k, const float *z, void *y, float *lse_dec,
-                float scale, void *ws, hipStream_t stream)
+static int decode_merging(const flare_shape &s, const void *q, const void *k, const float *z, void *y, float *lse_dec,
+                          float scale, void *ws, const MergeZ &g, hipStream_t stream)
 {
     // an fp32 y is what the backward will form delta from: at d <= 8 its rows carry Z as the
     // hi + lo pair that the backward's c chain carries (see mfma_token_stats)
     const int flags = s.y_f32 ? (2 | (s.d <= 8 ? 1 : 0)) : 0;
-    return decode_all<0>(s, q, k, z, y, nullptr, lse_dec, nullptr, scale, ws, stream, flags);
+    return decode_all<0>(s, q, k, z, y, nullptr, lse_dec, nullptr, scale, ws, g, stream, flags);
+}
+
+int mfma_decode(const flare_shape &s, const void *q, const void *k, const float *z, void *y, float *lse_dec,
+                float scale, void *ws, hipStream_t stream)
+{
+    return decode_merging(s, q, k, z, y, lse_dec, scale, ws, MergeZ{}, stream);
+}
+
+int mfma_forward(const flare_shape &s, const void *q, const void *k, const void *v, void *y, float *z, float *lse_enc,
+                 float *lse_dec, float scale, void *ws, hipStream_t stream)
+{
+    MergeZ g;
+    int rc = mfma_encode_partial(s, q, k, v, z, lse_enc, scale, ws, &g, stream);
+    if (rc != FLARE_OK) return rc;
+    if (s.M > kLatChunk || !merge_inline(s, g.parts)) {
+        rc = launch_encode_merge(s, g.m_part, g.l_part, g.o_part, z, lse_enc, g.parts, stream);
+        if (rc != FLARE_OK) return rc;
+        g = MergeZ{};
+    }
+    return decode_merging(s, q, k, z, y, lse_dec, scale, ws, g, stream);
 }
 
 int mfma_token_stats(const flare_shape &s, const void *q, const void *k, const float *z, const void *dy,
@@ -1481,7 +1581,7 @@ int mfma_token_stats(const flare_shape &s, const void *q, const void *k, const f
     // c = <Z_m, dY_n> carries that pair too (c - delta must cancel where one latent dominates a token): the
     // dQ kernel does, the dK/dV kernel that also forms dQ does, and the plain dK/dV kernel does at d = 4 only.
     const bool z_lo = s.d == 4 || (s.d == 8 && mfma_dkdv_supported(s) && mfma_dq_fused(s));
-    return decode_all<1>(s, q, k, z, nullptr, dy, lse_dec2, delta, scale, ws, stream, z_lo ? 1 : 0);
+    return decode_all<1>(s, q, k, z, nullptr, dy, lse_dec2, delta, scale, ws, MergeZ{}, stream, z_lo ? 1 : 0);
 }
 
 }  // namespace flare

@@ -19,12 +19,12 @@
 #include <type_traits>
 
 #include "flare_internal.h"
+#include "flare_merge.h"
 
 namespace flare {
 namespace {
 
 typedef uint16_t bf16_t;  // raw bfloat16 bits
-struct f16_t { uint16_t bits; };   // raw IEEE fp16 bits (a type of its own so that the row helpers can overload)
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -108,23 +108,6 @@ __device__ __forceinline__ void store_row(bf16_t *__restrict__ p, const float (&
 #pragma unroll
         for (int i = 0; i < D / 8; ++i) p4[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
     }
-}
-// two neighbouring elements of a row
-__device__ __forceinline__ void store_pair(float *p, float a, float b)
-{
-    *reinterpret_cast<float2 *>(p) = make_float2(a, b);
-}
-__device__ __forceinline__ void store_pair(bf16_t *p, float a, float b)
-{
-    *reinterpret_cast<uint32_t *>(p) = f32_to_bf16_rne(a) | (f32_to_bf16_rne(b) << 16);
-}
-__device__ __forceinline__ void store_pair(f16_t *p, float a, float b)
-{
-    typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-    half2_t t;
-    t[0] = (_Float16)a;
-    t[1] = (_Float16)b;
-    *reinterpret_cast<half2_t *>(p) = t;
 }
 template <int D>
 __device__ __forceinline__ float dot(const float (&a)[D], const float (&b)[D])
@@ -311,40 +294,16 @@ __global__ __launch_bounds__(256) void encode_merge_kernel(
     lse_enc[idx] = (gm + log2f(l)) * kLn2;
 }
 
-// The same merge for few partial slots (at most kFewSlots: many (b,h) pairs of short sequences).  With
-// 16 threads per latent striding over the slots most of them would idle and each would fetch whole rows
-// from scattered slots; here the D / 2 threads of a latent own two columns each and walk over the slots
-// in order, so a workgroup reads one contiguous piece per slot.  One maximum first (exact in any order),
-// then one pass of weighted sums in slot order: the bits depend on the slot count only.
+// The same merge for few partial slots (flare_merge.h).  With 16 threads per latent striding over the slots most of them
+// would idle and each would fetch whole rows from scattered slots; here the D / 4 threads of a latent take the
+// slots in order, so a workgroup reads one contiguous piece per slot.
 constexpr int kFewSlots = 8;   // (measured: with 16 and 32 slots in a row the slot-parallel kernels are the faster ones)
 template <int D>
-__global__ __launch_bounds__(256) void encode_merge_few_kernel(
-    const float *__restrict__ m_part, const float *__restrict__ l_part, const float *__restrict__ o_part,
-    float *__restrict__ z, float *__restrict__ lse_enc, int BH, int M, int parts)
+__global__ __launch_bounds__(256) void encode_merge_few_kernel(const MergeZ g, int M)
 {
-    constexpr int L = D / 2, ROWS = 256 / L;
-    const int j = threadIdx.x % L;
-    const int m = blockIdx.x * ROWS + threadIdx.x / L;
-    const int bh = blockIdx.y;
-    if (m >= M) return;
-    const size_t s0 = (size_t)bh * parts * M + m;   // slot p of this latent: s0 + p * M
-    float gm = -INFINITY;
-    for (int p = 0; p < parts; ++p) gm = fmaxf(gm, m_part[s0 + (size_t)p * M]);
-    float l = 0.f, o0 = 0.f, o1 = 0.f;
-    for (int p = 0; p < parts; ++p) {
-        const size_t slot = s0 + (size_t)p * M;
-        const float mp = m_part[slot];
-        if (mp == -INFINITY) continue;              // an empty slot contributes nothing
-        const float w = fast_exp2(mp - gm);
-        const float2 oc = *reinterpret_cast<const float2 *>(o_part + slot * D + 2 * j);
-        l = fmaf(l_part[slot], w, l);
-        o0 = fmaf(oc.x, w, o0);
-        o1 = fmaf(oc.y, w, o1);
-    }
-    const float inv = 1.f / l;
-    const size_t idx = (size_t)bh * M + m;
-    *reinterpret_cast<float2 *>(z + idx * D + 2 * j) = make_float2(o0 * inv, o1 * inv);
-    if (j == 0) lse_enc[idx] = (gm + log2f(l)) * kLn2;
+    constexpr int ROWS = 256 / (D / 4);
+    const int m0 = blockIdx.x * ROWS;
+    merge_z_rows<D>(g, blockIdx.y, M, m0, min(M, m0 + ROWS), threadIdx.x, 256, nullptr, true);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -577,7 +536,7 @@ __global__ __launch_bounds__(256) void dz_merge_kernel(
     const int bh = blockIdx.y;
     // matrix-core path: which variant of the next kernels runs for this (b,h) (every workgroup works it out for
     // itself: the one-exponential variant wants dZ scaled, see bwd_one_exp_ok); one more workgroup records it
-    __shared__ float plan_red[16];
+    __shared__ float plan_red[64];
     const bool one_exp = plan != nullptr && bwd_one_exp_ok(ld_range, lse_enc, bh, parts, M, force_two, plan_red);
     if (plan != nullptr && blockIdx.x == gridDim.x - 1) {
         if (threadIdx.x == 0) plan[bh] = one_exp ? 1 : 0;
@@ -599,9 +558,7 @@ __global__ __launch_bounds__(256) void dz_merge_kernel(
         // see the same values), instead of leaving <V_n, rounding error> uncancelled in every score.
 #pragma unroll
         for (int i = 0; i < D; ++i) {
-            uint32_t u = __float_as_uint(acc[i]);
-            u += 0x7fffu + ((u >> 16) & 1u);
-            acc[i] = __uint_as_float(u & 0xffff0000u);
+            acc[i] = bf16_rounded(acc[i]);
         }
     }
     load_row<D>(z + idx * D, zr);
@@ -609,65 +566,29 @@ __global__ __launch_bounds__(256) void dz_merge_kernel(
     eps[idx] = dot<D>(acc, zr);
 }
 
-// Few slots (at most kFewSlots in all): the D / 2 threads of a row own two columns each and add the slots in
-// order (see encode_merge_few_kernel); same slot addressing as sum_slots.
-template <int D>
-__device__ __forceinline__ float2 sum_slots_few(const float *__restrict__ part, int outer, int n_outer, int groups,
-                                                int inner, int M, int m, int j)
-{
-    float a0 = 0.f, a1 = 0.f;
-    for (int g = 0; g < groups; ++g)
-        for (int i = 0; i < inner; ++i) {
-            const size_t slot = ((size_t)g * n_outer + outer) * inner + i;
-            const float2 t = *reinterpret_cast<const float2 *>(part + (slot * M + m) * D + 2 * j);
-            a0 += t.x;
-            a1 += t.y;
-        }
-    return make_float2(a0, a1);
-}
-
+// Few slots: see encode_merge_few_kernel.
 template <int D>
 __global__ __launch_bounds__(256) void dz_merge_few_kernel(
     const float *__restrict__ dz_part, const float *__restrict__ z,
     float *__restrict__ dz, float *__restrict__ eps, int BH, int M, int parts, int round_bf16,
     const float *__restrict__ ld_range, const float *__restrict__ lse_enc, int *__restrict__ plan, int force_two)
 {
-    constexpr int L = D / 2, ROWS = 256 / L;
+    constexpr int L = D / 4, ROWS = 256 / L;
     const int j = threadIdx.x % L;
     const int m = blockIdx.x * ROWS + threadIdx.x / L;
     const int bh = blockIdx.y;
-    __shared__ float plan_red[16];                   // as in dz_merge_kernel
+    __shared__ float plan_red[64];                   // as in dz_merge_kernel
     const bool one_exp = plan != nullptr && bwd_one_exp_ok(ld_range, lse_enc, bh, parts, M, force_two, plan_red);
     if (plan != nullptr && blockIdx.x == gridDim.x - 1) {
         if (threadIdx.x == 0) plan[bh] = one_exp ? 1 : 0;
         return;
     }
-    const bool live = m < M;                         // no early exit: the row's lanes meet in the shuffles below
-    float2 a = sum_slots_few<D>(dz_part, bh, BH, 1, parts, M, live ? m : M - 1, j);
-    if (one_exp) {                                   // the one-exponential kernels take dZ scaled by 2^-lse_enc2[m]
-        const float em = exp2f(-lse_enc[(size_t)bh * M + (live ? m : M - 1)] * 1.4426950408889634f);
-        a.x *= em;
-        a.y *= em;
-    }
-    if (round_bf16) {                                // as in dz_merge_kernel: round before eps is formed
-        uint32_t u = __float_as_uint(a.x);
-        u += 0x7fffu + ((u >> 16) & 1u);
-        a.x = __uint_as_float(u & 0xffff0000u);
-        u = __float_as_uint(a.y);
-        u += 0x7fffu + ((u >> 16) & 1u);
-        a.y = __uint_as_float(u & 0xffff0000u);
-    }
-    const size_t idx = (size_t)bh * M + (live ? m : M - 1);
-    const float2 zr = *reinterpret_cast<const float2 *>(z + idx * D + 2 * j);
-    float e = fmaf(a.y, zr.y, a.x * zr.x);
-#pragma unroll
-    for (int off = 1; off < L; off <<= 1) {          // fixed tree over the row's lanes (L is a power of two)
-        const float o = __shfl_xor(e, off);
-        e = ((j & off) == 0) ? (e + o) : (o + e);
-    }
-    if (!live) return;
-    *reinterpret_cast<float2 *>(dz + idx * D + 2 * j) = a;
-    if (j == 0) eps[idx] = e;
+    const int mc = min(m, M - 1);                    // no early exit: the row's lanes meet in shuffles
+    float e;
+    const float4 a = merge_dz_row<D>(dz_part, z, lse_enc, bh, M, parts, mc, j, one_exp, round_bf16 != 0, e);
+    if (m >= M) return;
+    *reinterpret_cast<float4 *>(dz + ((size_t)bh * M + m) * D + 4 * j) = a;
+    if (j == 0) eps[(size_t)bh * M + m] = e;
 }
 
 // dq_lat in fp32, or (T: the storage type) rounded once as it is stored.
@@ -675,13 +596,19 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void dq_reduce_few_kernel(
     const float *__restrict__ dq_part, T *__restrict__ dq, int B, int H, int M, int parts, float scale)
 {
-    constexpr int L = D / 2, ROWS = 256 / L;
+    constexpr int L = D / 4, ROWS = 256 / L;
     const int j = threadIdx.x % L;
     const int m = blockIdx.x * ROWS + threadIdx.x / L;
     const int h = blockIdx.y;
     if (m >= M) return;
-    const float2 a = sum_slots_few<D>(dq_part, h, H, B, parts, M, m, j);
-    store_pair(dq + ((size_t)h * M + m) * D + 2 * j, a.x * scale, a.y * scale);
+    const int slots = B * parts;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int s = 0; s < kFewSlots; ++s)
+        if (s < slots)
+            add4(a, *reinterpret_cast<const float4 *>(
+                        dq_part + ((((size_t)(s / parts) * H + h) * parts + s % parts) * M + m) * D + 4 * j));
+    store_four(dq + ((size_t)h * M + m) * D + 4 * j, make_float4(a.x * scale, a.y * scale, a.z * scale, a.w * scale));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -808,7 +735,19 @@ __global__ __launch_bounds__(kTokenBlock) void dkdv_kernel(
 // ---- workspace carving --------------------------------------------------------------------
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-struct BwdWs { float *lse_dec2, *delta, *part, *dz, *eps, *ld_range; int *plan; void *tok_part; float *acc32; };
+// dq_part: the dQ slots, where they may not share `part` with the dZ slots (kernels that merge those themselves)
+struct BwdWs {
+    float *lse_dec2, *delta, *part, *dz, *eps, *ld_range, *dq_part;
+    int *plan;
+    void *tok_part;
+    float *acc32;
+};
+
+// Whether the kernels that need dZ merge its slots themselves.
+inline bool dz_inline(const flare_shape &s)
+{
+    return s.dtype == FLARE_F32 ? mfma32_inline(s) : mfma_supported(s) && mfma_dz_inline(s);
+}
 
 // `slots` = partial slots per (b,h) the shared partial buffer must hold
 size_t bwd_layout(const flare_shape &s, int slots, void *ws, BwdWs *out)
@@ -830,6 +769,11 @@ size_t bwd_layout(const flare_shape &s, int slots, void *ws, BwdWs *out)
     off += align256(BH * slots * 2 * 4);
     if (out) out->plan = reinterpret_cast<int *>(base + off);
     off += align256(BH * 4);
+    if (out) out->dq_part = out->part;
+    if (dz_inline(s)) {
+        if (out) out->dq_part = reinterpret_cast<float *>(base + off);
+        off += align256(BH * slots * s.M * s.d * 4);
+    }
     if (mfma_supported(s)) {   // only shapes with more than 256 latents on the matrix-core path use these
         if (out) out->tok_part = base + off;
         off += mfma_tok_part_bytes(s);
@@ -882,13 +826,34 @@ int decode_impl(const flare_shape &s, const T *q, const T *k, const float *z, T 
                 hipStream_t stream)
 {
     if constexpr (std::is_same_v<T, float>) {
-        return mfma32_decode(s, q, k, z, y, lse_dec, scale, stream);
+        return mfma32_decode(s, q, k, z, y, lse_dec, scale, MergeZ{}, stream);
     } else {
         LaunchTimer t(KID_DECODE, stream);
         token_pass_kernel<T, D, 0><<<dim3((s.N + kTokenBlock - 1) / kTokenBlock, s.B * s.H), kTokenBlock, 0, stream>>>(
             q, k, z, y, nullptr, lse_dec, nullptr, tok_stride(s), s.H, s.N, s.M, scale * kLog2e, s.y_f32);
         return check_launch();
     }
+}
+
+// encode and decode; fp32 storage with few encode slots: the decode merges them itself
+template <typename T, int D>
+int forward_impl(const flare_shape &s, const T *q, const T *k, const T *v, T *y, float *z, float *lse_enc, float *lse_dec,
+                 float scale, void *ws, hipStream_t stream)
+{
+    if constexpr (std::is_same_v<T, float>) {
+        if (mfma32_inline(s)) {
+            MergeZ g{nullptr, nullptr, nullptr, z, lse_enc, mfma32_split(s).chunks};
+            float *m_part, *l_part, *o_part;
+            valu_fwd_layout(s, mfma32_split(s), ws, &m_part, &l_part, &o_part);
+            g.m_part = m_part;
+            g.l_part = l_part;
+            g.o_part = o_part;
+            const int rc = mfma32_encode(s, q, k, v, m_part, l_part, o_part, scale, stream);
+            return rc != FLARE_OK ? rc : mfma32_decode(s, q, k, z, y, lse_dec, scale, g, stream);
+        }
+    }
+    const int rc = encode_impl<T, D>(s, q, k, v, z, lse_enc, scale, ws, stream);
+    return rc != FLARE_OK ? rc : decode_impl<T, D>(s, q, k, z, y, lse_dec, scale, stream);
 }
 
 template <typename T, int D>
@@ -973,8 +938,11 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
         }
         if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
     }
-    constexpr int kFewRows = 256 / (D / 2);   // rows per workgroup of the few-slot merge kernels
-    {
+    constexpr int kFewRows = 256 / (D / 4);   // rows per workgroup of the few-slot merge kernels
+    // what the dK/dV kernel has to merge itself, if anything
+    const MergeDz merge{w.part, w.ld_range, w.dz, w.eps, w.plan, dz_inline(s) ? dz_parts : 0,
+                        (s.variant & FLARE_VARIANT_TWO_EXP) ? 1 : 0, 0u};
+    if (merge.parts == 0) {
         LaunchTimer t(KID_BWD_DZ_MERGE, stream);
         if (dz_parts <= kFewSlots)
             dz_merge_few_kernel<D><<<dim3((s.M + kFewRows - 1) / kFewRows + (planned ? 1 : 0), BH), 256, 0, stream>>>(
@@ -986,64 +954,53 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
                 (s.variant & FLARE_VARIANT_TWO_EXP) ? 1 : 0);
     }
     if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
+    // dK and dV, then (with a kernel of its own for it) dQ: where dZ is merged by the dK/dV kernel, the dQ kernel reads
+    // what that one wrote
     int dq_parts = plan.bwd.chunks;
-    const bool dq_fused = mf && mfma_dkdv_supported(s) && mfma_dq_fused(s);   // dQ comes out of the dK/dV kernel
-    if (dq_fused) {
-        dq_parts = mfma_dkdv_blocks(s);
-    } else if constexpr (F32) {
-        const int rc = mfma32_dq_partial(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, w.part,
-                                         scale, stream);
-        if (rc != FLARE_OK) return rc;
-    } else if (mf) {
-        dq_parts = mfma_dq_parts(s);
-        const int rc = mfma_dq_partial(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, w.part,
-                                       scale, stream);   // each (b,h) slice by the variant its plan names
-        if (rc != FLARE_OK) return rc;
-    } else {
-        LaunchTimer t(KID_BWD_DQ_PARTIAL, stream);
-        dq_partial_kernel<T, D><<<lat_grid, kLatentBlock, 0, stream>>>(q, k, v, dy, z, lse_enc, w.dz, w.eps,
-                                                                       w.lse_dec2, w.delta, w.part, ts, s.H, s.N, s.M,
-                                                                       plan.bwd.chunk_len, plan.bwd.chunks, c2,
-                                                                       RowTouch{addr(k), addr(v), addr(dy), addr(w.lse_dec2), addr(w.delta)});
-    }
-    if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
-    auto reduce_dq = [&]() -> int {
-        LaunchTimer t(KID_BWD_DQ_REDUCE, stream);
-        // shared latents: one gradient for all heads, summed over (b, h) in that fixed order
-        const int groups = s.shared_latents ? BH : s.B, outers = s.shared_latents ? 1 : s.H;
-        auto launch = [&](auto *out) {
-            typedef std::remove_reference_t<decltype(*out)> O;
-            if ((long long)groups * dq_parts <= kFewSlots)
-                dq_reduce_few_kernel<O, D><<<dim3((s.M + kFewRows - 1) / kFewRows, outers), 256, 0, stream>>>(
-                    w.part, out, groups, outers, s.M, dq_parts, scale);
-            else
-                dq_reduce_kernel<O, D><<<dim3((s.M + 15) / 16, outers), 256, 0, stream>>>(
-                    w.part, out, groups, outers, s.M, dq_parts, scale);
-        };
-        if (dq_cast) launch(static_cast<T *>(dq));
-        else launch(static_cast<float *>(dq));
-        return check_launch();
-    };
-    if (!dq_fused) {
-        const int rc = reduce_dq();
-        if (rc != FLARE_OK) return rc;
-    }
-    if (mf && mfma_dkdv_supported(s)) {
-        const bool chunked = mfma_dkdv_acc_bytes(s) != 0;   // more than 256 latents: one pass per chunk
-        for (int m0 = 0; m0 < s.M; m0 += 256) {   // each (b,h) slice by the variant its plan names
-            const int rc = mfma_dkdv(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, dk, dv,
-                                     chunked ? w.acc32 : nullptr, dq_fused ? w.part : nullptr, m0, scale, stream);
-            if (rc != FLARE_OK) return rc;
-        }
-        return dq_fused ? reduce_dq() : FLARE_OK;
-    }
+    // shared latents: one gradient for all heads, summed over (b, h) in that fixed order
+    const int groups = s.shared_latents ? BH : s.B, outers = s.shared_latents ? 1 : s.H;
+    int rc = FLARE_OK;
     if constexpr (F32) {
-        return mfma32_dkdv(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, dk, dv, scale, stream);
+        rc = mfma32_dkdv(s, q, k, v, dy, z, lse_enc, ld, w.delta, ld_mul, dk, dv, scale, merge, stream);
+        if (rc == FLARE_OK)
+            rc = mfma32_dq_partial(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, w.dq_part, scale,
+                                   stream);
+    } else if (mf) {
+        const bool dq_fused = mfma_dq_fused(s);             // dQ comes out of the dK/dV kernel
+        const bool chunked = mfma_dkdv_acc_bytes(s) != 0;   // more than 256 latents: one pass per chunk
+        dq_parts = dq_fused ? mfma_dkdv_blocks(s) : mfma_dq_parts(s);
+        for (int m0 = 0; m0 < s.M && rc == FLARE_OK; m0 += 256)   // each (b,h) slice by the variant its plan names
+            rc = mfma_dkdv(s, q, k, v, dy, z, lse_enc, ld, w.delta, ld_mul, dk, dv, chunked ? w.acc32 : nullptr,
+                           dq_fused ? w.dq_part : nullptr, m0, scale, merge, stream);
+        if (!dq_fused && rc == FLARE_OK)
+            rc = mfma_dq_partial(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, w.dq_part, scale,
+                                 stream);
     } else {
-        LaunchTimer t(KID_BWD_DKDV, stream);
-        dkdv_kernel<T, D><<<tok_grid, kTokenBlock, 0, stream>>>(q, k, v, dy, z, lse_enc, w.dz, w.eps, w.lse_dec2,
-                                                                w.delta, dk, dv, ts, s.H, s.N, s.M, scale);
+        {
+            LaunchTimer t(KID_BWD_DKDV, stream);
+            dkdv_kernel<T, D><<<tok_grid, kTokenBlock, 0, stream>>>(q, k, v, dy, z, lse_enc, w.dz, w.eps, w.lse_dec2,
+                                                                    w.delta, dk, dv, ts, s.H, s.N, s.M, scale);
+        }
+        if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
+        LaunchTimer t(KID_BWD_DQ_PARTIAL, stream);
+        dq_partial_kernel<T, D><<<lat_grid, kLatentBlock, 0, stream>>>(
+            q, k, v, dy, z, lse_enc, w.dz, w.eps, w.lse_dec2, w.delta, w.dq_part, ts, s.H, s.N, s.M, plan.bwd.chunk_len,
+            plan.bwd.chunks, c2, RowTouch{addr(k), addr(v), addr(dy), addr(w.lse_dec2), addr(w.delta)});
+        rc = check_launch();
     }
+    if (rc != FLARE_OK) return rc;
+    auto reduce_dq = [&](auto *out) {
+        typedef std::remove_reference_t<decltype(*out)> O;
+        LaunchTimer t(KID_BWD_DQ_REDUCE, stream);
+        if ((long long)groups * dq_parts <= kFewSlots)
+            dq_reduce_few_kernel<O, D><<<dim3((s.M + kFewRows - 1) / kFewRows, outers), 256, 0, stream>>>(
+                w.dq_part, out, groups, outers, s.M, dq_parts, scale);
+        else
+            dq_reduce_kernel<O, D><<<dim3((s.M + 15) / 16, outers), 256, 0, stream>>>(w.dq_part, out, groups, outers, s.M,
+                                                                                     dq_parts, scale);
+    };
+    if (dq_cast) reduce_dq(static_cast<T *>(dq));
+    else reduce_dq(static_cast<float *>(dq));
     return check_launch();
 }
 
@@ -1101,10 +1058,10 @@ int launch_encode_merge(const flare_shape &s, const float *m_part, const float *
     const int BH = s.B * s.H;
     const dim3 blocks((s.M + 15) / 16, BH);
     LaunchTimer t(KID_ENCODE_MERGE, stream);
-    if (parts <= kFewSlots) {
-#define FLARE_EMF(DD)                                                                                          \
-    encode_merge_few_kernel<DD><<<dim3((s.M + 256 / (DD / 2) - 1) / (256 / (DD / 2)), BH), 256, 0, stream>>>(   \
-        m_part, l_part, o_part, z, lse_enc, BH, s.M, parts)
+    if (parts <= kFewSlots || merge_inline(s, parts)) {   // (the same bits wherever a shape's slots are merged)
+        const MergeZ g{m_part, l_part, o_part, z, lse_enc, parts};
+#define FLARE_EMF(DD)                                                                                           \
+    encode_merge_few_kernel<DD><<<dim3((s.M + 256 / (DD / 4) - 1) / (256 / (DD / 4)), BH), 256, 0, stream>>>(g, s.M)
         switch (s.d) {
             case 4: FLARE_EMF(4); break;
             case 8: FLARE_EMF(8); break;
@@ -1149,6 +1106,12 @@ int valu_encode(const flare_shape &s, const void *q, const void *k, const void *
                 float scale, void *ws, hipStream_t stream)
 {
     FLARE_DISPATCH(s, (encode_impl<T, D>(s, (const T *)q, (const T *)k, (const T *)v, z, lse_enc, scale, ws, stream)));
+}
+int valu_forward(const flare_shape &s, const void *q, const void *k, const void *v, void *y, float *z, float *lse_enc,
+                 float *lse_dec, float scale, void *ws, hipStream_t stream)
+{
+    FLARE_DISPATCH(s, (forward_impl<T, D>(s, (const T *)q, (const T *)k, (const T *)v, (T *)y, z, lse_enc, lse_dec, scale,
+                                          ws, stream)));
 }
 int valu_decode(const flare_shape &s, const void *q, const void *k, const float *z, void *y, float *lse_dec,
                 float scale, hipStream_t stream)
