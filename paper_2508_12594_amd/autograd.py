@@ -2,7 +2,7 @@
 
 Nothing is computed here: the forward calls flare_forward (keeping z, lse_enc, lse_dec and y for the
 backward), the backward calls flare_backward_cast (dq_lat in q_lat's dtype, which autograd requires of a
-gradient).  The autograd node is native (csrc/torch_binding.cpp, Mixer).  This is how the paper's layer
+gradient).  The autograd node is native (csrc/torch_binding.cpp, MixerBackward).  This is how the paper's layer
 would use the operator in place of its two attention calls (listing in Section 3.1).
 """
 from . import binding

@@ -150,15 +150,16 @@ struct Target {
     void *stream;
     std::optional<c10::Stream> other;   // set when it is not the current stream
 };
+// (called with the GIL; what follows it in the entry points, allocations and launches, runs without)
 Target target(const py::object &stream)
 {
     const c10::hip::HIPStream cur = c10::hip::getCurrentHIPStream();
     if (stream.is_none()) return Target{cur.stream(), std::nullopt};
     void *const handle = reinterpret_cast<void *>(stream.attr("cuda_stream").cast<uintptr_t>());
+    if (handle == cur.stream()) return Target{handle, std::nullopt};
     const c10::Stream s = c10::Stream::unpack3(stream.attr("stream_id").cast<int64_t>(),
                                                (c10::DeviceIndex)stream.attr("device_index").cast<int64_t>(),
                                                (c10::DeviceType)stream.attr("device_type").cast<int64_t>());
-    if (s.id() == cur.id() && s.device_index() == cur.device_index()) return Target{handle, std::nullopt};
     return Target{handle, s};
 }
 
@@ -213,6 +214,7 @@ std::tuple<Tensor, Tensor> encode(const Tensor &q, const Tensor &k, const Tensor
     const flare_shape s = shape_of(q, k, layout, false);
     const Dims dim(s);
     const Target to = target(stream);
+    const py::gil_scoped_release no_gil;
     Tensor z = out_or_new(z_in, dim.z, at::kFloat, k), le = out_or_new(le_in, dim.lse_enc, at::kFloat, k);
     const Workspace ws = workspace_for(fwd_bytes(s), ws_in, k, to);
     check(lib.encode(&s, dev(q, "q_lat"), dev(k, "k"), dev(v, "v", k.scalar_type(), k.sizes()),
@@ -229,6 +231,7 @@ Tensor decode(const Tensor &q, const Tensor &k, const Tensor &z, double scale, c
     const flare_shape s = shape_of(q, k, layout, wide);
     const Dims dim(s);
     const Target to = target(stream);
+    const py::gil_scoped_release no_gil;
     const at::ScalarType ydt = wide ? at::kFloat : k.scalar_type();
     Tensor y = out_or_new(y_in, k.sizes(), ydt, k);
     const Workspace ws = workspace_for(fwd_bytes(s), ws_in, k, to);
@@ -248,6 +251,7 @@ std::tuple<Tensor, Tensor, Tensor> forward(const Tensor &q, const Tensor &k, con
     const flare_shape s = shape_of(q, k, layout, wide);
     const Dims dim(s);
     const Target to = target(stream);
+    const py::gil_scoped_release no_gil;
     const at::ScalarType ydt = wide ? at::kFloat : k.scalar_type();
     Tensor y = out_or_new(y_in, k.sizes(), ydt, k), z = out_or_new(z_in, dim.z, at::kFloat, k),
            le = out_or_new(le_in, dim.lse_enc, at::kFloat, k);
@@ -266,10 +270,12 @@ void forward_static(const Tensor &q, const Tensor &k, const Tensor &v, double sc
     const bool wide = wants_f32_y(y, k, false);
     const flare_shape s = shape_of(q, k, layout, wide);
     const Dims dim(s);
+    const Target to = target(stream);
+    const py::gil_scoped_release no_gil;
     check(lib.forward_static(&s, dev(q, "q_lat"), dev(k, "k"), dev(v, "v", k.scalar_type(), k.sizes()),
                              dev(y, "y", wide ? at::kFloat : k.scalar_type(), k.sizes()),
                              f32(dev(z, "z", at::kFloat, dim.z)), f32(dev(le, "lse_enc", at::kFloat, dim.lse_enc)),
-                             f32(dev(ld, "lse_dec", at::kFloat, dim.lse_dec)), (float)scale, target(stream).stream),
+                             f32(dev(ld, "lse_dec", at::kFloat, dim.lse_dec)), (float)scale, to.stream),
           "flare_forward_static");
 }
 
@@ -282,6 +288,7 @@ std::tuple<Tensor, Tensor, Tensor> forward_project(const Tensor &q, const Tensor
     const flare_shape s = shape_of(q, k, FLARE_BNHD, false);
     const Dims dim(s);
     const Target to = target(stream);
+    const py::gil_scoped_release no_gil;
     const int64_t C = (int64_t)s.H * s.d;
     const at::ScalarType dt = k.scalar_type();
     const std::array<int64_t, 3> out_dim{s.B, s.N, C};
@@ -313,6 +320,7 @@ std::tuple<Tensor, Tensor, Tensor> backward(const Tensor &q, const Tensor &k, co
     s.variant = variant;
     const Dims dim(s);
     const Target to = target(stream);
+    const py::gil_scoped_release no_gil;
     const at::ScalarType dt = k.scalar_type();
     Tensor dq = out_or_new(dq_in, q.sizes(), at::kFloat, k), dk = out_or_new(dk_in, k.sizes(), dt, k),
            dv = out_or_new(dv_in, k.sizes(), dt, k);
@@ -379,13 +387,20 @@ struct MixerBackward : torch::autograd::Node {
 
 Tensor mixer(const Tensor &q_in, const Tensor &k_in, const Tensor &v_in, double scale, int layout, bool y_f32)
 {
+    for (const Tensor *t : {&q_in, &k_in, &v_in})   // a tangent would be lost without a word
+        if (t->_fw_grad(0).defined()) throw Error("flare_mixer has no forward-mode derivative");
     std::shared_ptr<MixerBackward> node;
     if (at::GradMode::is_enabled() && (q_in.requires_grad() || k_in.requires_grad() || v_in.requires_grad())) {
         node = std::shared_ptr<MixerBackward>(new MixerBackward(), torch::autograd::deleteNode);
         node->set_next_edges(torch::autograd::collect_next_edges(q_in, k_in, v_in));
     }
-    at::AutoDispatchBelowADInplaceOrView below;
-    const Tensor q = q_in.contiguous(), k = k_in.contiguous(), v = v_in.contiguous();
+    Tensor q = q_in, k = k_in, v = v_in;
+    {
+        const at::AutoDispatchBelowADInplaceOrView below;   // not around the saving: saved-tensor hooks run there
+        q = q.contiguous();
+        k = k.contiguous();
+        v = v.contiguous();
+    }
     const flare_shape s = shape_of(q, k, layout, y_f32);
     const Saved off(s);
     const Target to{c10::hip::getCurrentHIPStream().stream(), std::nullopt};

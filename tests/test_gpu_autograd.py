@@ -36,3 +36,55 @@ def test_autograd_matches_oracle(oracle, cfg, over, layout, y_f32):
     print("[case]    " + "  ".join("%s %.2e" % kv for kv in errs.items()), flush=True)
     # dq_lat is cast to q's dtype for autograd: one more rounding of a 16-bit type
     assert max(errs.values()) <= tol
+
+
+def test_autograd_hooks_and_refusals():
+    """Saved tensors pass through the caller's hooks, a second backward without retain_graph and an in-place change of
+    the output are errors, a forward-mode tangent is refused, and threads may call at the same time."""
+    import threading
+
+    import torch
+    import torch.autograd.forward_ad as fwad
+    print("[case] autograd hooks", flush=True)
+    inp = synth.make_inputs(2, B=1, H=2, N=300, M=32, d=16, dtype="bf16", with_dy=True)
+    dev = to_device(inp)
+    scale = inp["scale"]
+
+    def step(packed=None):
+        q, k, v = (dev[n].clone().requires_grad_(True) for n in ("q", "k", "v"))
+        pack = (lambda t: packed.append(t) or t) if packed is not None else (lambda t: t)
+        with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t.clone()):
+            y = flare_mixer(q, k, v, scale)
+        return y, torch.autograd.grad(y, (q, k, v), dev["dy"])
+
+    packed = []
+    y, grads = step(packed)
+    assert len(packed) == 5
+    results = [None] * 4
+
+    def work(i):
+        results[i] = step()
+        torch.cuda.synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    for y2, grads2 in results:
+        assert torch.equal(y, y2) and all(torch.equal(a, b) for a, b in zip(grads, grads2))
+
+    q = dev["q"].clone().requires_grad_(True)
+    y = flare_mixer(q, dev["k"], dev["v"], scale)
+    torch.autograd.grad(y, q, dev["dy"], retain_graph=True)
+    torch.autograd.grad(y, q, dev["dy"])
+    with pytest.raises(RuntimeError):
+        torch.autograd.grad(y, q, dev["dy"])
+    y = flare_mixer(q, dev["k"], dev["v"], scale)
+    y.mul_(2.0)
+    with pytest.raises(RuntimeError):
+        torch.autograd.grad(y, q, dev["dy"])
+    with fwad.dual_level():
+        dual = fwad.make_dual(dev["q"], torch.ones_like(dev["q"]))
+        with pytest.raises(RuntimeError):
+            flare_mixer(dual, dev["k"], dev["v"], scale)
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(lambda t: flare_mixer(dev["q"], t, t, scale))(torch.stack([dev["k"], dev["k"]]))
