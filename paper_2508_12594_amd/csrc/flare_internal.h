@@ -122,11 +122,12 @@ int mfma_forward(const flare_shape &s, const void *q, const void *k, const void 
 // The encode's partial slots only; *g says where they are, for a consumer to merge.
 int mfma_encode_partial(const flare_shape &s, const void *q, const void *k, const void *v, float *z, float *lse_enc,
                         float scale, void *ws, MergeZ *g, hipStream_t stream);
-// Shapes with M > 256 run the token-major kernels once per chunk of 256 latents.  The decode and the
+// Shapes with M > 256 run the token-major kernels once per chunk of at most 256 latents.  The decode and the
 // token statistics then need mfma_tok_part_bytes(s) of scratch (`ws`; unused and may be NULL
 // otherwise), the dK/dV step mfma_dkdv_acc_bytes(s) for its fp32 sums.
 size_t mfma_tok_part_bytes(const flare_shape &s);
 size_t mfma_dkdv_acc_bytes(const flare_shape &s);
+int mfma_lat_step(const flare_shape &s);   // latents per chunk
 int mfma_decode(const flare_shape &s, const void *q, const void *k, const float *z, void *y,
                 float *lse_dec, float scale, void *ws, hipStream_t stream);
 // decode fused with the output projection (flare_mfma_proj.hip); y and lse_dec may be NULL

@@ -450,7 +450,7 @@ __device__ __forceinline__ void dkdv_body(
     const float *__restrict__ dz, const float *__restrict__ eps, const float *__restrict__ lse_dec2,
     const float *__restrict__ delta, float ld_mul, bf16_t *__restrict__ dk,
     bf16_t *__restrict__ dv, float *__restrict__ acc32, float *__restrict__ dq_part, TokStride ts, int H, int N,
-    int Mtot, int m0, float c2, float scale)
+    int Mtot, int m0, int mend, float c2, float scale)
 {
     // DQ (d <= 16): the kernel also forms the dQ partials, so that the scores, a, c and dS of a tile
     // pair are computed once for all three gradients.  dS of a tile reaches the dQ product transposed
@@ -462,7 +462,7 @@ __device__ __forceinline__ void dkdv_body(
     // ([(b*h) * gridDim.x + x][Mtot][d], summed and scaled by dq_reduce_kernel).  The c chain
     // then carries the lo term of Z at d <= 8 (ZPACK below) and, with ZL, at d = 16 (dQ sums dS over the tokens of
     // one latent and adds up its rounding coherently, see the dQ kernel).
-    // The kernel works on the latents m0 .. m0 + M of the head's Mtot.  With acc32 given (more than one
+    // The kernel works on the latents m0 .. mend (at most 32 * MT) of the head's Mtot.  With acc32 given (more than one
     // latent chunk) it adds its dV and dK rows in fp32 to acc32[0][b*h][n][DR] and acc32[1][...] (the
     // chunk with m0 = 0 stores instead); the last chunk adds what is there to its own rows and rounds the
     // sums to dk and dv.  The chunks run as launches in a row on one stream, so the order of the sum is fixed.
@@ -516,10 +516,10 @@ __device__ __forceinline__ void dkdv_body(
         const float *dzb = dz + (size_t)m0 * DR;   // (dz, eps: the rows of this (b,h), in global memory or merged into LDS)
         const float *eb = eps + m0;
         const float *leb = lse_enc + (size_t)bh * Mtot + m0;
-        // Padding latents (at or beyond Mtot; mleft = real ones from m0 on): loads are clamped to the last
+        // Padding latents (at or beyond mend; mleft = real ones from m0 on): loads are clamped to the last
         // real latent and every value that could reach dK or dV is zero -- q, Z, dZ, eps, u and the ones
         // that pick -delta -- so that a = c = 0 and dS = 0 whatever P and R come out as.
-        const int mleft = Mtot - m0;
+        const int mleft = mend - m0;
         for (int idx = tid; idx < MT * PER_TILE * 64; idx += 64 * WV) {
             const int ln = idx & 63, sid = (idx >> 6) % PER_TILE, t = (idx >> 6) / PER_TILE;
             const int r32 = ln & 31, hf = ln >> 5;
@@ -861,16 +861,18 @@ __device__ __forceinline__ void dkdv_body(
                 tile_step(0, sa1, sa2, sb1, sb2);
             } else if constexpr (DQ) {   // unrolled: the dQ accumulators are indexed by the latent tile
 #pragma unroll
-                for (int t = 0; t < MT; t += 2) {
+                for (int t = 0; t + 1 < MT; t += 2) {
                     tile_step(t, sa1, sa2, sb1, sb2);
                     tile_step(t + 1, sb1, sb2, sa1, sa2);
                 }
+                if constexpr (MT % 2 != 0) tile_step(MT - 1, sa1, sa2, sb1, sb2);
             } else {
 #pragma unroll 1
-                for (int t = 0; t < MT; t += 2) {
+                for (int t = 0; t + 1 < MT; t += 2) {
                     tile_step(t, sa1, sa2, sb1, sb2);
                     tile_step(t + 1, sb1, sb2, sa1, sa2);
                 }
+                if constexpr (MT % 2 != 0) tile_step(MT - 1, sa1, sa2, sb1, sb2);
             }
         }
         // What was requested at the top of this tile is taken over here, ahead of the tile's stores: memory
@@ -889,7 +891,7 @@ __device__ __forceinline__ void dkdv_body(
         // More than one latent chunk: all but the first add what the chunks before them left in acc32, and all but
         // the head's last one leave their sums there; the last one rounds and stores them like a single chunk.
         const bool from_acc = acc32 != nullptr && m0 != 0;
-        const bool to_acc = acc32 != nullptr && m0 + 32 * MT < Mtot;
+        const bool to_acc = acc32 != nullptr && mend < Mtot;
         if (n < N) {
 #pragma unroll
             for (int hv = 0; hv < HV; ++hv)
@@ -951,7 +953,7 @@ __device__ __forceinline__ void dkdv_body(
             }
         }
         __syncthreads();
-        const int mleft = Mtot - m0;
+        const int mleft = mend - m0;
         float *out = dq_part + (((size_t)bh * gridDim.x + gp.x) * Mtot + m0) * DR;
         constexpr int PCS = DR / 4;                             // float4 pieces of a DR-element row
         for (int i = tid; i < 32 * MT * PCS; i += 512) {        // latent i / PCS, columns 4 (i % PCS) ..
@@ -968,9 +970,9 @@ __device__ __forceinline__ void dkdv_body(
         const bf16_t *__restrict__ dy, const float *__restrict__ z, const float *__restrict__ lse_enc,           \
         const float *__restrict__ lse_dec2, const float *__restrict__ delta, float ld_mul, bf16_t *__restrict__ dk, \
         bf16_t *__restrict__ dv, float *__restrict__ acc32, float *__restrict__ dq_part, TokStride ts, int H,    \
-        int N, int Mtot, int m0, float c2, float scale, MergeDz merge
+        int N, int Mtot, int m0, int mend, float c2, float scale, MergeDz merge
 #define FLARE_DKDV_PASS \
-    q, k, v, dy, z, lse_enc, dz_bh, eps_bh, lse_dec2, delta, ld_mul, dk, dv, acc32, dq_part, ts, H, N, Mtot, m0, c2, scale
+    q, k, v, dy, z, lse_enc, dz_bh, eps_bh, lse_dec2, delta, ld_mul, dk, dv, acc32, dq_part, ts, H, N, Mtot, m0, mend, c2, scale
 
 // One variant per launch (the workgroups of a (b,h) that the plan gives to the other variant leave at once) ...
 template <int DR, int MT, bool DQ, bool ONE, bool F, int WV = 8>
@@ -1011,12 +1013,11 @@ int mfma_dq_partial(const flare_shape &s, const void *q, const void *k, const vo
                     float scale, hipStream_t stream)
 {
     const MfmaPlan p = mfma_plan(s);
-    int zdim;
-    const EncGeom e = dq_geom(s, &zdim);
+    const EncGeom e = dq_geom(s);
     const int BH = s.B * s.H;
     const float c2 = scale * kLog2e;
     const int parts = p.enc.chunks * e.TG;
-    const dim3 grid(p.enc.chunks, BH, zdim);
+    const dim3 grid(p.enc.chunks, BH, e.Z);
     const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *vv = (const bf16_t *)v, *gg = (const bf16_t *)dy;
     LaunchTimer t(KID_BWD_DQ_PARTIAL, stream);
     const bool f16 = s.dtype == FLARE_F16;
@@ -1088,11 +1089,14 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
     const bool fuse = dq_part != nullptr;
     if (fuse && !mfma_dq_fused(s)) return FLARE_EUNSUPPORTED;
     const float c2 = scale * kLog2e;
-    const int MT = lat_eff(s.M) == 192 ? 8 : lat_eff(s.M) / 32;   // instantiated for 1, 2, 4, 8 tiles
+    const int mend = min(s.M, m0 + lat_eff(s.M));
+    int MT = lat_eff(s.M) / 32;
     const int pd = padded_dim(s.d);
     const int KS = pd / 16, HV = (pd == 32) ? 1 : pd / 16;   // d = 32: one 32-row block of row images
     // dQ from this kernel at d = 16 with fewer tokens than latents: one more image, the lo term of Z (see the kernel)
     const bool zlo = fuse && s.d == 16 && s.N < s.M;
+    // The forms that only few-token shapes and measurements take, and d = 4, exist for 1, 2, 4 and 8 tiles.
+    if (zlo || s.d == 4 || (!fuse && s.d <= 16)) MT = MT <= 2 ? MT : MT <= 4 ? 4 : 8;
     const int na = (zlo ? 5 : 4) * KS + 1;
     size_t lds = (size_t)MT * (na + 4 * HV) * 1024 + (fuse ? 8 * kFusedWaveLds * 2 : 0);
     MergeDz merge = merge_in;
@@ -1105,7 +1109,7 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
         auto kern = KERN;                                                                                        \
         kern<<<grid, THREADS, lds, stream>>>(qq, kk, vv, gg, z, lse_enc, lse_dec2, delta, ld_mul, \
                                              (bf16_t *)dk, (bf16_t *)dv, acc32, dq_part, tok_stride(s), s.H,     \
-                                             s.N, s.M, m0, c2, scale, merge);                                    \
+                                             s.N, s.M, m0, mend, c2, scale, merge);                                    \
     } while (0)
     if (s.d == 32 && MT == 8) {
         // d = 32, 256 latents: the one-exponential variant fits 168 registers, so twelve waves (three per SIMD) share
@@ -1127,7 +1131,7 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
         if (f16) FLARE_DKDV_LAUNCH((bwd_dkdv_planned_kernel<DD, MTT, LO, true>), 512);          \
         else FLARE_DKDV_LAUNCH((bwd_dkdv_planned_kernel<DD, MTT, LO, false>), 512);             \
     } while (0)
-#define FLARE_DKDV_MT(DD, LO)                       \
+#define FLARE_DKDV_POW2(DD, LO)                     \
     switch (MT) {                                   \
         case 1: FLARE_DKDV(DD, 1, LO); break;       \
         case 2: FLARE_DKDV(DD, 2, LO); break;       \
@@ -1135,8 +1139,16 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
         case 8: FLARE_DKDV(DD, 8, LO); break;       \
         default: return FLARE_EUNSUPPORTED;         \
     }
+#define FLARE_DKDV_MT(DD, LO)                       \
+    switch (MT) {                                   \
+        case 3: FLARE_DKDV(DD, 3, LO); break;       \
+        case 5: FLARE_DKDV(DD, 5, LO); break;       \
+        case 6: FLARE_DKDV(DD, 6, LO); break;       \
+        case 7: FLARE_DKDV(DD, 7, LO); break;       \
+        default: FLARE_DKDV_POW2(DD, LO)            \
+    }
     if (s.d == 4 && fuse) {
-        FLARE_DKDV_MT(4, true)
+        FLARE_DKDV_POW2(4, true)
     } else if (s.d == 8 && fuse) {
         FLARE_DKDV_MT(8, true)
     } else if (s.d == 16 && fuse && zlo) {
@@ -1156,20 +1168,25 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
     } else if (s.d == 16 && fuse) {
         FLARE_DKDV_MT(16, true)
     } else if (s.d == 4) {
-        FLARE_DKDV_MT(4, false)
+        FLARE_DKDV_POW2(4, false)
     } else if (s.d == 8) {
-        FLARE_DKDV_MT(8, false)
+        FLARE_DKDV_POW2(8, false)
     } else if (s.d == 16) {
-        FLARE_DKDV_MT(16, false)
+        FLARE_DKDV_POW2(16, false)
     } else {
         switch (MT) {   // d = 32 (with 256 latents: above)
             case 1: FLARE_DKDV(32, 1, false); break;
             case 2: FLARE_DKDV(32, 2, false); break;
+            case 3: FLARE_DKDV(32, 3, false); break;
             case 4: FLARE_DKDV(32, 4, false); break;
+            case 5: FLARE_DKDV(32, 5, false); break;
+            case 6: FLARE_DKDV(32, 6, false); break;
+            case 7: FLARE_DKDV(32, 7, false); break;
             default: return FLARE_EUNSUPPORTED;
         }
     }
 #undef FLARE_DKDV_MT
+#undef FLARE_DKDV_POW2
 #undef FLARE_DKDV
 #undef FLARE_DKDV_LAUNCH
     return check_launch();
@@ -1185,16 +1202,14 @@ size_t mfma_dkdv_acc_bytes(const flare_shape &s)
 // their own, nor at d = 32 with 256, where dK/dV is one launch per variant.
 bool mfma_dz_inline(const flare_shape &s)
 {
-    const int Me = lat_eff(s.M);
-    return s.M <= kLatChunk && !(s.d == 32 && (Me == 192 || Me == 256)) && merge_inline(s, mfma_plan(s).parts);
+    return s.M <= kLatChunk && !(s.d == 32 && lat_eff(s.M) == 256) && merge_inline(s, mfma_plan(s).parts);
 }
 
 // partial slots per (b,h) that mfma_dq_partial writes
 int mfma_dq_parts(const flare_shape &s)
 {
     const MfmaPlan p = mfma_plan(s);
-    int zdim;
-    return p.enc.chunks * dq_geom(s, &zdim).TG;
+    return p.enc.chunks * dq_geom(s).TG;
 }
 
 }  // namespace flare

@@ -381,22 +381,16 @@ __device__ __forceinline__ float pinned(float x)
     return x;
 }
 
-// More than 256 latents per head are taken 256 at a time: the latent-major kernels get one more grid
-// dimension (each workgroup owns one such chunk and streams the tokens again), the token-major ones
+// More than 256 latents per head are taken in chunks of at most 256: the latent-major kernels get one more grid
+// dimension (each workgroup owns some tiles of 32 latents and streams the tokens again), the token-major ones
 // run once per chunk and a merge kernel combines the chunks.
+// Any M runs as ceil(M / 32) tiles; the latents beyond M in the last tile are padding.  The token-major kernels are
+// instantiated for every number of tiles from one to eight, and the chunks of a larger M are equally long: with 1, 2, 4
+// and 8 tiles and chunks of 256 only, 130 or 300 latents paid for 256 and 512.
 constexpr int kLatChunk = 256;
-// Any M runs on the tile geometry of the next size the kernels are instantiated for: 32, 64, 128, 192
-// (only when M is exactly 192), 256, or whole chunks of 256; the latents beyond M are padding.
-inline int pad_latents(int M)
-{
-    if (M <= 32) return 32;
-    if (M <= 64) return 64;
-    if (M <= 128) return 128;
-    if (M == 192) return 192;
-    return (M + kLatChunk - 1) / kLatChunk * kLatChunk;
-}
-inline int lat_eff(int M) { return M > kLatChunk ? kLatChunk : pad_latents(M); }   // latents per chunk (padded)
+inline int lat_tiles(int M) { return (M + 31) / 32; }
 inline int lat_chunks(int M) { return (M + kLatChunk - 1) / kLatChunk; }
+inline int lat_eff(int M) { return 32 * ((lat_tiles(M) + lat_chunks(M) - 1) / lat_chunks(M)); }   // latents per chunk (padded)
 
 constexpr float kLazy = 16.f;   // the stabiliser moves when a score exceeds it by this much (log2 units)
 constexpr int kVtStride = 36;   // uint16 per LDS row: 32 tokens + 4 pad (72 B, conflict-free b64 reads)
@@ -454,45 +448,47 @@ __device__ __forceinline__ GridPos grid_pos_latents(const TokStride &ts, int H, 
 
 inline int check_launch() { return hipGetLastError() == hipSuccess ? FLARE_OK : FLARE_ELAUNCH; }
 
-// latent-group geometry of the encode for a given M
-// NB = 32-latent tiles per wave, G = latent groups (waves) per token tile, TG = token groups.
-struct EncGeom { int NB, G, TG, threads; };
+// Geometry of the encode and dZ kernels for M latents of head dimension d (padded): NB = 32-latent tiles per wave, G =
+// latent groups (waves) per token tile, TG = token groups; a workgroup owns NB * G tiles, the third grid dimension (Z)
+// covers the rest.  More tiles per wave share the loads and the transposed values of a token tile; six or eight tiles per
+// workgroup, whichever leaves less padding (eight where both leave the same).
+struct EncGeom { int NB, G, TG, threads, Z; };
 inline EncGeom enc_geom(int M, int d)
 {
     EncGeom e;
-    const int MB = M / 32;
-    if (MB == 1) e.NB = 1;
-    else if (d == 16 && MB % 4 == 0) e.NB = 4;
-    else e.NB = 2;
-    e.G = MB / e.NB;
-    e.TG = (e.G == 3) ? 1 : 4 / e.G;
+    const int T = lat_tiles(M);
+    if (T == 1) { e.NB = 1; e.G = 1; }
+    else if (T == 2) { e.NB = 2; e.G = 1; }
+    else if (T <= 4 && d == 16) { e.NB = T; e.G = 1; }
+    else if (T <= 4) { e.NB = 2; e.G = 2; }
+    else if ((T + 5) / 6 * 6 < (T + 7) / 8 * 8) { e.NB = 3; e.G = 2; }
+    else if (d == 16) { e.NB = 4; e.G = 2; }
+    else { e.NB = 2; e.G = 4; }
+    e.TG = 4 / e.G;
     e.threads = 64 * e.G * e.TG;
+    e.Z = (T + e.NB * e.G - 1) / (e.NB * e.G);
     return e;
 }
 
 // Geometry of the dQ kernel, which keeps more operands per latent tile than the encode: at most two
-// tiles per wave, and at d = 32 one (two waves per SIMD then fit; a workgroup covers 128 latents and
-// the third grid dimension the rest).  *zdim = workgroups along the latents.
-inline EncGeom dq_geom(const flare_shape &s, int *zdim)
+// tiles per wave, and at d = 32 one (two waves per SIMD then fit).
+inline EncGeom dq_geom(const flare_shape &s)
 {
-    const int Me = lat_eff(s.M);
-    EncGeom e = enc_geom(Me, padded_dim(s.d));
-    if (e.NB == 4) {
-        e.NB = 2;
-        e.G = Me / 64;
-        e.TG = (e.G == 3) ? 1 : 4 / e.G;
-    }
+    const int T = lat_tiles(s.M);
+    EncGeom e;
+    e.NB = T == 1 ? 1 : 2;
+    e.G = T <= 2 ? 1 : T <= 4 ? 2 : T <= 6 ? 3 : 4;
     // d = 32: one latent tile per wave and two waves per SIMD beat two tiles per wave at one wave per SIMD
     // (309 against 366 us at N = 262144, M = 256) -- except with the heads interleaved within a token, where
     // the waves of a workgroup, which all read the same token rows, run into the L1's line rate: there half
-    // as many waves per token tile win (345 against 460 us)
-    if (s.d == 32 && Me % 128 == 0 && s.layout != FLARE_BNHD) {
+    // as many waves per token tile win (345 against 460 us) -- and with five or six tiles, where it would pay for eight
+    if (s.d == 32 && T > 2 && e.G != 3 && s.layout != FLARE_BNHD) {
         e.NB = 1;
         e.G = 4;
-        e.TG = 1;
     }
+    e.TG = e.G == 3 ? 1 : 4 / e.G;
     e.threads = 64 * e.G * e.TG;
-    *zdim = pad_latents(s.M) / (32 * e.NB * e.G);
+    e.Z = (T + e.NB * e.G - 1) / (e.NB * e.G);
     return e;
 }
 

@@ -1131,13 +1131,15 @@ bool mfma_supported(const flare_shape &s)
 MfmaPlan mfma_plan(const flare_shape &s)
 {
     MfmaPlan p;
-    const EncGeom e = enc_geom(lat_eff(s.M), padded_dim(s.d));
+    const EncGeom e = enc_geom(s.M, padded_dim(s.d));
     const int BH = s.B * s.H;
     // each chunk gives every token group at least 8 tiles of 32 tokens
     p.enc = plan_split(s.N, BH, 256 * e.TG, kEncodeTargetBlocks);
     p.parts = p.enc.chunks;
     return p;
 }
+
+int mfma_lat_step(const flare_shape &s) { return lat_eff(s.M); }
 
 size_t mfma_fwd_bytes(const flare_shape &s)
 {
@@ -1152,7 +1154,7 @@ int mfma_encode_partial(const flare_shape &s, const void *q, const void *k, cons
                         float scale, void *ws, MergeZ *g, hipStream_t stream)
 {
     const MfmaPlan p = mfma_plan(s);
-    const EncGeom e = enc_geom(lat_eff(s.M), padded_dim(s.d));
+    const EncGeom e = enc_geom(s.M, padded_dim(s.d));
     Split sp;
     sp.chunks = p.parts;
     sp.chunk_len = 0;
@@ -1160,7 +1162,7 @@ int mfma_encode_partial(const flare_shape &s, const void *q, const void *k, cons
     valu_fwd_layout(s, sp, ws, &m_part, &l_part, &o_part);
     const int BH = s.B * s.H;
     const float c2 = scale * kLog2e;
-    const dim3 grid(p.enc.chunks, BH, lat_chunks(s.M));
+    const dim3 grid(p.enc.chunks, BH, e.Z);
     const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *vv = (const bf16_t *)v;
     {
         LaunchTimer t(KID_ENCODE_PARTIAL, stream);
@@ -1180,6 +1182,7 @@ int mfma_encode_partial(const flare_shape &s, const void *q, const void *k, cons
     do {                                   \
         if (e.NB == 1) FLARE_ENC(DD, 1);   \
         else if (e.NB == 2) FLARE_ENC(DD, 2); \
+        else if (e.NB == 3) FLARE_ENC(DD, 3); \
         else FLARE_ENC(DD, 4);             \
     } while (0)
         switch (s.d) {
@@ -1188,7 +1191,8 @@ int mfma_encode_partial(const flare_shape &s, const void *q, const void *k, cons
             case 16: FLARE_ENC_NB(16); break;
             default:
                 if (e.NB == 1) FLARE_ENC(32, 1);
-                else FLARE_ENC(32, 2);
+                else if (e.NB == 2) FLARE_ENC(32, 2);
+                else FLARE_ENC(32, 3);
         }
 #undef FLARE_ENC_NB
 #undef FLARE_ENC
@@ -1212,10 +1216,10 @@ int mfma_dz_partial(const flare_shape &s, const void *q, const void *k, const vo
                     hipStream_t stream)
 {
     const MfmaPlan p = mfma_plan(s);
-    const EncGeom e = enc_geom(lat_eff(s.M), padded_dim(s.d));
+    const EncGeom e = enc_geom(s.M, padded_dim(s.d));
     const int BH = s.B * s.H;
     const float c2 = scale * kLog2e;
-    const dim3 grid(p.enc.chunks, BH, lat_chunks(s.M));
+    const dim3 grid(p.enc.chunks, BH, e.Z);
     const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *gg = (const bf16_t *)dy;
     LaunchTimer t(KID_BWD_DZ_PARTIAL, stream);
     const bool f16 = s.dtype == FLARE_F16;
@@ -1244,6 +1248,7 @@ int mfma_dz_partial(const flare_shape &s, const void *q, const void *k, const vo
     do {                                  \
         if (e.NB == 1) FLARE_DZ(DD, 1);   \
         else if (e.NB == 2) FLARE_DZ(DD, 2); \
+        else if (e.NB == 3) FLARE_DZ(DD, 3); \
         else FLARE_DZ(DD, 4);             \
     } while (0)
     switch (s.d) {
@@ -1252,7 +1257,8 @@ int mfma_dz_partial(const flare_shape &s, const void *q, const void *k, const vo
         case 16: FLARE_DZ_NB(16); break;
         default:
             if (e.NB == 1) FLARE_DZ(32, 1);
-            else FLARE_DZ(32, 2);
+            else if (e.NB == 2) FLARE_DZ(32, 2);
+            else FLARE_DZ(32, 3);
     }
 #undef FLARE_DZ_NB
 #undef FLARE_DZ
@@ -1268,7 +1274,7 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
     const size_t lds = merge.parts ? (size_t)s.M * s.d * 4 : 0;
     const int BH = s.B * s.H;
     const int tiles = (s.N + 31) / 32;
-    // d = 32 with 192 or 256 latents (Z in LDS, 168 registers): three workgroups fit a CU
+    // d = 32 with more than 128 latents (Z in LDS, 168 registers): three workgroups fit a CU
     const bool three = padded_dim(s.d) == 32 && Mc > 128;
     int blocks = ((three ? 768 : kDecodeTargetBlocks) + BH - 1) / BH;
     if (blocks > (tiles + 3) / 4) blocks = (tiles + 3) / 4;
@@ -1301,8 +1307,11 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
     switch (MT) {                                      \
         case 1: FLARE_DEC(DD, 1, true, 2); break;      \
         case 2: FLARE_DEC(DD, 2, true, 2); break;      \
+        case 3: FLARE_DEC(DD, 3, true, 2); break;      \
         case 4: FLARE_DEC(DD, 4, true, 2); break;      \
+        case 5: FLARE_DEC(DD, 5, true, 2); break;      \
         case 6: FLARE_DEC(DD, 6, true, 2); break;      \
+        case 7: FLARE_DEC(DD, 7, true, 2); break;      \
         case 8: FLARE_DEC(DD, 8, true, 2); break;      \
         default: return FLARE_EUNSUPPORTED;            \
     }
@@ -1316,8 +1325,11 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
         switch (MT) {
             case 1: FLARE_DEC(32, 1, true, 2); break;
             case 2: FLARE_DEC(32, 2, true, 2); break;
+            case 3: FLARE_DEC(32, 3, true, 2); break;
             case 4: FLARE_DEC(32, 4, true, 2); break;
+            case 5: FLARE_DEC(32, 5, false, 2); break;
             case 6: FLARE_DEC(32, 6, false, 2); break;
+            case 7: FLARE_DEC(32, 7, false, 2); break;
             case 8: FLARE_DEC(32, 8, false, 2); break;
             default: return FLARE_EUNSUPPORTED;
         }
@@ -1443,7 +1455,7 @@ size_t mfma_tok_part_bytes(const flare_shape &s)
     return ((rows * s.d * (s.y_f32 ? 4 : 2) + 255) & ~(size_t)255) + ((rows * 4 + 255) & ~(size_t)255);
 }
 
-// decode (MODE 0) or token statistics (MODE 1) over all latents, in chunks of 256 when there are more
+// decode (MODE 0) or token statistics (MODE 1) over all latents, in chunks of at most 256 when there are more
 template <int MODE>
 static int decode_all(const flare_shape &s, const void *q, const void *k, const float *z, void *y, const void *dy,
                       float *lse_out, float *delta, float scale, void *ws, const MergeZ &merge, hipStream_t stream,
@@ -1452,7 +1464,7 @@ static int decode_all(const flare_shape &s, const void *q, const void *k, const 
     if (s.M <= kLatChunk)
         return launch_decode_family<MODE>(s, q, k, z, y, tok_stride(s), dy, lse_out, delta, 0, lat_eff(s.M), scale,
                                           merge, stream, flags);
-    const int C = lat_chunks(s.M);
+    const int C = lat_chunks(s.M), Mc = lat_eff(s.M);
     const size_t rows = (size_t)s.B * s.H * s.N;
     const size_t es = s.y_f32 ? 4 : 2;          // bytes per element of the partial rows
     float *lse_part = reinterpret_cast<float *>(static_cast<char *>(ws) + ((rows * C * s.d * es + 255) & ~(size_t)255));
@@ -1461,7 +1473,7 @@ static int decode_all(const flare_shape &s, const void *q, const void *k, const 
         float *delta_part = static_cast<float *>(ws);
         for (int c = 0; c < C; ++c) {
             const int rc = launch_decode_family<1>(s, q, k, z, nullptr, tok_stride(s), dy, lse_part + (size_t)c * rows,
-                                                   delta_part + (size_t)c * rows, c * kLatChunk, kLatChunk, scale,
+                                                   delta_part + (size_t)c * rows, c * Mc, Mc, scale,
                                                    merge, stream, flags);
             if (rc != FLARE_OK) return rc;
         }
@@ -1475,7 +1487,7 @@ static int decode_all(const flare_shape &s, const void *q, const void *k, const 
         for (int c = 0; c < C; ++c) {
             void *part_c = static_cast<char *>(ws) + (size_t)c * rows * s.d * es;
             const int rc = launch_decode_family<0>(s, q, k, z, part_c, tp, nullptr, lse_part + (size_t)c * rows, nullptr,
-                                                   c * kLatChunk, kLatChunk, scale, merge, stream, flags);
+                                                   c * Mc, Mc, scale, merge, stream, flags);
             if (rc != FLARE_OK) return rc;
         }
         const dim3 grid((s.N + 255) / 256, s.B * s.H);

@@ -285,8 +285,11 @@ int mfma_decode_project(const flare_shape &s, const void *q, const void *k, cons
     switch (MT) {
         case 1: FLARE_PROJ_H(1) break;
         case 2: FLARE_PROJ_H(2) break;
+        case 3: FLARE_PROJ_H(3) break;
         case 4: FLARE_PROJ_H(4) break;
+        case 5: FLARE_PROJ_H(5) break;
         case 6: FLARE_PROJ_H(6) break;
+        case 7: FLARE_PROJ_H(7) break;
         case 8: FLARE_PROJ_H(8) break;
         default: return FLARE_EUNSUPPORTED;
     }

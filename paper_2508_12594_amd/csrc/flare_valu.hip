@@ -969,7 +969,7 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
         const bool dq_fused = mfma_dq_fused(s);             // dQ comes out of the dK/dV kernel
         const bool chunked = mfma_dkdv_acc_bytes(s) != 0;   // more than 256 latents: one pass per chunk
         dq_parts = dq_fused ? mfma_dkdv_blocks(s) : mfma_dq_parts(s);
-        for (int m0 = 0; m0 < s.M && rc == FLARE_OK; m0 += 256)   // each (b,h) slice by the variant its plan names
+        for (int m0 = 0; m0 < s.M && rc == FLARE_OK; m0 += mfma_lat_step(s))   // each (b,h) slice by the variant its plan names
             rc = mfma_dkdv(s, q, k, v, dy, z, lse_enc, ld, w.delta, ld_mul, dk, dv, chunked ? w.acc32 : nullptr,
                            dq_fused ? w.dq_part : nullptr, m0, scale, merge, stream);
         if (!dq_fused && rc == FLARE_OK)

@@ -1,0 +1,64 @@
+"""GPU parity where the geometry of a launch changes: every number of 32-latent tiles with its remainders, chunks of
+more than 256 latents that are not whole multiples of anything, and the numbers of token chunks on either side of
+where the consumers stop merging the partial slots themselves.
+
+Bars: those of the other parity tests (tests/_util.py): 1e-5 for fp32, 2e-2 with 16-bit storage.
+"""
+import pytest
+import torch
+
+from paper_2508_12594_amd import binding, synth
+from tests._util import slice_relerr, to_device, to_host, tol_for
+
+pytestmark = pytest.mark.gpu
+
+# 3, 4 (ragged), 5, 6, 7, 8 tiles; two chunks of 5 and 7; three of 6; d = 16 with fewer tokens than latents
+TILES = [(M, d, 700) for M in (65, 96, 97, 130, 161, 192, 200, 225) for d in (8, 16, 32)]
+TILES += [(M, d, 1100) for M in (257, 300, 420, 545) for d in (4, 8, 16, 32)] + [(300, 16, 90), (161, 16, 100)]
+# H = 1: 1024 tokens per chunk at d = 16, so 16 and 17 slots; fp32: a chunk per 128 tokens
+SLOTS = [("bf16", 16 * 1024, 64, 16), ("f16", 16 * 1024 + 1, 64, 16), ("bf16", 16 * 1024 + 1, 64, 8),
+         ("bf16", 8 * 1024 + 1, 96, 32), ("f32", 2048, 48, 16), ("f32", 2049, 48, 16), ("f32", 1900, 40, 32)]
+
+
+def _check(oracle, dtype, H, N, M, d, layout, saved):
+    print("[case] %s H=%d N=%d M=%d d=%d %s saved=%s" % (dtype, H, N, M, d, layout, saved), flush=True)
+    inp = synth.make_inputs(1, B=1, H=H, N=N, M=M, d=d, dtype=dtype, with_dy=True, seed=31 + N + M + d)
+    scale, tol, dev = inp["scale"], tol_for(inp), to_device(inp)
+    order = (lambda t: t.permute(0, 2, 1, 3).contiguous()) if layout == "bnhd" else (lambda t: t)
+    k, v, dy = (order(dev[n]) for n in ("k", "v", "dy"))
+    ld = torch.empty((1, H, N), dtype=torch.float32, device="cuda") if saved else None
+    y, z, lse = binding.forward(dev["q"], k, v, scale, lse_dec=ld, layout=layout)
+    dq, dk, dv = binding.backward(dev["q"], k, v, dy, z, lse, scale, y=y if saved else None, lse_dec=ld, layout=layout)
+    y_ref, z_ref, _ = oracle.forward(inp["q"], inp["k"], inp["v"], scale)
+    dq_ref, dk_ref, dv_ref = oracle.backward(inp["q"], inp["k"], inp["v"], inp["dy"], scale)
+    errs = dict(y=slice_relerr(to_host(order(y)), y_ref), z=slice_relerr(to_host(z), z_ref),
+                dq=slice_relerr(to_host(dq), dq_ref), dk=slice_relerr(to_host(order(dk)), dk_ref),
+                dv=slice_relerr(to_host(order(dv)), dv_ref))
+    print("[case]    " + "  ".join("%s %.2e" % kv for kv in errs.items()), flush=True)
+    assert max(errs.values()) <= tol
+
+
+@pytest.mark.parametrize("M,d,N", TILES)
+def test_latent_tiles(oracle, M, d, N):
+    _check(oracle, "f16" if M % 3 == 0 else "bf16", 2, N, M, d, "bnhd" if M % 2 else "bhnd", saved=M % 5 != 0)
+
+
+@pytest.mark.parametrize("dtype,N,M,d", SLOTS)
+def test_slots_merged_by_consumer_or_kernel(oracle, dtype, N, M, d):
+    _check(oracle, dtype, 1, N, M, d, "bhnd", saved=True)
+
+
+@pytest.mark.parametrize("M", [70, 150, 200])
+def test_projection_of_ragged_latents(M):
+    """The fused projection forms the y that the decode forms, bit for bit, whatever the number of tiles."""
+    print("[case] projection M=%d" % M, flush=True)
+    inp = synth.make_inputs(1, B=1, H=4, N=777, M=M, d=16, dtype="bf16", seed=5 + M)
+    dev = to_device(inp, ("q", "k", "v"))
+    k, v = (dev[n].permute(0, 2, 1, 3).contiguous() for n in ("k", "v"))
+    y_ref, z_ref, lse_ref = binding.forward(dev["q"], k, v, inp["scale"], layout="bnhd")
+    y = torch.empty_like(k)
+    w = torch.eye(64, dtype=k.dtype, device="cuda")
+    out, z, lse = binding.forward_project(dev["q"], k, v, w, inp["scale"], y=y)
+    assert torch.equal(z, z_ref) and torch.equal(lse, lse_ref)
+    # (z that the decode merged for itself and z from memory are the same numbers)
+    assert torch.equal(y, y_ref) and torch.equal(out.view_as(y), y)
