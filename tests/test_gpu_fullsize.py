@@ -124,7 +124,7 @@ MILLION_VARIANTS = [
     (dict(M=200), True, False),                   # 56 padding latents in the last tiles
     (dict(d=8), False, True),                     # the paper's head dimension for PDE meshes, token-major layout
     (dict(M=512, H=2, d=8), True, False),         # two latent chunks
-    (dict(dtype="f32", M=64), True, False),       # the fp32 vector kernels: sums of 10^6 terms within 1e-5
+    (dict(dtype="f32", M=64), True, False),       # fp32 storage on the matrix cores: sums of 10^6 terms within 1e-5
 ]
 
 

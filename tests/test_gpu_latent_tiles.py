@@ -19,6 +19,11 @@ TILES += [(M, d, 1100) for M in (257, 300, 420, 545) for d in (4, 8, 16, 32)] + 
 SLOTS = [("bf16", 16 * 1024, 64, 16), ("f16", 16 * 1024 + 1, 64, 16), ("bf16", 16 * 1024 + 1, 64, 8),
          ("bf16", 8 * 1024 + 1, 96, 32), ("f32", 2048, 48, 16), ("f32", 2049, 48, 16), ("f32", 1900, 40, 32)]
 
+# fp32: remainders of a tile, the last number of latents whose planes fit in LDS together and the first that runs in
+# chunks (d = 8, 16, 32: 256; a token batch is then 1024 tokens in the decode, 512 in dK/dV), more than 2048 latents
+F32 = [(33, 4, 129), (31, 8, 33), (97, 16, 260), (160, 32, 257), (256, 16, 1000), (257, 16, 1025), (289, 32, 2049),
+       (600, 8, 1100), (2049, 16, 90)]
+
 
 def _check(oracle, dtype, H, N, M, d, layout, saved):
     print("[case] %s H=%d N=%d M=%d d=%d %s saved=%s" % (dtype, H, N, M, d, layout, saved), flush=True)
@@ -41,6 +46,11 @@ def _check(oracle, dtype, H, N, M, d, layout, saved):
 @pytest.mark.parametrize("M,d,N", TILES)
 def test_latent_tiles(oracle, M, d, N):
     _check(oracle, "f16" if M % 3 == 0 else "bf16", 2, N, M, d, "bnhd" if M % 2 else "bhnd", saved=M % 5 != 0)
+
+
+@pytest.mark.parametrize("M,d,N", F32)
+def test_latent_tiles_of_fp32_storage(oracle, M, d, N):
+    _check(oracle, "f32", 2, N, M, d, "bnhd" if M % 2 else "bhnd", saved=M % 3 != 0)
 
 
 @pytest.mark.parametrize("dtype,N,M,d", SLOTS)

@@ -26,7 +26,7 @@ def _bnhd(t):
 
 
 CASES = [
-    (1, dict(N=777, B=2)),          # fp32 vector path
+    (1, dict(N=777, B=2)),          # fp32 storage
     (1, dict(N=300, M=40, d=4)),    # smallest head dimension, ragged M
     (2, dict(B=2, N=2050)),         # matrix-core path, d=16, M=64
     (3, dict(B=2, N=1500)),         # d=32, M=128
