@@ -477,6 +477,10 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
             row_ops<DR, false>(tile + L::Y + l32 * Geo::RD, hh, tok);
             f32x16 cc = row_dot<DR, true>(zp, tok, tile_rows(stat + 32, hh));
             const f32x16 w = tile_rows(stat, hh);
+            if (tok0 + 32 > n1) {     // no weight behind the chunk's end: 2^(0 - lse_enc2) need not be a number
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[i] = tok0 + tile_row(i, hh) < n1 ? s[i] : -INFINITY;
+            }
             if (one_exp) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) s[i] = fast_exp2(s[i]) * fmaf(w[i], cc[i], a[i]);
