@@ -30,9 +30,11 @@
  *     either flare_layout for the token tensors (every "[B][H][N][d]" below reads [B][N][H][d]
  *     when shape->layout is FLARE_BNHD; the per-token statistic lse_dec is [B][H][N] always).
  *     Shapes with dtype bf16 or f16, M <= 2048 and N >= 16 run on the matrix-core kernels (d < 16 with the
- *     contraction padded to 16; M in whole tiles of 32, the latents beyond M being padding that is
- *     masked; M > 256 in chunks of at most 256 latents, all equally long); dtype f32 runs on matrix-core kernels of its own (every fp32 operand as the exact sum
- *     of three bf16 terms, products good to 2^-26, fp32 sums); everything else runs on the fp32 vector kernels.
+ *     contraction padded to 16; M in whole tiles of 32, the latents beyond M being padding that is masked;
+ *     M > 256 in chunks of at most 256 latents, all equally long).  dtype f32 runs on matrix-core kernels
+ *     of its own (every fp32 operand as the exact sum of three bf16 terms, products good to 2^-26, fp32
+ *     sums; v, dy and the products <dZ, v>, <z, dy> count in full where their magnitude is 1e-20 ... 1e34).
+ *     Everything else runs on the fp32 vector kernels.
  *     With 16-bit storage on the matrix cores the scores come from exact products of the stored 16-bit
  *     values, the softmax weights and dS are rounded to bf16 whatever the storage type (with f16 storage v
  *     and dy are rounded to bf16 as they are read), sums are fp32, and outputs are rounded once from fp32.

@@ -81,21 +81,26 @@ __device__ __forceinline__ void merge_z_rows(const MergeZ &g, int bh, int M, int
 // ---- the variant of the last backward kernels ---------------------------------------------------
 // They exist with one and with two exponentials per score.
 // One exponential: P~ = 2^S2 as it comes, without a normaliser (S2 <= lse_enc2[m] and S2 <= lse_dec2[n], so with
-// both log-sum-exps of a (b,h) within +-kPlanSpan nothing overflows and every weight that matters is a normal
+// both log-sum-exps of a (b,h) within +-span nothing overflows and every weight that matters is a normal
 // number), P = P~ e_m with e_m = 2^-lse_enc2[m] and R = P~ w_n with w_n = 2^-lse_dec2[n]:
 //   dS = P (a - eps) + R (c - delta) = P~ (e_m (a - eps_m) + w_n (c - delta_n)),   dV += (e_m dZ_m) P~.
 // e_m is folded into dZ where its partials are merged, BEFORE dZ is rounded to bf16 and eps = <dZ, Z> is formed
 // (bwd_one_exp_ok decides there, and the kernels that follow take dZ and eps as they find them), so that a and
 // eps still see the same rounded values and the score products need no correction k-step; w_n is a per-token
-// scalar.  Anything else (log-sum-exps beyond +-kPlanSpan, non-finite statistics) takes the two-exponential
+// scalar.  Anything else (log-sum-exps beyond +-span, non-finite statistics) takes the two-exponential
 // form with dZ as it is.
 // ld_range[b*h][part] = (min, max) of lse_dec2 as the dZ kernels recorded it.
 // Called by a whole workgroup of at most 16 waves, all of whose threads take part in the reads (one memory latency, not
 // one per 64 values); one barrier inside; every thread returns the same answer.  red: 64 floats of LDS.
+// span: kPlanSpan, or kSpan32 with fp32 storage; below zero: two exponentials whatever the statistics.
 constexpr float kPlanSpan = 60.f;
+// fp32 storage: the third plane of a value or gradient x (2^-18 of it) beside a factor 2^-span must not fall below 2^-126,
+// where the matrix cores read zero: x from 2^-68 = 3e-21 up with 40 log2 units.  (The one plane of 16-bit storage is good
+// to 2^-66 with 60.)
+constexpr float kSpan32 = 40.f;
 __device__ __forceinline__ bool is_nan(float x) { return (__float_as_uint(x) & 0x7fffffffu) > 0x7f800000u; }
 __device__ __forceinline__ bool bwd_one_exp_ok(const float *__restrict__ ld_range, const float *__restrict__ lse_enc,
-                                               int bh, int parts, int M, int force_two, float *red)
+                                               int bh, int parts, int M, float span, float *red)
 {
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
     // the largest of lse_enc2, -lse_enc2, lse_dec2, -lse_dec2
@@ -117,7 +122,7 @@ __device__ __forceinline__ bool bwd_one_exp_ok(const float *__restrict__ ld_rang
     if (lane == 0) red[wave] = worst;
     __syncthreads();
     for (int i = 0; i < nt / 64; ++i) worst = fmaxf(worst, red[i]);
-    return worst <= kPlanSpan && !force_two;
+    return worst <= span;
 }
 
 // ---- dZ and eps of one (b,h) ------------------------------------------------------------------
@@ -126,7 +131,7 @@ struct MergeDz {
     float *dz, *eps;                // [b*h][M][d], [b*h][M]
     int *plan;                      // [b*h]: 1 = one exponential
     int parts;                      // 0: dz, eps and plan are complete
-    int force_two;
+    float span;                     // of bwd_one_exp_ok
     unsigned lds;                   // byte offset of the merged rows in the workgroup's dynamic LDS
 };
 
@@ -195,7 +200,7 @@ __device__ __forceinline__ bool merged_dz(const MergeDz &g, const float *z, cons
     eps = g.eps + (size_t)bh * M;
     if (g.parts == 0) return g.plan[bh] != 0;
     constexpr int L = D / 4;
-    const bool one = bwd_one_exp_ok(g.ld_range, lse_enc, bh, g.parts, M, g.force_two, red);
+    const bool one = bwd_one_exp_ok(g.ld_range, lse_enc, bh, g.parts, M, g.span, red);
     const int j = threadIdx.x % L, rows = blockDim.x / L;
     for (int m0 = 0; m0 < M; m0 += rows) {           // whole rows of lanes stay together (shuffles)
         const int m = m0 + threadIdx.x / L;

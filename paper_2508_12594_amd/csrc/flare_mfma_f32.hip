@@ -5,8 +5,9 @@
 //     a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1 + a0 b0        (small terms first, fp32 accumulation)
 // of v_mfma_f32_32x32x16_bf16; what is left out (a1 b2, a2 b1, a2 b2) is below 2^-26 |a||b|, a quarter of the rounding
 // an fp32 multiplication makes.  Exponentials, normalisers, dS and every sum stay fp32; a weight enters its value
-// product as three planes as well, so nothing is rounded to 16 bits anywhere.  The range is fp32's own (bf16 has its
-// exponent field).
+// product as three planes as well, so nothing is rounded to 16 bits anywhere.  The range is that of bf16's exponent field:
+// a value or gradient counts in full from 1e-20 (its third plane beside an unnormalised weight, kSpan32) to 1e34 (sums of
+// up to 8192 of them).
 //
 // Why: the vector ALU does an fp32 multiply-add for a wave in about 4.5 clocks, 145 clocks for one score with its value
 // product at d = 16; a 32 x 32 tile of scores took 2800 clocks per SIMD in the vector kernels this file replaces.  On
@@ -259,9 +260,18 @@ __device__ __forceinline__ float sum16(const f32x16 &t)
     return (a[0] + a[1]) + (a[2] + a[3]);
 }
 
-// Log-sum-exps within this many log2 units of zero need no normaliser inside an exponential: 2^S and 2^-lse are then
-// normal numbers wherever they matter (as kPlanSpan for the variants of the backward).
-constexpr float kSpan = 60.f;
+// Weights are summed as 2^S, without a normaliser, while that loses nothing: the sum of weights l at least 2^-40 (for the
+// small planes, as kSpan32) and at most 2^100, the sums of weighted values below 2^100, so that
+// what the chunks add up to stays finite.  Otherwise the sums are taken again behind a maximum, where a sum overflows
+// only for values beyond 2^115.  Tested on the bits: the compiler may take it that there are no NaNs.
+__device__ __forceinline__ bool needs_maximum(float l, const f32x16 &o)
+{
+    const uint32_t lb = __float_as_uint(l);
+    uint32_t top = 0u;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) top = max(top, __float_as_uint(o[i]) & 0x7fffffffu);
+    return lb < ((127u - 40u) << 23) || lb > ((127u + 100u) << 23) || top > ((127u + 100u) << 23);
+}
 
 // ============================================================================================
 // Latent-major pass over a chunk of tokens: encode partials (MODE 0), dZ partials (1), dQ partials (2).
@@ -269,9 +279,9 @@ constexpr float kSpan = 60.f;
 // of the chunk.  The workgroup stages TG token tiles at a time: every thread loads pieces of eight elements, splits them
 // into planes and puts them into one of two LDS buffers, a stage ahead of their use; one barrier per stage.  (Split by
 // every wave for itself, the rows of a tile would cost each of the G waves 125 clocks per tensor and tile.)
-//   MODE 0: weights 2^S as they come; when a latent's sum leaves [2^-80, 2^100] the workgroup does the chunk again with
+//   MODE 0: weights 2^S as they come; when a latent's sums say so (needs_maximum) the workgroup does the chunk again with
 //           a running maximum.  Writes (c, l, O) of the chunk.
-//   MODE 1: weights 2^S, values 2^-lse_dec2[n] dY_n (|lse_dec2| beyond kSpan: what is beyond goes into the exponent).
+//   MODE 1: weights 2^S, values 2^-lse_dec2[n] dY_n (|lse_dec2| beyond kSpan32: what is beyond goes into the exponent).
 //           Also delta[n] = <dY_n, Y_n> when y is given, and the range of lse_dec2 for bwd_one_exp_ok.
 //   MODE 2: dS = 2^S (<dZ'_m, V_n> - eps'_m + 2^-lse_dec2[n] (<Z_m, dY_n> - delta_n)) with dZ', eps' carrying
 //           2^-lse_enc2[m] (plan 1), or with both exponentials (plan 0); values K.
@@ -409,7 +419,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
                     ld_min = fminf(ld_min, ld);
                     ld_max = fmaxf(ld_max, ld);
                 }
-                const float lc = fminf(fmaxf(ld, -kSpan), kSpan), w = fast_exp2(-lc);
+                const float lc = fminf(fmaxf(ld, -kSpan32), kSpan32), w = fast_exp2(-lc);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[it][i] *= w;
                 if (piece == 0) stat[t32] = in ? ld - lc : 0.f;
@@ -506,8 +516,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
     if constexpr (MODE == 0) {
         l += __shfl_xor(l, 32);
         // waves without a tile in this chunk (l = 0) and padding latents have nothing to say
-        const uint32_t lb = __float_as_uint(l);
-        const bool bad = m < M && 32 * tg < n1 - n0 && (lb < ((127u - 80u) << 23) || lb > ((127u + 100u) << 23));
+        const bool bad = m < M && 32 * tg < n1 - n0 && needs_maximum(l, o);
         if (__syncthreads_or(bad)) {
             o = splat16(0.f);
             l = 0.f;
@@ -586,7 +595,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
 //   MODE 2: dK and dV.
 // The planes of up to CT latent tiles lie in LDS (built by the workgroup).  With more latents than that (T = 4) a wave
 // keeps the sums of T token tiles in registers while the workgroup goes over the chunks of latents.
-// Weights are 2^S as they come; a token whose denominator leaves [2^-80, 2^100] is done again from its exact maximum.
+// Weights are 2^S as they come; a token whose sums say so (needs_maximum) is done again from its exact maximum.
 // MODE 2 has a one- and a two-exponential form (plan) as the latent-major kernel.
 // ============================================================================================
 struct TokenArgs {
@@ -808,10 +817,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
             sweep(std::integral_constant<int, 0>{});
             bool bad = false;
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const uint32_t lb = __float_as_uint(l[t]);
-                bad |= tile_of(b, t) < tiles && (lb < ((127u - 80u) << 23) || lb > ((127u + 100u) << 23));
-            }
+            for (int t = 0; t < T; ++t) bad |= tile_of(b, t) < tiles && needs_maximum(l[t], acc[t]);
             if (T > 1 ? __syncthreads_or(bad) : __any(bad)) {
                 sweep(std::integral_constant<int, 1>{});
                 sweep(std::integral_constant<int, 2>{});

@@ -529,7 +529,7 @@ template <int D>
 __global__ __launch_bounds__(256) void dz_merge_kernel(
     const float *__restrict__ dz_part, const float *__restrict__ z,
     float *__restrict__ dz, float *__restrict__ eps, int BH, int M, int parts, int round_bf16,
-    const float *__restrict__ ld_range, const float *__restrict__ lse_enc, int *__restrict__ plan, int force_two)
+    const float *__restrict__ ld_range, const float *__restrict__ lse_enc, int *__restrict__ plan, float span)
 {
     const int j = threadIdx.x & 15;
     const int m = blockIdx.x * 16 + (threadIdx.x >> 4);
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(256) void dz_merge_kernel(
     // matrix-core path: which variant of the next kernels runs for this (b,h) (every workgroup works it out for
     // itself: the one-exponential variant wants dZ scaled, see bwd_one_exp_ok); one more workgroup records it
     __shared__ float plan_red[64];
-    const bool one_exp = plan != nullptr && bwd_one_exp_ok(ld_range, lse_enc, bh, parts, M, force_two, plan_red);
+    const bool one_exp = plan != nullptr && bwd_one_exp_ok(ld_range, lse_enc, bh, parts, M, span, plan_red);
     if (plan != nullptr && blockIdx.x == gridDim.x - 1) {
         if (threadIdx.x == 0) plan[bh] = one_exp ? 1 : 0;
         return;
@@ -571,14 +571,14 @@ template <int D>
 __global__ __launch_bounds__(256) void dz_merge_few_kernel(
     const float *__restrict__ dz_part, const float *__restrict__ z,
     float *__restrict__ dz, float *__restrict__ eps, int BH, int M, int parts, int round_bf16,
-    const float *__restrict__ ld_range, const float *__restrict__ lse_enc, int *__restrict__ plan, int force_two)
+    const float *__restrict__ ld_range, const float *__restrict__ lse_enc, int *__restrict__ plan, float span)
 {
     constexpr int L = D / 4, ROWS = 256 / L;
     const int j = threadIdx.x % L;
     const int m = blockIdx.x * ROWS + threadIdx.x / L;
     const int bh = blockIdx.y;
     __shared__ float plan_red[64];                   // as in dz_merge_kernel
-    const bool one_exp = plan != nullptr && bwd_one_exp_ok(ld_range, lse_enc, bh, parts, M, force_two, plan_red);
+    const bool one_exp = plan != nullptr && bwd_one_exp_ok(ld_range, lse_enc, bh, parts, M, span, plan_red);
     if (plan != nullptr && blockIdx.x == gridDim.x - 1) {
         if (threadIdx.x == 0) plan[bh] = one_exp ? 1 : 0;
         return;
@@ -939,19 +939,20 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
         if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
     }
     constexpr int kFewRows = 256 / (D / 4);   // rows per workgroup of the few-slot merge kernels
+    const float span = (s.variant & FLARE_VARIANT_TWO_EXP) ? -1.f : F32 ? kSpan32 : kPlanSpan;   // bwd_one_exp_ok
     // what the dK/dV kernel has to merge itself, if anything
     const MergeDz merge{w.part, w.ld_range, w.dz, w.eps, w.plan, dz_inline(s) ? dz_parts : 0,
-                        (s.variant & FLARE_VARIANT_TWO_EXP) ? 1 : 0, 0u};
+                        span, 0u};
     if (merge.parts == 0) {
         LaunchTimer t(KID_BWD_DZ_MERGE, stream);
         if (dz_parts <= kFewSlots)
             dz_merge_few_kernel<D><<<dim3((s.M + kFewRows - 1) / kFewRows + (planned ? 1 : 0), BH), 256, 0, stream>>>(
                 w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, planned ? w.plan : nullptr,
-                (s.variant & FLARE_VARIANT_TWO_EXP) ? 1 : 0);
+                span);
         else
             dz_merge_kernel<D><<<dim3((s.M + 15) / 16 + (planned ? 1 : 0), BH), 256, 0, stream>>>(
                 w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, planned ? w.plan : nullptr,
-                (s.variant & FLARE_VARIANT_TWO_EXP) ? 1 : 0);
+                span);
     }
     if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
     // dK and dV, then (with a kernel of its own for it) dQ: where dZ is merged by the dK/dV kernel, the dQ kernel reads

@@ -85,6 +85,18 @@ def test_wide_score_range(oracle, M, d, saved):
     _check(oracle, dict(inp, q=q, k=k), saved)
 
 
+# Weights are summed as 2^S while nothing leaves the range of fp32 that way: scores within that range, and values or
+# gradients large or small enough that 2^S times them is not.
+@pytest.mark.parametrize("N,M,d", SHAPES)
+@pytest.mark.parametrize("nats,v_size,dy_size", [(61.0, 1e12, 1.0), (25.0, 1e25, 1e-18), (-55.0, 1e-21, 1.0),
+                                                 (-40.0, 1.0, 1e-20), (38.0, 1.0, 1e-20), (18.0, 1.0, 1e-20)])
+def test_size_of_values_and_gradients(oracle, nats, v_size, dy_size, N, M, d):
+    print("[case] fp32, scores shifted by %g, v of %g, dY of %g: N=%d M=%d d=%d" % (nats, v_size, dy_size, N, M, d), flush=True)
+    inp = _shift_scores(_inputs(N, M, d), nats)
+    inp = dict(inp, v=inp["v"] * np.float32(v_size), dy=inp["dy"] * np.float32(dy_size))
+    _check(oracle, inp, saved=N > 600)
+
+
 @pytest.mark.parametrize("N,M,d", SHAPES)
 def test_two_exponential_kernels(oracle, N, M, d):
     """The two-exponential form of the backward, forced on ordinary inputs."""
