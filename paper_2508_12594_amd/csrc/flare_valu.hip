@@ -793,7 +793,12 @@ inline int bwd_slots(const flare_shape &s, const ValuPlan &plan)
     int mf = 0;
     if (mfma_supported(s)) {
         mf = mfma_plan(s).parts;
-        if (mfma_dq_parts(s) > mf) mf = mfma_dq_parts(s);
+        // the dQ kernel's slots depend on the token order (dq_geom); what the caller is told to bring does not
+        for (const flare_layout layout : {FLARE_BHND, FLARE_BNHD}) {
+            flare_shape t = s;
+            t.layout = layout;
+            if (mfma_dq_parts(t) > mf) mf = mfma_dq_parts(t);
+        }
         if (mfma_dkdv_blocks(s) > mf) mf = mfma_dkdv_blocks(s);
     }
     return plan.bwd.chunks > mf ? plan.bwd.chunks : mf;

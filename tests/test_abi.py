@@ -50,6 +50,28 @@ def test_version_and_strerror(lib):
         assert len(binding.strerror(code)) > 0
 
 
+def test_workspace_bytes_do_not_depend_on_the_layout(lib):
+    """binding.workspace_bytes has no layout argument: what it reports has to serve both.  Few tokens, where one slot more
+    per chunk is the largest count there is, every tile count and head dimension."""
+    def both(*dims):
+        out = []
+        for layout in (binding.FLARE_BHND, binding.FLARE_BNHD):
+            f, b = ctypes.c_size_t(0), ctypes.c_size_t(0)
+            shp = binding.FlareShape(*dims, layout)
+            assert lib.flare_workspace_bytes(ctypes.byref(shp), ctypes.byref(f), ctypes.byref(b)) == 0
+            out.append((f.value, b.value))
+        return out
+
+    for dtype in (binding.FLARE_F32, binding.FLARE_BF16, binding.FLARE_F16):
+        for d in (4, 8, 16, 32):
+            for M in (1, 33, 65, 96, 100, 128, 129, 200, 256, 300, 2048):
+                for N in (1, 16, 31, 57, 300, 5000, 100000):
+                    for B, H in ((1, 1), (1, 8), (3, 8), (25, 2), (64, 32), (300, 100)):
+                        bhnd, bnhd = both(B, H, N, M, d, dtype)
+                        assert bhnd == bnhd, (B, H, N, M, d, dtype)
+                        assert binding.workspace_bytes(B, H, N, M, d, dtype) == bnhd
+
+
 def test_workspace_bytes_and_shape_checks(lib):
     f, b = binding.workspace_bytes(1, 8, 1000000, 256, 16, binding.FLARE_BF16)
     assert 0 < f < 64 << 20 and b > 0
