@@ -7,6 +7,7 @@
 #include <torch/csrc/autograd/function.h>
 #include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/saved_variable.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/utils/pybind.h>
 
 #include <ATen/ATen.h>
@@ -31,6 +32,7 @@ namespace {
 struct Error : std::runtime_error {
     using std::runtime_error::runtime_error;
 };
+py::object *error_class = nullptr;   // what an Error surfaces as in Python
 
 // The entry points of the libflare.so that the package loaded (see load_library).
 struct Library {
@@ -81,6 +83,11 @@ flare_dtype dtype_code(const Tensor &t)
         case at::kHalf: return FLARE_F16;
         default: throw Error(std::string("dtype must be float32, bfloat16 or float16, got ") + c10::toString(t.scalar_type()));
     }
+}
+
+at::ScalarType scalar_type(flare_dtype dt)
+{
+    return dt == FLARE_F32 ? at::kFloat : dt == FLARE_BF16 ? at::kBFloat16 : at::kHalf;
 }
 
 flare_shape shape_of(const Tensor &q, const Tensor &k, int layout, bool y_f32)
@@ -364,22 +371,42 @@ struct MixerBackward : torch::autograd::Node {
     torch::autograd::variable_list apply(torch::autograd::variable_list &&grads) override
     {
         std::lock_guard<std::mutex> lock(mutex_);
-        if (!grads[0].defined()) return {Tensor(), Tensor(), Tensor()};
+        try {
+            return gradients(std::move(grads[0]));
+        } catch (const Error &e) {   // (the engine would turn it into a plain RuntimeError)
+            const py::gil_scoped_acquire gil;
+            PyErr_SetString(error_class->ptr(), e.what());
+            python_error raised;
+            raised.persist();
+            throw raised;
+        }
+    }
+    torch::autograd::variable_list gradients(Tensor &&dy)
+    {
+        if (!dy.defined()) return {Tensor(), Tensor(), Tensor()};
         const Tensor tq = q.unpack(), tk = k.unpack(), tv = v.unpack(), ty = y.unpack(shared_from_this()),
                      ts = stats.unpack();
-        const at::ScalarType dt = tk.scalar_type();
+        // The kernels go by the forward's shape, and a saved-tensor hook may have handed back anything: everything is
+        // held against that shape before anything is allocated or launched.
+        const at::ScalarType dt = scalar_type(shape.dtype);
+        const bool heads_first = shape.layout == FLARE_BHND;
+        const std::array<int64_t, 4> tok{shape.B, heads_first ? shape.H : shape.N, heads_first ? shape.N : shape.H, shape.d};
+        const std::array<int64_t, 3> lat{shape.H, shape.M, shape.d};
+        const at::IntArrayRef lat_dim = at::IntArrayRef(lat).slice(shape.shared_latents ? 1 : 0);
+        const Saved off(shape);
+        const std::array<int64_t, 1> stats_dim{(int64_t)off.bytes};
+        const void *const pq = dev(tq, "q_lat", dt, lat_dim), *const pk = dev(tk, "k", dt, tok),
+                   *const pv = dev(tv, "v", dt, tok), *const py = dev(ty, "y", shape.y_f32 ? at::kFloat : dt, tok);
+        char *const st = static_cast<char *>(dev(ts, "saved statistics", at::kByte, stats_dim));
         // (with an fp32 y autograd hands over an fp32 dY: the library takes it in the storage type)
-        Tensor dy = std::move(grads[0]);
         if (dy.scalar_type() != dt) dy = dy.to(dt);
         dy = dy.contiguous();
-        const Saved off(shape);
         const Target to{c10::hip::getCurrentHIPStream().stream(), std::nullopt};
-        Tensor dq = new_empty(tq.sizes(), dt, tk), dk = new_empty(tk.sizes(), dt, tk), dv = new_empty(tk.sizes(), dt, tk);
+        Tensor dq = new_empty(lat_dim, dt, tk), dk = new_empty(tok, dt, tk), dv = new_empty(tok, dt, tk);
         const Workspace ws = workspace_for(bwd_bytes(shape), std::nullopt, tk, to);
-        char *const st = static_cast<char *>(ts.data_ptr());
-        check(lib.backward_cast(&shape, dev(tq, "q_lat"), dev(tk, "k"), dev(tv, "v"), dev(ty, "y"),
-                                f32(st + off.lse_dec), dev(dy, "dy", dt, tk.sizes()), f32(st), f32(st + off.lse_enc),
-                                dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), scale, ws.ptr, ws.bytes, to.stream),
+        check(lib.backward_cast(&shape, pq, pk, pv, py, f32(st + off.lse_dec), dev(dy, "dy", dt, tok), f32(st),
+                                f32(st + off.lse_enc), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), scale, ws.ptr, ws.bytes,
+                                to.stream),
               "flare_backward_cast");
         return {dq, dk, dv};
     }
@@ -431,14 +458,13 @@ PYBIND11_MODULE(_native, m)
     m.def("load_library", &load_library);
     // errors surface as the package's own exception class
     m.def("set_error_class", [](py::object cls) {
-        static py::object *error = nullptr;
-        if (error) return;
-        error = new py::object(std::move(cls));
+        if (error_class) return;
+        error_class = new py::object(std::move(cls));
         py::register_exception_translator([](std::exception_ptr p) {
             try {
                 if (p) std::rethrow_exception(p);
             } catch (const Error &e) {
-                PyErr_SetString(error->ptr(), e.what());
+                PyErr_SetString(error_class->ptr(), e.what());
             }
         });
     });

@@ -88,3 +88,46 @@ def test_autograd_hooks_and_refusals():
             flare_mixer(dual, dev["k"], dev["v"], scale)
     with pytest.raises(RuntimeError):
         torch.func.vmap(lambda t: flare_mixer(dev["q"], t, t, scale))(torch.stack([dev["k"], dev["k"]]))
+
+
+@pytest.mark.parametrize("dtype,shared,layout,y_f32", [("f32", False, "bhnd", False), ("bf16", True, "bnhd", False),
+                                                       ("f16", False, "bhnd", True)])
+def test_unpacked_tensors_are_held_against_the_forward(dtype, shared, layout, y_f32):
+    """A saved-tensor hook that hands back another type, shape, order or device for any one of the saved tensors is an
+    error before anything is launched; handing back equal copies is not."""
+    import torch
+
+    from paper_2508_12594_amd.binding import FlareError
+    print("[case] unpacked tensors %s shared=%s %s y_f32=%s" % (dtype, shared, layout, y_f32), flush=True)
+    inp = synth.make_inputs(2, B=1, H=2, N=300, M=32, d=16, dtype=dtype, with_dy=True)
+    dev = to_device(inp)
+    order = (lambda t: t.permute(0, 2, 1, 3).contiguous()) if layout == "bnhd" else (lambda t: t)
+    k, v, dy = (order(dev[n]) for n in ("k", "v", "dy"))
+    q = (dev["q"][0].contiguous() if shared else dev["q"]).requires_grad_(True)
+
+    def gradient(which, change):
+        count = [0]
+
+        def unpack(t):
+            count[0] += 1
+            return change(t) if count[0] - 1 == which else t.clone()
+
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t, unpack):
+            y = flare_mixer(q, k, v, inp["scale"], layout=layout, y_f32=y_f32)
+        dq, = torch.autograd.grad(y, q, dy.float() if y_f32 else dy)
+        assert count[0] == 5
+        return dq
+
+    y = flare_mixer(q, k, v, inp["scale"], layout=layout, y_f32=y_f32)
+    dq_ref, = torch.autograd.grad(y, q, dy.float() if y_f32 else dy)
+    assert torch.equal(gradient(-1, None), dq_ref)
+    changes = [lambda t: t.to(torch.float64), lambda t: t.flatten()[:-64].clone(),
+               lambda t: t.unsqueeze(0), lambda t: torch.stack([t, t], -1)[..., 0], lambda t: t.cpu()]
+    for which in range(5):
+        for change in changes:
+            with pytest.raises(FlareError):
+                gradient(which, change)
+    for which in range(4):                      # 16 bits, or single precision, that was not undone
+        with pytest.raises(FlareError):
+            gradient(which, lambda t: t.half() if t.dtype == torch.float32 else t.float())
+    assert torch.equal(gradient(-1, None), dq_ref)
