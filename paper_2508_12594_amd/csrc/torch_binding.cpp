@@ -8,6 +8,7 @@
 #include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/saved_variable.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/jit/frontend/tracer.h>
 #include <torch/csrc/utils/pybind.h>
 
 #include <ATen/ATen.h>
@@ -412,8 +413,11 @@ struct MixerBackward : torch::autograd::Node {
     }
 };
 
-Tensor mixer(const Tensor &q_in, const Tensor &k_in, const Tensor &v_in, double scale, int layout, bool y_f32)
+// Nothing under torch.jit.trace: y is made behind the dispatcher, so a trace would hold it as a constant (the caller then
+// records the step as an operation, see autograd.py).
+OptTensor mixer(const Tensor &q_in, const Tensor &k_in, const Tensor &v_in, double scale, int layout, bool y_f32)
 {
+    if (torch::jit::tracer::isTracing()) return std::nullopt;
     for (const Tensor *t : {&q_in, &k_in, &v_in})   // a tangent would be lost without a word
         if (t->_fw_grad(0).defined()) throw Error("flare_mixer has no forward-mode derivative");
     std::shared_ptr<MixerBackward> node;

@@ -131,3 +131,37 @@ def test_unpacked_tensors_are_held_against_the_forward(dtype, shared, layout, y_
         with pytest.raises(FlareError):
             gradient(which, lambda t: t.half() if t.dtype == torch.float32 else t.float())
     assert torch.equal(gradient(-1, None), dq_ref)
+
+
+@pytest.mark.parametrize("grad", [False, True])
+@pytest.mark.parametrize("dtype,layout,y_f32", [("f32", "bhnd", False), ("bf16", "bnhd", False), ("bf16", "bhnd", True)])
+def test_traced_mixer_is_an_operation(dtype, layout, y_f32, grad):
+    """torch.jit.trace records the mixer, under no_grad too: the traced function gives other inputs (and another number of
+    tokens) their own output and gradients, the bits of a direct call."""
+    import torch
+    print("[case] jit.trace %s %s y_f32=%s grad=%s" % (dtype, layout, y_f32, grad), flush=True)
+
+    def draw(N, seed):
+        inp = synth.make_inputs(2, B=1, H=2, N=N, M=32, d=16, dtype=dtype, with_dy=True, seed=seed)
+        dev = to_device(inp)
+        order = (lambda t: t.permute(0, 2, 1, 3).contiguous()) if layout == "bnhd" else (lambda t: t)
+        return inp["scale"], [dev["q"]] + [order(dev[n]) for n in ("k", "v", "dy")]
+
+    scale, (q, k, v, _) = draw(300, 1)
+
+    def layer(a, b, c):
+        return flare_mixer(a, b, c, scale, layout=layout, y_f32=y_f32) * 2.0
+
+    with torch.set_grad_enabled(grad):
+        traced = torch.jit.trace(layer, (q, k, v))
+    for N, seed in ((300, 1), (300, 2), (77, 3)):
+        _, (q, k, v, dy) = draw(N, seed)
+        dy = dy.float() if y_f32 else dy
+        for t in (q, k, v):
+            t.requires_grad_(True)
+        y, y_ref = traced(q, k, v), layer(q, k, v)
+        assert torch.equal(y, y_ref)
+        for a, b in zip(torch.autograd.grad(y, (q, k, v), dy), torch.autograd.grad(y_ref, (q, k, v), dy)):
+            assert torch.equal(a, b)
+        with torch.no_grad():
+            assert torch.equal(traced(q, k, v), y_ref)
