@@ -384,7 +384,6 @@ struct MixerBackward : torch::autograd::Node {
     }
     torch::autograd::variable_list gradients(Tensor &&dy)
     {
-        if (!dy.defined()) return {Tensor(), Tensor(), Tensor()};
         const Tensor tq = q.unpack(), tk = k.unpack(), tv = v.unpack(), ty = y.unpack(shared_from_this()),
                      ts = stats.unpack();
         // The kernels go by the forward's shape, and a saved-tensor hook may have handed back anything: everything is
@@ -399,6 +398,7 @@ struct MixerBackward : torch::autograd::Node {
         const void *const pq = dev(tq, "q_lat", dt, lat_dim), *const pk = dev(tk, "k", dt, tok),
                    *const pv = dev(tv, "v", dt, tok), *const py = dev(ty, "y", shape.y_f32 ? at::kFloat : dt, tok);
         char *const st = static_cast<char *>(dev(ts, "saved statistics", at::kByte, stats_dim));
+        if (!dy.defined()) dy = at::zeros(tok, ty.options().requires_grad(false));   // nothing came back to y
         // (with an fp32 y autograd hands over an fp32 dY: the library takes it in the storage type)
         if (dy.scalar_type() != dt) dy = dy.to(dt);
         dy = dy.contiguous();

@@ -165,3 +165,25 @@ def test_traced_mixer_is_an_operation(dtype, layout, y_f32, grad):
             assert torch.equal(a, b)
         with torch.no_grad():
             assert torch.equal(traced(q, k, v), y_ref)
+
+
+def test_nothing_came_back_to_the_output():
+    """A consumer of y whose backward returns no gradient: the gradients are zeros, not missing."""
+    import torch
+    print("[case] undefined gradient", flush=True)
+
+    class Detour(torch.autograd.Function):
+        @staticmethod
+        def forward(ctx, x):
+            return x.clone()
+
+        @staticmethod
+        def backward(ctx, g):
+            return None
+
+    inp = synth.make_inputs(2, B=1, H=2, N=300, M=32, d=16, dtype="bf16")
+    q, k, v = (t.requires_grad_(True) for t in to_device(inp, ("q", "k", "v")).values())
+    for y_f32 in (False, True):
+        y = Detour.apply(flare_mixer(q, k, v, inp["scale"], y_f32=y_f32))
+        for t, g in zip((q, k, v), torch.autograd.grad(y, (q, k, v), torch.ones_like(y))):
+            assert g.dtype == t.dtype and g.shape == t.shape and not g.any()
