@@ -153,18 +153,19 @@ Tensor out_or_new(const OptTensor &t, at::IntArrayRef shape, at::ScalarType dt, 
     return t ? *t : new_empty(shape, dt, like);
 }
 
-// Where a call is enqueued: torch's current stream, or the one that was handed in (a torch.cuda.Stream).
+// Where a call is enqueued: torch's current stream, or the one that was handed in (a torch.cuda.Stream, or with a
+// workspace of the caller's anything that has a cuda_stream).
 struct Target {
     void *stream;
-    std::optional<c10::Stream> other;   // set when it is not the current stream
+    std::optional<c10::Stream> other;   // set when it is not the current stream and a temporary has to be recorded there
 };
 // (called with the GIL; what follows it in the entry points, allocations and launches, runs without)
-Target target(const py::object &stream)
+Target target(const py::object &stream, bool temporaries)
 {
     const c10::hip::HIPStream cur = c10::hip::getCurrentHIPStream();
     if (stream.is_none()) return Target{cur.stream(), std::nullopt};
     void *const handle = reinterpret_cast<void *>(stream.attr("cuda_stream").cast<uintptr_t>());
-    if (handle == cur.stream()) return Target{handle, std::nullopt};
+    if (handle == cur.stream() || !temporaries) return Target{handle, std::nullopt};
     const c10::Stream s = c10::Stream::unpack3(stream.attr("stream_id").cast<int64_t>(),
                                                (c10::DeviceIndex)stream.attr("device_index").cast<int64_t>(),
                                                (c10::DeviceType)stream.attr("device_type").cast<int64_t>());
@@ -221,7 +222,7 @@ std::tuple<Tensor, Tensor> encode(const Tensor &q, const Tensor &k, const Tensor
 {
     const flare_shape s = shape_of(q, k, layout, false);
     const Dims dim(s);
-    const Target to = target(stream);
+    const Target to = target(stream, !ws_in);
     const py::gil_scoped_release no_gil;
     Tensor z = out_or_new(z_in, dim.z, at::kFloat, k), le = out_or_new(le_in, dim.lse_enc, at::kFloat, k);
     const Workspace ws = workspace_for(fwd_bytes(s), ws_in, k, to);
@@ -238,7 +239,7 @@ Tensor decode(const Tensor &q, const Tensor &k, const Tensor &z, double scale, c
     const bool wide = wants_f32_y(y_in, k, y_f32);
     const flare_shape s = shape_of(q, k, layout, wide);
     const Dims dim(s);
-    const Target to = target(stream);
+    const Target to = target(stream, !ws_in);
     const py::gil_scoped_release no_gil;
     const at::ScalarType ydt = wide ? at::kFloat : k.scalar_type();
     Tensor y = out_or_new(y_in, k.sizes(), ydt, k);
@@ -258,7 +259,7 @@ std::tuple<Tensor, Tensor, Tensor> forward(const Tensor &q, const Tensor &k, con
     const bool wide = wants_f32_y(y_in, k, y_f32);
     const flare_shape s = shape_of(q, k, layout, wide);
     const Dims dim(s);
-    const Target to = target(stream);
+    const Target to = target(stream, !ws_in);
     const py::gil_scoped_release no_gil;
     const at::ScalarType ydt = wide ? at::kFloat : k.scalar_type();
     Tensor y = out_or_new(y_in, k.sizes(), ydt, k), z = out_or_new(z_in, dim.z, at::kFloat, k),
@@ -278,7 +279,7 @@ void forward_static(const Tensor &q, const Tensor &k, const Tensor &v, double sc
     const bool wide = wants_f32_y(y, k, false);
     const flare_shape s = shape_of(q, k, layout, wide);
     const Dims dim(s);
-    const Target to = target(stream);
+    const Target to = target(stream, false);
     const py::gil_scoped_release no_gil;
     check(lib.forward_static(&s, dev(q, "q_lat"), dev(k, "k"), dev(v, "v", k.scalar_type(), k.sizes()),
                              dev(y, "y", wide ? at::kFloat : k.scalar_type(), k.sizes()),
@@ -295,7 +296,7 @@ std::tuple<Tensor, Tensor, Tensor> forward_project(const Tensor &q, const Tensor
 {
     const flare_shape s = shape_of(q, k, FLARE_BNHD, false);
     const Dims dim(s);
-    const Target to = target(stream);
+    const Target to = target(stream, !ws_in);
     const py::gil_scoped_release no_gil;
     const int64_t C = (int64_t)s.H * s.d;
     const at::ScalarType dt = k.scalar_type();
@@ -327,7 +328,7 @@ std::tuple<Tensor, Tensor, Tensor> backward(const Tensor &q, const Tensor &k, co
     flare_shape s = shape_of(q, k, layout, wide);
     s.variant = variant;
     const Dims dim(s);
-    const Target to = target(stream);
+    const Target to = target(stream, !ws_in);
     const py::gil_scoped_release no_gil;
     const at::ScalarType dt = k.scalar_type();
     Tensor dq = out_or_new(dq_in, q.sizes(), at::kFloat, k), dk = out_or_new(dk_in, k.sizes(), dt, k),

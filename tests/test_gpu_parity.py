@@ -622,3 +622,30 @@ def test_side_stream_and_caller_buffers():
     assert torch.equal(y, y0) and torch.equal(z, z0) and torch.equal(l, l0)
     with pytest.raises(binding.FlareError):
         binding.forward(dev["q"], dev["k"], dev["v"], inp["scale"], workspace=ws[:64])
+
+
+def test_stream_that_is_not_torchs():
+    """With the caller's own workspace a stream is whatever has a cuda_stream (another library's stream object)."""
+    import types
+
+    import torch
+    inp = synth.make_inputs(1, N=300, with_dy=True)
+    dev = to_device(inp)
+    q, k, v, dy, scale = dev["q"], dev["k"], dev["v"], dev["dy"], inp["scale"]
+    ws = torch.empty(max(binding.workspace_bytes(inp["B"], inp["H"], inp["N"], inp["M"], inp["d"], binding.FLARE_F32)),
+                     dtype=torch.uint8, device="cuda")
+    ref = binding.forward(q, k, v, scale)
+    ref += binding.backward(q, k, v, dy, ref[1], ref[2], scale)
+    torch.cuda.synchronize()
+    own = torch.cuda.Stream()
+    s = types.SimpleNamespace(cuda_stream=own.cuda_stream)
+    got = binding.forward(q, k, v, scale, workspace=ws, stream=s)
+    got += binding.backward(q, k, v, dy, got[1], got[2], scale, workspace=ws, stream=s)
+    own.synchronize()
+    y, z, lse = (torch.empty_like(t) for t in ref[:3])
+    binding.forward_static(q, k, v, scale, y, z, lse, stream=s)
+    z2, lse2 = binding.encode(q, k, v, scale, workspace=ws, stream=s)
+    y2 = binding.decode(q, k, z2, scale, workspace=ws, stream=s)
+    own.synchronize()
+    for a, b in zip(ref + ref[:3] * 2, got + (y, z, lse) + (y2, z2, lse2)):
+        assert torch.equal(a, b)
