@@ -163,6 +163,7 @@ def _native():
     global _ext
     if _ext is None:
         load()
+        _torch()    # its libraries, which _native.so is linked to, have to be in the process
         try:
             from . import _native as ext
         except ImportError as e:

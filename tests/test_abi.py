@@ -110,3 +110,12 @@ def test_null_and_misaligned_pointers_are_rejected(lib):
                               1 << 20, None) == -1
     assert lib.flare_backward(ctypes.byref(shp), p, p, p, None, None, p, p, p, p, p, p, one, p,
                               16, None) == -4
+
+
+def test_native_half_loads_by_itself(lib):
+    """The native half of the binding loads in a program that has not imported torch yet."""
+    import subprocess
+    import sys
+    code = "from paper_2508_12594_amd import binding; print(binding._native().__name__)"
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("_native"), r.stderr
