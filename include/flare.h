@@ -20,6 +20,8 @@
  *     passed as void*; NULL is the default stream).  Results are ready when the stream reaches
  *     the point after the call.
  *   - Outputs are overwritten, never accumulated into.
+ *   - A token's rows are read before its outputs are written: y may be the buffer of k or v, dk and dv
+ *     (each) that of k, v, dy or y.
  *   - `workspace` is caller-provided device scratch of at least the size that
  *     flare_workspace_bytes reports for the same shape; its contents are undefined on return.
  *     Two calls that share a workspace must be ordered on the same stream.

@@ -861,6 +861,12 @@ int forward_impl(const flare_shape &s, const T *q, const T *k, const T *v, T *y,
     return rc != FLARE_OK ? rc : decode_impl<T, D>(s, q, k, z, y, lse_dec, scale, stream);
 }
 
+inline bool overlap(const void *a, const void *b, size_t bytes)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + bytes && y < x + bytes;
+}
+
 template <typename T, int D>
 int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, const T *y, const float *lse_dec,
                   const T *dy, const float *z, const float *lse_enc, void *dq, bool dq_cast, T *dk, T *dv, float scale,
@@ -945,12 +951,19 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
     }
     constexpr int kFewRows = 256 / (D / 4);   // rows per workgroup of the few-slot merge kernels
     const float span = (s.variant & FLARE_VARIANT_TWO_EXP) ? -1.f : F32 ? kSpan32 : kPlanSpan;   // bwd_one_exp_ok
+    // A dQ kernel of its own runs before dK and dV are written, which may be over k, v or dy -- unless the dK/dV kernel
+    // merges dZ for it.  Then it has to run behind that one, so dZ is merged first where the outputs lie over the inputs
+    // (the same bits: merge_dz_row either way).
+    const bool dq_fused = mf && mfma_dq_fused(s);           // dQ comes out of the dK/dV kernel
+    const size_t tok_bytes = (size_t)BH * s.N * D * sizeof(T);
+    const bool in_place = overlap(dk, k, tok_bytes) || overlap(dk, v, tok_bytes) || overlap(dk, dy, tok_bytes) ||
+                          overlap(dv, k, tok_bytes) || overlap(dv, v, tok_bytes) || overlap(dv, dy, tok_bytes);
     // what the dK/dV kernel has to merge itself, if anything
-    const MergeDz merge{w.part, w.ld_range, w.dz, w.eps, w.plan, dz_inline(s) ? dz_parts : 0,
+    const MergeDz merge{w.part, w.ld_range, w.dz, w.eps, w.plan, dz_inline(s) && (dq_fused || !in_place) ? dz_parts : 0,
                         span, 0u};
     if (merge.parts == 0) {
         LaunchTimer t(KID_BWD_DZ_MERGE, stream);
-        if (dz_parts <= kFewSlots)
+        if (dz_parts <= kFewSlots || dz_inline(s))
             dz_merge_few_kernel<D><<<dim3((s.M + kFewRows - 1) / kFewRows + (planned ? 1 : 0), BH), 256, 0, stream>>>(
                 w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, planned ? w.plan : nullptr,
                 span);
@@ -960,40 +973,46 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
                 span);
     }
     if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
-    // dK and dV, then (with a kernel of its own for it) dQ: where dZ is merged by the dK/dV kernel, the dQ kernel reads
-    // what that one wrote
     int dq_parts = plan.bwd.chunks;
     // shared latents: one gradient for all heads, summed over (b, h) in that fixed order
     const int groups = s.shared_latents ? BH : s.B, outers = s.shared_latents ? 1 : s.H;
-    int rc = FLARE_OK;
-    if constexpr (F32) {
-        rc = mfma32_dkdv(s, q, k, v, dy, z, lse_enc, ld, w.delta, ld_mul, dk, dv, scale, merge, stream);
-        if (rc == FLARE_OK)
-            rc = mfma32_dq_partial(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, w.dq_part, scale,
-                                   stream);
-    } else if (mf) {
-        const bool dq_fused = mfma_dq_fused(s);             // dQ comes out of the dK/dV kernel
-        const bool chunked = mfma_dkdv_acc_bytes(s) != 0;   // more than 256 latents: one pass per chunk
-        dq_parts = dq_fused ? mfma_dkdv_blocks(s) : mfma_dq_parts(s);
-        for (int m0 = 0; m0 < s.M && rc == FLARE_OK; m0 += mfma_lat_step(s))   // each (b,h) slice by the variant its plan names
-            rc = mfma_dkdv(s, q, k, v, dy, z, lse_enc, ld, w.delta, ld_mul, dk, dv, chunked ? w.acc32 : nullptr,
-                           dq_fused ? w.dq_part : nullptr, m0, scale, merge, stream);
-        if (!dq_fused && rc == FLARE_OK)
-            rc = mfma_dq_partial(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, w.dq_part, scale,
-                                 stream);
-    } else {
-        {
+    if (mf) dq_parts = dq_fused ? mfma_dkdv_blocks(s) : mfma_dq_parts(s);
+    auto dkdv = [&]() -> int {
+        if constexpr (F32) {
+            return mfma32_dkdv(s, q, k, v, dy, z, lse_enc, ld, w.delta, ld_mul, dk, dv, scale, merge, stream);
+        } else if (mf) {
+            const bool chunked = mfma_dkdv_acc_bytes(s) != 0;   // more than 256 latents: one pass per chunk
+            int rc = FLARE_OK;
+            for (int m0 = 0; m0 < s.M && rc == FLARE_OK; m0 += mfma_lat_step(s))   // each (b,h) slice by the variant its plan names
+                rc = mfma_dkdv(s, q, k, v, dy, z, lse_enc, ld, w.delta, ld_mul, dk, dv, chunked ? w.acc32 : nullptr,
+                               dq_fused ? w.dq_part : nullptr, m0, scale, merge, stream);
+            return rc;
+        } else {
             LaunchTimer t(KID_BWD_DKDV, stream);
             dkdv_kernel<T, D><<<tok_grid, kTokenBlock, 0, stream>>>(q, k, v, dy, z, lse_enc, w.dz, w.eps, w.lse_dec2,
                                                                     w.delta, dk, dv, ts, s.H, s.N, s.M, scale);
+            return check_launch();
         }
-        if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
-        LaunchTimer t(KID_BWD_DQ_PARTIAL, stream);
-        dq_partial_kernel<T, D><<<lat_grid, kLatentBlock, 0, stream>>>(
-            q, k, v, dy, z, lse_enc, w.dz, w.eps, w.lse_dec2, w.delta, w.dq_part, ts, s.H, s.N, s.M, plan.bwd.chunk_len,
-            plan.bwd.chunks, c2, RowTouch{addr(k), addr(v), addr(dy), addr(w.lse_dec2), addr(w.delta)});
-        rc = check_launch();
-    }
+    };
+    auto dq_partials = [&]() -> int {
+        if constexpr (F32) {
+            return mfma32_dq_partial(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, w.dq_part, scale,
+                                     stream);
+        } else if (mf) {
+            return mfma_dq_partial(s, q, k, v, dy, z, lse_enc, w.dz, w.eps, ld, w.delta, ld_mul, w.plan, w.dq_part, scale,
+                                   stream);
+        } else {
+            LaunchTimer t(KID_BWD_DQ_PARTIAL, stream);
+            dq_partial_kernel<T, D><<<lat_grid, kLatentBlock, 0, stream>>>(
+                q, k, v, dy, z, lse_enc, w.dz, w.eps, w.lse_dec2, w.delta, w.dq_part, ts, s.H, s.N, s.M,
+                plan.bwd.chunk_len, plan.bwd.chunks, c2, RowTouch{addr(k), addr(v), addr(dy), addr(w.lse_dec2), addr(w.delta)});
+            return check_launch();
+        }
+    };
+    int rc = FLARE_OK;
+    if (!dq_fused && merge.parts == 0) rc = dq_partials();
+    if (rc == FLARE_OK) rc = dkdv();
+    if (!dq_fused && merge.parts != 0 && rc == FLARE_OK) rc = dq_partials();
     if (rc != FLARE_OK) return rc;
     auto reduce_dq = [&](auto *out) {
         typedef std::remove_reference_t<decltype(*out)> O;

@@ -649,3 +649,42 @@ def test_stream_that_is_not_torchs():
     own.synchronize()
     for a, b in zip(ref + ref[:3] * 2, got + (y, z, lse) + (y2, z2, lse2)):
         assert torch.equal(a, b)
+
+
+# dQ from a kernel of its own (fp32, d = 32, the fp32 kernels of many latents) behind dZ merged by a kernel and by dK/dV, with
+# latents in chunks; and dQ out of the dK/dV kernel
+IN_PLACE = [(500, 48, 16, "f32"), (12, 48, 16, "f32"), (2049, 48, 16, "f32"), (20000, 300, 8, "f32"), (500, 48, 32, "bf16"),
+            (40000, 64, 32, "f16"), (700, 300, 32, "bf16"), (1500, 256, 32, "bf16"), (300, 2100, 8, "bf16"),
+            (12, 48, 16, "f16"), (500, 48, 16, "bf16"), (700, 300, 16, "f16")]
+
+
+@pytest.mark.parametrize("layout", ["bhnd", "bnhd"])
+@pytest.mark.parametrize("N,M,d,dtype", IN_PLACE)
+def test_outputs_over_the_inputs(N, M, d, dtype, layout):
+    """Every token's rows are read before its outputs are written, in every kernel of a call: y may lie over k or v, dk and
+    dv over k, v, dy or the saved y.  The bits of separate buffers."""
+    import torch
+    _say("in place N=%d M=%d d=%d %s %s" % (N, M, d, dtype, layout))
+    inp = synth.make_inputs(1, B=1, H=2, N=N, M=M, d=d, dtype=dtype, with_dy=True, seed=8)
+    dev, scale = to_device(inp), inp["scale"]
+    if layout == "bnhd":
+        dev.update({n: dev[n].transpose(1, 2).contiguous() for n in ("k", "v", "dy")})
+
+    def forward(over=None):
+        t = {n: dev[n].clone() for n in ("k", "v")}
+        return binding.forward(dev["q"], t["k"], t["v"], scale, y=t.get(over), layout=layout)
+
+    def backward(saved, dk=None, dv=None):
+        t = {n: dev[n].clone() for n in ("k", "v", "dy")}
+        ld = torch.empty((1, 2, N), dtype=torch.float32, device="cuda") if saved else None
+        t["y"], z, lse = binding.forward(dev["q"], t["k"], t["v"], scale, lse_dec=ld, layout=layout)
+        return binding.backward(dev["q"], t["k"], t["v"], t["dy"], z, lse, scale, y=t["y"] if saved else None, lse_dec=ld,
+                                dk=t.get(dk), dv=t.get(dv), layout=layout)
+
+    ref = forward()
+    for over in ("k", "v"):
+        assert all(torch.equal(a, b) for a, b in zip(forward(over), ref)), over
+    for saved in (True, False):
+        ref = backward(saved)
+        for dk, dv in (("k", "v"), ("v", "k"), ("dy", None), (None, "dy"), ("k", None), ("y", "dy")):
+            assert all(torch.equal(a, b) for a, b in zip(backward(saved, dk, dv), ref)), (saved, dk, dv)
