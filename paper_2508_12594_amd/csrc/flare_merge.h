@@ -20,11 +20,29 @@ inline bool merge_inline(const flare_shape &s, int parts)
     return parts <= kInlineSlots && (size_t)parts * s.M * (s.d + 2) * 4 <= kInlineBytes;
 }
 
+// ---- log-sum-exps of fp32 storage --------------------------------------------------------------
+// log2 (l 2^m).  v_log_f32 cuts its result, half an ulp on average (3e-7 nats for a sum of 2^15), the same way for every
+// latent and token, and dV is proportional to both weights: the exponent is split off, so that what is cut is below 2^-24,
+// and put back with one rounding to nearest.
+__device__ __forceinline__ float lse_log2(float m, float l, float &frac)
+{
+    frac = log2f(__builtin_amdgcn_frexp_mantf(l));
+    return m + (float)__builtin_amdgcn_frexp_expf(l);
+}
+__device__ __forceinline__ float lse_nat(float m, float l)
+{
+    constexpr float kLn2Low = -1.904654299957768e-9f;   // ln 2 - kLn2
+    float frac;
+    const float whole = lse_log2(m, l, frac);
+    return fmaf(whole, kLn2, fmaf(whole, kLn2Low, frac * kLn2));
+}
+
 // ---- encode: z and lse_enc of one (b,h) -------------------------------------------------------
 struct MergeZ {
     const float *m_part, *l_part, *o_part;   // slot p of latent m at [(b*h) * parts + p][M]
     float *z, *lse_enc;                      // [b*h][M][d], [b*h][M]
     int parts;                               // 0: z is complete, there is nothing to merge
+    bool f32;                                // fp32 storage
 };
 
 // D / 4 threads per latent own four columns each; the slots are folded in order behind one maximum (exact in any order),
@@ -63,7 +81,7 @@ __device__ __forceinline__ void merge_z_row(const MergeZ &g, int bh, int M, int 
     if (z_lds) *reinterpret_cast<float4 *>(z_lds + (size_t)m * D + 4 * j) = o;
     if (write) {
         *reinterpret_cast<float4 *>(g.z + idx * D + 4 * j) = o;
-        if (j == 0) g.lse_enc[idx] = (gm + log2f(l)) * kLn2;
+        if (j == 0) g.lse_enc[idx] = g.f32 ? lse_nat(gm, l) : (gm + log2f(l)) * kLn2;
     }
 }
 // Rows m0 .. m1 by the nt threads of a workgroup; z_lds (when given) gets them, and with `write` they go to global memory.
@@ -94,9 +112,9 @@ __device__ __forceinline__ void merge_z_rows(const MergeZ &g, int bh, int M, int
 // one per 64 values); one barrier inside; every thread returns the same answer.  red: 64 floats of LDS.
 // span: kPlanSpan, or kSpan32 with fp32 storage; below zero: two exponentials whatever the statistics.
 constexpr float kPlanSpan = 60.f;
-// fp32 storage: the third plane of a value or gradient x (2^-18 of it) beside a factor 2^-span must not fall below 2^-126,
-// where the matrix cores read zero: x from 2^-68 = 3e-21 up with 40 log2 units.  (The one plane of 16-bit storage is good
-// to 2^-66 with 60.)
+// fp32 storage: the planes of a value or gradient x beside a factor 2^-span end at 2^-133, bf16's smallest number, which must
+// not be seen beside x: x from 2^-69 = 2e-21 up with 40 log2 units.  (The one plane of 16-bit storage is good to 2^-66
+// with 60.)
 constexpr float kSpan32 = 40.f;
 __device__ __forceinline__ bool is_nan(float x) { return (__float_as_uint(x) & 0x7fffffffu) > 0x7f800000u; }
 __device__ __forceinline__ bool bwd_one_exp_ok(const float *__restrict__ ld_range, const float *__restrict__ lse_enc,
@@ -172,7 +190,8 @@ __device__ __forceinline__ float4 merge_dz_row(const float *__restrict__ part, c
     float4 a = parts <= 4 ? sum_slots_upto<4>(p, stride, parts) : parts <= 8 ? sum_slots_upto<8>(p, stride, parts)
                                                                 : sum_slots_upto<kInlineSlots>(p, stride, parts);
     if (one_exp) {                                   // the one-exponential kernels take dZ scaled by 2^-lse_enc2[m]
-        const float em = exp2f(-le * kLog2e);
+        // (of fp32 storage without the rounding of le log2 e, up to 1e-6 of 2^20)
+        const float em = round_bf16 ? exp2f(-le * kLog2e) : expf(-le);
         a = make_float4(a.x * em, a.y * em, a.z * em, a.w * em);
     }
     // The 16-bit kernels take dZ as a bf16 operand.  Rounding it here, before eps is formed, keeps

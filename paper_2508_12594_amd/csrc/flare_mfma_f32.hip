@@ -260,6 +260,18 @@ __device__ __forceinline__ float sum16(const f32x16 &t)
     return (a[0] + a[1]) + (a[2] + a[3]);
 }
 
+// 2^-lse of a log-sum-exp in log2 units (mul = 1) or natural ones (mul = log2 e): the rounding of the product, up to 1e-6 of
+// 2^20, and of log2 e, of one sign for all, are taken along.  `a` gets the rounded product, of which the caller may hold
+// back what lies beyond +-span.
+__device__ __forceinline__ float exp2_neg_lse(float lse, float mul, float span, float &a)
+{
+    constexpr float kLog2eLow = 1.9259629e-8f;   // log2 e - kLog2e
+    a = lse * mul;
+    const float low = fmaf(lse, mul, -a) + (mul == 1.f ? 0.f : lse * kLog2eLow);
+    const float e = fast_exp2(-fminf(fmaxf(a, -span), span));
+    return fmaf(e, -kLn2 * low, e);
+}
+
 // Weights are summed as 2^S, without a normaliser, while that loses nothing: the sum of weights l at least 2^-40 (for the
 // small planes, as kSpan32) and at most 2^100, the sums of weighted values below 2^100, so that
 // what the chunks add up to stays finite.  Otherwise the sums are taken again behind a maximum, where a sum overflows
@@ -343,7 +355,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
 
     // this wave's latents
     bf16x8 qp[Geo::NP], zp[MODE == 2 ? Geo::NP : 1], dzp[MODE == 2 ? Geo::NP : 1];
-    float le2 = 0.f, ep = 0.f;
+    float le = 0.f, ep = 0.f;
     {
         float x[Geo::KS][8];
         load_row_half<DR>(A.q + (size_t)h * A.ts.sq + (size_t)mc * DR, hh, x);
@@ -358,7 +370,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
             reg_ops<DR, true>(x, hh, zp);
             load_row_half<DR>(A.dz + row * DR, hh, x);
             reg_ops<DR, true>(x, hh, dzp);
-            le2 = A.lse_enc[row] * kLog2e;
+            le = A.lse_enc[row];
             ep = A.eps[row];
         }
     }
@@ -406,7 +418,8 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
             uint16_t *tile = smem + ((st & 1) * TG + (tok >> 5)) * L::TILE;
             float *stat = reinterpret_cast<float *>(tile + L::ST);
             if (MODE == 1 && a == 1) {
-                const float ld = st0[it] * A.ld_mul;
+                float ld;
+                const float w = exp2_neg_lse(st0[it], A.ld_mul, kSpan32, ld), lc = fminf(fmaxf(ld, -kSpan32), kSpan32);
                 if (do_delta) {
                     float d = 0.f;
 #pragma unroll
@@ -419,14 +432,14 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
                     ld_min = fminf(ld_min, ld);
                     ld_max = fmaxf(ld_max, ld);
                 }
-                const float lc = fminf(fmaxf(ld, -kSpan32), kSpan32), w = fast_exp2(-lc);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) x[it][i] *= w;
                 if (piece == 0) stat[t32] = in ? ld - lc : 0.f;
             }
             if (MODE == 2 && a == 0 && piece == 0) {
-                const float ld = in ? st0[it] * A.ld_mul : 0.f;
-                stat[t32] = one_exp ? fast_exp2(-ld) : ld;
+                float ld;
+                const float w = exp2_neg_lse(in ? st0[it] : 0.f, A.ld_mul, kSpan32, ld);
+                stat[t32] = one_exp ? w : ld;
                 stat[32 + t32] = in ? -st1[it] : 0.f;
             }
             if (!in) {                            // behind the chunk's end: rows of zeros
@@ -497,7 +510,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
             } else {
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
-                    s[i] = fmaf(fast_exp2(s[i] - le2), a[i], fast_exp2(s[i] - w[i]) * cc[i]);
+                    s[i] = fmaf(fast_exp2(fmaf(le, -kLog2e, s[i])), a[i], fast_exp2(s[i] - w[i]) * cc[i]);
             }
             o = value_product<DR>(tile + L::K, tl, s, o);
         }
@@ -613,7 +626,7 @@ struct TokenLds {   // in uint16 units, per latent tile
     static constexpr int Q = 0, QR = MODE == 2 ? Geo::RT : Geo::RD;
     static constexpr int Z = Q + 32 * QR, ZR = MODE == 2 ? Geo::RD : Geo::RT;
     static constexpr int D = Z + 32 * ZR;                                  // dZ (MODE 2)
-    static constexpr int ST = D + (MODE == 2 ? 32 * Geo::RT : 0);          // per latent: bias of the scores, -eps, lse_enc2
+    static constexpr int ST = D + (MODE == 2 ? 32 * Geo::RT : 0);          // per latent: bias of the scores, -eps, lse_enc
     static constexpr int TILE = ST + 192;
 };
 
@@ -680,7 +693,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
                 if (a == 0) stat[row & 31] = mm < M ? 0.f : -1e30f;   // no weight for the padding latents
                 if constexpr (MODE == 2) {
                     if (a == 1) stat[32 + (row & 31)] = mm < M ? -epr[mc] : 0.f;
-                    if (a == 2) stat[64 + (row & 31)] = A.lse_enc[(size_t)bh * M + mc] * kLog2e;
+                    if (a == 2) stat[64 + (row & 31)] = A.lse_enc[(size_t)bh * M + mc];
                 }
             }
         }
@@ -723,7 +736,8 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
                     reg_ops<DR, false>(kx, hh, vp);
                     load_row_half<DR>(A.dy + off, hh, kx);
                     reg_ops<DR, false>(kx, hh, gq);
-                    const float ld = A.lse_dec[rows + n] * A.ld_mul, w = fast_exp2(-ld), dl = A.delta[rows + n];
+                    float ld;
+                    const float w = exp2_neg_lse(A.lse_dec[rows + n], A.ld_mul, kSpan32, ld), dl = A.delta[rows + n];
                     for (int lt = 0; lt < nlt; ++lt) {
                         const uint16_t *im = smem + lt * L::TILE;
                         const float *stat = reinterpret_cast<const float *>(im + L::ST);
@@ -745,7 +759,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
 #pragma unroll
                             for (int i = 0; i < 16; ++i) {
                                 const float r = fast_exp2(s[i] - ld);
-                                s[i] = fast_exp2(s[i] - le[i]);
+                                s[i] = fast_exp2(fmaf(le[i], -kLog2e, s[i]));
                                 a[i] = fmaf(s[i], a[i], r * c[i]);
                             }
                         }
@@ -826,7 +840,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
             for (int t = 0; t < T; ++t) {
                 const int tile = tile_of(b, t), n = tile * 32 + l32;
                 if (tile >= tiles) continue;
-                const float inv = 1.f / l[t], lse2 = bias[t] + log2f(l[t]);
+                const float inv = 1.f / l[t];
                 float out[Geo::OUT];
                 fold_planes<DR>(acc[t], out);
 #pragma unroll
@@ -835,7 +849,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
                 if constexpr (MODE == 0) {
                     if (n < A.N) {
                         store_quartets<DR>(A.out0 + off, hh, out);
-                        if (A.out1 && hh == 0) A.out1[rows + n] = lse2 * kLn2;
+                        if (A.out1 && hh == 0) A.out1[rows + n] = lse_nat(bias[t], l[t]);
                     }
                 } else {
                     float d = 0.f;
@@ -850,7 +864,9 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
                         }
                     d += __shfl_xor(d, 32);
                     if (n < A.N && hh == 0) {
-                        A.out0[rows + n] = lse2;
+                        float frac;
+                        const float whole = lse_log2(bias[t], l[t], frac);
+                        A.out0[rows + n] = whole + frac;
                         A.out1[rows + n] = d;
                     }
                 }

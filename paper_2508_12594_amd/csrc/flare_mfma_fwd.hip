@@ -1197,7 +1197,7 @@ int mfma_encode_partial(const flare_shape &s, const void *q, const void *k, cons
 #undef FLARE_ENC_NB
 #undef FLARE_ENC
     }
-    *g = MergeZ{m_part, l_part, o_part, z, lse_enc, p.parts};
+    *g = MergeZ{m_part, l_part, o_part, z, lse_enc, p.parts, false};
     return check_launch();
 }
 

@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kLatentBlock) void encode_partial_kernel(
 template <int D>
 __global__ __launch_bounds__(256) void encode_merge_kernel(
     const float *__restrict__ m_part, const float *__restrict__ l_part, const float *__restrict__ o_part,
-    float *__restrict__ z, float *__restrict__ lse_enc, int BH, int M, int parts)
+    float *__restrict__ z, float *__restrict__ lse_enc, int BH, int M, int parts, bool f32)
 {
     const int j = threadIdx.x & 15;
     const int m = blockIdx.x * 16 + (threadIdx.x >> 4);
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(256) void encode_merge_kernel(
     for (int i = 0; i < D; ++i) o[i] *= inv;
     const size_t idx = (size_t)bh * M + m;
     store_row<D>(z + idx * D, o);
-    lse_enc[idx] = (gm + log2f(l)) * kLn2;
+    lse_enc[idx] = f32 ? lse_nat(gm, l) : (gm + log2f(l)) * kLn2;
 }
 
 // The same merge for few partial slots (flare_merge.h).  With 16 threads per latent striding over the slots most of them
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(256) void dz_merge_kernel(
     if (!live || j != 0) return;
     const size_t idx = (size_t)bh * M + m;
     if (one_exp) {
-        const float em = exp2f(-lse_enc[idx] * 1.4426950408889634f);
+        const float em = round_bf16 ? exp2f(-lse_enc[idx] * 1.4426950408889634f) : expf(-lse_enc[idx]);   // as merge_dz_row
 #pragma unroll
         for (int i = 0; i < D; ++i) acc[i] *= em;
     }
@@ -847,7 +847,7 @@ int forward_impl(const flare_shape &s, const T *q, const T *k, const T *v, T *y,
 {
     if constexpr (std::is_same_v<T, float>) {
         if (mfma32_inline(s)) {
-            MergeZ g{nullptr, nullptr, nullptr, z, lse_enc, mfma32_split(s).chunks};
+            MergeZ g{nullptr, nullptr, nullptr, z, lse_enc, mfma32_split(s).chunks, true};
             float *m_part, *l_part, *o_part;
             valu_fwd_layout(s, mfma32_split(s), ws, &m_part, &l_part, &o_part);
             g.m_part = m_part;
@@ -1084,7 +1084,7 @@ int launch_encode_merge(const flare_shape &s, const float *m_part, const float *
     const dim3 blocks((s.M + 15) / 16, BH);
     LaunchTimer t(KID_ENCODE_MERGE, stream);
     if (parts <= kFewSlots || merge_inline(s, parts)) {   // (the same bits wherever a shape's slots are merged)
-        const MergeZ g{m_part, l_part, o_part, z, lse_enc, parts};
+        const MergeZ g{m_part, l_part, o_part, z, lse_enc, parts, s.dtype == FLARE_F32};
 #define FLARE_EMF(DD)                                                                                           \
     encode_merge_few_kernel<DD><<<dim3((s.M + 256 / (DD / 4) - 1) / (256 / (DD / 4)), BH), 256, 0, stream>>>(g, s.M)
         switch (s.d) {
@@ -1098,10 +1098,10 @@ int launch_encode_merge(const flare_shape &s, const float *m_part, const float *
         return check_launch();
     }
     switch (s.d) {
-        case 4: encode_merge_kernel<4><<<blocks, 256, 0, stream>>>(m_part, l_part, o_part, z, lse_enc, BH, s.M, parts); break;
-        case 8: encode_merge_kernel<8><<<blocks, 256, 0, stream>>>(m_part, l_part, o_part, z, lse_enc, BH, s.M, parts); break;
-        case 16: encode_merge_kernel<16><<<blocks, 256, 0, stream>>>(m_part, l_part, o_part, z, lse_enc, BH, s.M, parts); break;
-        case 32: encode_merge_kernel<32><<<blocks, 256, 0, stream>>>(m_part, l_part, o_part, z, lse_enc, BH, s.M, parts); break;
+        case 4: encode_merge_kernel<4><<<blocks, 256, 0, stream>>>(m_part, l_part, o_part, z, lse_enc, BH, s.M, parts, s.dtype == FLARE_F32); break;
+        case 8: encode_merge_kernel<8><<<blocks, 256, 0, stream>>>(m_part, l_part, o_part, z, lse_enc, BH, s.M, parts, s.dtype == FLARE_F32); break;
+        case 16: encode_merge_kernel<16><<<blocks, 256, 0, stream>>>(m_part, l_part, o_part, z, lse_enc, BH, s.M, parts, s.dtype == FLARE_F32); break;
+        case 32: encode_merge_kernel<32><<<blocks, 256, 0, stream>>>(m_part, l_part, o_part, z, lse_enc, BH, s.M, parts, s.dtype == FLARE_F32); break;
         default: return FLARE_EUNSUPPORTED;
     }
     return check_launch();

@@ -102,3 +102,28 @@ def test_two_exponential_kernels(oracle, N, M, d):
     """The two-exponential form of the backward, forced on ordinary inputs."""
     print("[case] fp32, two exponentials forced: N=%d M=%d d=%d" % (N, M, d), flush=True)
     _check(oracle, _inputs(N, M, d), saved=N != 515, variant=binding.VARIANT_TWO_EXP)
+
+
+# Rounding to nearest averages out over the terms of a sum; an error of one sign does not.  With independent roundings the
+# weights are good to a few 2^-24 (|S2| below 10 here), and means of values and gradients under them no worse: 8 * 2^-24.
+# (The logarithm's one-sided cut and a rounded lse log2 e gave dV 8e-7 ... 1.2e-6 on these inputs.)
+UNBIASED = 8 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("kind,N,M,d", [(1, 60000, 256, 16), (4, 2485, 128, 16), (2, 20000, 32, 8)])
+def test_roundings_average_out(oracle, kind, N, M, d):
+    """Sums over many tokens: mean-zero values (kind 1), whose mean is small, and mesh-like ones."""
+    print("[case] fp32, unbiased sums: kind %d N=%d M=%d d=%d" % (kind, N, M, d), flush=True)
+    inp = synth.make_inputs(kind, B=1, H=2, N=N, M=M, d=d, dtype="f32", with_dy=True, seed=71 + N)
+    dev, scale = to_device(inp), inp["scale"]
+    ld = torch.empty((1, 2, N), dtype=torch.float32, device="cuda")
+    y, z, lse = binding.forward(dev["q"], dev["k"], dev["v"], scale, lse_dec=ld)
+    dq, dk, dv = binding.backward(dev["q"], dev["k"], dev["v"], dev["dy"], z, lse, scale, y=y, lse_dec=ld)
+    y_ref, _, lse_ref = oracle.forward(inp["q"], inp["k"], inp["v"], scale)
+    dv_ref = oracle.backward(inp["q"], inp["k"], inp["v"], inp["dy"], scale)[2]
+    err = lse.double().cpu().numpy() - lse_ref
+    print("[case]    y %.2e dv %.2e; lse_enc mean error %.1e" % (slice_relerr(to_host(y), y_ref),
+                                                                slice_relerr(to_host(dv), dv_ref), err.mean()), flush=True)
+    assert slice_relerr(to_host(y), y_ref) <= UNBIASED and slice_relerr(to_host(dv), dv_ref) <= UNBIASED
+    assert abs(err.mean()) <= 2.0 ** -22     # rounded to nearest its mean vanishes; half an ulp of 8 ... 16 is 2^-21
+
