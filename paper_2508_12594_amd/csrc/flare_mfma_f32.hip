@@ -21,6 +21,13 @@
 // In the score product of d <= 8 the two lane halves of the 16-slot contraction hold different planes: three products
 // instead of six.
 //
+// The matrix cores do not round to nearest throughout: a group of eight products is cut toward zero at 2^-24 of the largest,
+// and an accumulator below that product is cut downwards there.  That is -2^-25 of the largest product per group, of one sign
+// whatever the data, which over N tokens adds up while a sum of N terms of either sign grows with their root: z of
+// 195000 normal tokens was off by 1.5e-6, the same way in every latent, so that y, an average over them, was 5 times
+// further off than with fp32 multiply-adds.  The latent-major kernels therefore take every other tile of a stage, and in every
+// other chunk the others, with opposite signs (the rows of V and dY, -eps and -delta, and so dS).
+//
 // Equations: Section 3.1, Eq. flare_encode / Eq. flare_decode; Appendix F; backward as in include/flare.h.
 #include <type_traits>
 #include <utility>
@@ -343,6 +350,9 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
     const size_t base = tok_base(A.ts, bh, A.H);
     const TrLane tl(lane);
 
+    // the sign with which a stage's t-th tile is taken (see the head of the file)
+    auto sign_of = [&](int t) __attribute__((always_inline)) { return ((t + chunk) & 1) ? -1.f : 1.f; };
+
     // the zeros that complete the last transposed operand, in both buffers
     if constexpr (Geo::RT - 8 > 3 * Geo::PD) {
         constexpr int ROWS0 = MODE == 2 ? L::K : L::V, Z0 = 3 * Geo::PD, ZN = (Geo::RT - 8 - Z0) / 8;
@@ -371,7 +381,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
             load_row_half<DR>(A.dz + row * DR, hh, x);
             reg_ops<DR, true>(x, hh, dzp);
             le = A.lse_enc[row];
-            ep = A.eps[row];
+            ep = sign_of(tg) * A.eps[row];
         }
     }
     const bool one_exp = MODE == 2 && A.plan[bh] != 0;
@@ -415,6 +425,7 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
             if (!item(it, a, tok, piece)) return;
             const int n = n0 + st * stage_tok + tok, t32 = tok & 31;
             const bool in = n < n1;
+            const float sign = sign_of(tok >> 5);
             uint16_t *tile = smem + ((st & 1) * TG + (tok >> 5)) * L::TILE;
             float *stat = reinterpret_cast<float *>(tile + L::ST);
             if (MODE == 1 && a == 1) {
@@ -440,19 +451,18 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
                 float ld;
                 const float w = exp2_neg_lse(in ? st0[it] : 0.f, A.ld_mul, kSpan32, ld);
                 stat[t32] = one_exp ? w : ld;
-                stat[32 + t32] = in ? -st1[it] : 0.f;
+                stat[32 + t32] = in ? -sign * st1[it] : 0.f;
             }
-            if (!in) {                            // behind the chunk's end: rows of zeros
+            const float f = !in ? 0.f : a == 0 ? 1.f : sign;   // (behind the chunk's end: rows of zeros)
 #pragma unroll
-                for (int i = 0; i < 8; ++i) x[it][i] = 0.f;
-            }
+            for (int i = 0; i < 8; ++i) x[it][i] *= f;
             uint16_t *row = tile + (a == 0 ? L::K + t32 * L::KR : a == 1 ? L::V + t32 * L::VR : L::Y + t32 * Geo::RD);
             store_planes<DR>(row, piece, x[it]);
         }, std::make_integer_sequence<int, IT>{});
     };
 
     // ---- one sweep over the chunk ----
-    f32x16 o = splat16(0.f);
+    f32x16 o = splat16(0.f);    // with this wave's sign
     float l = 0.f, c = 0.f;
     auto compute = [&](int st, auto online_tag) {
         constexpr bool ONLINE = decltype(online_tag)::value;
@@ -542,6 +552,8 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
     // ---- the TG waves of a latent tile, added in order ----
     float out[Geo::OUT];
     fold_planes<DR>(o, out);
+#pragma unroll
+    for (int i = 0; i < Geo::OUT; ++i) out[i] *= sign_of(tg);
     float *red = reinterpret_cast<float *>(smem);
     if (TG > 1) {
         __syncthreads();                         // the staging buffers are free now

@@ -106,11 +106,12 @@ def test_two_exponential_kernels(oracle, N, M, d):
 
 # Rounding to nearest averages out over the terms of a sum; an error of one sign does not.  With independent roundings the
 # weights are good to a few 2^-24 (|S2| below 10 here), and means of values and gradients under them no worse: 8 * 2^-24.
-# (The logarithm's one-sided cut and a rounded lse log2 e gave dV 8e-7 ... 1.2e-6 on these inputs.)
+# (The logarithm's one-sided cut and a rounded lse log2 e gave dV 8e-7 ... 1.2e-6 on these inputs, small accumulators that the
+# matrix cores cut downwards y 4.7e-7 and dV another 3e-7 on the first.)
 UNBIASED = 8 * 2.0 ** -24
 
 
-@pytest.mark.parametrize("kind,N,M,d", [(1, 60000, 256, 16), (4, 2485, 128, 16), (2, 20000, 32, 8)])
+@pytest.mark.parametrize("kind,N,M,d", [(1, 100000, 64, 32), (1, 60000, 256, 16), (4, 2485, 128, 16), (2, 20000, 32, 8)])
 def test_roundings_average_out(oracle, kind, N, M, d):
     """Sums over many tokens: mean-zero values (kind 1), whose mean is small, and mesh-like ones."""
     print("[case] fp32, unbiased sums: kind %d N=%d M=%d d=%d" % (kind, N, M, d), flush=True)
@@ -127,3 +128,23 @@ def test_roundings_average_out(oracle, kind, N, M, d):
     assert slice_relerr(to_host(y), y_ref) <= UNBIASED and slice_relerr(to_host(dv), dv_ref) <= UNBIASED
     assert abs(err.mean()) <= 2.0 ** -22     # rounded to nearest its mean vanishes; half an ulp of 8 ... 16 is 2^-21
 
+
+@pytest.mark.parametrize("B,N,M,d", [(60, 4930, 4, 16), (12, 3410, 2, 16), (4, 6019, 14, 32), (8, 1500, 300, 8)])
+def test_keys_far_from_their_spread(oracle, B, N, M, d):
+    """Keys whose common part is many times what tells them apart: the terms of dQ are K times as large as their sum, and eps
+    and the normalisers, rounded to 2^-24, enter them: 8 * 2^-24 K as in test_gpu_fp32_conditioning.py, with nothing for an
+    error that all tokens share."""
+    print("[case] fp32, long common key: B=%d N=%d M=%d d=%d" % (B, N, M, d), flush=True)
+    inp = synth.make_inputs(1, B=B, H=1, N=N, M=M, d=d, dtype="f32", with_dy=True, seed=5 + N)
+    common = np.random.Generator(np.random.PCG64(N)).standard_normal(d).astype(np.float32)
+    inp["k"] = np.float32(0.3) * inp["k"] + np.float32(2.0) * common
+    dev, scale = to_device(inp), inp["scale"]
+    refs = oracle.backward(inp["q"], inp["k"], inp["v"], inp["dy"], scale)
+    K = _cancellation_factor(inp["q"], inp["k"], inp["v"], inp["dy"], scale, refs[0])
+    for saved in (True, False):
+        ld = torch.empty((B, 1, N), dtype=torch.float32, device="cuda") if saved else None
+        y, z, lse = binding.forward(dev["q"], dev["k"], dev["v"], scale, lse_dec=ld)
+        dq, _, _ = binding.backward(dev["q"], dev["k"], dev["v"], dev["dy"], z, lse, scale, y=y if saved else None, lse_dec=ld)
+        e = slice_relerr(to_host(dq), refs[0])
+        print("[case]    saved=%s dq %.2e, K %.0f: bound %.2e" % (saved, e, K, UNBIASED + 8 * 2.0 ** -24 * K), flush=True)
+        assert e <= UNBIASED + 8 * 2.0 ** -24 * K
