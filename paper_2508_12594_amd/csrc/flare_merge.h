@@ -46,34 +46,43 @@ struct MergeZ {
 };
 
 // D / 4 threads per latent own four columns each; the slots are folded in order behind one maximum (exact in any order),
-// so the bits depend on the slot count only.  A slot with m = -inf is empty.  P >= g.parts: everything a thread needs of P
-// slots is requested before anything is used (one memory latency).
-template <int D, int P>
+// so the bits depend on the slot count only.  A slot with m = -inf is empty.  The slots come four at a time, everything of
+// four requested before anything is used: with all of kInlineSlots in flight the decode kernels around this took every
+// register (68 ... 122 without it), and where their workgroups no longer all fit on the chip, half as much time again (12 x 8
+// heads, 56656 tokens, 32 latents: 151 us, 105 us like this).
+template <int D>
 __device__ __forceinline__ void merge_z_row(const MergeZ &g, int bh, int M, int m, int j, float *z_lds, bool write)
 {
+    constexpr int P = 4;
     const size_t s0 = (size_t)bh * g.parts * M + m;   // slot p of this latent: s0 + p * M
-    float mp[P], lp[P];
-    float4 oc[P];
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const size_t slot = s0 + (size_t)min(p, g.parts - 1) * M;
-        mp[p] = g.m_part[slot];
-        lp[p] = g.l_part[slot];
-        oc[p] = *reinterpret_cast<const float4 *>(g.o_part + slot * D + 4 * j);
-    }
     float gm = -INFINITY;
+    if (g.parts > P) {
 #pragma unroll
-    for (int p = 0; p < P; ++p) gm = fmaxf(gm, mp[p]);
+        for (int p = 0; p < kInlineSlots; ++p) gm = fmaxf(gm, g.m_part[s0 + (size_t)min(p, g.parts - 1) * M]);
+    }
     float l = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+    for (int p0 = 0; p0 < g.parts; p0 += P) {
+        float mp[P], lp[P];
+        float4 oc[P];
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const float w = (p >= g.parts || mp[p] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mp[p] - gm);
-        l = fmaf(lp[p], w, l);
-        o.x = fmaf(oc[p].x, w, o.x);
-        o.y = fmaf(oc[p].y, w, o.y);
-        o.z = fmaf(oc[p].z, w, o.z);
-        o.w = fmaf(oc[p].w, w, o.w);
+        for (int i = 0; i < P; ++i) {
+            const size_t slot = s0 + (size_t)min(p0 + i, g.parts - 1) * M;
+            mp[i] = g.m_part[slot];
+            lp[i] = g.l_part[slot];
+            oc[i] = *reinterpret_cast<const float4 *>(g.o_part + slot * D + 4 * j);
+        }
+        if (g.parts <= P) gm = fmaxf(fmaxf(mp[0], mp[1]), fmaxf(mp[2], mp[3]));
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const float w = (p0 + i >= g.parts || mp[i] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mp[i] - gm);
+            l = fmaf(lp[i], w, l);
+            o.x = fmaf(oc[i].x, w, o.x);
+            o.y = fmaf(oc[i].y, w, o.y);
+            o.z = fmaf(oc[i].z, w, o.z);
+            o.w = fmaf(oc[i].w, w, o.w);
+        }
     }
     const float inv = 1.f / l;
     const size_t idx = (size_t)bh * M + m;
@@ -90,11 +99,8 @@ __device__ __forceinline__ void merge_z_rows(const MergeZ &g, int bh, int M, int
                                              float *z_lds, bool write)
 {
     constexpr int L = D / 4;
-    for (int m = m0 + tid / L; m < m1; m += nt / L) {
-        if (g.parts <= 4) merge_z_row<D, 4>(g, bh, M, m, tid % L, z_lds, write);
-        else if (g.parts <= 8) merge_z_row<D, 8>(g, bh, M, m, tid % L, z_lds, write);
-        else merge_z_row<D, kInlineSlots>(g, bh, M, m, tid % L, z_lds, write);
-    }
+#pragma unroll 1
+    for (int m = m0 + tid / L; m < m1; m += nt / L) merge_z_row<D>(g, bh, M, m, tid % L, z_lds, write);
 }
 // ---- the variant of the last backward kernels ---------------------------------------------------
 // They exist with one and with two exponentials per score.
