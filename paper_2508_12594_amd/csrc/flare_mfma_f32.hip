@@ -896,7 +896,7 @@ constexpr int kWorkgroups = 512;    // and workgroups of the token-major kernels
 struct LatentGeom { int G, TG, zdim; };
 inline LatentGeom latent_geom(int M, int tile_bytes)
 {
-    const int MT = (M + 31) / 32;
+    const int MT = M / 32 + (M % 32 != 0);
     LatentGeom g;
     g.zdim = (MT + 7) / 8;
     g.G = (MT + g.zdim - 1) / g.zdim;
@@ -988,9 +988,10 @@ Split mfma32_split(const flare_shape &s)
     constexpr int kMinChunk = 128;
     const int tile = s.d <= 8 ? LatentLds<8, 0>::TILE : s.d == 16 ? LatentLds<16, 0>::TILE : LatentLds<32, 0>::TILE;
     const LatentGeom g = latent_geom(s.M, tile * 2);
-    const int stage = 32 * g.TG, per = s.B * s.H * g.zdim * g.G * g.TG;
+    const int stage = 32 * g.TG;
+    const long long per = (long long)s.B * s.H * g.zdim * g.G * g.TG;   // (any shape may be asked about)
     const int stages = (s.N + stage - 1) / stage;
-    int want = (kWaves + per - 1) / per;
+    int want = (int)((kWaves + per - 1) / per);
     const int most = (s.N + kMinChunk - 1) / kMinChunk;
     if (want > most) want = most;
     if (want > stages) want = stages;

@@ -50,6 +50,16 @@ def test_version_and_strerror(lib):
         assert len(binding.strerror(code)) > 0
 
 
+def test_workspace_bytes_of_any_shape(lib):
+    """Shapes far beyond any memory are answered like others (a crash here would take the program with it)."""
+    for dtype in (binding.FLARE_F32, binding.FLARE_BF16):
+        for B, H, N, M, d in ((65535, 1, 100, 1 << 21, 4), (8191, 8, 1000, 1 << 24, 8), (1, 1, 100, (1 << 31) - 1, 4),
+                              (60000, 1, 1 << 23, (1 << 22) + 32, 4), (1, 65535, (1 << 24) - 1, 1, 4)):
+            f, b = binding.workspace_bytes(B, H, N, M, d, dtype)
+            assert f >= B * H * M * (d + 2) * 4 or M == 1
+            assert b >= f // 2
+
+
 def test_workspace_bytes_do_not_depend_on_the_layout(lib):
     """binding.workspace_bytes has no layout argument: what it reports has to serve both.  Few tokens, where one slot more
     per chunk is the largest count there is, every tile count and head dimension."""
