@@ -106,7 +106,7 @@ int valu_backward(const flare_shape &s, const void *q, const void *k, const void
                   const float *lse_dec, const void *dy, const float *z, const float *lse_enc, void *dq,
                   bool dq_cast, void *dk, void *dv, float scale, void *ws, hipStream_t stream);
 
-// ---- bf16 matrix-core path (d in {16,32}; M = 32 or a multiple of 64 up to 256) --------------
+// ---- matrix-core path of 16-bit storage (M <= 2048, N >= 16; mfma_supported) -----------------
 struct MfmaPlan {
     Split enc;   // token chunks of the encode (one workgroup each)
     int parts;   // partial slots per (b,h) of the encode and dZ kernels: one per chunk
@@ -136,7 +136,6 @@ int mfma_decode_project(const flare_shape &s, const void *q, const void *k, cons
                         const float *bias, void *out, void *y, float *lse_dec, float scale, hipStream_t stream);
 int mfma_token_stats(const flare_shape &s, const void *q, const void *k, const float *z, const void *dy,
                      float *lse_dec2, float *delta, float scale, void *ws, hipStream_t stream);
-bool mfma_dkdv_supported(const flare_shape &s);
 // In the backward launchers below the per-token decode statistic is read as
 // ld_mul * lse_dec2[n]: pass the workspace array with ld_mul = 1, or the forward's natural-log
 // lse_dec with ld_mul = log2(e).

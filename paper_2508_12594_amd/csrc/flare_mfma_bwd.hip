@@ -1050,12 +1050,7 @@ int mfma_dq_partial(const flare_shape &s, const void *q, const void *k, const vo
 
 // dK and dV of the backward.  One workgroup of 8 waves per (b,h) slice and block of token tiles;
 // the operand images need (4 or 6)*KS + 1 + 4*HV KiB of LDS per latent tile.
-bool mfma_dkdv_supported(const flare_shape &s)
-{
-    return mfma_supported(s);
-}
-
-// workgroups per (b,h) of the dK/dV kernel (= dQ partial slots per (b,h) when it also forms dQ)
+// Workgroups per (b,h) (= dQ partial slots per (b,h) when it also forms dQ)
 int mfma_dkdv_blocks(const flare_shape &s)
 {
     const int BH = s.B * s.H;

@@ -630,7 +630,7 @@ struct TokenArgs {
     float *out0, *out1;      // y, lse_dec | lse_dec2, delta | dk, dv
     TokStride ts;
     int H, N, M, CT;
-    float c2, ld_mul, scale;
+    float c2, ld_mul;
 };
 template <int DR, int MODE>
 struct TokenLds {   // in uint16 units, per latent tile
@@ -1060,7 +1060,7 @@ int mfma32_dkdv(const flare_shape &s, const float *q, const float *k, const floa
     a.mdz = g;
     a.q = q; a.k = k; a.v = v; a.dy = dy; a.z = z; a.lse_enc = lse_enc;
     a.lse_dec = lse_dec; a.delta = delta; a.ld_mul = ld_mul; a.out0 = dk; a.out1 = dv;
-    a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e; a.scale = scale;
+    a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e;
     FLARE_D(s, (launch_token<D, 2>(s, a, KID_BWD_DKDV, stream)));
 }
 

@@ -902,7 +902,7 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
                           !(s.y_f32 && mf);   // an fp32 y is not coarse (the fp32 kernels, which take the
                                               // 16-bit shapes of fewer than 16 tokens, never read it: they recompute)
     const bool saved = y && lse_dec && !coarse_y;
-    const bool fused = saved && (F32 || (mf && mfma_dkdv_supported(s)));   // every later kernel is a matrix-core one
+    const bool fused = saved && planned;   // every later kernel is a matrix-core one
     const float *ld = fused ? lse_dec : w.lse_dec2;
     const float ld_mul = fused ? kLog2e : 1.f;
     // delta from the fp32 y: at d <= 8 inside the dZ kernel like from a 16-bit y, else by a pass of its own
