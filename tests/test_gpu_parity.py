@@ -376,7 +376,7 @@ def test_large_score_offsets(oracle, dtype):
 
 
 @pytest.mark.parametrize("dtype,M,d", [("bf16", 256, 16), ("bf16", 64, 8), ("f16", 128, 32), ("bf16", 256, 32),
-                                       ("f32", 64, 16)])
+                                       ("f32", 64, 16), ("f32", 300, 16), ("f32", 290, 8)])
 def test_decode_with_every_token_shifted_differently(dtype, M, d):
     """The decode's softmax runs over the latents of one token, so adding the same amount to all scores of a token
     leaves y unchanged and moves lse_dec by that amount.  Here token n's scores are shifted by a ramp from -138 to
