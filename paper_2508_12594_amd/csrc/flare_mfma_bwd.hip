@@ -1055,9 +1055,9 @@ int mfma_dkdv_blocks(const flare_shape &s)
 {
     const int BH = s.B * s.H;
     const int tiles = (s.N + 31) / 32;
-    int blocks = (256 + BH - 1) / BH;                 // one 8-wave workgroup per CU
-    if (blocks > (tiles + 7) / 8) blocks = (tiles + 7) / 8;
-    return blocks;
+    int most = BH <= 256 ? (256 + BH - 1) / BH : 4;   // one 8-wave workgroup per CU
+    if (most > (tiles + 7) / 8) most = (tiles + 7) / 8;
+    return round_blocks(BH, 1, tiles, 8, 1 + 8 / (lat_eff(s.M) / 32), most);   // (setup: the operand images)
 }
 
 // The dK/dV kernel can form the dQ partials as well (one pass over the scores for all three gradients);

@@ -495,6 +495,26 @@ inline EncGeom dq_geom(const flare_shape &s)
 constexpr int kEncodeTargetBlocks = 512;   // two 4-wave workgroups per CU
 constexpr int kDecodeTargetBlocks = 512;
 
+// Workgroups per (b,h), at most `most`, where those of a (b,h) share `steps` equal steps among `waves` waves each and a
+// workgroup costs `setup` more, `cu` of which run side by side on a CU.  The work is dealt out beforehand, so a launch is over when the CU with the most
+// workgroups is: 24 (b,h) by 22 (512 places, rounded up) leave 16 CUs with three workgroups and the others with two, by 21
+// none.  Of counts that cost nearly the same (5 %) the largest: two on a CU cover each other's waits.  (3 x 8 heads, 50021
+// tokens, 200 latents: d = 8 forward 126 -> 91 us, d = 16 training 388 -> 269 us; 5 x 8 heads, 30000 tokens, 128 latents,
+// d = 32 505 -> 381 us.)
+inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int most)
+{
+    constexpr int kCus = 256;
+    auto cost = [&](int b) {
+        const long long on_cu = ((long long)b * BH + kCus - 1) / kCus;
+        return on_cu * ((steps + b * waves - 1) / (b * waves)) + (on_cu + cu - 1) / cu * setup;
+    };
+    long long least = cost(1);
+    for (int b = 2; b <= most; ++b) least = cost(b) < least ? cost(b) : least;
+    int best = most > 1 ? most : 1;
+    while (best > 1 && 20 * cost(best) > 21 * least) --best;
+    return best;
+}
+
 }  // namespace
 }  // namespace flare
 

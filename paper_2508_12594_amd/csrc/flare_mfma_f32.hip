@@ -891,8 +891,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
 // Latent-major: up to 8 waves per workgroup; one 32-latent tile per wave, what is left of the 8 waves splits the
 // tokens as far as two staging buffers of kStageLds hold a tile for each.
 constexpr int kStageLds = 80 * 1024;   // (two workgroups per CU)
-constexpr int kWaves = 4096;        // waves a launch aims at: 16 per CU
-constexpr int kWorkgroups = 512;    // and workgroups of the token-major kernels
+constexpr int kCuWaves = 16;        // waves per CU that a launch aims at
 struct LatentGeom { int G, TG, zdim; };
 inline LatentGeom latent_geom(int M, int tile_bytes)
 {
@@ -951,12 +950,14 @@ int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t 
     // eight waves share a workgroup's planes; with less than half of the CUs busy that way, four (1024 tokens, 4 heads:
     // dK/dV 17 -> 15.5 us)
     const int waves = (tiles + kTokenWaves - 1) / kTokenWaves * BH <= 128 ? kTokenWaves / 2 : kTokenWaves;
-    const int batch = waves * (fits ? 1 : MODE == 2 ? 2 : 4);
-    int blocks = (tiles + batch - 1) / batch;
-    const int most = (kWorkgroups + BH - 1) / BH;
-    if (blocks > most) blocks = most;
+    const int batches = (tiles + (fits ? 1 : MODE == 2 ? 2 : 4) - 1) / (fits ? 1 : MODE == 2 ? 2 : 4);   // a wave's steps
+    // resident workgroups: as many as waves (dK/dV keeps two on a SIMD) and LDS allow
+    int cu = (MODE == 2 ? kCuWaves / 2 : kCuWaves) / waves;
+    if (cu > (int)(kLds / lds)) cu = (int)(kLds / lds) > 1 ? (int)(kLds / lds) : 1;
+    int most = BH <= 256 * cu ? (256 * cu + BH - 1) / BH : 4;
+    if (most > (batches + waves - 1) / waves) most = (batches + waves - 1) / waves;
+    const dim3 grid(round_blocks(BH, cu, batches, waves, 1, most), BH);
     LaunchTimer t(kid, stream);
-    const dim3 grid(blocks, BH);
     if constexpr (MODE != 1) {
         if (merge) {
             token_pass_f32_kernel<DR, MODE, 1, true><<<grid, 64 * waves, lds, stream>>>(A);
@@ -981,7 +982,7 @@ int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t 
 
 }  // namespace
 
-// Chunks of tokens of the latent-major kernels: enough for kWaves waves, at least one stage of the encode and kMinChunk
+// Chunks of tokens of the latent-major kernels: enough for kCuWaves waves per CU, at least one stage of the encode and kMinChunk
 // tokens (shorter ones would cost more in slots to merge than they gain) and at most 8192 tokens long (a chunk's sums are taken one after the other in fp32).
 Split mfma32_split(const flare_shape &s)
 {
@@ -989,12 +990,12 @@ Split mfma32_split(const flare_shape &s)
     const int tile = s.d <= 8 ? LatentLds<8, 0>::TILE : s.d == 16 ? LatentLds<16, 0>::TILE : LatentLds<32, 0>::TILE;
     const LatentGeom g = latent_geom(s.M, tile * 2);
     const int stage = 32 * g.TG;
-    const long long per = (long long)s.B * s.H * g.zdim * g.G * g.TG;   // (any shape may be asked about)
-    const int stages = (s.N + stage - 1) / stage;
-    int want = (int)((kWaves + per - 1) / per);
-    const int most = (s.N + kMinChunk - 1) / kMinChunk;
-    if (want > most) want = most;
-    if (want > stages) want = stages;
+    const long long per = (long long)s.B * s.H * g.zdim;                 // workgroups of a chunk (any shape may be asked about)
+    const int stages = (s.N + stage - 1) / stage, places = 256 * (kCuWaves / (g.G * g.TG));
+    int most = (int)((places + per - 1) / per);
+    if (most > (s.N + kMinChunk - 1) / kMinChunk) most = (s.N + kMinChunk - 1) / kMinChunk;
+    if (most > stages) most = stages;
+    const int want = per > places ? most : round_blocks((int)per, places / 256, stages, 1, 1, most);
     int len = (stages + want - 1) / want * stage;
     if (len > 8192) len = 8192;
     return Split{(s.N + len - 1) / len, len};

@@ -1134,7 +1134,13 @@ MfmaPlan mfma_plan(const flare_shape &s)
     const EncGeom e = enc_geom(s.M, padded_dim(s.d));
     const int BH = s.B * s.H;
     // each chunk gives every token group at least 8 tiles of 32 tokens
-    p.enc = plan_split(s.N, BH, 256 * e.TG, kEncodeTargetBlocks);
+    const int min_len = 256 * e.TG, tiles = (s.N + 31) / 32;
+    int most = (kEncodeTargetBlocks + BH - 1) / BH;
+    if (most > (s.N + min_len - 1) / min_len) most = (s.N + min_len - 1) / min_len;
+    const int want = round_blocks(BH, kEncodeTargetBlocks / 256, tiles, e.TG, 1, most);
+    // (chunks in whole tiles: only the last one ends within a tile)
+    p.enc.chunk_len = (tiles + want - 1) / want * 32;
+    p.enc.chunks = (s.N + p.enc.chunk_len - 1) / p.enc.chunk_len;
     p.parts = p.enc.chunks;
     return p;
 }
@@ -1276,9 +1282,10 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
     const int tiles = (s.N + 31) / 32;
     // d = 32 with more than 128 latents (Z in LDS, 168 registers): three workgroups fit a CU
     const bool three = padded_dim(s.d) == 32 && Mc > 128;
-    int blocks = ((three ? 768 : kDecodeTargetBlocks) + BH - 1) / BH;
-    if (blocks > (tiles + 3) / 4) blocks = (tiles + 3) / 4;
-    const dim3 grid(blocks, BH);
+    const int places = three ? 768 : kDecodeTargetBlocks;
+    int most = BH <= places ? (places + BH - 1) / BH : 4;
+    if (most > (tiles + 3) / 4) most = (tiles + 3) / 4;
+    const dim3 grid(round_blocks(BH, places / 256, tiles, 4, 1, most), BH);
     const float c2 = scale * kLog2e;
     const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *gg = (const bf16_t *)dy;
     bf16_t *yy = (bf16_t *)y;

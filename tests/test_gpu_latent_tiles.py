@@ -25,13 +25,18 @@ F32 = [(33, 4, 129), (31, 8, 33), (97, 16, 260), (160, 32, 257), (256, 16, 1000)
        (600, 8, 1100), (2049, 16, 90)]
 
 
-def _check(oracle, dtype, H, N, M, d, layout, saved):
-    print("[case] %s H=%d N=%d M=%d d=%d %s saved=%s" % (dtype, H, N, M, d, layout, saved), flush=True)
-    inp = synth.make_inputs(1, B=1, H=H, N=N, M=M, d=d, dtype=dtype, with_dy=True, seed=31 + N + M + d)
+# numbers of (b,h) that do not divide the chip's workgroups: 3 x 8, 7 x 4, 5 x 4; and more than one per CU
+HEADS = [("bf16", 3, 8, 5100, 72, 8), ("f16", 7, 4, 5300, 64, 16), ("bf16", 5, 4, 2700, 130, 32), ("f32", 12, 4, 900, 70, 8),
+         ("bf16", 17, 16, 1111, 33, 16), ("f32", 20, 16, 390, 40, 16)]
+
+
+def _check(oracle, dtype, H, N, M, d, layout, saved, B=1):
+    print("[case] %s B=%d H=%d N=%d M=%d d=%d %s saved=%s" % (dtype, B, H, N, M, d, layout, saved), flush=True)
+    inp = synth.make_inputs(1, B=B, H=H, N=N, M=M, d=d, dtype=dtype, with_dy=True, seed=31 + N + M + d)
     scale, tol, dev = inp["scale"], tol_for(inp), to_device(inp)
     order = (lambda t: t.permute(0, 2, 1, 3).contiguous()) if layout == "bnhd" else (lambda t: t)
     k, v, dy = (order(dev[n]) for n in ("k", "v", "dy"))
-    ld = torch.empty((1, H, N), dtype=torch.float32, device="cuda") if saved else None
+    ld = torch.empty((B, H, N), dtype=torch.float32, device="cuda") if saved else None
     y, z, lse = binding.forward(dev["q"], k, v, scale, lse_dec=ld, layout=layout)
     dq, dk, dv = binding.backward(dev["q"], k, v, dy, z, lse, scale, y=y if saved else None, lse_dec=ld, layout=layout)
     y_ref, z_ref, _ = oracle.forward(inp["q"], inp["k"], inp["v"], scale)
@@ -58,6 +63,11 @@ def test_slots_merged_by_consumer_or_kernel(oracle, dtype, N, M, d):
     _check(oracle, dtype, 1, N, M, d, "bhnd", saved=True)
 
 
+@pytest.mark.parametrize("dtype,B,H,N,M,d", HEADS)
+def test_heads_that_do_not_divide_the_chip(oracle, dtype, B, H, N, M, d):
+    _check(oracle, dtype, H, N, M, d, "bnhd" if M % 2 else "bhnd", saved=True, B=B)
+
+
 @pytest.mark.parametrize("M", [70, 150, 200])
 def test_projection_of_ragged_latents(M):
     """The fused projection forms the y that the decode forms, bit for bit, whatever the number of tiles."""
@@ -72,3 +82,15 @@ def test_projection_of_ragged_latents(M):
     assert torch.equal(z, z_ref) and torch.equal(lse, lse_ref)
     # (z that the decode merged for itself and z from memory are the same numbers)
     assert torch.equal(y, y_ref) and torch.equal(out.view_as(y), y)
+
+
+@pytest.mark.parametrize("B,H", [(11, 8), (7, 4), (5, 2)])
+def test_projection_of_items_that_do_not_divide_the_chip(B, H):
+    print("[case] projection B=%d H=%d" % (B, H), flush=True)
+    inp = synth.make_inputs(1, B=B, H=H, N=1111, M=50, d=16, dtype="bf16", seed=5 + B)
+    dev = to_device(inp, ("q", "k", "v"))
+    k, v = (dev[n].permute(0, 2, 1, 3).contiguous() for n in ("k", "v"))
+    y_ref = binding.forward(dev["q"], k, v, inp["scale"], layout="bnhd")[0]
+    w = torch.eye(16 * H, dtype=k.dtype, device="cuda")
+    out = binding.forward_project(dev["q"], k, v, w, inp["scale"])[0]
+    assert torch.equal(out.view_as(y_ref), y_ref)
