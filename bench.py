@@ -63,7 +63,6 @@ def algorithmic_bytes(kernel, B, H, N, M, d, elem):
         "bwd_dz_partial": 3 * row + 8,          # k, dy, y, lse_dec in; delta out (saved-statistics path)
         "bwd_dq_partial": 3 * row + 8,          # k, v, dy, lse_dec, delta in
         "bwd_dkdv": 5 * row + 8,                # k, v, dy in; dk, dv out
-        "bwd_dkdv_2exp": 5 * row + 8,
     }
     if kernel in per_token:
         return bhn * per_token[kernel]
@@ -73,10 +72,9 @@ def algorithmic_bytes(kernel, B, H, N, M, d, elem):
 def exponentials(kernel, B, H, N, M):
     """v_exp_f32 lane-operations one launch of `kernel` cannot avoid: one per score.  (The last two
     backward kernels need both softmax weights of a score, but the second follows from the first by
-    a multiplication, R = P * 2^(lse_enc2[m] - lse_dec2[n]); their two-exponential fall-backs are
-    priced at two.)"""
+    a multiplication, R = P * 2^(lse_enc2[m] - lse_dec2[n]).)"""
     per_pair = {"encode_partial": 1, "decode": 1, "bwd_token_stats": 1, "bwd_dz_partial": 1,
-                "bwd_dq_partial": 1, "bwd_dkdv": 1, "bwd_dkdv_2exp": 2}
+                "bwd_dq_partial": 1, "bwd_dkdv": 1}
     return per_pair.get(kernel, 0) * B * H * N * M
 
 
@@ -96,9 +94,8 @@ def issue_clocks_per_tile(kernel, d, fused_dq):
         "bwd_dz_partial": (16, 8, 0, score + value),
         # dS = P (a + w u c): per score one exponential, two multiply-adds, a pack of P and a pack of dS
         "bwd_dq_partial": (16, 16, 32, score + 2 * ks + value),                       # scores, a, c, dS.K
-        "bwd_dkdv": (16, 16, 32, score + 2 * ks + 2 * value + (1 if fused_dq else 0)),  # + dV, dK (, dQ: 16-row products)
+        "bwd_dkdv": (16, 16, 32, score + 2 * ks + 2 * value + (ks if fused_dq else 0)),  # + dV, dK (, dQ: 16-row products)
     }
-    mix["bwd_dkdv_2exp"] = (32,) + mix["bwd_dkdv"][1:]
     if kernel not in mix:
         return None
     n_exp, n_pack, n_fma, n_mfma = mix[kernel]
@@ -234,10 +231,6 @@ def run_workload(cfg, args, steps, warmup, primary):
         ab = algorithmic_bytes(name, B, H, N, M, d, elem)
         ex = exponentials(name, B, H, N, M)
         ic = issue_clocks_per_tile(name, d, fused_dq) if inp["dtype"] != "f32" else None
-        twin = name[:-5] if name.endswith("_2exp") else name + "_2exp"
-        twin_ms = prof[twin][0] / prof[twin][1] if twin in prof else 0.0
-        if ms / cnt < 0.05 * twin_ms or (ms / cnt < 0.010 and ms / cnt < 0.3 * twin_ms):
-            ab, ex, ic = None, 0, None     # launched, but every (b,h) slice went to the other variant: it left at once
         kernels[name] = {"mean_us": round(mean_s * 1e6, 2), "launches_per_step": cnt // prof_steps,
                          "algorithmic_GBps": (round(ab / per_step_s / 1e9, 1) if ab else None),
                          "hbm_frac": (round(ab / per_step_s / 1e9 / HBM_PEAK_GBS, 4) if ab else None),

@@ -104,7 +104,7 @@ typedef struct {
 typedef enum {
     FLARE_VARIANT_TWO_EXP = 1,      /* backward: both softmax weights of a score from an exponential of their own
                                        in every (b,h), as for inputs whose normalisers span too wide a range */
-    FLARE_VARIANT_SEPARATE_DQ = 2   /* backward, d <= 16: dQ from the latent-major kernel of its own (as at d = 32)
+    FLARE_VARIANT_SEPARATE_DQ = 2   /* backward: dQ from a latent-major kernel of its own
                                        instead of out of the dK/dV kernel */
 } flare_variant;
 

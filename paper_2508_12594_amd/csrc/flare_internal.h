@@ -24,7 +24,6 @@ enum KernelId {
     KID_BWD_DQ_PARTIAL,
     KID_BWD_DQ_REDUCE,
     KID_BWD_DKDV,
-    KID_BWD_DKDV_2EXP,
     KID_DECODE_MERGE,
     KID_SPECTRAL_GRAM,
     KID_SPECTRAL_REDUCE,

@@ -1,4 +1,4 @@
-// Matrix-core kernels of the second backward pass: dQ, dK, dV (one kernel at d <= 16, two otherwise),
+// Matrix-core kernels of the second backward pass: dQ, dK, dV (one kernel; two with FLARE_VARIANT_SEPARATE_DQ),
 // the per-(b,h) choice between the one- and two-exponential variants, and the fp32 sums of latent chunks.
 // Operand layouts, helpers and the tile geometry are in flare_mfma_common.h.
 #include "flare_mfma_common.h"
@@ -7,7 +7,8 @@ namespace flare {
 namespace {
 
 // ============================================================================================
-// Backward, dQ partials (latent-major, same wave geometry as the encode).  For its NB latent tiles
+// Backward, dQ partials (latent-major, same wave geometry as the encode), where the dK/dV kernel is asked to leave them
+// out (FLARE_VARIANT_SEPARATE_DQ).  For its NB latent tiles
 // a wave keeps, as B operands (column = latent, contraction over d): q' hi and lo, dZ (bf16-exact: it is
 // rounded where it is merged, before eps is formed) and Z in bf16 (hi and, at d = 16, lo).  Per 32-token tile it streams K, V and dY as A operands
 // (row = token) and forms, all on the matrix cores,
@@ -438,12 +439,16 @@ __global__ __launch_bounds__(256, MINB) void bwd_dq_mfma_kernel(
 // ============================================================================================
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kDsStride = 36;   // uint16 per row of the dS tile [token][latent] (72 B: conflict-free 8-byte stores)
-constexpr int kKtStride = 16;   // uint16 per row of the key tile [token][d] of the fused dQ product (rows as loaded)
-constexpr int kFusedWaveLds = 32 * kDsStride + 32 * kKtStride;   // uint16 per wave: dS tile, then the key tile
+// uint16 per row of the key tile [token][d] of the fused dQ product (rows as loaded; d = 32: 80 B, two 16-byte stores)
+constexpr int kt_stride(int d) { return d == 32 ? 40 : 16; }
+// uint16 per wave: dS tile (at least as long as an accumulator where two waves share a token tile, which they exchange
+// there), then the key tile
+constexpr bool dkdv_pair(int d, int mt) { return d == 32 && mt > 4; }
+constexpr int ds_tile_lds(int d, int mt) { return dkdv_pair(d, mt) ? 64 * 16 * 2 : 32 * kDsStride; }
+constexpr int fused_wave_lds(int d, int mt) { return ds_tile_lds(d, mt) + 32 * kt_stride(d); }
 
-// WV: waves per workgroup (one workgroup per CU).  Eight, or twelve where the kernel fits 168 registers (three waves
-// per SIMD): d = 32 with one exponential.
-template <int DR, int MT, bool DQ, bool ONE, bool F, int WV = 8, bool ZL = false>
+constexpr int WV = 8;           // waves per workgroup (one workgroup per CU)
+template <int DR, int MT, bool DQ, bool ONE, bool F, bool ZL = false>
 __device__ __forceinline__ void dkdv_body(
     const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
     const bf16_t *__restrict__ dy, const float *__restrict__ z, const float *__restrict__ lse_enc,
@@ -452,12 +457,12 @@ __device__ __forceinline__ void dkdv_body(
     bf16_t *__restrict__ dv, float *__restrict__ acc32, float *__restrict__ dq_part, TokStride ts, int H, int N,
     int Mtot, int m0, int mend, float c2, float scale)
 {
-    // DQ (d <= 16): the kernel also forms the dQ partials, so that the scores, a, c and dS of a tile
+    // DQ: the kernel also forms the dQ partials, so that the scores, a, c and dS of a tile
     // pair are computed once for all three gradients.  dS of a tile reaches the dQ product transposed
     // (contraction over the tokens) through a wave-private LDS tile, and that product is
     //     dQ^T[dd][m] += K^T[dd][n] dS^T[n][m]     with v_mfma_f32_16x16x32_bf16
-    // (16 output rows = d: no wasted rows, four accumulator registers per 16 latents), so a wave keeps
-    // dQ of all 32*MT latents in 8*MT registers.  At the end the eight waves add their partials in a
+    // (16 output rows = d, two such products at d = 32: no wasted rows, four accumulator registers per 16 latents), so a
+    // wave keeps dQ of all 32*MT latents in 8*MT registers (d = 32: 16*MT).  At the end the eight waves add their partials in a
     // fixed order through LDS and the workgroup writes slot x (its grid position) of dq_part
     // ([(b*h) * gridDim.x + x][Mtot][d], summed and scaled by dq_reduce_kernel).  The c chain
     // then carries the lo term of Z at d <= 8 (ZPACK below) and, with ZL, at d = 16 (dQ sums dS over the tokens of
@@ -474,7 +479,18 @@ __device__ __forceinline__ void dkdv_body(
     constexpr bool WIDE = (D == 32);
     constexpr int HV = WIDE ? 1 : D / 16;
     constexpr int QUARTS = WIDE ? 4 : 2;        // 4-column pieces per lane and accumulator: columns 8 q + 4 hh (+ 16 hv)
-    static_assert(!DQ || DR <= 16, "the fused dQ product is written for d <= 16 (16 output rows)");
+    // PAIR (d = 32, more than 128 latents): the dQ accumulators of all latents would take more than 64 registers, so two
+    // waves share a token tile, each with half of the latent tiles.  At the end of the tile the first hands its part of dK
+    // to the second and takes that one's part of dV (16 values a lane, through the dS tiles, which are free by then); the
+    // two wait for each other by counters in LDS, not at a barrier of the workgroup, which would bring all eight waves
+    // into step.  (262144 tokens, 8 heads, 256 latents: a dQ kernel of its own 283 us and dK/dV 235, this one 320; 32 x 8
+    // heads, 4096 tokens, 128 latents without PAIR: training 316 -> 248 us.)
+    constexpr bool PAIR = DQ && dkdv_pair(D, MT);
+    static_assert(!PAIR || MT % 2 == 0, "the latent tiles are halved");
+    constexpr int HT = PAIR ? MT / 2 : MT;      // latent tiles of a wave
+    constexpr int TW = PAIR ? WV / 2 : WV;      // token tiles a workgroup works on at a time
+    constexpr int DB = D / 16;                  // 16-row blocks of the dQ product
+    constexpr int kKtStride = kt_stride(D);
     // ZL (DQ at d = 16, shapes with fewer tokens than latents): the c chain carries the lo term of Z as one more image
     // and product (at d <= 8 it rides in the free upper half of the Z image, ZPACK below).  dQ sums dS over the tokens
     // of one latent, so the rounding of Z_m adds up coherently there, and on rows whose halves cancel it shows:
@@ -500,6 +516,7 @@ __device__ __forceinline__ void dkdv_body(
     // c - delta cancels where one latent dominates a token, down to a single latent.
     constexpr bool ZPACK = PACK && DQ;
     extern __shared__ __attribute__((aligned(16))) u32x4 img[];   // [MT][PER_TILE][64 lanes]
+    __shared__ volatile int posted[PAIR ? 8 : 1], taken[PAIR ? 8 : 1];   // PAIR: parts handed over / picked up so far
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
@@ -509,6 +526,9 @@ __device__ __forceinline__ void dkdv_body(
     const bool lower = hh == 0;
     constexpr float kap = 0.f;                  // w[n] = 2^(kap - lse_dec2[n])
 
+    if constexpr (PAIR) {
+        if (tid < 8) { posted[tid] = 0; taken[tid] = 0; }
+    }
     // ---- build the operand images ----
     {
         const bf16_t *qh_ = q + (size_t)h * ts.sq + (size_t)m0 * DR;
@@ -645,8 +665,8 @@ __device__ __forceinline__ void dkdv_body(
     const float *lb = lse_dec2 + (size_t)bh * N;
     const float *db = delta + (size_t)bh * N;
     const int tiles = (N + 31) / 32;
-    static_assert(!DQ || WV == 8, "the fused dQ reduction is written for eight waves");
-    const int stride = gridDim.x * WV;
+    const int stride = gridDim.x * TW;
+    const int half = PAIR ? wave & 1 : 0;
     // B operand: column = token.  rep (PACK only): both lane halves get elements 0-7 of the row.
     auto load_cols = [&](const bf16_t *base, int tile, bf16x8 (&t)[KS], bool rep) {
         const int n = min(tile * 32 + l32, N - 1);
@@ -660,22 +680,26 @@ __device__ __forceinline__ void dkdv_body(
         if (PACK && !lower) w[0] = 0x3f803f80u;
         return as_bf16x8(w);
     };
-    auto image = [&](int t, int sid) { return as_bf16x8(img[(t * PER_TILE + sid) * 64 + lane]); };
+    const u32x4 *img_w = img + half * (HT * PER_TILE * 64);   // this wave's latent tiles
+    auto image = [&](int t, int sid) { return as_bf16x8(img_w[(t * PER_TILE + sid) * 64 + lane]); };
 
-    // fused dQ: wave-private LDS tiles and the accumulators dQ^T[dd = 4 (lane / 16) + r][m = 32 t + 16 jb + lane % 16]
-    uint16_t *ds_t = reinterpret_cast<uint16_t *>(img + MT * PER_TILE * 64) + (DQ ? wave * kFusedWaveLds : 0);
-    uint16_t *k_t = ds_t + 32 * kDsStride;
+    // fused dQ: wave-private LDS tiles and the accumulators dQ^T[dd = 16 db + 4 (lane / 16) + r][m = 32 t + 16 jb + lane % 16]
+    uint16_t *ds_t = reinterpret_cast<uint16_t *>(img + MT * PER_TILE * 64) + (DQ ? wave * fused_wave_lds(D, MT) : 0);
+    uint16_t *k_t = ds_t + ds_tile_lds(D, MT);
     if constexpr (DQ && PACK) {   // columns 8-15 of the key tile are never written at d <= 8: zero (the output rows 8-15 are dropped)
         if (lane < 32) *reinterpret_cast<u32x4 *>(k_t + lane * kKtStride + 8) = u32x4{0u, 0u, 0u, 0u};
     }
-    f32x4 dqa[DQ ? MT : 1][2];
+    f32x4 dqa[DQ ? HT : 1][2][DB];
 #pragma unroll
-    for (int t = 0; t < (DQ ? MT : 1); ++t)
+    for (int t = 0; t < (DQ ? HT : 1); ++t)
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb) dqa[t][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) dqa[t][jb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int c16 = lane & 15, g16 = lane >> 4;
 
-    int tile = gp.x * WV + wave;
+    int tile = gp.x * TW + (PAIR ? wave >> 1 : wave);
+    int round = 0;   // PAIR: token tiles so far
     bf16x8 kt[KS], vt[KS], gt[KS], ktn[KS], vtn[KS], gtn[KS];
     if (tile < tiles) {
         load_cols(kb, tile, kt, true);
@@ -745,19 +769,23 @@ __device__ __forceinline__ void dkdv_body(
 
         // fused dQ: K^T of this token tile as the A operand of the 16x16x32 product (row = dd = lane % 16,
         // tokens 8 (lane / 16) .. + 7), through the wave's LDS tile; rows of tokens past N are zero
-        bf16x8 k_op = zero_operand();
+        bf16x8 k_op[DB];
         if constexpr (DQ) {
-            const u32x4 w = (n < N) ? to_bf16_row<F>(__builtin_bit_cast(u32x4, kt[0])) : __builtin_bit_cast(u32x4, zero_operand());
-            // the tile as loaded, row = token (one 16-byte store per lane); the transposing read hands lane c16 of block
-            // g16 column c16 of the rows 8 g16 .. + 3 (second read: + 4 .. + 7), as for the dS tile below
-            if (!(PACK && hh))     // d <= 8: the upper lane half holds a copy of the same elements
-                *reinterpret_cast<u32x4 *>(k_t + l32 * kKtStride + 8 * hh) = w;
+            // the tile as loaded, row = token (one 16-byte store per lane and k-step); the transposing read hands lane c16 of
+            // block g16 column c16 of the rows 8 g16 .. + 3 (second read: + 4 .. + 7), as for the dS tile below
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const u32x4 w = (n < N) ? to_bf16_row<F>(__builtin_bit_cast(u32x4, kt[s])) : __builtin_bit_cast(u32x4, zero_operand());
+                if (!(PACK && hh))     // d <= 8: the upper lane half holds a copy of the same elements
+                    *reinterpret_cast<u32x4 *>(k_t + l32 * kKtStride + (D / 2) * hh + 8 * s) = w;
+            }
             compiler_fence();
-            const uint16_t *src = k_t + (8 * g16 + c16 / 4) * kKtStride + 4 * (c16 % 4);
-            const u32x2 lo2 = lds_read_tr16(src), hi2 = lds_read_tr16(src + 4 * kKtStride);
-            u32x4 ka;
-            ka[0] = lo2[0]; ka[1] = lo2[1]; ka[2] = hi2[0]; ka[3] = hi2[1];
-            k_op = as_bf16x8(ka);
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const uint16_t *src = k_t + (8 * g16 + c16 / 4) * kKtStride + 16 * db + 4 * (c16 % 4);
+                const u32x2 lo2 = lds_read_tr16(src), hi2 = lds_read_tr16(src + 4 * kKtStride);
+                k_op[db] = as_bf16x8(u32x4{lo2[0], lo2[1], hi2[0], hi2[1]});
+            }
         }
 
         // Score products of latent tile t (minus lse_enc2 / minus lse_dec2): 2*KS + 2 MFMAs.
@@ -802,7 +830,7 @@ __device__ __forceinline__ void dkdv_body(
                 if constexpr (ZLO) cv = mfma(image(t, 4 * KS + ks), gc[ks], cv);
             }
             if constexpr (PIPE) {
-                if (t + 1 < MT) scores(t + 1, s1n, s2n);
+                if (t + 1 < HT) scores(t + 1, s1n, s2n);
             }
             bf16x8 rw[NR];
 #pragma unroll
@@ -835,6 +863,10 @@ __device__ __forceinline__ void dkdv_body(
                 // dS (this lane: token l32, latents 8 (r/4) + 4 hh + r%4 for r = 0..15) -> LDS as it is, row = token:
                 // four 8-byte stores of four latents each.  The product wants it the other way round (column =
                 // latent, 8 consecutive tokens per lane): four transposing reads, each four tokens of one latent.
+                if constexpr (PAIR) {   // the other wave has what was left here at the end of the tile before
+                    if (t == 0) while (taken[wave ^ 1] < round) {}
+                    compiler_fence();
+                }
                 uint16_t *drow = ds_t + l32 * kDsStride + 4 * hh;
                 *reinterpret_cast<u32x2 *>(drow) = u32x2{d0[0], d0[1]};
                 *reinterpret_cast<u32x2 *>(drow + 8) = u32x2{d0[2], d0[3]};
@@ -847,7 +879,9 @@ __device__ __forceinline__ void dkdv_body(
                     const uint16_t *src = ds_t + (8 * g16 + c16 / 4) * kDsStride + 16 * jb + 4 * (c16 % 4);
                     const u32x2 b_lo = lds_read_tr16(src), b_hi = lds_read_tr16(src + 4 * kDsStride);
                     const u32x4 bop = u32x4{b_lo[0], b_lo[1], b_hi[0], b_hi[1]};
-                    dqa[t][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_op, as_bf16x8(bop), dqa[t][jb], 0, 0, 0);
+#pragma unroll
+                    for (int db = 0; db < DB; ++db)
+                        dqa[t][jb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_op[db], as_bf16x8(bop), dqa[t][jb][db], 0, 0, 0);
                 }
                 compiler_fence();
             }
@@ -857,15 +891,15 @@ __device__ __forceinline__ void dkdv_body(
         {
             f32x16 sa1 = splat16(0.f), sa2 = splat16(0.f), sb1 = splat16(0.f), sb2 = splat16(0.f);
             if constexpr (PIPE) scores(0, sa1, sa2);
-            if constexpr (MT == 1) {
+            if constexpr (HT == 1) {
                 tile_step(0, sa1, sa2, sb1, sb2);
             } else if constexpr (DQ) {   // unrolled: the dQ accumulators are indexed by the latent tile
 #pragma unroll
-                for (int t = 0; t + 1 < MT; t += 2) {
+                for (int t = 0; t + 1 < HT; t += 2) {
                     tile_step(t, sa1, sa2, sb1, sb2);
                     tile_step(t + 1, sb1, sb2, sa1, sa2);
                 }
-                if constexpr (MT % 2 != 0) tile_step(MT - 1, sa1, sa2, sb1, sb2);
+                if constexpr (HT % 2 != 0) tile_step(HT - 1, sa1, sa2, sb1, sb2);
             } else {
 #pragma unroll 1
                 for (int t = 0; t + 1 < MT; t += 2) {
@@ -874,6 +908,18 @@ __device__ __forceinline__ void dkdv_body(
                 }
                 if constexpr (MT % 2 != 0) tile_step(MT - 1, sa1, sa2, sb1, sb2);
             }
+        }
+        if constexpr (PAIR) {
+            // [4][64 lanes] float4: the part that the other wave finishes
+            float4 *give = reinterpret_cast<float4 *>(ds_t) + lane;
+            const f32x16 &part = half ? acc1[0] : acc2[0];
+            compiler_fence();
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                give[64 * i] = make_float4(part[4 * i], part[4 * i + 1], part[4 * i + 2], part[4 * i + 3]);
+            ++round;
+            compiler_fence();
+            if (lane == 0) posted[wave] = round;   // (a wave's LDS operations complete in order)
         }
         // What was requested at the top of this tile is taken over here, ahead of the tile's stores: memory
         // operations complete in order, so taking it over after them (at the top of the next tile) would make the
@@ -887,6 +933,20 @@ __device__ __forceinline__ void dkdv_body(
         nld_cur = pinned(-lse_next * ld_mul);
         dl_cur = pinned(delta_next);
         compiler_fence();
+        if constexpr (PAIR) {
+            while (posted[wave ^ 1] < round) {}
+            compiler_fence();
+            const float4 *get = reinterpret_cast<const float4 *>(ds_t + (1 - 2 * half) * fused_wave_lds(D, MT)) + lane;
+            f32x16 &mine = half ? acc2[0] : acc1[0];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 o = get[64 * i];
+                mine[4 * i] += o.x; mine[4 * i + 1] += o.y; mine[4 * i + 2] += o.z; mine[4 * i + 3] += o.w;
+            }
+            compiler_fence();
+            if (lane == 0) taken[wave] = round;
+        }
+        const bool has_dv = !PAIR || half == 0, has_dk = !PAIR || half != 0;
         // registers 4 q .. 4 q + 3 of an accumulator: columns (16 hv +) 8 q + 4 hh .. + 3 of this lane's token
         // More than one latent chunk: all but the first add what the chunks before them left in acc32, and all but
         // the head's last one leave their sums there; the last one rounds and stores them like a single chunk.
@@ -907,25 +967,27 @@ __device__ __forceinline__ void dkdv_body(
                         float *dvr = acc32 + ((size_t)bh * N + n) * DR + o;
                         float *dkr = dvr + (size_t)gridDim.y * N * DR;
                         if (from_acc) {
-                            const float4 pa = *reinterpret_cast<const float4 *>(dvr);
-                            const float4 pb = *reinterpret_cast<const float4 *>(dkr);
-                            a.x += pa.x; a.y += pa.y; a.z += pa.z; a.w += pa.w;
-                            b.x += pb.x; b.y += pb.y; b.z += pb.z; b.w += pb.w;
+                            if (has_dv) add4(a, *reinterpret_cast<const float4 *>(dvr));
+                            if (has_dk) add4(b, *reinterpret_cast<const float4 *>(dkr));
                         }
                         if (to_acc) {
-                            *reinterpret_cast<float4 *>(dvr) = a;
-                            *reinterpret_cast<float4 *>(dkr) = b;
+                            if (has_dv) *reinterpret_cast<float4 *>(dvr) = a;
+                            if (has_dk) *reinterpret_cast<float4 *>(dkr) = b;
                         }
                     }
                     if (!to_acc) {
                         const size_t at = tok_base(ts, bh, H) + tok_off(ts, n) + o;
                         u32x2 w;
-                        w[0] = pack_elems<F>(a.x, a.y);
-                        w[1] = pack_elems<F>(a.z, a.w);
-                        *reinterpret_cast<u32x2 *>(dv + at) = w;
-                        w[0] = pack_elems<F>(b.x, b.y);
-                        w[1] = pack_elems<F>(b.z, b.w);
-                        *reinterpret_cast<u32x2 *>(dk + at) = w;
+                        if (has_dv) {
+                            w[0] = pack_elems<F>(a.x, a.y);
+                            w[1] = pack_elems<F>(a.z, a.w);
+                            *reinterpret_cast<u32x2 *>(dv + at) = w;
+                        }
+                        if (has_dk) {
+                            w[0] = pack_elems<F>(b.x, b.y);
+                            w[1] = pack_elems<F>(b.z, b.w);
+                            *reinterpret_cast<u32x2 *>(dk + at) = w;
+                        }
                     }
                 }
         }
@@ -933,23 +995,27 @@ __device__ __forceinline__ void dkdv_body(
 
     if constexpr (DQ) {
         // The eight waves add their dQ partials in wave order (fixed, so the bits are reproducible) in a
-        // [32*MT][16] fp32 buffer that reuses the image memory, then the workgroup stores its slot.
+        // [32*MT][D] fp32 buffer that reuses the image memory, then the workgroup stores its slot.
         float *red = reinterpret_cast<float *>(img);
-        for (int w = 0; w < 8; ++w) {
+        constexpr int STEP = PAIR ? 2 : 1;   // (the two halves of the latents side by side)
+        for (int w = 0; w < 8; w += STEP) {
             __syncthreads();   // first pass: every wave is done with the images
-            if (wave == w) {
+            if (wave / STEP == w / STEP) {
 #pragma unroll
-                for (int t = 0; t < MT; ++t)
+                for (int t = 0; t < HT; ++t)
 #pragma unroll
-                    for (int jb = 0; jb < 2; ++jb) {
-                        float4 *cell = reinterpret_cast<float4 *>(red + (32 * t + 16 * jb + c16) * 16 + 4 * g16);
-                        float4 x = make_float4(dqa[t][jb][0], dqa[t][jb][1], dqa[t][jb][2], dqa[t][jb][3]);
-                        if (w > 0) {
-                            const float4 o = *cell;
-                            x.x += o.x; x.y += o.y; x.z += o.z; x.w += o.w;
+                    for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+                        for (int db = 0; db < DB; ++db) {
+                            float4 *cell = reinterpret_cast<float4 *>(red + (32 * (half * HT + t) + 16 * jb + c16) * D + 16 * db + 4 * g16);
+                            const f32x4 &q4 = dqa[t][jb][db];
+                            float4 x = make_float4(q4[0], q4[1], q4[2], q4[3]);
+                            if (w > 0) {
+                                const float4 o = *cell;
+                                x.x += o.x; x.y += o.y; x.z += o.z; x.w += o.w;
+                            }
+                            *cell = x;
                         }
-                        *cell = x;
-                    }
             }
         }
         __syncthreads();
@@ -960,7 +1026,7 @@ __device__ __forceinline__ void dkdv_body(
             const int lat = i / PCS, pc = i % PCS;
             if (lat < mleft)
                 *reinterpret_cast<float4 *>(out + (size_t)lat * DR + 4 * pc) =
-                    *reinterpret_cast<const float4 *>(red + (size_t)lat * 16 + 4 * pc);
+                    *reinterpret_cast<const float4 *>(red + (size_t)lat * D + 4 * pc);
         }
     }
 }
@@ -974,18 +1040,8 @@ __device__ __forceinline__ void dkdv_body(
 #define FLARE_DKDV_PASS \
     q, k, v, dy, z, lse_enc, dz_bh, eps_bh, lse_dec2, delta, ld_mul, dk, dv, acc32, dq_part, ts, H, N, Mtot, m0, mend, c2, scale
 
-// One variant per launch (the workgroups of a (b,h) that the plan gives to the other variant leave at once) ...
-template <int DR, int MT, bool DQ, bool ONE, bool F, int WV = 8>
-__global__ __launch_bounds__(64 * WV, 1) void bwd_dkdv_mfma_kernel(FLARE_DKDV_PARAMS)
-{
-    const int bh = grid_pos_latents(ts, H, DR * 2).y;
-    if ((merge.plan[bh] != 0) != ONE) return;   // the other variant owns this (b,h); uniform over the workgroup
-    const float *dz_bh = merge.dz + (size_t)bh * Mtot * DR, *eps_bh = merge.eps + (size_t)bh * Mtot;
-    dkdv_body<DR, MT, DQ, ONE, F, WV>(FLARE_DKDV_PASS);
-}
-
-// ... or both in one launch, each workgroup taking the variant that the plan names for its (b,h): one launch less per
-// step (a launch whose workgroups all leave at once still costs 4-6 us).  Both bodies share the kernel's registers,
+// Both variants in one launch, each workgroup taking the one that the plan names for its (b,h): one launch less per step
+//  (a launch whose workgroups all leave at once still costs 4-6 us).  Both bodies share the kernel's registers,
 // which at one workgroup per CU costs nothing.
 template <int DR, int MT, bool DQ, bool F, bool ZL = false>
 __global__ __launch_bounds__(512, 1) void bwd_dkdv_planned_kernel(FLARE_DKDV_PARAMS)
@@ -997,9 +1053,9 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_planned_kernel(FLARE_DKDV_PAR
     const float *dz_bh, *eps_bh;
     // (a dQ kernel of its own runs behind this one and reads what workgroup 0 writes)
     if (merged_dz<DR>(merge, z, lse_enc, gp.y, Mtot, true, !DQ && gp.x == 0, rows, red, dz_bh, eps_bh))
-        dkdv_body<DR, MT, DQ, true, F, 8, ZL>(FLARE_DKDV_PASS);
+        dkdv_body<DR, MT, DQ, true, F, ZL>(FLARE_DKDV_PASS);
     else
-        dkdv_body<DR, MT, DQ, false, F, 8, ZL>(FLARE_DKDV_PASS);
+        dkdv_body<DR, MT, DQ, false, F, ZL>(FLARE_DKDV_PASS);
 }
 #undef FLARE_DKDV_PASS
 #undef FLARE_DKDV_PARAMS
@@ -1055,19 +1111,19 @@ int mfma_dkdv_blocks(const flare_shape &s)
 {
     const int BH = s.B * s.H;
     const int tiles = (s.N + 31) / 32;
+    const int MT = lat_eff(s.M) / 32, waves = (mfma_dq_fused(s) && dkdv_pair(padded_dim(s.d), MT)) ? 4 : 8;   // token tiles at a time
     int most = BH <= 256 ? (256 + BH - 1) / BH : 4;   // one 8-wave workgroup per CU
-    if (most > (tiles + 7) / 8) most = (tiles + 7) / 8;
-    return round_blocks(BH, 1, tiles, 8, 1 + 8 / (lat_eff(s.M) / 32), most);   // (setup: the operand images)
+    if (most > (tiles + waves - 1) / waves) most = (tiles + waves - 1) / waves;
+    return round_blocks(BH, 1, tiles, waves, 1 + 8 / MT, most);   // (setup: the operand images)
 }
 
-// The dK/dV kernel can form the dQ partials as well (one pass over the scores for all three gradients);
-// written for and used at d <= 16 (at d = 32 the dQ accumulators alone would take 128 registers).  At d <= 8
+// The dK/dV kernel also forms the dQ partials (one pass over the scores for all three gradients).  At d <= 8
 // it carries the lo term of Z in the upper half of its Z image (ZPACK in the kernel), like the token-statistics
 // kernel that forms the delta it subtracts.  flare_shape.variant with FLARE_VARIANT_SEPARATE_DQ keeps the separate dQ
 // kernel (tests, measurements).
 bool mfma_dq_fused(const flare_shape &s)
 {
-    if (!mfma_supported(s) || s.d == 32) return false;
+    if (!mfma_supported(s)) return false;
     return (s.variant & FLARE_VARIANT_SEPARATE_DQ) == 0;
 }
 
@@ -1091,9 +1147,10 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
     // dQ from this kernel at d = 16 with fewer tokens than latents: one more image, the lo term of Z (see the kernel)
     const bool zlo = fuse && s.d == 16 && s.N < s.M;
     // The forms that only few-token shapes and measurements take, and d = 4, exist for 1, 2, 4 and 8 tiles.
-    if (zlo || s.d == 4 || (!fuse && s.d <= 16)) MT = MT <= 2 ? MT : MT <= 4 ? 4 : 8;
+    if (zlo || s.d == 4 || !fuse) MT = MT <= 2 ? MT : MT <= 4 ? 4 : 8;
+    if (fuse && dkdv_pair(s.d, MT)) MT += MT % 2;   // halved between two waves
     const int na = (zlo ? 5 : 4) * KS + 1;
-    size_t lds = (size_t)MT * (na + 4 * HV) * 1024 + (fuse ? 8 * kFusedWaveLds * 2 : 0);
+    size_t lds = (size_t)MT * (na + 4 * HV) * 1024 + (fuse ? 8 * fused_wave_lds(pd, MT) * 2 : 0);
     MergeDz merge = merge_in;
     merge.lds = (unsigned)lds;
     if (merge.parts) lds += (size_t)s.M * (s.d + 1) * 4;
@@ -1106,20 +1163,6 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
                                              (bf16_t *)dk, (bf16_t *)dv, acc32, dq_part, tok_stride(s), s.H,     \
                                              s.N, s.M, m0, mend, c2, scale, merge);                                    \
     } while (0)
-    if (s.d == 32 && MT == 8) {
-        // d = 32, 256 latents: the one-exponential variant fits 168 registers, so twelve waves (three per SIMD) share
-        // its images; the two-exponential variant keeps eight.  One launch each.
-        {
-            LaunchTimer t(KID_BWD_DKDV, stream);
-            if (f16) FLARE_DKDV_LAUNCH((bwd_dkdv_mfma_kernel<32, 8, false, true, true, 12>), 768);
-            else FLARE_DKDV_LAUNCH((bwd_dkdv_mfma_kernel<32, 8, false, true, false, 12>), 768);
-        }
-        if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
-        LaunchTimer t(KID_BWD_DKDV_2EXP, stream);
-        if (f16) FLARE_DKDV_LAUNCH((bwd_dkdv_mfma_kernel<32, 8, false, false, true, 8>), 512);
-        else FLARE_DKDV_LAUNCH((bwd_dkdv_mfma_kernel<32, 8, false, false, false, 8>), 512);
-        return check_launch();
-    }
     LaunchTimer t(KID_BWD_DKDV, stream);
 #define FLARE_DKDV(DD, MTT, LO)                                                                 \
     do {                                                                                        \
@@ -1168,17 +1211,18 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
         FLARE_DKDV_POW2(8, false)
     } else if (s.d == 16) {
         FLARE_DKDV_POW2(16, false)
-    } else {
-        switch (MT) {   // d = 32 (with 256 latents: above)
-            case 1: FLARE_DKDV(32, 1, false); break;
-            case 2: FLARE_DKDV(32, 2, false); break;
-            case 3: FLARE_DKDV(32, 3, false); break;
-            case 4: FLARE_DKDV(32, 4, false); break;
-            case 5: FLARE_DKDV(32, 5, false); break;
-            case 6: FLARE_DKDV(32, 6, false); break;
-            case 7: FLARE_DKDV(32, 7, false); break;
+    } else if (fuse) {   // d = 32
+        switch (MT) {
+            case 1: FLARE_DKDV(32, 1, true); break;
+            case 2: FLARE_DKDV(32, 2, true); break;
+            case 3: FLARE_DKDV(32, 3, true); break;
+            case 4: FLARE_DKDV(32, 4, true); break;
+            case 6: FLARE_DKDV(32, 6, true); break;
+            case 8: FLARE_DKDV(32, 8, true); break;
             default: return FLARE_EUNSUPPORTED;
         }
+    } else {
+        FLARE_DKDV_POW2(32, false)
     }
 #undef FLARE_DKDV_MT
 #undef FLARE_DKDV_POW2
@@ -1194,10 +1238,10 @@ size_t mfma_dkdv_acc_bytes(const flare_shape &s)
 }
 
 // With few dZ slots the dK/dV kernel merges them.  Not with more than 256 latents, whose chunks are launches of
-// their own, nor at d = 32 with 256, where dK/dV is one launch per variant.
+// their own, nor at d = 32 where the merged rows of more than 192 latents do not fit beside their images in LDS.
 bool mfma_dz_inline(const flare_shape &s)
 {
-    return s.M <= kLatChunk && !(s.d == 32 && lat_eff(s.M) == 256) && merge_inline(s, mfma_plan(s).parts);
+    return s.M <= kLatChunk && !(s.d == 32 && s.M > 192) && merge_inline(s, mfma_plan(s).parts);
 }
 
 // partial slots per (b,h) that mfma_dq_partial writes

@@ -68,6 +68,23 @@ def test_heads_that_do_not_divide_the_chip(oracle, dtype, B, H, N, M, d):
     _check(oracle, dtype, H, N, M, d, "bnhd" if M % 2 else "bhnd", saved=True, B=B)
 
 
+# d = 32: dQ out of the dK/dV kernel, with all latents in a wave (up to four tiles) or halved between two (three and four
+# tiles each, the last ones padding), in chunks of latents; token tiles that leave the last pairs of waves idle or ragged
+@pytest.mark.parametrize("M,N,B,layout", [(32, 700, 1, "bhnd"), (128, 1000, 2, "bnhd"), (129, 40, 1, "bhnd"),
+                                          (190, 33, 3, "bnhd"), (224, 2049, 1, "bnhd"), (256, 130, 2, "bhnd"),
+                                          (256, 4100, 1, "bhnd"), (330, 1000, 1, "bnhd")])
+def test_fused_dq_of_wide_heads(oracle, M, N, B, layout):
+    """Against the oracle and against the dQ kernel of its own."""
+    _check(oracle, "f16" if M == 190 else "bf16", 2, N, M, 32, layout, saved=M != 128, B=B)
+    inp = synth.make_inputs(1, B=B, H=2, N=N, M=M, d=32, dtype="bf16", with_dy=True, seed=3 + N + M)
+    dev = to_device(inp)
+    y, z, lse = binding.forward(dev["q"], dev["k"], dev["v"], inp["scale"])
+    one, two = (binding.backward(dev["q"], dev["k"], dev["v"], dev["dy"], z, lse, inp["scale"], variant=x)
+                for x in (0, binding.VARIANT_SEPARATE_DQ))
+    for a, b in zip(one, two):
+        assert slice_relerr(to_host(a), to_host(b)) <= tol_for(inp)
+
+
 @pytest.mark.parametrize("M", [70, 150, 200])
 def test_projection_of_ragged_latents(M):
     """The fused projection forms the y that the decode forms, bit for bit, whatever the number of tiles."""

@@ -438,8 +438,7 @@ def test_backward_two_exponential_kernels(oracle, cfg, over):
 @pytest.mark.parametrize("cfg,over", [(4, dict(N=3001)), (2, dict(B=1, N=1500, d=8)), (2, dict(B=1, N=1500, d=4)),
                                       (4, dict(N=900, M=100, dtype="f16"))])
 def test_backward_separate_dq_kernel(oracle, cfg, over):
-    """At d <= 16 the dK/dV kernel also forms dQ; FLARE_VARIANT_SEPARATE_DQ runs the separate dQ kernel
-    (the one d = 32 uses) on the same shapes.  Both must meet the bar and agree closely."""
+    """The dK/dV kernel also forms dQ; FLARE_VARIANT_SEPARATE_DQ runs the separate dQ kernel on the same shapes.  Both must meet the bar and agree closely."""
     _say("backward with the separate dQ kernel, cfg%d %s" % (cfg, over))
     inp = synth.make_inputs(cfg, with_dy=True, **over)
     tol = TOL["bf16"]
@@ -455,7 +454,7 @@ def test_backward_wide_score_range_picks_variant_per_head(oracle, M, d):
     """Head 0 has ordinary scores; head 1 has per-latent score offsets hundreds of log2 units apart,
     where one exponential per score would underflow: the library must take the two-exponential
     kernels for that head alone and stay within tolerance on both.  (d = 16: dQ, dK and dV from one kernel that
-    holds both variants; d = 32: a dQ kernel of that kind and, at 256 latents, one dK/dV launch per variant.)"""
+    holds both variants; d = 32: the same, with 256 latents halved between two waves.)"""
     _say("backward wide score range, mixed heads, M = %d, d = %d" % (M, d))
     inp = synth.make_inputs(2, B=1, H=2, N=1500, M=M, d=d, with_dy=True)
     q, k = inp["q"].copy(), inp["k"].copy()

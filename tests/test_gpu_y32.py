@@ -17,7 +17,7 @@ CASES = [
     (4, dict(N=2500, d=8), "bhnd"),                  # the head dimensions that otherwise recompute
     (4, dict(N=2500, d=4, M=100), "bnhd"),
     (2, dict(B=2, N=1500, d=8), "bnhd"),
-    (5, dict(N=2048), "bhnd"),                       # d = 32: separate dQ kernel
+    (5, dict(N=2048), "bhnd"),                       # d = 32
     (3, dict(B=2, N=700, dtype="f16"), "bhnd"),
     (2, dict(B=1, N=20, M=7, d=8), "bhnd"),          # a single token tile, few latents
     (2, dict(B=2, H=3, N=365, M=200, d=4, seed=777 + 1375), "bhnd"),   # a latent that dominates many tokens
