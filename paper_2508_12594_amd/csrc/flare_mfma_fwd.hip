@@ -1133,10 +1133,17 @@ MfmaPlan mfma_plan(const flare_shape &s)
     MfmaPlan p;
     const EncGeom e = enc_geom(s.M, padded_dim(s.d));
     const int BH = s.B * s.H;
-    // each chunk gives every token group at least 8 tiles of 32 tokens
+    // Each chunk gives every token group at least 8 tiles of 32 tokens.  Consumers that merge the slots read four at a time, so
+    // a count is made up to the next multiple of four as far as chunks of 2 tiles per group go (8 heads, 1024 tokens, 64
+    // latents: one chunk a head 11.1 us, four 10.1; past the multiple of four what the encode gains the merge takes: 4 heads,
+    // 8192 tokens, 100 latents 18.6 us with 8, 18.7 with 11).
     const int min_len = 256 * e.TG, tiles = (s.N + 31) / 32;
-    int most = (kEncodeTargetBlocks + BH - 1) / BH;
-    if (most > (s.N + min_len - 1) / min_len) most = (s.N + min_len - 1) / min_len;
+    int most = (s.N + min_len - 1) / min_len;
+    for (int finer = (most + 3) / 4 * 4; finer > most; --finer)
+        if (s.N >= finer * (min_len / 4) && s.M <= kLatChunk && merge_inline(s, finer) &&
+            (size_t)BH * finer * s.M * (s.d + 2) * 4 <= FLARE_STATIC_SCRATCH_BYTES / 2)   // (what fits there still does)
+            most = finer;
+    if (most > (kEncodeTargetBlocks + BH - 1) / BH) most = (kEncodeTargetBlocks + BH - 1) / BH;
     const int want = round_blocks(BH, kEncodeTargetBlocks / 256, tiles, e.TG, 1, most);
     // (chunks in whole tiles: only the last one ends within a tile)
     p.enc.chunk_len = (tiles + want - 1) / want * 32;

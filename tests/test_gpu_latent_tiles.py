@@ -15,8 +15,9 @@ pytestmark = pytest.mark.gpu
 # 3, 4 (ragged), 5, 6, 7, 8 tiles; two chunks of 5 and 7; three of 6; d = 16 with fewer tokens than latents
 TILES = [(M, d, 700) for M in (65, 96, 97, 130, 161, 192, 200, 225) for d in (8, 16, 32)]
 TILES += [(M, d, 1100) for M in (257, 300, 420, 545) for d in (4, 8, 16, 32)] + [(300, 16, 90), (161, 16, 100)]
-# H = 1: 1024 tokens per chunk at d = 16, so 16 and 17 slots; fp32: a chunk per 128 tokens
+# H = 1: 1024 tokens per chunk at d = 16, so 16 and 17 slots; short ones with the slots made up to four and eight; fp32: a chunk per 128 tokens
 SLOTS = [("bf16", 16 * 1024, 64, 16), ("f16", 16 * 1024 + 1, 64, 16), ("bf16", 16 * 1024 + 1, 64, 8),
+         ("bf16", 511, 64, 16), ("bf16", 512, 64, 16), ("f16", 1025, 60, 16), ("bf16", 5000, 33, 8), ("bf16", 140, 256, 32),
          ("bf16", 8 * 1024 + 1, 96, 32), ("f32", 2048, 48, 16), ("f32", 2049, 48, 16), ("f32", 1900, 40, 32)]
 
 # fp32: remainders of a tile, the last number of latents whose planes fit in LDS together and the first that runs in
