@@ -132,8 +132,9 @@ int flare_encode(const flare_shape *shape, const void *q_lat, const void *k, con
 
 /*
  * Decode (Eq. flare_decode; Appendix F, per-token form of y_n): per-token softmax over the M
- * latents applied to Z.  Only matrix-core shapes with M > 256 use the workspace (per-chunk partial
- * results, merged in chunk order); for all others it may be NULL.
+ * latents applied to Z.  Only matrix-core shapes with M > 256 use the workspace (an fp32 row per token
+ * that the chunks of latents add to in order; d = 32: per-chunk partial results, merged in chunk order);
+ * for all others it may be NULL.
  *   q_lat [H][M][d] dtype, k [B][H][N][d] dtype, z [B][H][M][d] fp32        (in)
  *   y [B][H][N][d] dtype                                                    (out)
  *   lse_dec [B][H][N] fp32: log sum_m exp(S[m][n]), natural log; may be NULL (out, optional)
@@ -180,7 +181,7 @@ int flare_forward_project(const flare_shape *shape, const void *q_lat, const voi
  * flare_forward for callers that cannot allocate and have no workspace to pass: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and kernels as
  * flare_forward, but the scratch (the encode's per-wave partial sums; with M > 256 also the decode's
- * per-chunk rows) lives in an array of FLARE_STATIC_SCRATCH_BYTES that the library's code object holds in
+ * rows) lives in an array of FLARE_STATIC_SCRATCH_BYTES that the library's code object holds in
  * device memory, once per GPU the library runs on, until the process ends.  The call allocates and frees
  * nothing and calls no allocating routine; on its first call on a device it looks the array's address up
  * (hipGetSymbolAddress) and keeps it, so make that first call outside a capture.  A shape whose

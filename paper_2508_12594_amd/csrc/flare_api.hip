@@ -128,7 +128,7 @@ int flare_workspace_bytes(const flare_shape *shape, size_t *fwd_bytes, size_t *b
         *fwd_bytes = p.fwd_bytes;
         if (mfma_supported(*shape)) {   // the encode's partials are dead when the decode starts: one region
             *fwd_bytes = mfma_fwd_bytes(*shape);
-            if (mfma_tok_part_bytes(*shape) > *fwd_bytes) *fwd_bytes = mfma_tok_part_bytes(*shape);
+            if (mfma_tok_run_bytes(*shape) > *fwd_bytes) *fwd_bytes = mfma_tok_run_bytes(*shape);
         }
     }
     if (bwd_bytes) *bwd_bytes = p.bwd_bytes;
@@ -170,7 +170,7 @@ int flare_decode(const flare_shape *shape, const void *q_lat, const void *k, con
         !aligned16(workspace))
         return FLARE_EALIGN;
     if (mfma_supported(*shape)) {
-        const size_t need = mfma_tok_part_bytes(*shape);
+        const size_t need = mfma_tok_run_bytes(*shape);
         if (need != 0 && (!workspace || workspace_bytes < need)) return FLARE_EWORKSPACE;
         return mfma_decode(*shape, q_lat, k, z, y, lse_dec, scale, workspace, static_cast<hipStream_t>(stream));
     }

@@ -121,10 +121,11 @@ int mfma_forward(const flare_shape &s, const void *q, const void *k, const void 
 // The encode's partial slots only; *g says where they are, for a consumer to merge.
 int mfma_encode_partial(const flare_shape &s, const void *q, const void *k, const void *v, float *z, float *lse_enc,
                         float scale, void *ws, MergeZ *g, hipStream_t stream);
-// Shapes with M > 256 run the token-major kernels once per chunk of at most 256 latents.  The decode and the
-// token statistics then need mfma_tok_part_bytes(s) of scratch (`ws`; unused and may be NULL
+// Shapes with M > 256 run the token-major kernels once per chunk of at most 256 latents.  The decode then needs
+// mfma_tok_run_bytes(s) of scratch, the token statistics mfma_tok_stats_bytes(s) (`ws`; unused and may be NULL
 // otherwise), the dK/dV step mfma_dkdv_acc_bytes(s) for its fp32 sums.
-size_t mfma_tok_part_bytes(const flare_shape &s);
+size_t mfma_tok_run_bytes(const flare_shape &s);
+size_t mfma_tok_stats_bytes(const flare_shape &s);
 size_t mfma_dkdv_acc_bytes(const flare_shape &s);
 int mfma_lat_step(const flare_shape &s);   // latents per chunk
 int mfma_decode(const flare_shape &s, const void *q, const void *k, const float *z, void *y,

@@ -26,18 +26,26 @@ namespace {
 // MODE 0 writes y and, when lse_dec2 is not NULL, log sum_m exp(S[m][n]) (natural log) there.
 // MODE 1 (first step of the backward when nothing was saved) writes per token
 //   lse_dec2[n] = log2 sum_m 2^S2[m][n]   and   delta[n] = <dY_n, Y_n>   (Y_n kept in fp32).
+// MODE 2 (d <= 16) is MODE 0 over one chunk of more than 256 latents: the chunks run one after the other, and what those
+// so far amount to is one fp32 row a token (run [b*h][n][DR], normalised) and its log2-sum (delta [b*h][n]).  Each chunk
+// adds itself to the row, the last one writes y.  The row is requested at the top of the tile, a sweep before its use: the
+// launch is bound by instruction issue, so its bytes cost less than a merge of one row per chunk at the end, which
+// HBM bounds.  (10^6 tokens, 8 heads, 2048 latents, d = 8, y in fp32: the 512 us of the merge go, the launches take 165 us
+// more, training 12655 -> 12306 us; 4 x 16 heads, 122070 tokens, 1024 latents, d = 16: decode 1157 + merge 254 -> 1318 us.
+// At d = 32 the rows are as long as four of 16 bits and find no registers: 2 x 16 heads, 64102 tokens, 1950 latents
+// 944 + 260 -> 1340 us, so MODE 0 and the merge stay there.)
 template <int DR, int MT, bool PRE, int MINB, int MODE, bool F, bool MERGE>
 __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
     const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const float *__restrict__ z,
     bf16_t *__restrict__ y, const bf16_t *__restrict__ dy, float *__restrict__ lse_dec2,
-    float *__restrict__ delta, TokStride ts, TokStride ts_y, int H, int N, int Mtot, int m0, float c2, int flags,
+    float *__restrict__ delta, float *__restrict__ run, TokStride ts, TokStride ts_y, int H, int N, int Mtot, int m0, float c2, int flags,
     MergeZ merge)
 {
     // flags: bit 0 (d <= 8): Z enters the value product as a hi + lo pair (see the Zaug operand below);
-    // bit 1 (MODE 0): y is an fp32 tensor of the same layout (flare_shape.y_f32)
+    // bit 1 (MODE 0, 2): y is an fp32 tensor of the same layout (flare_shape.y_f32); bits 2, 3 (MODE 2): first, last chunk
     const bool z_lo = (flags & 1) != 0, y32 = (flags & 2) != 0;
-    // The kernel works on the latents m0 .. m0 + M of the head's Mtot (M = 32*MT of them); with more than
-    // one chunk its outputs are one chunk's partial result (y normalised within the chunk, lse_dec of the
+    // The kernel works on the latents m0 .. m0 + M of the head's Mtot (M = 32*MT of them); in MODE 0 with more than
+    // one chunk (d = 32) its outputs are one chunk's partial result (y normalised within the chunk, lse_dec of the
     // chunk) that decode_merge_kernel combines.  ts_y: where the rows of y go.
     // Latents at or beyond Mtot are padding and cost no mask code in the loops: a padding latent gets the
     // queries of the last real one (the clamped load), so its score never exceeds the real maximum and
@@ -184,6 +192,24 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
             }
         };
         if constexpr (MODE == 1 && EARLY_G) request_g();
+        // MODE 2: what the chunks before this one left of the same quartets, requested as early
+        float4 rq[MODE == 2 ? HV : 1][2];
+        float run_lse = 0.f;
+        auto request_run = [&]() {
+            const size_t row = (size_t)bh * N + min(n, N - 1);
+#pragma unroll
+            for (int hv = 0; hv < HV; ++hv)
+#pragma unroll
+                for (int up = 0; up < 2; ++up) {
+                    rq[hv][up] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (quartet_inside<DR>(hv, hh, up))
+                        rq[hv][up] = *reinterpret_cast<const float4 *>(run + row * DR + 16 * hv + 8 * up + 4 * hh);
+                }
+            run_lse = delta[row];
+        };
+        if constexpr (MODE == 2) {
+            if ((flags & 4) == 0) request_run();
+        }
         // An opaque copy of the keys for the hi products, so that the compiler keeps them apart from the lo ones.
         bf16x8 kt2[KS];
 #pragma unroll
@@ -347,7 +373,7 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
         s_cur0 = first_scores(s_ahead, mx_next, ktn);
         // row 16 (register 8 of the lower lane half) is the softmax denominator
         const float den = __shfl(acc[0][8], l32);
-        const float inv = 1.f / den;
+        float inv = 1.f / den;
         if constexpr (MODE == 1) {
             const size_t row = (size_t)bh * N + min(n, N - 1);
             if constexpr (!EARLY_G) request_g();
@@ -376,15 +402,49 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
                 delta[row] = part;
             }
         } else if (n < N) {
-            if (lse_dec2 && hh == 0) {   // optional saved statistic of the forward, natural log
-                const float used = PRE ? mx : b2;
-                lse_dec2[(size_t)bh * N + n] = (used + log2f(den)) * kLn2;
-            }
             if constexpr (DR <= 8) {   // rows 8 + j: the lo part of column j (zero unless z_lo), same lane
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[0][i] += acc[0][4 + i];
             }
-            if (y32) {
+            float used = PRE ? mx : b2;
+            if constexpr (MODE == 2) {
+                const size_t row = (size_t)bh * N + n;
+                used += log2f(den);
+                if ((flags & 4) == 0) {
+                    const float top = fmaxf(used, run_lse);
+                    const float mine = fast_exp2(used - top), before = fast_exp2(run_lse - top);
+                    const float all = mine + before, w = before / all;
+                    inv *= mine / all;
+                    used = top + log2f(all);
+#pragma unroll
+                    for (int hv = 0; hv < HV; ++hv)
+#pragma unroll
+                        for (int up = 0; up < 2; ++up) {
+                            const float4 o = rq[hv][up];
+                            acc[hv][4 * up] = fmaf(acc[hv][4 * up], inv, o.x * w);
+                            acc[hv][4 * up + 1] = fmaf(acc[hv][4 * up + 1], inv, o.y * w);
+                            acc[hv][4 * up + 2] = fmaf(acc[hv][4 * up + 2], inv, o.z * w);
+                            acc[hv][4 * up + 3] = fmaf(acc[hv][4 * up + 3], inv, o.w * w);
+                        }
+                    inv = 1.f;
+                }
+                if ((flags & 8) == 0) {
+                    if (hh == 0) delta[row] = used;
+#pragma unroll
+                    for (int hv = 0; hv < HV; ++hv)
+#pragma unroll
+                        for (int up = 0; up < 2; ++up)
+                            if (quartet_inside<DR>(hv, hh, up))
+                                *reinterpret_cast<float4 *>(run + row * DR + 16 * hv + 8 * up + 4 * hh) =
+                                    make_float4(acc[hv][4 * up] * inv, acc[hv][4 * up + 1] * inv, acc[hv][4 * up + 2] * inv,
+                                                acc[hv][4 * up + 3] * inv);
+                }
+            }
+            const bool out = MODE == 0 || (flags & 8) != 0;
+            if (out && lse_dec2 && hh == 0)    // optional saved statistic of the forward, natural log
+                lse_dec2[(size_t)bh * N + n] = (MODE == 2 ? used : used + log2f(den)) * kLn2;
+            if (!out) {
+            } else if (y32) {
                 float *yf = reinterpret_cast<float *>(y) + tok_base(ts_y, bh, H) + tok_off(ts_y, n);
 #pragma unroll
                 for (int hv = 0; hv < HV; ++hv)
@@ -1281,7 +1341,7 @@ int mfma_dz_partial(const flare_shape &s, const void *q, const void *k, const vo
 
 template <int MODE>
 static int launch_decode_family(const flare_shape &s, const void *q, const void *k, const float *z, void *y,
-                                TokStride ts_y, const void *dy, float *lse_dec2, float *delta, int m0, int Mc,
+                                TokStride ts_y, const void *dy, float *lse_dec2, float *delta, float *run, int m0, int Mc,
                                 float scale, const MergeZ &merge, hipStream_t stream, int flags = 0)
 {
     const size_t lds = merge.parts ? (size_t)s.M * s.d * 4 : 0;
@@ -1296,18 +1356,20 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
     const float c2 = scale * kLog2e;
     const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *gg = (const bf16_t *)dy;
     bf16_t *yy = (bf16_t *)y;
-    LaunchTimer t(MODE == 0 ? KID_DECODE : KID_BWD_TOKEN_STATS, stream);
+    LaunchTimer t(MODE == 1 ? KID_BWD_TOKEN_STATS : KID_DECODE, stream);
     const bool f16 = s.dtype == FLARE_F16;
-#define FLARE_DEC_ARGS qq, kk, z, yy, gg, lse_dec2, delta, tok_stride(s), ts_y, s.H, s.N, s.M, m0, c2, flags, merge
+#define FLARE_DEC_ARGS qq, kk, z, yy, gg, lse_dec2, delta, run, tok_stride(s), ts_y, s.H, s.N, s.M, m0, c2, flags, merge
 #define FLARE_DEC_F(DD, MTT, PREE, MINB, FF)                                                                       \
     do {                                                                                                           \
+        if constexpr (MODE == 2 && (MTT < 5 || DD > 16)) return FLARE_EUNSUPPORTED;   /* (see decode_all) */       \
         if constexpr (MODE == 0) {                                                                                 \
             if (merge.parts) {                                                                                     \
                 decode_mfma_kernel<DD, MTT, PREE, MINB, 0, FF, true><<<grid, 256, lds, stream>>>(FLARE_DEC_ARGS);  \
                 break;                                                                                             \
             }                                                                                                      \
         }                                                                                                          \
-        decode_mfma_kernel<DD, MTT, PREE, MINB, MODE, FF, false><<<grid, 256, 0, stream>>>(FLARE_DEC_ARGS);        \
+        if constexpr (MODE != 2 || (MTT >= 5 && DD <= 16))                                                         \
+            decode_mfma_kernel<DD, MTT, PREE, MINB, MODE, FF, false><<<grid, 256, 0, stream>>>(FLARE_DEC_ARGS);    \
     } while (0)
 #define FLARE_DEC(DD, MTT, PREE, MINB)                                                                          \
     do {                                                                                                        \
@@ -1356,7 +1418,7 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
 }
 
 namespace {
-// Combine the per-chunk results of the decode (M > 256): for token n of (b,h),
+// Combine the per-chunk results of the decode (M > 256, d = 32): for token n of (b,h),
 //   lse = log sum_c exp(lse_c),   y = sum_c exp(lse_c - lse) y_c        (softmax over all M latents).
 // Writes y in the caller's layout and, when asked, lse_dec (natural log).
 // thread = token; the partial rows are [chunk][b*h][n][DR] in the storage type, the partial lse [chunk][b*h][n].
@@ -1461,12 +1523,25 @@ __global__ __launch_bounds__(256) void stats_merge_kernel(const float *__restric
 }
 }  // namespace
 
-// bytes of the per-chunk partial results of the token-major forward kernels (0 when M <= 256)
-size_t mfma_tok_part_bytes(const flare_shape &s)
+static size_t up256(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+
+// More than 256 latents: does the decode add its chunks to one fp32 row per token, or keep a row per chunk and merge?
+// (see the kernel)
+static bool decode_running(const flare_shape &s) { return s.d <= 16; }
+
+// bytes of the decode's running rows, or of its rows per chunk, and their log-sums (0 when M <= 256)
+size_t mfma_tok_run_bytes(const flare_shape &s)
 {
     if (s.M <= kLatChunk) return 0;
-    const size_t rows = (size_t)s.B * s.H * s.N * lat_chunks(s.M);
-    return ((rows * s.d * (s.y_f32 ? 4 : 2) + 255) & ~(size_t)255) + ((rows * 4 + 255) & ~(size_t)255);
+    const size_t rows = (size_t)s.B * s.H * s.N * (decode_running(s) ? 1 : lat_chunks(s.M));
+    return up256(rows * s.d * (decode_running(s) || s.y_f32 ? 4 : 2)) + up256(rows * 4);
+}
+
+// bytes of the token statistics' two floats per chunk and token (0 when M <= 256)
+size_t mfma_tok_stats_bytes(const flare_shape &s)
+{
+    if (s.M <= kLatChunk) return 0;
+    return 2 * up256((size_t)s.B * s.H * s.N * lat_chunks(s.M) * 4);
 }
 
 // decode (MODE 0) or token statistics (MODE 1) over all latents, in chunks of at most 256 when there are more
@@ -1476,63 +1551,54 @@ static int decode_all(const flare_shape &s, const void *q, const void *k, const 
                       int flags = 0)
 {
     if (s.M <= kLatChunk)
-        return launch_decode_family<MODE>(s, q, k, z, y, tok_stride(s), dy, lse_out, delta, 0, lat_eff(s.M), scale,
+        return launch_decode_family<MODE>(s, q, k, z, y, tok_stride(s), dy, lse_out, delta, nullptr, 0, lat_eff(s.M), scale,
                                           merge, stream, flags);
     const int C = lat_chunks(s.M), Mc = lat_eff(s.M);
     const size_t rows = (size_t)s.B * s.H * s.N;
-    const size_t es = s.y_f32 ? 4 : 2;          // bytes per element of the partial rows
-    float *lse_part = reinterpret_cast<float *>(static_cast<char *>(ws) + ((rows * C * s.d * es + 255) & ~(size_t)255));
     if constexpr (MODE == 1) {
-        // per-chunk statistics in fp32 (delta_c in the space of the partial rows, which this mode does not need)
         float *delta_part = static_cast<float *>(ws);
+        float *lse_part = reinterpret_cast<float *>(static_cast<char *>(ws) + up256(rows * C * 4));
         for (int c = 0; c < C; ++c) {
             const int rc = launch_decode_family<1>(s, q, k, z, nullptr, tok_stride(s), dy, lse_part + (size_t)c * rows,
-                                                   delta_part + (size_t)c * rows, c * Mc, Mc, scale,
-                                                   merge, stream, flags);
+                                                   delta_part + (size_t)c * rows, nullptr, c * Mc, Mc, scale, merge,
+                                                   stream, flags);
             if (rc != FLARE_OK) return rc;
         }
         LaunchTimer t(KID_DECODE_MERGE, stream);
         stats_merge_kernel<<<(unsigned)((rows + 255) / 256), 256, 0, stream>>>(lse_part, delta_part, C, lse_out, delta,
                                                                               rows);
         return check_launch();
+    } else if (decode_running(s)) {
+        float *run = static_cast<float *>(ws);
+        float *run_lse = reinterpret_cast<float *>(static_cast<char *>(ws) + up256(rows * s.d * 4));
+        for (int c = 0; c < C; ++c) {
+            const int rc = launch_decode_family<2>(s, q, k, z, y, tok_stride(s), nullptr, lse_out, run_lse, run, c * Mc, Mc,
+                                                   scale, merge, stream, flags | (c == 0 ? 4 : 0) | (c + 1 == C ? 8 : 0));
+            if (rc != FLARE_OK) return rc;
+        }
+        return FLARE_OK;
     } else {
-        bf16_t *y_part = static_cast<bf16_t *>(ws);
+        const size_t es = s.y_f32 ? 4 : 2;          // bytes per element of the partial rows
+        float *lse_part = reinterpret_cast<float *>(static_cast<char *>(ws) + up256(rows * C * s.d * es));
         const TokStride tp{(long long)s.H * s.N * s.d, (long long)s.N * s.d, s.d, 0};   // partial rows: [b][h][n][d]
         for (int c = 0; c < C; ++c) {
             void *part_c = static_cast<char *>(ws) + (size_t)c * rows * s.d * es;
             const int rc = launch_decode_family<0>(s, q, k, z, part_c, tp, nullptr, lse_part + (size_t)c * rows, nullptr,
-                                                   c * Mc, Mc, scale, merge, stream, flags);
+                                                   nullptr, c * Mc, Mc, scale, merge, stream, flags);
             if (rc != FLARE_OK) return rc;
         }
         const dim3 grid((s.N + 255) / 256, s.B * s.H);
+        const bf16_t *y_part = static_cast<const bf16_t *>(ws);
         LaunchTimer t(KID_DECODE_MERGE, stream);
-        if (s.y_f32) {
-            const float *yp = static_cast<const float *>(ws);
-            switch (s.d) {
-                case 4: decode_merge_f32_kernel<4><<<grid, 256, 0, stream>>>(yp, lse_part, C, (float *)y, lse_out, tok_stride(s), s.H, s.N, rows); break;
-                case 8: decode_merge_f32_kernel<8><<<grid, 256, 0, stream>>>(yp, lse_part, C, (float *)y, lse_out, tok_stride(s), s.H, s.N, rows); break;
-                case 16: decode_merge_f32_kernel<16><<<grid, 256, 0, stream>>>(yp, lse_part, C, (float *)y, lse_out, tok_stride(s), s.H, s.N, rows); break;
-                default: decode_merge_f32_kernel<32><<<grid, 256, 0, stream>>>(yp, lse_part, C, (float *)y, lse_out, tok_stride(s), s.H, s.N, rows); break;
-            }
-            return check_launch();
-        }
-        const bool f16 = s.dtype == FLARE_F16;
-#define FLARE_DM(DD)                                                                                              \
-    do {                                                                                                          \
-        if (f16)                                                                                                  \
-            decode_merge_kernel<DD, true><<<grid, 256, 0, stream>>>(y_part, lse_part, C, (bf16_t *)y, lse_out,    \
-                                                                    tok_stride(s), s.H, s.N, rows);               \
-        else                                                                                                      \
-            decode_merge_kernel<DD, false><<<grid, 256, 0, stream>>>(y_part, lse_part, C, (bf16_t *)y, lse_out,   \
-                                                                     tok_stride(s), s.H, s.N, rows);              \
-    } while (0)
-        switch (s.d) {
-            case 4: FLARE_DM(4); break;
-            case 8: FLARE_DM(8); break;
-            case 16: FLARE_DM(16); break;
-            default: FLARE_DM(32); break;
-        }
-#undef FLARE_DM
+        if (s.y_f32)
+            decode_merge_f32_kernel<32><<<grid, 256, 0, stream>>>(static_cast<const float *>(ws), lse_part, C, (float *)y,
+                                                                  lse_out, tok_stride(s), s.H, s.N, rows);
+        else if (s.dtype == FLARE_F16)
+            decode_merge_kernel<32, true><<<grid, 256, 0, stream>>>(y_part, lse_part, C, (bf16_t *)y, lse_out,
+                                                                    tok_stride(s), s.H, s.N, rows);
+        else
+            decode_merge_kernel<32, false><<<grid, 256, 0, stream>>>(y_part, lse_part, C, (bf16_t *)y, lse_out,
+                                                                     tok_stride(s), s.H, s.N, rows);
         return check_launch();
     }
 }

@@ -776,7 +776,7 @@ size_t bwd_layout(const flare_shape &s, int slots, void *ws, BwdWs *out)
     }
     if (mfma_supported(s)) {   // only shapes with more than 256 latents on the matrix-core path use these
         if (out) out->tok_part = base + off;
-        off += mfma_tok_part_bytes(s);
+        off += mfma_tok_stats_bytes(s);
         if (out) out->acc32 = reinterpret_cast<float *>(base + off);
         off += mfma_dkdv_acc_bytes(s);
     } else if (out) {

@@ -86,6 +86,31 @@ def test_fused_dq_of_wide_heads(oracle, M, N, B, layout):
         assert slice_relerr(to_host(a), to_host(b)) <= tol_for(inp)
 
 
+# the decode of more than 256 latents, chunk after chunk: chunks whose scores lie far above or below those so far, the last
+# one all but empty, tokens behind the last whole tile, both types of y
+@pytest.mark.parametrize("M,d,N,layout,y_f32,gains", [
+    (257, 8, 95, "bhnd", True, (1, 60)), (300, 16, 333, "bnhd", False, (60, 1)), (545, 4, 1000, "bhnd", False, (1, 60, 1)),
+    (768, 16, 64, "bhnd", True, (60, 1, 20)), (1030, 8, 700, "bnhd", False, (1, 5, 40, 1, 80)), (300, 32, 333, "bhnd", True, (60, 1))])
+def test_decode_of_chunks_far_apart(M, d, N, layout, y_f32, gains):
+    """Against the softmax in 64 bits."""
+    print("[case] decode M=%d d=%d N=%d" % (M, d, N), flush=True)
+    inp = synth.make_inputs(1, B=2, H=2, N=N, M=M, d=d, dtype="bf16", seed=M + N)
+    dev = to_device(inp, ("q", "k", "v"))
+    step = 32 * -(-(-(-M // 32)) // len(gains))
+    gain = torch.cat([torch.full((step,), float(g)) for g in gains])[:M].to("cuda")
+    q = (dev["q"] * gain[:, None]).to(dev["q"].dtype)
+    k, v = (t.permute(0, 2, 1, 3).contiguous() if layout == "bnhd" else t for t in (dev["k"], dev["v"]))
+    ld = torch.empty((2, 2, N), dtype=torch.float32, device="cuda")
+    y, z, _ = binding.forward(q, k, v, inp["scale"], lse_dec=ld, layout=layout, y_f32=y_f32)
+    y = y.permute(0, 2, 1, 3) if layout == "bnhd" else y
+    s = torch.matmul(dev["k"].double().cpu(), q.double().cpu().transpose(1, 2)) * inp["scale"]
+    y_ref = torch.matmul(s.softmax(-1), z.double().cpu())
+    assert slice_relerr(to_host(y), y_ref.numpy()) <= tol_for(inp)
+    # log-sums: queries as a pair of bf16 terms (2^-16 of a score's terms), weights rounded to bf16 (2^-9)
+    terms = torch.matmul(dev["k"].double().cpu().abs(), q.double().cpu().abs().transpose(1, 2)).amax(-1) * inp["scale"]
+    assert ((ld.double().cpu() - s.logsumexp(-1)).abs() <= 2.0 ** -16 * terms + 2.0 ** -8).all()
+
+
 @pytest.mark.parametrize("M", [70, 150, 200])
 def test_projection_of_ragged_latents(M):
     """The fused projection forms the y that the decode forms, bit for bit, whatever the number of tiles."""
