@@ -1112,9 +1112,10 @@ int mfma_dkdv_blocks(const flare_shape &s)
     const int BH = s.B * s.H;
     const int tiles = (s.N + 31) / 32;
     const int MT = lat_eff(s.M) / 32, waves = (mfma_dq_fused(s) && dkdv_pair(padded_dim(s.d), MT)) ? 4 : 8;   // token tiles at a time
-    int most = BH <= 256 ? (256 + BH - 1) / BH : 4;   // one 8-wave workgroup per CU
-    if (most > (tiles + waves - 1) / waves) most = (tiles + waves - 1) / waves;
-    return round_blocks(BH, 1, tiles, waves, 1 + 8 / MT, most);   // (setup: the operand images)
+    const int most = BH <= 256 ? (256 + BH - 1) / BH : 4;   // one 8-wave workgroup per CU
+    const int limit = min(4 * most, (tiles + waves - 1) / waves);
+    // (setup: the operand images and the sum of the waves' dQ, 20 us beside 4.9 us a step at 256 latents and d = 16)
+    return round_blocks(BH, 1, tiles, waves, 3 + 8 / MT, most, limit);
 }
 
 // The dK/dV kernel also forms the dQ partials (one pass over the scores for all three gradients).  At d <= 8

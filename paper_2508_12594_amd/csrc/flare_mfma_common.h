@@ -495,23 +495,31 @@ inline EncGeom dq_geom(const flare_shape &s)
 constexpr int kEncodeTargetBlocks = 512;   // two 4-wave workgroups per CU
 constexpr int kDecodeTargetBlocks = 512;
 
-// Workgroups per (b,h), at most `most`, where those of a (b,h) share `steps` equal steps among `waves` waves each and a
-// workgroup costs `setup` more, `cu` of which run side by side on a CU.  The work is dealt out beforehand, so a launch is over when the CU with the most
-// workgroups is: 24 (b,h) by 22 (512 places, rounded up) leave 16 CUs with three workgroups and the others with two, by 21
-// none.  Of counts that cost nearly the same (5 %) the largest: two on a CU cover each other's waits.  (3 x 8 heads, 50021
-// tokens, 200 latents: d = 8 forward 126 -> 91 us, d = 16 training 388 -> 269 us; 5 x 8 heads, 30000 tokens, 128 latents,
-// d = 32 505 -> 381 us.)
-inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int most)
+// Workgroups per (b,h) where those of a (b,h) share `steps` equal steps among `waves` waves each and a workgroup costs
+// `setup` more, `cu` of which run side by side on a CU: `most` fill the chip.  The work is dealt out beforehand, so a launch
+// is over when the CU with the most workgroups is: 24 (b,h) by 22 (512 places, rounded up) leave 16 CUs with three
+// workgroups and the others with two, by 21 none.  Of counts that cost nearly the same (5 %) the largest: two on a CU cover
+// each other's waits.  (3 x 8 heads, 50021 tokens, 200 latents: d = 8 forward 126 -> 91 us, d = 16 training 388 -> 269 us;
+// 5 x 8 heads, 30000 tokens, 128 latents, d = 32 505 -> 381 us.)
+// More than one round of them, up to `limit` a (b,h), only where that is 10 % cheaper: 144 (b,h) fill 256 places with one
+// workgroup each to 56 %, and so with two, by five to 94 %.  (5 x 8 heads, 30703 tokens, 512 latents, d = 16 training
+// 803 -> 555 us, of it a start's counts of 264 for 256 places; 9 x 16 heads, 36229 tokens, 136 latents, fp32 3973 -> 3402.)
+// from: the fewest there may be.
+inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int most, int limit, int from = 1)
 {
     constexpr int kCus = 256;
     auto cost = [&](int b) {
         const long long on_cu = ((long long)b * BH + kCus - 1) / kCus;
         return on_cu * ((steps + b * waves - 1) / (b * waves)) + (on_cu + cu - 1) / cu * setup;
     };
-    long long least = cost(1);
-    for (int b = 2; b <= most; ++b) least = cost(b) < least ? cost(b) : least;
-    int best = most > 1 ? most : 1;
-    while (best > 1 && 20 * cost(best) > 21 * least) --best;
+    int top = most < limit ? most : limit;
+    if (top < from) top = from;
+    long long least = cost(from);
+    for (int b = from + 1; b <= top; ++b) least = cost(b) < least ? cost(b) : least;
+    int best = top;
+    while (best > from && 20 * cost(best) > 21 * least) --best;
+    for (int b = top + 1; b <= limit; ++b)
+        if (10 * cost(b) < 9 * cost(best)) best = b;
     return best;
 }
 

@@ -954,9 +954,10 @@ int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t 
     // resident workgroups: as many as waves (dK/dV keeps two on a SIMD) and LDS allow
     int cu = (MODE == 2 ? kCuWaves / 2 : kCuWaves) / waves;
     if (cu > (int)(kLds / lds)) cu = (int)(kLds / lds) > 1 ? (int)(kLds / lds) : 1;
-    int most = BH <= 256 * cu ? (256 * cu + BH - 1) / BH : 4;
-    if (most > (batches + waves - 1) / waves) most = (batches + waves - 1) / waves;
-    const dim3 grid(round_blocks(BH, cu, batches, waves, 1, most), BH);
+    // two rounds where one workgroup fits a CU: the second evens out what the first leaves (16 (b,h), 213277 tokens, 21
+    // latents: dK/dV 316 us in one round, 292 in two)
+    const int most = BH <= 512 ? (512 + BH - 1) / BH : 4;
+    const dim3 grid(round_blocks(BH, cu, batches, waves, 1, most, min(4 * most, (batches + waves - 1) / waves)), BH);
     LaunchTimer t(kid, stream);
     if constexpr (MODE != 1) {
         if (merge) {
@@ -992,12 +993,17 @@ Split mfma32_split(const flare_shape &s)
     const int stage = 32 * g.TG;
     const long long per = (long long)s.B * s.H * g.zdim;                 // workgroups of a chunk (any shape may be asked about)
     const int stages = (s.N + stage - 1) / stage, places = 256 * (kCuWaves / (g.G * g.TG));
-    int most = (int)((places + per - 1) / per);
-    if (most > (s.N + kMinChunk - 1) / kMinChunk) most = (s.N + kMinChunk - 1) / kMinChunk;
-    if (most > stages) most = stages;
-    const int want = per > places ? most : round_blocks((int)per, places / 256, stages, 1, 1, most);
-    int len = (stages + want - 1) / want * stage;
-    if (len > 8192) len = 8192;
+    const int least = (stages + 8192 / stage - 1) / (8192 / stage);      // (a stage divides 8192)
+    const int fill = (int)((places + per - 1) / per), cap = min((s.N + kMinChunk - 1) / kMinChunk, stages);
+    int want = least;
+    if (per <= places) {
+        // (2 x 16 heads, 152439 tokens, 164 latents: 16 chunks fill the chip, but 19 are the fewest; 24 are a third faster)
+        int limit = min(cap, 2 * (fill > least ? fill : least));
+        if (limit > fill && (size_t)s.B * s.H * limit * s.M * (s.d + 2) * 4 > FLARE_STATIC_SCRATCH_BYTES / 2)
+            limit = min(cap, fill);
+        want = round_blocks((int)per, places / 256, stages, 1, 1, fill, limit, least);
+    }
+    const int len = (stages + want - 1) / want * stage;
     return Split{(s.N + len - 1) / len, len};
 }
 

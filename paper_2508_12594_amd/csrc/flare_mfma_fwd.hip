@@ -1203,8 +1203,10 @@ MfmaPlan mfma_plan(const flare_shape &s)
         if (s.N >= finer * (min_len / 4) && s.M <= kLatChunk && merge_inline(s, finer) &&
             (size_t)BH * finer * s.M * (s.d + 2) * 4 <= FLARE_STATIC_SCRATCH_BYTES / 2)   // (what fits there still does)
             most = finer;
-    if (most > (kEncodeTargetBlocks + BH - 1) / BH) most = (kEncodeTargetBlocks + BH - 1) / BH;
-    const int want = round_blocks(BH, kEncodeTargetBlocks / 256, tiles, e.TG, 1, most);
+    const int fill = (kEncodeTargetBlocks + BH - 1) / BH;
+    int limit = min(most, 2 * fill);
+    if (limit > fill && (size_t)BH * limit * s.M * (s.d + 2) * 4 > FLARE_STATIC_SCRATCH_BYTES / 2) limit = fill;
+    const int want = round_blocks(BH, kEncodeTargetBlocks / 256, tiles, e.TG, 1, fill, limit);
     // (chunks in whole tiles: only the last one ends within a tile)
     p.enc.chunk_len = (tiles + want - 1) / want * 32;
     p.enc.chunks = (s.N + p.enc.chunk_len - 1) / p.enc.chunk_len;
@@ -1350,9 +1352,8 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
     // d = 32 with more than 128 latents (Z in LDS, 168 registers): three workgroups fit a CU
     const bool three = padded_dim(s.d) == 32 && Mc > 128;
     const int places = three ? 768 : kDecodeTargetBlocks;
-    int most = BH <= places ? (places + BH - 1) / BH : 4;
-    if (most > (tiles + 3) / 4) most = (tiles + 3) / 4;
-    const dim3 grid(round_blocks(BH, places / 256, tiles, 4, 1, most), BH);
+    const int most = BH <= places ? (places + BH - 1) / BH : 4;
+    const dim3 grid(round_blocks(BH, places / 256, tiles, 4, 1 + 256 / Mc, most, min(4 * most, (tiles + 3) / 4)), BH);
     const float c2 = scale * kLog2e;
     const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *gg = (const bf16_t *)dy;
     bf16_t *yy = (bf16_t *)y;

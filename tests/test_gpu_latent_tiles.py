@@ -29,6 +29,8 @@ F32 = [(33, 4, 129), (31, 8, 33), (97, 16, 260), (160, 32, 257), (256, 16, 1000)
 # numbers of (b,h) that do not divide the chip's workgroups: 3 x 8, 7 x 4, 5 x 4; and more than one per CU
 HEADS = [("bf16", 3, 8, 5100, 72, 8), ("f16", 7, 4, 5300, 64, 16), ("bf16", 5, 4, 2700, 130, 32), ("f32", 12, 4, 900, 70, 8),
          ("bf16", 17, 16, 1111, 33, 16), ("f32", 20, 16, 390, 40, 16)]
+# more than one round of workgroups: 9 x 16 in every kernel; fp32 chunks of at most 8192 tokens, more than fill the chip
+HEADS += [("bf16", 9, 16, 2600, 40, 16), ("f16", 9, 16, 1900, 130, 32), ("f32", 9, 16, 2100, 33, 16), ("f32", 2, 16, 132000, 33, 8)]
 
 
 def _check(oracle, dtype, H, N, M, d, layout, saved, B=1):
