@@ -512,14 +512,23 @@ inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int mos
         const long long on_cu = ((long long)b * BH + kCus - 1) / kCus;
         return on_cu * ((steps + b * waves - 1) / (b * waves)) + (on_cu + cu - 1) / cu * setup;
     };
+    // Only the largest counts that put as many on the fullest CU can be best, a handful (this runs on every call).
+    auto widest = [&](int b, int most_) {
+        const long long w = ((long long)b * BH + kCus - 1) / kCus * kCus / BH;
+        return w < most_ ? (int)w : most_;
+    };
     int top = most < limit ? most : limit;
     if (top < from) top = from;
-    long long least = cost(from);
-    for (int b = from + 1; b <= top; ++b) least = cost(b) < least ? cost(b) : least;
+    long long least = cost(top);
+    for (int b = widest(from, top); b < top; b = widest(b + 1, top)) least = cost(b) < least ? cost(b) : least;
     int best = top;
-    while (best > from && 20 * cost(best) > 21 * least) --best;
-    for (int b = top + 1; b <= limit; ++b)
+    if (20 * cost(top) > 21 * least)
+        for (int b = widest(from, top); b < top; b = widest(b + 1, top))
+            if (20 * cost(b) <= 21 * least) best = b;
+    for (int b = top; b < limit;) {
+        b = widest(b + 1, limit);
         if (10 * cost(b) < 9 * cost(best)) best = b;
+    }
     return best;
 }
 
