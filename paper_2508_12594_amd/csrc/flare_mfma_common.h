@@ -503,7 +503,7 @@ constexpr int kDecodeTargetBlocks = 512;
 // 5 x 8 heads, 30000 tokens, 128 latents, d = 32 505 -> 381 us.)
 // More than one round of them, up to `limit` a (b,h), only where that is 10 % cheaper: 144 (b,h) fill 256 places with one
 // workgroup each to 56 %, and so with two, by five to 94 %.  (5 x 8 heads, 30703 tokens, 512 latents, d = 16 training
-// 803 -> 555 us, of it a start's counts of 264 for 256 places; 9 x 16 heads, 36229 tokens, 136 latents, fp32 3973 -> 3402.)
+// 803 us with counts rounded up, 555; 9 x 16 heads, 36229 tokens, 136 latents, fp32 3973 -> 3402.)
 // from: the fewest there may be.
 inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int most, int limit, int from = 1)
 {

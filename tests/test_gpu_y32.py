@@ -21,7 +21,7 @@ CASES = [
     (3, dict(B=2, N=700, dtype="f16"), "bhnd"),
     (2, dict(B=1, N=20, M=7, d=8), "bhnd"),          # a single token tile, few latents
     (2, dict(B=2, H=3, N=365, M=200, d=4, seed=777 + 1375), "bhnd"),   # a latent that dominates many tokens
-    (2, dict(B=1, N=1500, M=512, d=8), "bhnd"),      # more than 256 latents: fp32 partial rows per chunk of latents
+    (2, dict(B=1, N=1500, M=512, d=8), "bhnd"),      # more than 256 latents: fp32 rows that the chunks add to
     (4, dict(N=900, M=300, d=16), "bnhd"),
     (2, dict(B=1, H=2, N=700, M=1000, d=4, dtype="f16"), "bhnd"),
     # fp16 storage at d = 16: delta comes from a pass of its own, which must round dY to bf16 as the kernels do

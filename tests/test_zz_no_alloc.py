@@ -61,7 +61,7 @@ def test_static_scratch_forward_matches_workspace_forward(dtype):
 def test_static_scratch_refuses_shapes_beyond_its_size():
     import torch
     lib = binding.load()
-    B, H, N, M, d = 1, 8, 1 << 20, 2048, 8          # 1.2 GiB of per-chunk decode rows
+    B, H, N, M, d = 1, 8, 1 << 20, 2048, 8          # 288 MiB of decode rows
     fwd_b, _ = binding.workspace_bytes(B, H, N, M, d, binding.FLARE_BF16)
     assert fwd_b > binding.STATIC_SCRATCH_BYTES
     shp = binding.FlareShape(B, H, N, M, d, binding.FLARE_BF16, binding.FLARE_BHND, 0, 0)
