@@ -680,8 +680,10 @@ __device__ __forceinline__ void dkdv_body(
         if (PACK && !lower) w[0] = 0x3f803f80u;
         return as_bf16x8(w);
     };
-    const u32x4 *img_w = img + half * (HT * PER_TILE * 64);   // this wave's latent tiles
-    auto image = [&](int t, int sid) { return as_bf16x8(img_w[(t * PER_TILE + sid) * 64 + lane]); };
+    // t: of this wave's latent tiles.  (As an index: a pointer to the wave's first image took two registers more also where
+    // half is the constant 0, and the d = 16 kernel of six tiles spilled: two exponentials, 131072 tokens, 8 heads, 336
+    // latents 217 us, 203 like this.)
+    auto image = [&](int t, int sid) { return as_bf16x8(img[((half * HT + t) * PER_TILE + sid) * 64 + lane]); };
 
     // fused dQ: wave-private LDS tiles and the accumulators dQ^T[dd = 16 db + 4 (lane / 16) + r][m = 32 t + 16 jb + lane % 16]
     uint16_t *ds_t = reinterpret_cast<uint16_t *>(img + MT * PER_TILE * 64) + (DQ ? wave * fused_wave_lds(D, MT) : 0);

@@ -1,0 +1,55 @@
+"""What the compiler made of kernels whose speed rests on their registers, read from the metadata in the built library.  No
+GPU needed."""
+import os
+import re
+import struct
+
+import msgpack
+import pytest
+
+from paper_2508_12594_amd import binding
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    """Metadata of every kernel in libflare.so, by mangled name."""
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2508_12594_amd import build
+        build.build_library(verbose=False)
+    with open(binding.LIB_PATH, "rb") as f:
+        blob = f.read()
+    found, at = {}, 0
+    while True:
+        at = blob.find(b"\x7fELF\x02\x01", at + 1)
+        if at < 0:
+            break
+        if struct.unpack_from("<H", blob, at + 18)[0] != 224:    # EM_AMDGPU
+            continue
+        shoff = struct.unpack_from("<Q", blob, at + 40)[0]
+        shentsize, shnum = struct.unpack_from("<HH", blob, at + 58)
+        for i in range(shnum):
+            kind, _, _, off, size = struct.unpack_from("<IQQQQ", blob, at + shoff + i * shentsize + 4)
+            if kind != 7:                                        # SHT_NOTE
+                continue
+            p, end = at + off, at + off + size
+            while p < end:
+                nsz, dsz, ntype = struct.unpack_from("<III", blob, p)
+                name, desc = p + 12, p + 12 + (nsz + 3) // 4 * 4
+                if blob[name:name + 6] == b"AMDGPU" and ntype == 32:
+                    for k in msgpack.unpackb(blob[desc:desc + dsz], raw=False)["amdhsa.kernels"]:
+                        found[k[".name"]] = k
+                p = desc + (dsz + 3) // 4 * 4
+    return found
+
+
+def spilled(kernels, head, latent_tiles):
+    pat = re.compile(r"bwd_dkdv_planned_kernelILi%dELi%dELb1E" % (head, latent_tiles))    # (the form that also makes dQ)
+    counts = [k[".vgpr_spill_count"] for n, k in kernels.items() if pat.search(n)]
+    assert len(counts) >= 2, "no such kernels in the library"
+    return max(counts)
+
+
+@pytest.mark.parametrize("latent_tiles,most", [(1, 0), (2, 0), (3, 0), (4, 0), (5, 0), (6, 0), (7, 11), (8, 27)])
+def test_dkdv_registers_at_16_columns(kernels, latent_tiles, most):
+    """Seven and eight latent tiles have never fitted with two exponentials; up to six fit."""
+    assert spilled(kernels, 16, latent_tiles) <= most
