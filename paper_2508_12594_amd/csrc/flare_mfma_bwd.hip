@@ -682,7 +682,7 @@ __device__ __forceinline__ void dkdv_body(
     };
     // t: of this wave's latent tiles.  (As an index: a pointer to the wave's first image took two registers more also where
     // half is the constant 0, and the d = 16 kernel of six tiles spilled: two exponentials, 131072 tokens, 8 heads, 336
-    // latents 217 us, 203 like this.)
+    // latents 230 us, 213 like this.)
     auto image = [&](int t, int sid) { return as_bf16x8(img[((half * HT + t) * PER_TILE + sid) * 64 + lane]); };
 
     // fused dQ: wave-private LDS tiles and the accumulators dQ^T[dd = 16 db + 4 (lane / 16) + r][m = 32 t + 16 jb + lane % 16]
@@ -834,9 +834,16 @@ __device__ __forceinline__ void dkdv_body(
             if constexpr (PIPE) {
                 if (t + 1 < HT) scores(t + 1, s1n, s2n);
             }
+            // Two exponentials at d = 32: both scores, a and c are 64 registers, and with the row images beside them 26 to 39
+            // others were spilled and read again in every latent tile.  So these come behind the vector block there (0 to 4
+            // spilled): 131072 tokens, 8 heads, 128 latents 167 -> 109 us, 256 latents 280 -> 194 (with a dQ kernel of its
+            // own 174 and 293).
+            constexpr bool LATE_ROWS = WIDE && !ONE;
             bf16x8 rw[NR];
+            if constexpr (!LATE_ROWS) {
 #pragma unroll
-            for (int r = 0; r < NR; ++r) rw[r] = image(t, NA + r);
+                for (int r = 0; r < NR; ++r) rw[r] = image(t, NA + r);
+            }
             sched_fence();
             __builtin_amdgcn_s_setprio(0);
             f32x16 pv, rv;
@@ -853,6 +860,11 @@ __device__ __forceinline__ void dkdv_body(
                 p1[i] = cvt_pk_bf16(pv[8 + 2 * i], pv[8 + 2 * i + 1]);
                 d0[i] = cvt_pk_bf16(rv[2 * i], rv[2 * i + 1]);
                 d1[i] = cvt_pk_bf16(rv[8 + 2 * i], rv[8 + 2 * i + 1]);
+            }
+            if constexpr (LATE_ROWS) {
+                sched_fence();
+#pragma unroll
+                for (int r = 0; r < NR; ++r) rw[r] = image(t, NA + r);
             }
 #pragma unroll
             for (int hv = 0; hv < HV; ++hv) {

@@ -88,6 +88,20 @@ def test_fused_dq_of_wide_heads(oracle, M, N, B, layout):
         assert slice_relerr(to_host(a), to_host(b)) <= tol_for(inp)
 
 
+@pytest.mark.parametrize("dtype,M,N,d", [("bf16", 32, 300, 32), ("f16", 90, 515, 32), ("bf16", 128, 1000, 32), ("bf16", 190, 333, 32),
+                                         ("bf16", 256, 1100, 32), ("f16", 330, 700, 32), ("bf16", 336, 1000, 16)])
+def test_two_exponentials_in_the_fused_kernel(oracle, dtype, M, N, d):
+    """The form that inputs with far log-sum-exps take, at every way to hold the latents."""
+    inp = synth.make_inputs(1, B=2, H=2, N=N, M=M, d=d, dtype=dtype, with_dy=True, seed=5 + N + M)
+    dev, scale, tol = to_device(inp), inp["scale"], tol_for(inp)
+    ld = torch.empty((2, 2, N), dtype=torch.float32, device="cuda")
+    y, z, lse = binding.forward(dev["q"], dev["k"], dev["v"], scale, lse_dec=ld)
+    got = binding.backward(dev["q"], dev["k"], dev["v"], dev["dy"], z, lse, scale, y=y, lse_dec=ld,
+                           variant=binding.VARIANT_TWO_EXP)
+    for a, ref in zip(got, oracle.backward(inp["q"], inp["k"], inp["v"], inp["dy"], scale)):
+        assert slice_relerr(to_host(a), ref) <= tol
+
+
 # the decode of more than 256 latents, chunk after chunk: chunks whose scores lie far above or below those so far, the last
 # one all but empty, tokens behind the last whole tile, both types of y
 @pytest.mark.parametrize("M,d,N,layout,y_f32,gains", [
