@@ -1129,7 +1129,7 @@ int mfma_dkdv_blocks(const flare_shape &s)
     const int most = BH <= 256 ? (256 + BH - 1) / BH : 4;   // one 8-wave workgroup per CU
     const int limit = min(4 * most, (tiles + waves - 1) / waves);
     // (setup: the operand images and the sum of the waves' dQ, 20 us beside 4.9 us a step at 256 latents and d = 16)
-    return round_blocks(BH, 1, tiles, waves, 3 + 8 / MT, most, limit);
+    return round_blocks(BH, 1, tiles, waves, 3 + 8 / MT, most, limit, kNever);
 }
 
 // The dK/dV kernel also forms the dQ partials (one pass over the scores for all three gradients).  At d <= 8

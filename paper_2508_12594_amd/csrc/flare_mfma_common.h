@@ -505,7 +505,14 @@ constexpr int kDecodeTargetBlocks = 512;
 // workgroup each to 56 %, and so with two, by five to 94 %.  (5 x 8 heads, 30703 tokens, 512 latents, d = 16 training
 // 803 us with counts rounded up, 555; 9 x 16 heads, 36229 tokens, 136 latents, fp32 3973 -> 3402.)
 // from: the fewest there may be.
-inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int most, int limit, int from = 1)
+// hide: with at least so many steps a wave (kNever: whatever they are) a workgroup is not left alone on its CU where two
+// fit.  The cost above takes the two to share the CU's time, but where a step is short, few latents, they wait for memory
+// in turn, and one alone takes as long as two: counts below that are better only where each workgroup has a price of its
+// own beside its few steps (slots to merge, operands to load).  (fp32, 4 heads, 119557 tokens, 50 latents: dQ 58 us by 63 chunks,
+// 41 by 117; 4 x 16 heads, 6181 tokens, 64 latents: 51 us by 4, 37 by 7; bf16, 8 heads, 26779 tokens, 32 latents: forward 17.9 us
+// by 32 workgroups in the decode, 16.4 by 64; but 2 x 8 heads, 5999 tokens, 128 latents: decode 12.6 us by 16, 14.9 by 32.)
+constexpr int kNever = 1 << 20;
+inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int most, int limit, int hide, int from = 1)
 {
     constexpr int kCus = 256;
     auto cost = [&](int b) {
@@ -519,6 +526,10 @@ inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int mos
     };
     int top = most < limit ? most : limit;
     if (top < from) top = from;
+    if (from < top && cu > 1 && (long long)most * BH >= 2 * kCus && steps > (long long)(hide - 1) * top * waves) {
+        const int two = kCus / BH + 1;
+        from = two < from ? from : two < top ? two : top;
+    }
     long long least = cost(top);
     for (int b = widest(from, top); b < top; b = widest(b + 1, top)) least = cost(b) < least ? cost(b) : least;
     int best = top;

@@ -957,7 +957,7 @@ int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t 
     // two rounds where one workgroup fits a CU: the second evens out what the first leaves (16 (b,h), 213277 tokens, 21
     // latents: dK/dV 316 us in one round, 292 in two)
     const int most = BH <= 512 ? (512 + BH - 1) / BH : 4;
-    const dim3 grid(round_blocks(BH, cu, batches, waves, 1, most, min(4 * most, (batches + waves - 1) / waves)), BH);
+    const dim3 grid(round_blocks(BH, cu, batches, waves, 1, most, min(4 * most, (batches + waves - 1) / waves), 3), BH);
     LaunchTimer t(kid, stream);
     if constexpr (MODE != 1) {
         if (merge) {
@@ -1001,7 +1001,8 @@ Split mfma32_split(const flare_shape &s)
         int limit = min(cap, 2 * (fill > least ? fill : least));
         if (limit > fill && (size_t)s.B * s.H * limit * s.M * (s.d + 2) * 4 > FLARE_STATIC_SCRATCH_BYTES / 2)
             limit = min(cap, fill);
-        want = round_blocks((int)per, places / 256, stages, 1, 1, fill, limit, least);
+        // (workgroups of eight waves and up to 64 latents: see round_blocks; the others have enough waves without it)
+        want = round_blocks((int)per, places / 256, stages, 1, 1, fill, limit, places == 512 && g.G <= 2 ? 5 : kNever, least);
     }
     const int len = (stages + want - 1) / want * stage;
     return Split{(s.N + len - 1) / len, len};

@@ -1206,7 +1206,10 @@ MfmaPlan mfma_plan(const flare_shape &s)
     const int fill = (kEncodeTargetBlocks + BH - 1) / BH;
     int limit = min(most, 2 * fill);
     if (limit > fill && (size_t)BH * limit * s.M * (s.d + 2) * 4 > FLARE_STATIC_SCRATCH_BYTES / 2) limit = fill;
-    const int want = round_blocks(BH, kEncodeTargetBlocks / 256, tiles, e.TG, 1, fill, limit);
+    // (few latents: a workgroup is left alone only where more slots would cost a merge of their own; 4 x 8 heads, 16598
+    // tokens, 16 latents, d = 8: dZ 16 us by 8 chunks, 12 by 16)
+    const int want = round_blocks(BH, kEncodeTargetBlocks / 256, tiles, e.TG, 1, fill, limit,
+                                  s.M <= 64 && merge_inline(s, min(fill, limit)) ? 9 : kNever);
     // (chunks in whole tiles: only the last one ends within a tile)
     p.enc.chunk_len = (tiles + want - 1) / want * 32;
     p.enc.chunks = (s.N + p.enc.chunk_len - 1) / p.enc.chunk_len;
@@ -1349,11 +1352,16 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
     const size_t lds = merge.parts ? (size_t)s.M * s.d * 4 : 0;
     const int BH = s.B * s.H;
     const int tiles = (s.N + 31) / 32;
-    // d = 32 with more than 128 latents (Z in LDS, 168 registers): three workgroups fit a CU
-    const bool three = padded_dim(s.d) == 32 && Mc > 128;
-    const int places = three ? 768 : kDecodeTargetBlocks;
+    // Workgroups that fit a CU by the kernel's registers (d = 32 with more than 128 latents keeps Z in LDS).  Two are launched
+    // for each, there three where they fit: not with seven tiles, 174 registers.  What all of them load first is paid once for
+    // those that fit (26 x 16 heads, 5521 tokens, 32 latents: 42 us by one workgroup a head, taken for cheaper when two
+    // were thought to fit, 35 by two).  hide: see round_blocks; from 65 latents on a step is long enough.
+    const int MT = Mc / 32, pd = padded_dim(s.d);
+    const int cu = pd == 32 ? (MT == 1 ? 4 : MT == 2 || (MT > 4 && MT != 7) ? 3 : 2) : MT <= 2 ? 4 : MT <= 4 ? 3 : 2;
+    const int places = pd == 32 && MT > 4 && cu == 3 ? 768 : kDecodeTargetBlocks;
     const int most = BH <= places ? (places + BH - 1) / BH : 4;
-    const dim3 grid(round_blocks(BH, places / 256, tiles, 4, 1 + 256 / Mc, most, min(4 * most, (tiles + 3) / 4)), BH);
+    const dim3 grid(round_blocks(BH, cu, tiles, 4, 1 + 256 / Mc, most, min(4 * most, (tiles + 3) / 4),
+                                 Mc <= 64 || places == 768 ? 3 : kNever), BH);
     const float c2 = scale * kLog2e;
     const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *gg = (const bf16_t *)dy;
     bf16_t *yy = (bf16_t *)y;
@@ -1379,7 +1387,6 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
         else                                                                                                    \
             FLARE_DEC_F(DD, MTT, PREE, MINB, false);                                                            \
     } while (0)
-    const int MT = Mc / 32;
 #define FLARE_DEC_MT(DD)                               \
     switch (MT) {                                      \
         case 1: FLARE_DEC(DD, 1, true, 2); break;      \

@@ -262,7 +262,7 @@ int mfma_decode_project(const flare_shape &s, const void *q, const void *k, cons
     const int tiles = (s.N + 31) / 32;
     const int cu = 8 / s.H;                                   // eight waves (two per SIMD) on a compute unit
     const int most = s.B <= 256 * cu ? (256 * cu + s.B - 1) / s.B : 4;
-    const dim3 grid(round_blocks(s.B, cu, tiles, 1, 2, most, min(4 * most, tiles)), s.B);
+    const dim3 grid(round_blocks(s.B, cu, tiles, 1, 2, most, min(4 * most, tiles), kNever), s.B);
     const float c2 = scale * kLog2e;
     const long long sq = s.shared_latents ? 0 : (long long)s.M * s.d;
     const int MT = lat_eff(s.M) / 32;

@@ -60,6 +60,15 @@ def test_workspace_bytes_of_any_shape(lib):
             assert b >= f // 2
 
 
+@pytest.mark.parametrize("B,H,N,M", [(1, 4, 119557, 50), (4, 16, 6181, 64), (1, 8, 41742, 40)])
+def test_fp32_chunks_of_few_latents_fill_the_chip(lib, B, H, N, M):
+    """Chunks of tokens (a partial slot each, so the forward's workspace counts them): with several steps a wave there are two
+    workgroups of eight waves on each of the 256 compute units, not one."""
+    f, _ = binding.workspace_bytes(B, H, N, M, 16, binding.FLARE_F32)
+    slots = f // (4 * B * H * M * (16 + 2))
+    assert slots * B * H > 256
+
+
 def test_workspace_bytes_do_not_depend_on_the_layout(lib):
     """binding.workspace_bytes has no layout argument: what it reports has to serve both.  Few tokens, where one slot more
     per chunk is the largest count there is, every tile count and head dimension."""
