@@ -1135,10 +1135,14 @@ int mfma_dkdv_blocks(const flare_shape &s)
 // The dK/dV kernel also forms the dQ partials (one pass over the scores for all three gradients).  At d <= 8
 // it carries the lo term of Z in the upper half of its Z image (ZPACK in the kernel), like the token-statistics
 // kernel that forms the delta it subtracts.  flare_shape.variant with FLARE_VARIANT_SEPARATE_DQ keeps the separate dQ
-// kernel (tests, measurements).
+// kernel (tests, measurements), and so do few tokens beside chunks of seven or eight latent tiles at d = 32: each chunk is a launch
+// whose workgroups sum the waves' dQ at its end (6 us), and one dQ kernel for all of them costs less where not every other
+// pair of waves has a token tile (4 heads, 2644 tokens, 813 latents, backward 118 us fused, 103 apart; 72 heads, 306 tokens, 712
+// latents 154 and 168; 16 heads and 2400 tokens or more 1.03 to 1.3 times as long apart).
 bool mfma_dq_fused(const flare_shape &s)
 {
     if (!mfma_supported(s)) return false;
+    if (s.d == 32 && s.M > kLatChunk && lat_eff(s.M) > 192 && (long long)((s.N + 31) / 32) * s.B * s.H <= 2 * 256) return false;
     return (s.variant & FLARE_VARIANT_SEPARATE_DQ) == 0;
 }
 
@@ -1161,8 +1165,8 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
     const int KS = pd / 16, HV = (pd == 32) ? 1 : pd / 16;   // d = 32: one 32-row block of row images
     // dQ from this kernel at d = 16 with fewer tokens than latents: one more image, the lo term of Z (see the kernel)
     const bool zlo = fuse && s.d == 16 && s.N < s.M;
-    // The forms that only few-token shapes and measurements take, and d = 4, exist for 1, 2, 4 and 8 tiles.
-    if (zlo || s.d == 4 || !fuse) MT = MT <= 2 ? MT : MT <= 4 ? 4 : 8;
+    // The forms that only few-token shapes and measurements take, and d = 4, exist for 1, 2, 4 and 8 tiles (and 7 at d = 32).
+    if (zlo || s.d == 4 || (!fuse && !(s.d == 32 && MT == 7))) MT = MT <= 2 ? MT : MT <= 4 ? 4 : 8;
     if (fuse && dkdv_pair(s.d, MT)) MT += MT % 2;   // halved between two waves
     const int na = (zlo ? 5 : 4) * KS + 1;
     size_t lds = (size_t)MT * (na + 4 * HV) * 1024 + (fuse ? 8 * fused_wave_lds(pd, MT) * 2 : 0);
@@ -1236,6 +1240,8 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
             case 8: FLARE_DKDV(32, 8, true); break;
             default: return FLARE_EUNSUPPORTED;
         }
+    } else if (MT == 7) {
+        FLARE_DKDV(32, 7, false);
     } else {
         FLARE_DKDV_POW2(32, false)
     }

@@ -102,6 +102,13 @@ def test_two_exponentials_in_the_fused_kernel(oracle, dtype, M, N, d):
         assert slice_relerr(to_host(a), ref) <= tol
 
 
+# d = 32, chunks of seven and eight latent tiles: the last number of tokens with a dQ kernel of its own, the first without
+@pytest.mark.parametrize("dtype,M,N,layout", [("bf16", 450, 8192, "bhnd"), ("f16", 450, 8193, "bnhd"), ("f16", 385, 65, "bnhd"),
+                                              ("bf16", 640, 300, "bhnd")])
+def test_few_tokens_beside_chunks_of_wide_latents(oracle, dtype, M, N, layout):
+    _check(oracle, dtype, 2, N, M, 32, layout, saved=True)
+
+
 # the decode of more than 256 latents, chunk after chunk: chunks whose scores lie far above or below those so far, the last
 # one all but empty, tokens behind the last whole tile, both types of y
 @pytest.mark.parametrize("M,d,N,layout,y_f32,gains", [
