@@ -749,10 +749,27 @@ inline bool dz_inline(const flare_shape &s)
     return s.dtype == FLARE_F32 ? mfma32_inline(s) : mfma_supported(s) && mfma_dz_inline(s);
 }
 
-// `slots` = partial slots per (b,h) the shared partial buffer must hold
-size_t bwd_layout(const flare_shape &s, int slots, void *ws, BwdWs *out)
+// Partial slots per (b,h) of dZ and dQ, each region as long as its own kernels need.  (The vector kernels' 2048 / (b,h) slots,
+// in both regions, made it up to 1.9 times as long: 3 x 16 heads, 2573 tokens, 104 latents, d = 32 54 MB, 11 like this.)
+struct BwdSlots { int dz, dq; };
+inline BwdSlots bwd_slots(const flare_shape &s, const ValuPlan &plan)
+{
+    if (!mfma_supported(s)) return BwdSlots{plan.bwd.chunks, plan.bwd.chunks};
+    int dq = mfma_dq_fused(s) ? mfma_dkdv_blocks(s) : 0;
+    // the dQ kernel's slots depend on the token order (dq_geom); what the caller is told to bring does not
+    for (const flare_layout layout : {FLARE_BHND, FLARE_BNHD}) {
+        flare_shape t = s;
+        t.layout = layout;
+        if (mfma_dq_parts(t) > dq) dq = mfma_dq_parts(t);
+    }
+    return BwdSlots{mfma_plan(s).parts, dq};
+}
+
+size_t bwd_layout(const flare_shape &s, const ValuPlan &plan, void *ws, BwdWs *out)
 {
     const size_t BH = (size_t)s.B * s.H;
+    const BwdSlots slots = bwd_slots(s, plan);
+    const bool apart = dz_inline(s);   // else the dQ slots lie over those of dZ, merged by then
     size_t off = 0;
     char *base = static_cast<char *>(ws);
     if (out) out->lse_dec2 = reinterpret_cast<float *>(base + off);
@@ -760,19 +777,19 @@ size_t bwd_layout(const flare_shape &s, int slots, void *ws, BwdWs *out)
     if (out) out->delta = reinterpret_cast<float *>(base + off);
     off += align256(BH * s.N * 4);
     if (out) out->part = reinterpret_cast<float *>(base + off);
-    off += align256(BH * slots * s.M * s.d * 4);
+    off += align256(BH * (apart || slots.dz > slots.dq ? slots.dz : slots.dq) * s.M * s.d * 4);
     if (out) out->dz = reinterpret_cast<float *>(base + off);
     off += align256(BH * s.M * s.d * 4);
     if (out) out->eps = reinterpret_cast<float *>(base + off);
     off += align256(BH * s.M * 4);
     if (out) out->ld_range = reinterpret_cast<float *>(base + off);
-    off += align256(BH * slots * 2 * 4);
+    off += align256(BH * slots.dz * 2 * 4);
     if (out) out->plan = reinterpret_cast<int *>(base + off);
     off += align256(BH * 4);
     if (out) out->dq_part = out->part;
-    if (dz_inline(s)) {
+    if (apart) {
         if (out) out->dq_part = reinterpret_cast<float *>(base + off);
-        off += align256(BH * slots * s.M * s.d * 4);
+        off += align256(BH * slots.dq * s.M * s.d * 4);
     }
     if (mfma_supported(s)) {   // only shapes with more than 256 latents on the matrix-core path use these
         if (out) out->tok_part = base + off;
@@ -787,22 +804,6 @@ size_t bwd_layout(const flare_shape &s, int slots, void *ws, BwdWs *out)
 }
 
 inline int check_launch() { return hipGetLastError() == hipSuccess ? FLARE_OK : FLARE_ELAUNCH; }
-
-inline int bwd_slots(const flare_shape &s, const ValuPlan &plan)
-{
-    int mf = 0;
-    if (mfma_supported(s)) {
-        mf = mfma_plan(s).parts;
-        // the dQ kernel's slots depend on the token order (dq_geom); what the caller is told to bring does not
-        for (const flare_layout layout : {FLARE_BHND, FLARE_BNHD}) {
-            flare_shape t = s;
-            t.layout = layout;
-            if (mfma_dq_parts(t) > mf) mf = mfma_dq_parts(t);
-        }
-        if (mfma_dkdv_blocks(s) > mf) mf = mfma_dkdv_blocks(s);
-    }
-    return plan.bwd.chunks > mf ? plan.bwd.chunks : mf;
-}
 
 template <typename T, int D>
 int encode_impl(const flare_shape &s, const T *q, const T *k, const T *v, float *z, float *lse_enc,
@@ -878,7 +879,7 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
     const bool planned = F32 || mf;                  // their kernels choose between one and two exponentials by (b,h)
     const int dz_parts = mf ? mfma_plan(s).parts : plan.bwd.chunks;
     BwdWs w;
-    bwd_layout(s, bwd_slots(s, plan), ws, &w);
+    bwd_layout(s, plan, ws, &w);
     const int BH = s.B * s.H;
     const float c2 = scale * kLog2e;
     const TokStride ts = tok_stride(s);
@@ -1123,7 +1124,7 @@ ValuPlan valu_plan(const flare_shape &s)
     if (s.dtype == FLARE_F32) p.enc = mfma32_split(s);
     p.bwd = p.enc;
     p.fwd_bytes = valu_fwd_layout(s, p.enc, nullptr, nullptr, nullptr, nullptr);
-    p.bwd_bytes = bwd_layout(s, bwd_slots(s, p), nullptr, nullptr);
+    p.bwd_bytes = bwd_layout(s, p, nullptr, nullptr);
     return p;
 }
 

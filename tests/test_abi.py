@@ -69,6 +69,30 @@ def test_fp32_chunks_of_few_latents_fill_the_chip(lib, B, H, N, M):
     assert slots * B * H > 256
 
 
+@pytest.mark.parametrize("B,H,N,M,d,slots", [(56, 1, 2285, 136, 32, 24), (5, 8, 3695, 89, 32, 24), (50, 1, 3206, 224, 16, 24),
+                                             (14, 4, 2509, 149, 32, 24), (3, 16, 2573, 104, 32, 24)])
+def test_backward_workspace_holds_the_slots_that_are_written(lib, B, H, N, M, d, slots):
+    """16-bit storage, dZ merged by its consumer (at most 16 slots): beside the per-token statistics and one row per latent the
+    workspace holds a few slots of dZ and of dQ, not the vector kernels' 2048 / (B H) of each."""
+    _, b = binding.workspace_bytes(B, H, N, M, d, binding.FLARE_BF16)
+    assert b - 8 * B * H * N <= (slots + 2) * 4 * B * H * M * d
+
+
+def test_backward_workspace_serves_the_variants(lib):
+    """The size for a shape as it comes is enough for the same shape with a dQ kernel of its own."""
+    for d in (4, 8, 16, 32):
+        for M in (33, 129, 200, 256, 300, 450, 2048):
+            for N in (16, 300, 5000, 100000):
+                for B, H in ((1, 1), (1, 8), (3, 8), (14, 4), (64, 32)):
+                    size = []
+                    for variant in (0, binding.VARIANT_SEPARATE_DQ, binding.VARIANT_TWO_EXP):
+                        b = ctypes.c_size_t(0)
+                        shp = binding.FlareShape(B, H, N, M, d, binding.FLARE_BF16, 0, 0, 0, variant)
+                        assert lib.flare_workspace_bytes(ctypes.byref(shp), None, ctypes.byref(b)) == 0
+                        size.append(b.value)
+                    assert max(size) == size[0]
+
+
 def test_workspace_bytes_do_not_depend_on_the_layout(lib):
     """binding.workspace_bytes has no layout argument: what it reports has to serve both.  Few tokens, where one slot more
     per chunk is the largest count there is, every tile count and head dimension."""
