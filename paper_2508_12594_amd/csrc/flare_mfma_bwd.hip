@@ -447,6 +447,19 @@ constexpr bool dkdv_pair(int d, int mt) { return d == 32 && mt > 4; }
 constexpr int ds_tile_lds(int d, int mt) { return dkdv_pair(d, mt) ? 64 * 16 * 2 : 32 * kDsStride; }
 constexpr int fused_wave_lds(int d, int mt) { return ds_tile_lds(d, mt) + 32 * kt_stride(d); }
 
+// One wave tells another of its workgroup how far it is: what its lanes have written to LDS and read from it until here comes
+// before the counter, and what the waiting wave does there after it.
+__device__ __forceinline__ void lds_post(int *counter, int value, int lane)
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    if (lane == 0) __hip_atomic_store(counter, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_wait(const int *counter, int value)
+{
+    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < value) {}
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 constexpr int WV = 8;           // waves per workgroup (one workgroup per CU)
 template <int DR, int MT, bool DQ, bool ONE, bool F, bool ZL = false>
 __device__ __forceinline__ void dkdv_body(
@@ -482,8 +495,9 @@ __device__ __forceinline__ void dkdv_body(
     // PAIR (d = 32, more than 128 latents): the dQ accumulators of all latents would take more than 64 registers, so two
     // waves share a token tile, each with half of the latent tiles.  At the end of the tile the first hands its part of dK
     // to the second and takes that one's part of dV (16 values a lane, through the dS tiles, which are free by then); the
-    // two wait for each other by counters in LDS, not at a barrier of the workgroup, which would bring all eight waves
-    // into step.  (262144 tokens, 8 heads, 256 latents: a dQ kernel of its own 283 us and dK/dV 235, this one 320; 32 x 8
+    // two wait for each other by counters in LDS (lds_post, lds_wait), not at a barrier of the workgroup, which would bring
+    // all eight waves into step.  Every wait ends: both waves are in the workgroup, and they take the same token tiles, since
+    // `tile` and `stride` depend on wave >> 1 only.  (262144 tokens, 8 heads, 256 latents: a dQ kernel of its own 283 us and dK/dV 235, this one 320; 32 x 8
     // heads, 4096 tokens, 128 latents without PAIR: training 316 -> 248 us.)
     constexpr bool PAIR = DQ && dkdv_pair(D, MT);
     static_assert(!PAIR || MT % 2 == 0, "the latent tiles are halved");
@@ -516,7 +530,7 @@ __device__ __forceinline__ void dkdv_body(
     // c - delta cancels where one latent dominates a token, down to a single latent.
     constexpr bool ZPACK = PACK && DQ;
     extern __shared__ __attribute__((aligned(16))) u32x4 img[];   // [MT][PER_TILE][64 lanes]
-    __shared__ volatile int posted[PAIR ? 8 : 1], taken[PAIR ? 8 : 1];   // PAIR: parts handed over / picked up so far
+    __shared__ int posted[PAIR ? 8 : 1], taken[PAIR ? 8 : 1];   // PAIR: parts handed over / picked up so far
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
@@ -878,8 +892,7 @@ __device__ __forceinline__ void dkdv_body(
                 // four 8-byte stores of four latents each.  The product wants it the other way round (column =
                 // latent, 8 consecutive tokens per lane): four transposing reads, each four tokens of one latent.
                 if constexpr (PAIR) {   // the other wave has what was left here at the end of the tile before
-                    if (t == 0) while (taken[wave ^ 1] < round) {}
-                    compiler_fence();
+                    if (t == 0) lds_wait(taken + (wave ^ 1), round);
                 }
                 uint16_t *drow = ds_t + l32 * kDsStride + 4 * hh;
                 *reinterpret_cast<u32x2 *>(drow) = u32x2{d0[0], d0[1]};
@@ -931,9 +944,7 @@ __device__ __forceinline__ void dkdv_body(
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 give[64 * i] = make_float4(part[4 * i], part[4 * i + 1], part[4 * i + 2], part[4 * i + 3]);
-            ++round;
-            compiler_fence();
-            if (lane == 0) posted[wave] = round;   // (a wave's LDS operations complete in order)
+            lds_post(posted + wave, ++round, lane);
         }
         // What was requested at the top of this tile is taken over here, ahead of the tile's stores: memory
         // operations complete in order, so taking it over after them (at the top of the next tile) would make the
@@ -948,8 +959,7 @@ __device__ __forceinline__ void dkdv_body(
         dl_cur = pinned(delta_next);
         compiler_fence();
         if constexpr (PAIR) {
-            while (posted[wave ^ 1] < round) {}
-            compiler_fence();
+            lds_wait(posted + (wave ^ 1), round);
             const float4 *get = reinterpret_cast<const float4 *>(ds_t + (1 - 2 * half) * fused_wave_lds(D, MT)) + lane;
             f32x16 &mine = half ? acc2[0] : acc1[0];
 #pragma unroll
@@ -957,8 +967,7 @@ __device__ __forceinline__ void dkdv_body(
                 const float4 o = get[64 * i];
                 mine[4 * i] += o.x; mine[4 * i + 1] += o.y; mine[4 * i + 2] += o.z; mine[4 * i + 3] += o.w;
             }
-            compiler_fence();
-            if (lane == 0) taken[wave] = round;
+            lds_post(taken + wave, round, lane);
         }
         const bool has_dv = !PAIR || half == 0, has_dk = !PAIR || half != 0;
         // registers 4 q .. 4 q + 3 of an accumulator: columns (16 hv +) 8 q + 4 hh .. + 3 of this lane's token
