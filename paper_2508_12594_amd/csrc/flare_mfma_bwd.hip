@@ -530,7 +530,7 @@ __device__ __forceinline__ void dkdv_body(
     // c - delta cancels where one latent dominates a token, down to a single latent.
     constexpr bool ZPACK = PACK && DQ;
     extern __shared__ __attribute__((aligned(16))) u32x4 img[];   // [MT][PER_TILE][64 lanes]
-    __shared__ int posted[PAIR ? 8 : 1], taken[PAIR ? 8 : 1];   // PAIR: parts handed over / picked up so far
+    __shared__ int posted[PAIR ? WV : 1], taken[PAIR ? WV : 1];   // PAIR: parts handed over / picked up so far
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
@@ -541,7 +541,7 @@ __device__ __forceinline__ void dkdv_body(
     constexpr float kap = 0.f;                  // w[n] = 2^(kap - lse_dec2[n])
 
     if constexpr (PAIR) {
-        if (tid < 8) { posted[tid] = 0; taken[tid] = 0; }
+        if (tid < WV) { posted[tid] = 0; taken[tid] = 0; }
     }
     // ---- build the operand images ----
     {
@@ -1017,11 +1017,11 @@ __device__ __forceinline__ void dkdv_body(
     }
 
     if constexpr (DQ) {
-        // The eight waves add their dQ partials in wave order (fixed, so the bits are reproducible) in a
+        // The waves add their dQ partials in wave order (fixed, so the bits are reproducible) in a
         // [32*MT][D] fp32 buffer that reuses the image memory, then the workgroup stores its slot.
         float *red = reinterpret_cast<float *>(img);
         constexpr int STEP = PAIR ? 2 : 1;   // (the two halves of the latents side by side)
-        for (int w = 0; w < 8; w += STEP) {
+        for (int w = 0; w < WV; w += STEP) {
             __syncthreads();   // first pass: every wave is done with the images
             if (wave / STEP == w / STEP) {
 #pragma unroll
@@ -1045,7 +1045,7 @@ __device__ __forceinline__ void dkdv_body(
         const int mleft = mend - m0;
         float *out = dq_part + (((size_t)bh * gridDim.x + gp.x) * Mtot + m0) * DR;
         constexpr int PCS = DR / 4;                             // float4 pieces of a DR-element row
-        for (int i = tid; i < 32 * MT * PCS; i += 512) {        // latent i / PCS, columns 4 (i % PCS) ..
+        for (int i = tid; i < 32 * MT * PCS; i += 64 * WV) {   // latent i / PCS, columns 4 (i % PCS) ..
             const int lat = i / PCS, pc = i % PCS;
             if (lat < mleft)
                 *reinterpret_cast<float4 *>(out + (size_t)lat * DR + 4 * pc) =
@@ -1064,10 +1064,10 @@ __device__ __forceinline__ void dkdv_body(
     q, k, v, dy, z, lse_enc, dz_bh, eps_bh, lse_dec2, delta, ld_mul, dk, dv, acc32, dq_part, ts, H, N, Mtot, m0, mend, c2, scale
 
 // Both variants in one launch, each workgroup taking the one that the plan names for its (b,h): one launch less per step
-//  (a launch whose workgroups all leave at once still costs 4-6 us).  Both bodies share the kernel's registers,
+// (a launch whose workgroups all leave at once still costs 4-6 us).  Both bodies share the kernel's registers,
 // which at one workgroup per CU costs nothing.
 template <int DR, int MT, bool DQ, bool F, bool ZL = false>
-__global__ __launch_bounds__(512, 1) void bwd_dkdv_planned_kernel(FLARE_DKDV_PARAMS)
+__global__ __launch_bounds__(64 * WV, 1) void bwd_dkdv_planned_kernel(FLARE_DKDV_PARAMS)
 {
     extern __shared__ __attribute__((aligned(16))) u32x4 img[];
     __shared__ float red[64];
@@ -1134,7 +1134,7 @@ int mfma_dkdv_blocks(const flare_shape &s)
 {
     const int BH = s.B * s.H;
     const int tiles = (s.N + 31) / 32;
-    const int MT = lat_eff(s.M) / 32, waves = (mfma_dq_fused(s) && dkdv_pair(padded_dim(s.d), MT)) ? 4 : 8;   // token tiles at a time
+    const int MT = lat_eff(s.M) / 32, waves = (mfma_dq_fused(s) && dkdv_pair(padded_dim(s.d), MT)) ? WV / 2 : WV;   // token tiles at a time
     const int most = BH <= 256 ? (256 + BH - 1) / BH : 4;   // one 8-wave workgroup per CU
     const int limit = min(4 * most, (tiles + waves - 1) / waves);
     // (setup: the operand images and the sum of the waves' dQ, 20 us beside 4.9 us a step at 256 latents and d = 16)
@@ -1178,24 +1178,24 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
     if (zlo || s.d == 4 || (!fuse && !(s.d == 32 && MT == 7))) MT = MT <= 2 ? MT : MT <= 4 ? 4 : 8;
     if (fuse && dkdv_pair(s.d, MT)) MT += MT % 2;   // halved between two waves
     const int na = (zlo ? 5 : 4) * KS + 1;
-    size_t lds = (size_t)MT * (na + 4 * HV) * 1024 + (fuse ? 8 * fused_wave_lds(pd, MT) * 2 : 0);
+    size_t lds = (size_t)MT * (na + 4 * HV) * 1024 + (fuse ? WV * fused_wave_lds(pd, MT) * 2 : 0);
     MergeDz merge = merge_in;
     merge.lds = (unsigned)lds;
     if (merge.parts) lds += (size_t)s.M * (s.d + 1) * 4;
     const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *vv = (const bf16_t *)v, *gg = (const bf16_t *)dy;
     const bool f16 = s.dtype == FLARE_F16;
-#define FLARE_DKDV_LAUNCH(KERN, THREADS)                                                                         \
+#define FLARE_DKDV_LAUNCH(KERN)                                                                                  \
     do {                                                                                                         \
         auto kern = KERN;                                                                                        \
-        kern<<<grid, THREADS, lds, stream>>>(qq, kk, vv, gg, z, lse_enc, lse_dec2, delta, ld_mul, \
+        kern<<<grid, 64 * WV, lds, stream>>>(qq, kk, vv, gg, z, lse_enc, lse_dec2, delta, ld_mul, \
                                              (bf16_t *)dk, (bf16_t *)dv, acc32, dq_part, tok_stride(s), s.H,     \
                                              s.N, s.M, m0, mend, c2, scale, merge);                                    \
     } while (0)
     LaunchTimer t(KID_BWD_DKDV, stream);
 #define FLARE_DKDV(DD, MTT, LO)                                                                 \
     do {                                                                                        \
-        if (f16) FLARE_DKDV_LAUNCH((bwd_dkdv_planned_kernel<DD, MTT, LO, true>), 512);          \
-        else FLARE_DKDV_LAUNCH((bwd_dkdv_planned_kernel<DD, MTT, LO, false>), 512);             \
+        if (f16) FLARE_DKDV_LAUNCH((bwd_dkdv_planned_kernel<DD, MTT, LO, true>));               \
+        else FLARE_DKDV_LAUNCH((bwd_dkdv_planned_kernel<DD, MTT, LO, false>));                  \
     } while (0)
 #define FLARE_DKDV_POW2(DD, LO)                     \
     switch (MT) {                                   \
@@ -1220,8 +1220,8 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
     } else if (s.d == 16 && fuse && zlo) {
 #define FLARE_DKDV_Z(MTT)                                                                          \
     do {                                                                                           \
-        if (f16) FLARE_DKDV_LAUNCH((bwd_dkdv_planned_kernel<16, MTT, true, true, true>), 512);     \
-        else FLARE_DKDV_LAUNCH((bwd_dkdv_planned_kernel<16, MTT, true, false, true>), 512);        \
+        if (f16) FLARE_DKDV_LAUNCH((bwd_dkdv_planned_kernel<16, MTT, true, true, true>));          \
+        else FLARE_DKDV_LAUNCH((bwd_dkdv_planned_kernel<16, MTT, true, false, true>));             \
     } while (0)
         switch (MT) {
             case 1: FLARE_DKDV_Z(1); break;

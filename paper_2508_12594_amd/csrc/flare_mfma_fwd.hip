@@ -1429,8 +1429,9 @@ namespace {
 // Combine the per-chunk results of the decode (M > 256, d = 32): for token n of (b,h),
 //   lse = log sum_c exp(lse_c),   y = sum_c exp(lse_c - lse) y_c        (softmax over all M latents).
 // Writes y in the caller's layout and, when asked, lse_dec (natural log).
-// thread = token; the partial rows are [chunk][b*h][n][DR] in the storage type, the partial lse [chunk][b*h][n].
-template <int DR, bool F>
+// thread = token; the partial rows are [chunk][b*h][n][32] in the storage type, the partial lse [chunk][b*h][n].
+constexpr int kMergeDim = 32;
+template <bool F>
 __global__ __launch_bounds__(256) void decode_merge_kernel(
     const bf16_t *__restrict__ y_part, const float *__restrict__ lse_part, int chunks, bf16_t *__restrict__ y,
     float *__restrict__ lse_out, TokStride ts, int H, int N, size_t rows_all)
@@ -1441,15 +1442,15 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(
     const size_t row = (size_t)bh * N + n;
     float mx = -INFINITY;
     for (int c = 0; c < chunks; ++c) mx = fmaxf(mx, lse_part[(size_t)c * rows_all + row]);
-    float acc[DR], tot = 0.f;
+    float acc[kMergeDim], tot = 0.f;
 #pragma unroll
-    for (int j = 0; j < DR; ++j) acc[j] = 0.f;
+    for (int j = 0; j < kMergeDim; ++j) acc[j] = 0.f;
     for (int c = 0; c < chunks; ++c) {
         const float w = __expf(lse_part[(size_t)c * rows_all + row] - mx);
         tot += w;
-        const bf16_t *src = y_part + ((size_t)c * rows_all + row) * DR;
+        const bf16_t *src = y_part + ((size_t)c * rows_all + row) * kMergeDim;
 #pragma unroll
-        for (int j = 0; j < DR; j += 4) {
+        for (int j = 0; j < kMergeDim; j += 4) {
             const u32x2 t = *reinterpret_cast<const u32x2 *>(src + j);
             acc[j] = fmaf(w, elem_lo<F>(t[0]), acc[j]);
             acc[j + 1] = fmaf(w, elem_hi<F>(t[0]), acc[j + 1]);
@@ -1460,7 +1461,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(
     const float inv = 1.f / tot;
     const size_t trow = tok_base(ts, bh, H) + tok_off(ts, n);
 #pragma unroll
-    for (int j = 0; j < DR; j += 4) {
+    for (int j = 0; j < kMergeDim; j += 4) {
         u32x2 w;
         w[0] = pack_elems<F>(acc[j] * inv, acc[j + 1] * inv);
         w[1] = pack_elems<F>(acc[j + 2] * inv, acc[j + 3] * inv);
@@ -1470,7 +1471,6 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(
 }
 
 // The same for fp32 rows (flare_shape.y_f32): fp32 partial rows in, fp32 y out.
-template <int DR>
 __global__ __launch_bounds__(256) void decode_merge_f32_kernel(
     const float *__restrict__ y_part, const float *__restrict__ lse_part, int chunks, float *__restrict__ y,
     float *__restrict__ lse_out, TokStride ts, int H, int N, size_t rows_all)
@@ -1481,15 +1481,15 @@ __global__ __launch_bounds__(256) void decode_merge_f32_kernel(
     const size_t row = (size_t)bh * N + n;
     float mx = -INFINITY;
     for (int c = 0; c < chunks; ++c) mx = fmaxf(mx, lse_part[(size_t)c * rows_all + row]);
-    float acc[DR], tot = 0.f;
+    float acc[kMergeDim], tot = 0.f;
 #pragma unroll
-    for (int j = 0; j < DR; ++j) acc[j] = 0.f;
+    for (int j = 0; j < kMergeDim; ++j) acc[j] = 0.f;
     for (int c = 0; c < chunks; ++c) {
         const float w = __expf(lse_part[(size_t)c * rows_all + row] - mx);
         tot += w;
-        const float *src = y_part + ((size_t)c * rows_all + row) * DR;
+        const float *src = y_part + ((size_t)c * rows_all + row) * kMergeDim;
 #pragma unroll
-        for (int j = 0; j < DR; j += 4) {
+        for (int j = 0; j < kMergeDim; j += 4) {
             const float4 t = *reinterpret_cast<const float4 *>(src + j);
             acc[j] = fmaf(w, t.x, acc[j]);
             acc[j + 1] = fmaf(w, t.y, acc[j + 1]);
@@ -1500,7 +1500,7 @@ __global__ __launch_bounds__(256) void decode_merge_f32_kernel(
     const float inv = 1.f / tot;
     float *dst = y + tok_base(ts, bh, H) + tok_off(ts, n);
 #pragma unroll
-    for (int j = 0; j < DR; j += 4)
+    for (int j = 0; j < kMergeDim; j += 4)
         *reinterpret_cast<float4 *>(dst + j) = make_float4(acc[j] * inv, acc[j + 1] * inv, acc[j + 2] * inv, acc[j + 3] * inv);
     if (lse_out) lse_out[row] = mx + __logf(tot);
 }
@@ -1599,13 +1599,13 @@ static int decode_all(const flare_shape &s, const void *q, const void *k, const 
         const bf16_t *y_part = static_cast<const bf16_t *>(ws);
         LaunchTimer t(KID_DECODE_MERGE, stream);
         if (s.y_f32)
-            decode_merge_f32_kernel<32><<<grid, 256, 0, stream>>>(static_cast<const float *>(ws), lse_part, C, (float *)y,
+            decode_merge_f32_kernel<<<grid, 256, 0, stream>>>(static_cast<const float *>(ws), lse_part, C, (float *)y,
                                                                   lse_out, tok_stride(s), s.H, s.N, rows);
         else if (s.dtype == FLARE_F16)
-            decode_merge_kernel<32, true><<<grid, 256, 0, stream>>>(y_part, lse_part, C, (bf16_t *)y, lse_out,
+            decode_merge_kernel<true><<<grid, 256, 0, stream>>>(y_part, lse_part, C, (bf16_t *)y, lse_out,
                                                                     tok_stride(s), s.H, s.N, rows);
         else
-            decode_merge_kernel<32, false><<<grid, 256, 0, stream>>>(y_part, lse_part, C, (bf16_t *)y, lse_out,
+            decode_merge_kernel<false><<<grid, 256, 0, stream>>>(y_part, lse_part, C, (bf16_t *)y, lse_out,
                                                                      tok_stride(s), s.H, s.N, rows);
         return check_launch();
     }
