@@ -984,7 +984,10 @@ int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t 
 }  // namespace
 
 // Chunks of tokens of the latent-major kernels: enough for kCuWaves waves per CU, at least one stage of the encode and kMinChunk
-// tokens (shorter ones would cost more in slots to merge than they gain) and at most 8192 tokens long (a chunk's sums are taken one after the other in fp32).
+// tokens (shorter ones would cost more in slots to merge than they gain) and at most 8192 tokens long.  A chunk's sums are
+// taken one after the other in fp32, so fewer, longer chunks are less exact and are not taken even where they would be
+// faster (8 heads, 13407 tokens, 44 latents, d = 32 by 30 chunks: z off by 2.5e-7, by these 105 1.7e-7; 8 heads, 19358 tokens, 18 latents:
+// forward 22.5 us by 31, 25 by 76).
 Split mfma32_split(const flare_shape &s)
 {
     constexpr int kMinChunk = 128;
@@ -992,20 +995,22 @@ Split mfma32_split(const flare_shape &s)
     const LatentGeom g = latent_geom(s.M, tile * 2);
     const int stage = 32 * g.TG;
     const long long per = (long long)s.B * s.H * g.zdim;                 // workgroups of a chunk (any shape may be asked about)
-    const int stages = (s.N + stage - 1) / stage, places = 256 * (kCuWaves / (g.G * g.TG));
-    const int least = (stages + 8192 / stage - 1) / (8192 / stage);      // (a stage divides 8192)
-    const int fill = (int)((places + per - 1) / per), cap = min((s.N + kMinChunk - 1) / kMinChunk, stages);
+    const long long waves = per * g.G * g.TG;
+    const int stages = (s.N + stage - 1) / stage, cap = min((s.N + kMinChunk - 1) / kMinChunk, stages);
+    const int fill = min((int)((256 * kCuWaves + waves - 1) / waves), cap);
+    const int len = min((stages + fill - 1) / fill * stage, 8192), least = (s.N + len - 1) / len;   // (a stage divides 8192)
+    const int places = 256 * (kCuWaves / (g.G * g.TG));
     int want = least;
     if (per <= places) {
-        // (2 x 16 heads, 152439 tokens, 164 latents: 16 chunks fill the chip, but 19 are the fewest; 24 are a third faster)
+        // More of them where they share the chip more evenly (2 x 16 heads, 152439 tokens, 164 latents: 16 chunks fill the chip, but
+        // 19 are the fewest; 24 are a third faster).
         int limit = min(cap, 2 * (fill > least ? fill : least));
         if (limit > fill && (size_t)s.B * s.H * limit * s.M * (s.d + 2) * 4 > FLARE_STATIC_SCRATCH_BYTES / 2)
             limit = min(cap, fill);
-        // (workgroups of eight waves and up to 64 latents: see round_blocks; the others have enough waves without it)
-        want = round_blocks((int)per, places / 256, stages, 1, 1, fill, limit, places == 512 && g.G <= 2 ? 5 : kNever, least);
+        want = round_blocks((int)per, places / 256, stages, 1, 1, least, limit, kNever, least);
     }
-    const int len = (stages + want - 1) / want * stage;
-    return Split{(s.N + len - 1) / len, len};
+    const int chunk = (stages + want - 1) / want * stage;
+    return Split{(s.N + chunk - 1) / chunk, chunk};
 }
 
 // The decode and dK/dV kernels merge the slots where these are few and the merged rows fit beside all latents' planes.
