@@ -501,18 +501,17 @@ constexpr int kDecodeTargetBlocks = 512;
 // workgroups and the others with two, by 21 none.  Of counts that cost nearly the same (5 %) the largest: two on a CU cover
 // each other's waits.  (3 x 8 heads, 50021 tokens, 200 latents: d = 8 forward 126 -> 91 us, d = 16 training 388 -> 269 us;
 // 5 x 8 heads, 30000 tokens, 128 latents, d = 32 505 -> 381 us.)
-// More than one round of them, up to `limit` a (b,h), only where that is 10 % cheaper: 144 (b,h) fill 256 places with one
+// More than one round of them, up to `limit` a (b,h), only where that is `less` per cent cheaper: 144 (b,h) fill 256 places with one
 // workgroup each to 56 %, and so with two, by five to 94 %.  (5 x 8 heads, 30703 tokens, 512 latents, d = 16 training
-// 803 us with counts rounded up, 555; 9 x 16 heads, 36229 tokens, 136 latents, fp32 3973 -> 3402.)
+// 803 us with counts rounded up, 555; 9 x 16 heads, 36229 tokens, 136 latents, fp32 3608 -> 3336.)
 // from: the fewest there may be.
 // hide: with at least so many steps a wave (kNever: whatever they are) a workgroup is not left alone on its CU where two
 // fit.  The cost above takes the two to share the CU's time, but where a step is short, few latents, they wait for memory
 // in turn, and one alone takes as long as two: counts below that are better only where each workgroup has a price of its
-// own beside its few steps (slots to merge, operands to load).  (fp32, 4 heads, 119557 tokens, 50 latents: dQ 58 us by 63 chunks,
-// 41 by 117; 4 x 16 heads, 6181 tokens, 64 latents: 51 us by 4, 37 by 7; bf16, 8 heads, 26779 tokens, 32 latents: forward 17.9 us
-// by 32 workgroups in the decode, 16.4 by 64; but 2 x 8 heads, 5999 tokens, 128 latents: decode 12.6 us by 16, 14.9 by 32.)
+// own beside its few steps (slots to merge, operands to load).  (fp16, 8 heads, 26779 tokens, 32 latents: forward 17.9 us by 32
+// workgroups in the decode, 16.4 by 64; but 2 x 8 heads, 5999 tokens, 128 latents: decode 12.6 us by 16, 14.9 by 32.)
 constexpr int kNever = 1 << 20;
-inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int most, int limit, int hide, int from = 1)
+inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int most, int limit, int hide, int from = 1, int less = 10)
 {
     constexpr int kCus = 256;
     auto cost = [&](int b) {
@@ -538,7 +537,7 @@ inline int round_blocks(int BH, int cu, int steps, int waves, int setup, int mos
             if (20 * cost(b) <= 21 * least) best = b;
     for (int b = top; b < limit;) {
         b = widest(b + 1, limit);
-        if (10 * cost(b) < 9 * cost(best)) best = b;
+        if (100 * cost(b) < (100 - less) * cost(best)) best = b;
     }
     return best;
 }

@@ -1002,12 +1002,14 @@ Split mfma32_split(const flare_shape &s)
     const int places = 256 * (kCuWaves / (g.G * g.TG));
     int want = least;
     if (per <= places) {
-        // More of them where they share the chip more evenly (2 x 16 heads, 152439 tokens, 164 latents: 16 chunks fill the chip, but
-        // 19 are the fewest; 24 are a third faster).
+        // More of them where they share the chip more evenly, as far as the slots fit the static scratch (what fits there still
+        // does): 2 x 16 heads, 152439 tokens, 164 latents: 16 chunks fill the chip, but 19 are the fewest; 24 are a third faster.
+        // 3 x 8 heads, 117199 tokens, 256 latents: 22 are 528 workgroups for 512 places, 763 us forward; 42, 623 us.  Long chunks
+        // move for 4 per cent: their slots cost little beside them.
+        const size_t slot = (size_t)s.B * s.H * s.M * (s.d + 2) * 4, room = FLARE_STATIC_SCRATCH_BYTES - 1024;
         int limit = min(cap, 2 * (fill > least ? fill : least));
-        if (limit > fill && (size_t)s.B * s.H * limit * s.M * (s.d + 2) * 4 > FLARE_STATIC_SCRATCH_BYTES / 2)
-            limit = min(cap, fill);
-        want = round_blocks((int)per, places / 256, stages, 1, 1, least, limit, kNever, least);
+        if (limit * slot > room) limit = (int)(room / slot) > least ? (int)(room / slot) : least;
+        want = round_blocks((int)per, places / 256, stages, 1, 1, least, limit, kNever, least, stages >= 16 * least ? 4 : 10);
     }
     const int chunk = (stages + want - 1) / want * stage;
     return Split{(s.N + chunk - 1) / chunk, chunk};

@@ -70,6 +70,14 @@ def test_fp32_chunks_are_short_enough(lib, B, H, N, M, d, chunks):
     assert f // (4 * B * H * M * (d + 2)) >= chunks
 
 
+@pytest.mark.parametrize("B,H,N,M,d", [(2, 8, 6397, 357, 32), (1, 8, 8472, 543, 32), (4, 16, 8983, 1766, 16), (3, 8, 117199, 256, 16),
+                                       (1, 16, 12731, 176, 32)])
+def test_more_fp32_chunks_still_fit_the_static_scratch(lib, B, H, N, M, d):
+    """Taking more chunks than the chip calls for must not make flare_forward_static refuse a shape (32 MiB)."""
+    f, _ = binding.workspace_bytes(B, H, N, M, d, binding.FLARE_F32)
+    assert f <= 32 << 20
+
+
 @pytest.mark.parametrize("B,H,N,M,d,slots", [(56, 1, 2285, 136, 32, 24), (5, 8, 3695, 89, 32, 24), (50, 1, 3206, 224, 16, 24),
                                              (14, 4, 2509, 149, 32, 24), (3, 16, 2573, 104, 32, 24)])
 def test_backward_workspace_holds_the_slots_that_are_written(lib, B, H, N, M, d, slots):
