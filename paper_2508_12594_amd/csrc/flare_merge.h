@@ -46,61 +46,81 @@ struct MergeZ {
 };
 
 // D / 4 threads per latent own four columns each; the slots are folded in order behind one maximum (exact in any order),
-// so the bits depend on the slot count only.  A slot with m = -inf is empty.  The slots come four at a time, everything of
-// four requested before anything is used: with all of kInlineSlots in flight the decode kernels around this took every
-// register (68 ... 122 without it), and where their workgroups no longer all fit on the chip, half as much time again (12 x 8
-// heads, 56656 tokens, 32 latents: 151 us, 105 us like this).
-template <int D>
-__device__ __forceinline__ void merge_z_row(const MergeZ &g, int bh, int M, int m, int j, float *z_lds, bool write)
+// so the bits depend on the slot count only.  A slot with m = -inf is empty.  R rows (`step` apart) go together, and the
+// slots come four at a time, everything of four requested before anything is used: with all of kInlineSlots in flight the decode
+// kernels around this took every register (68 ... 122 without it), and where their workgroups no longer all fit on the chip, half
+// as much time again (12 x 8 heads, 56656 tokens, 32 latents: 151 us, 105 us like this).
+template <int D, int R, typename Put>
+__device__ __forceinline__ void merge_z_row(const MergeZ &g, int bh, int M, int m1, int m0, int step, int j, const Put &put,
+                                            bool write)
 {
     constexpr int P = 4;
-    const size_t s0 = (size_t)bh * g.parts * M + m;   // slot p of this latent: s0 + p * M
-    float gm = -INFINITY;
+    float gm[R], l[R];
+    float4 o[R];
+    size_t s0[R];                                         // slot p of row r: s0[r] + p * M
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        s0[r] = (size_t)bh * g.parts * M + min(m0 + r * step, m1 - 1);
+        gm[r] = -INFINITY;
+        l[r] = 0.f;
+        o[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
     if (g.parts > P) {
 #pragma unroll
-        for (int p = 0; p < kInlineSlots; ++p) gm = fmaxf(gm, g.m_part[s0 + (size_t)min(p, g.parts - 1) * M]);
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int p = 0; p < kInlineSlots; ++p) gm[r] = fmaxf(gm[r], g.m_part[s0[r] + (size_t)min(p, g.parts - 1) * M]);
     }
-    float l = 0.f;
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 1
     for (int p0 = 0; p0 < g.parts; p0 += P) {
-        float mp[P], lp[P];
-        float4 oc[P];
+        float mp[R][P], lp[R][P];
+        float4 oc[R][P];
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-            const size_t slot = s0 + (size_t)min(p0 + i, g.parts - 1) * M;
-            mp[i] = g.m_part[slot];
-            lp[i] = g.l_part[slot];
-            oc[i] = *reinterpret_cast<const float4 *>(g.o_part + slot * D + 4 * j);
-        }
-        if (g.parts <= P) gm = fmaxf(fmaxf(mp[0], mp[1]), fmaxf(mp[2], mp[3]));
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-            const float w = (p0 + i >= g.parts || mp[i] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mp[i] - gm);
-            l = fmaf(lp[i], w, l);
-            o.x = fmaf(oc[i].x, w, o.x);
-            o.y = fmaf(oc[i].y, w, o.y);
-            o.z = fmaf(oc[i].z, w, o.z);
-            o.w = fmaf(oc[i].w, w, o.w);
+            for (int i = 0; i < P; ++i) {
+                const size_t slot = s0[r] + (size_t)min(p0 + i, g.parts - 1) * M;
+                mp[r][i] = g.m_part[slot];
+                lp[r][i] = g.l_part[slot];
+                oc[r][i] = *reinterpret_cast<const float4 *>(g.o_part + slot * D + 4 * j);
+            }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (g.parts <= P) gm[r] = fmaxf(fmaxf(mp[r][0], mp[r][1]), fmaxf(mp[r][2], mp[r][3]));
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                const float w = (p0 + i >= g.parts || mp[r][i] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mp[r][i] - gm[r]);
+                l[r] = fmaf(lp[r][i], w, l[r]);
+                o[r].x = fmaf(oc[r][i].x, w, o[r].x);
+                o[r].y = fmaf(oc[r][i].y, w, o[r].y);
+                o[r].z = fmaf(oc[r][i].z, w, o[r].z);
+                o[r].w = fmaf(oc[r][i].w, w, o[r].w);
+            }
         }
     }
-    const float inv = 1.f / l;
-    const size_t idx = (size_t)bh * M + m;
-    o = make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
-    if (z_lds) *reinterpret_cast<float4 *>(z_lds + (size_t)m * D + 4 * j) = o;
-    if (write) {
-        *reinterpret_cast<float4 *>(g.z + idx * D + 4 * j) = o;
-        if (j == 0) g.lse_enc[idx] = g.f32 ? lse_nat(gm, l) : (gm + log2f(l)) * kLn2;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int m = m0 + r * step;
+        if (m >= m1) continue;
+        const float inv = 1.f / l[r];
+        const size_t idx = (size_t)bh * M + m;
+        const float4 x = make_float4(o[r].x * inv, o[r].y * inv, o[r].z * inv, o[r].w * inv);
+        put(m, j, x);
+        if (write) {
+            *reinterpret_cast<float4 *>(g.z + idx * D + 4 * j) = x;
+            if (j == 0) g.lse_enc[idx] = g.f32 ? lse_nat(gm[r], l[r]) : (gm[r] + log2f(l[r])) * kLn2;
+        }
     }
 }
-// Rows m0 .. m1 by the nt threads of a workgroup; z_lds (when given) gets them, and with `write` they go to global memory.
-template <int D>
+// Rows m0 .. m1 by the nt threads of a workgroup; put(m, j, x) gets columns 4 j ... of row m, and with `write` they go to global
+// memory.
+template <int D, int R, typename Put>
 __device__ __forceinline__ void merge_z_rows(const MergeZ &g, int bh, int M, int m0, int m1, int tid, int nt,
-                                             float *z_lds, bool write)
+                                             const Put &put, bool write)
 {
     constexpr int L = D / 4;
 #pragma unroll 1
-    for (int m = m0 + tid / L; m < m1; m += nt / L) merge_z_row<D>(g, bh, M, m, tid % L, z_lds, write);
+    for (int m = m0 + tid / L; m < m1; m += R * (nt / L)) merge_z_row<D, R>(g, bh, M, m1, m, nt / L, tid % L, put, write);
 }
 // ---- the variant of the last backward kernels ---------------------------------------------------
 // They exist with one and with two exponentials per score.
@@ -181,30 +201,37 @@ __device__ __forceinline__ float4 sum_slots_upto(const float *__restrict__ p, si
         if (i < n) add4(a, t[i]);
     return a;
 }
-// Row m (four columns, D / 4 lanes per row, called together) of dZ, scaled and rounded as its consumers want it, and eps_m
-// (in every lane of the row).
+// Row m (four columns, D / 4 lanes per row, called together) of dZ: the sum of its slots, and what else goes into it.
+struct DzRow { float4 a, z; float lse_enc; };
 template <int D>
-__device__ __forceinline__ float4 merge_dz_row(const float *__restrict__ part, const float *__restrict__ z,
-                                               const float *__restrict__ lse_enc, int bh, int M, int parts, int m,
-                                               int j, bool one_exp, bool round_bf16, float &eps)
+__device__ __forceinline__ DzRow load_dz_row(const float *__restrict__ part, const float *__restrict__ z,
+                                             const float *__restrict__ lse_enc, int bh, int M, int parts, int m, int j)
 {
-    constexpr int L = D / 4;
     const size_t idx = (size_t)bh * M + m, stride = (size_t)M * D;
     const float *p = part + ((size_t)bh * parts * M + m) * D + 4 * j;
-    const float4 zr = *reinterpret_cast<const float4 *>(z + idx * D + 4 * j);
-    const float le = lse_enc[idx];
-    float4 a = parts <= 4 ? sum_slots_upto<4>(p, stride, parts) : parts <= 8 ? sum_slots_upto<8>(p, stride, parts)
-                                                                : sum_slots_upto<kInlineSlots>(p, stride, parts);
+    DzRow r;
+    r.z = *reinterpret_cast<const float4 *>(z + idx * D + 4 * j);
+    r.lse_enc = lse_enc[idx];
+    r.a = parts <= 4 ? sum_slots_upto<4>(p, stride, parts) : parts <= 8 ? sum_slots_upto<8>(p, stride, parts)
+                                                                 : sum_slots_upto<kInlineSlots>(p, stride, parts);
+    return r;
+}
+// The row scaled and rounded as its consumers want it, and eps_m (in every lane of the row).
+template <int D>
+__device__ __forceinline__ float4 finish_dz_row(const DzRow &r, int j, bool one_exp, bool round_bf16, float &eps)
+{
+    constexpr int L = D / 4;
+    float4 a = r.a;
     if (one_exp) {                                   // the one-exponential kernels take dZ scaled by 2^-lse_enc2[m]
         // (of fp32 storage without the rounding of le log2 e, up to 1e-6 of 2^20)
-        const float em = round_bf16 ? exp2f(-le * kLog2e) : expf(-le);
+        const float em = round_bf16 ? exp2f(-r.lse_enc * kLog2e) : expf(-r.lse_enc);
         a = make_float4(a.x * em, a.y * em, a.z * em, a.w * em);
     }
     // The 16-bit kernels take dZ as a bf16 operand.  Rounding it here, before eps is formed, keeps
     // a[m][n] = <dZ_m, V_n - Z_m> an exact expression in the rounded dZ (eps and the products see the same
     // values), instead of leaving <V_n, rounding error> uncancelled in every score.
     if (round_bf16) a = make_float4(bf16_rounded(a.x), bf16_rounded(a.y), bf16_rounded(a.z), bf16_rounded(a.w));
-    float e = fmaf(a.w, zr.w, fmaf(a.z, zr.z, fmaf(a.y, zr.y, a.x * zr.x)));
+    float e = fmaf(a.w, r.z.w, fmaf(a.z, r.z.z, fmaf(a.y, r.z.y, a.x * r.z.x)));
 #pragma unroll
     for (int off = 1; off < L; off <<= 1) {          // fixed tree over the row's lanes (L is a power of two)
         const float o = __shfl_xor(e, off);
@@ -212,6 +239,13 @@ __device__ __forceinline__ float4 merge_dz_row(const float *__restrict__ part, c
     }
     eps = e;
     return a;
+}
+template <int D>
+__device__ __forceinline__ float4 merge_dz_row(const float *__restrict__ part, const float *__restrict__ z,
+                                               const float *__restrict__ lse_enc, int bh, int M, int parts, int m,
+                                               int j, bool one_exp, bool round_bf16, float &eps)
+{
+    return finish_dz_row<D>(load_dz_row<D>(part, z, lse_enc, bh, M, parts, m, j), j, one_exp, round_bf16, eps);
 }
 // What a consuming workgroup needs of one (b,h): the variant, and rows of dZ and eps: merged into `lds` (M * D, then M
 // floats; with `write` they and the plan also go to global memory, for a later kernel) or in global memory.  Ends with
@@ -225,18 +259,31 @@ __device__ __forceinline__ bool merged_dz(const MergeDz &g, const float *z, cons
     eps = g.eps + (size_t)bh * M;
     if (g.parts == 0) return g.plan[bh] != 0;
     constexpr int L = D / 4;
-    const bool one = bwd_one_exp_ok(g.ld_range, lse_enc, bh, g.parts, M, g.span, red);
+    // R rows a thread go together, all of their slots requested before the variant is decided (its test waits for memory too)
+    constexpr int R = D == 32 ? 2 : 1;
     const int j = threadIdx.x % L, rows = blockDim.x / L;
-    for (int m0 = 0; m0 < M; m0 += rows) {           // whole rows of lanes stay together (shuffles)
-        const int m = m0 + threadIdx.x / L;
-        float e;
-        const float4 a = merge_dz_row<D>(g.part, z, lse_enc, bh, M, g.parts, min(m, M - 1), j, one, round_bf16, e);
-        if (m < M) {
-            *reinterpret_cast<float4 *>(lds + (size_t)m * D + 4 * j) = a;
-            if (j == 0) lds[(size_t)M * D + m] = e;
-            if (write) {
-                *reinterpret_cast<float4 *>(g.dz + ((size_t)bh * M + m) * D + 4 * j) = a;
-                if (j == 0) g.eps[(size_t)bh * M + m] = e;
+    DzRow r[R];
+    auto load = [&](int m0) {
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+            r[i] = load_dz_row<D>(g.part, z, lse_enc, bh, M, g.parts, min(m0 + i * rows + (int)threadIdx.x / L, M - 1), j);
+    };
+    load(0);
+    const bool one = bwd_one_exp_ok(g.ld_range, lse_enc, bh, g.parts, M, g.span, red);
+    for (int m0 = 0; m0 < M; m0 += R * rows) {       // whole rows of lanes stay together (shuffles)
+        if (m0 > 0) load(m0);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int m = m0 + i * rows + threadIdx.x / L;
+            float e;
+            const float4 a = finish_dz_row<D>(r[i], j, one, round_bf16, e);
+            if (m < M) {
+                *reinterpret_cast<float4 *>(lds + (size_t)m * D + 4 * j) = a;
+                if (j == 0) lds[(size_t)M * D + m] = e;
+                if (write) {
+                    *reinterpret_cast<float4 *>(g.dz + ((size_t)bh * M + m) * D + 4 * j) = a;
+                    if (j == 0) g.eps[(size_t)bh * M + m] = e;
+                }
             }
         }
     }

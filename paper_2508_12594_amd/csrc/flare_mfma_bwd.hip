@@ -447,6 +447,10 @@ constexpr bool dkdv_pair(int d, int mt) { return d == 32 && mt > 4; }
 constexpr int ds_tile_lds(int d, int mt) { return dkdv_pair(d, mt) ? 64 * 16 * 2 : 32 * kDsStride; }
 constexpr int fused_wave_lds(int d, int mt) { return ds_tile_lds(d, mt) + 32 * kt_stride(d); }
 
+// operand images per latent tile: A-type ones (the last: corrections), then row images (RW1, RW2) x 2 k-steps
+constexpr int dkdv_a_images(int dr, bool dq, bool zl) { return (dq && !pack_dim(dr) && zl ? 5 : 4) * (padded_dim(dr) / 16) + 1; }
+constexpr int dkdv_images(int dr, bool dq, bool zl) { return dkdv_a_images(dr, dq, zl) + 4; }
+
 // One wave tells another of its workgroup how far it is: what its lanes have written to LDS and read from it until here comes
 // before the counter, and what the waiting wave does there after it.
 __device__ __forceinline__ void lds_post(int *counter, int value, int lane)
@@ -461,6 +465,33 @@ __device__ __forceinline__ void lds_wait(const int *counter, int value)
 }
 
 constexpr int WV = 8;           // waves per workgroup (one workgroup per CU)
+
+// The latents' rows of z and q and their lse_enc in LDS while the operand images are built from them: in the part that the
+// waves' dS and key tiles take afterwards.  (Each image reading its elements from global memory waited for them seven
+// times over, at 128 latents and d = 32.)
+template <int DR>
+struct LatentStage {
+    float *z, *lse;
+    bf16_t *q;
+    __device__ __forceinline__ LatentStage(void *at, int M)
+    {
+        z = static_cast<float *>(at);
+        q = reinterpret_cast<bf16_t *>(z + M * DR);
+        lse = reinterpret_cast<float *>(q + M * DR);
+    }
+    static constexpr int kBytes = DR * 6 + 4;   // per latent
+};
+template <int DR, int MT>
+__device__ __forceinline__ void stage_latents(void *at, const bf16_t *q, const float *z, const float *lse_enc, int M)
+{
+    static_assert(LatentStage<DR>::kBytes * 32 * MT <= WV * fused_wave_lds(padded_dim(DR), MT) * 2, "as long as the waves' tiles");
+    const LatentStage<DR> st(at, M);
+    const int tid = threadIdx.x, nt = 64 * WV;
+    for (int i = tid; i < M * DR / 4; i += nt) reinterpret_cast<float4 *>(st.z)[i] = reinterpret_cast<const float4 *>(z)[i];
+    for (int i = tid; i < M * DR / 4; i += nt) reinterpret_cast<u32x2 *>(st.q)[i] = reinterpret_cast<const u32x2 *>(q)[i];
+    for (int i = tid; i < M; i += nt) st.lse[i] = lse_enc[i];
+}
+
 template <int DR, int MT, bool DQ, bool ONE, bool F, bool ZL = false>
 __device__ __forceinline__ void dkdv_body(
     const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
@@ -513,9 +544,9 @@ __device__ __forceinline__ void dkdv_body(
     // in 30 000 left the bar, and that one for another reason (delta from the saved bf16 y), the lo term or not.
     constexpr bool ZLO = DQ && !pack_dim(DR) && ZL;
     static_assert(!ZL || (DQ && !pack_dim(DR)), "the extra image is for the fused dQ product at d = 16");
-    constexpr int NA = (ZLO ? 5 : 4) * KS + 1;  // A-type images per latent tile (the last one: corrections)
+    constexpr int NA = dkdv_a_images(DR, DQ, ZL), PER_TILE = dkdv_images(DR, DQ, ZL);
     constexpr int NR = 4 * HV;                  // row images per latent tile (RW1, RW2) x 2 k-steps
-    constexpr int PER_TILE = NA + NR;
+    static_assert(PER_TILE == NA + NR && ZLO == (NA == 5 * KS + 1), "as counted");
     constexpr bool PIPE = (D == 16);            // look one latent tile ahead where registers allow
     // d <= 8: the upper half of the padded contraction carries what otherwise needs products of its own.
     // Images: q' hi | lo in one (keys repeated in both lane halves), slots 8,9 of the dZ image = -eps
@@ -543,136 +574,6 @@ __device__ __forceinline__ void dkdv_body(
     if constexpr (PAIR) {
         if (tid < WV) { posted[tid] = 0; taken[tid] = 0; }
     }
-    // ---- build the operand images ----
-    {
-        const bf16_t *qh_ = q + (size_t)h * ts.sq + (size_t)m0 * DR;
-        const float *zb = z + ((size_t)bh * Mtot + m0) * DR;
-        const float *dzb = dz + (size_t)m0 * DR;   // (dz, eps: the rows of this (b,h), in global memory or merged into LDS)
-        const float *eb = eps + m0;
-        const float *leb = lse_enc + (size_t)bh * Mtot + m0;
-        // Padding latents (at or beyond mend; mleft = real ones from m0 on): loads are clamped to the last
-        // real latent and every value that could reach dK or dV is zero -- q, Z, dZ, eps, u and the ones
-        // that pick -delta -- so that a = c = 0 and dS = 0 whatever P and R come out as.
-        const int mleft = mend - m0;
-        for (int idx = tid; idx < MT * PER_TILE * 64; idx += 64 * WV) {
-            const int ln = idx & 63, sid = (idx >> 6) % PER_TILE, t = (idx >> 6) / PER_TILE;
-            const int r32 = ln & 31, hf = ln >> 5;
-            u32x4 w;
-            if (sid == NA - 1) {
-                // correction operand: slots 0,1 = -lse_enc2 (hi + lo pair), slots 2,3 = 1, else zero
-                const bool real = 32 * t + r32 < mleft;
-                const int mc = min(32 * t + r32, mleft - 1);
-                const float le2 = real ? leb[mc] * kLog2e : 0.f;
-                w[0] = hf == 0 ? split_pair<F>(-le2) : 0u;
-                w[1] = hf == 0 ? kOnePair<F> : 0u;
-                w[2] = 0u; w[3] = 0u;
-                // Slots 4-6 belong to the c product and slots 8,9 to the a product, whose operands are bf16
-                // whatever the storage type; the score products meet them with zeros in the token operand
-                // (and the a and c products meet slots 0-3 with zeros).  u <= 1 and finite 16-bit patterns of either type read as finite values
-                // of the other, so the foreign slots contribute exact zeros.
-                if constexpr (ONE) {   // slots 4,5,6 := u hi, u hi, u lo
-                    const uint32_t us = split_bf16_pair(real ? 1.f : 0.f);   // (the latent's factor of the c chain: 1)
-                    w[2] = hf == 0 ? ((us & 0xffffu) | (us << 16)) : 0u;
-                    w[3] = hf == 0 ? (us >> 16) : 0u;
-                }
-                if (hf == 1) {
-                    w[0] = split_bf16_pair(real ? -eb[mc] : 0.f);          // slots 8,9 := -eps (bf16: the a chain)
-                    if (!ONE && real) w[1] = 0x3f803f80u;                  // slots 10,11 := 1 (picks -delta, two exponentials)
-                }
-            } else if (sid < NA) {
-                const int kind = sid / KS, ks = sid % KS;          // 0 q' hi, 1 q' lo, 2 dZ, 3 Z hi, 4 Z lo (DQ only)
-                const bool real = 32 * t + r32 < mleft;
-                const int m = min(32 * t + r32, mleft - 1);
-                const int d0 = (D / 2) * hf + 8 * ks;
-                float x[8];
-                if (kind <= 1) {
-                    const u32x4 raw = row8_bf16<DR>(qh_ + (size_t)m * DR, PACK ? 0 : d0);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) { x[2 * i] = elem_lo<F>(raw[i]) * c2; x[2 * i + 1] = elem_hi<F>(raw[i]) * c2; }
-                } else {
-                    const bool is_z = kind >= 3;
-                    row8_f32<DR>((is_z ? zb : dzb) + (size_t)m * DR, (ZPACK && is_z) ? 0 : d0, x);
-                }
-                if (!real) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) x[i] = 0.f;
-                }
-                const bool want_lo = (kind == 1 || kind >= 4 || (PACK && kind == 0 && hf == 1) ||
-                                      (ZPACK && kind == 3 && hf == 1));
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    uint32_t a, b;
-                    if (kind <= 1) {   // q' feeds the score products: storage type
-                        a = rne_elem<F>(x[2 * i]); b = rne_elem<F>(x[2 * i + 1]);
-                        if (want_lo) {
-                            a = rne_elem<F>(x[2 * i] - elem_value<F>(a));
-                            b = rne_elem<F>(x[2 * i + 1] - elem_value<F>(b));
-                        }
-                    } else {
-                        a = rne_bf16(x[2 * i]); b = rne_bf16(x[2 * i + 1]);
-                        if (want_lo) {
-                            a = rne_bf16(x[2 * i] - __uint_as_float(a << 16));
-                            b = rne_bf16(x[2 * i + 1] - __uint_as_float(b << 16));
-                        }
-                    }
-                    w[i] = a | (b << 16);
-                }
-                if constexpr (DR == 4 && !ZPACK) {   // slots 4-7 of the Z image := its lo part (dY repeated there)
-                    if (kind == 3 && hf == 0) {
-#pragma unroll
-                        for (int i = 0; i < 2; ++i) {
-                            const uint32_t a = rne_bf16(x[2 * i] - __uint_as_float(w[i] << 16));
-                            const uint32_t b = rne_bf16(x[2 * i + 1] - __uint_as_float(w[i] & 0xffff0000u));
-                            w[2 + i] = a | (b << 16);
-                        }
-                    }
-                }
-                if (PACK && hf == 1 && kind == 2 && real) w[0] = split_bf16_pair(-eb[m]);   // slots 8,9 := -eps
-                if (PACK && !ZPACK && hf == 1 && kind == 3 && real) {                // slots 8,9,10 := u, u, u lo / 1, 1
-                    if constexpr (ONE) {
-                        const uint32_t us = split_bf16_pair(1.f);
-                        w[0] = (us & 0xffffu) | (us << 16);
-                        w[1] = us >> 16;
-                    } else {
-                        w[0] = 0x3f803f80u;
-                    }
-                }
-            } else {
-                const int rsid = sid - NA;                          // (which, hv, s2)
-                const int which = rsid / (2 * HV), hv = (rsid / 2) % HV, s2 = rsid % 2;
-                const int dd = WIDE ? r32 : 16 * hv + (r32 & 15);
-                const bool row_live = WIDE || r32 < 16;
-#pragma unroll
-                for (int i = 0; i < 8; i += 2) {
-                    float a, b;
-                    const int ma = 32 * t + perm_index(s2, hf, i), mb = 32 * t + perm_index(s2, hf, i + 1);
-                    const bool in = dd < DR;   // beyond the real head dimension every row image is zero
-                    const bool ina = in && ma < mleft, inb = in && mb < mleft;
-                    const float q0 = ina ? elem_value<F>(qh_[(size_t)ma * DR + dd]) : 0.f;
-                    const float q1 = inb ? elem_value<F>(qh_[(size_t)mb * DR + dd]) : 0.f;
-                    if (which == 0) {
-                        a = (row_live && ina) ? dzb[(size_t)ma * DR + dd] : 0.f;
-                        b = (row_live && inb) ? dzb[(size_t)mb * DR + dd] : 0.f;
-                    } else {
-                        a = row_live ? q0 : 0.f;
-                        b = row_live ? q1 : 0.f;
-                    }
-                    w[i / 2] = rne_bf16(a) | (rne_bf16(b) << 16);
-                }
-            }
-            img[idx] = w;
-        }
-    }
-    __syncthreads();
-
-    u32x4 w11;
-    w11[1] = 0u; w11[2] = 0u; w11[3] = 0u;
-    w11[0] = lower ? kOnePair<F> : 0u;
-    const bf16x8 ones_s = as_bf16x8(w11);        // the same in the type of the score products
-    w11[0] = lower ? 0u : 0x3f803f80u;
-    const bf16x8 ones_eps = as_bf16x8(w11);      // slots 8,9 = 1 (bf16): picks -eps out of the correction image
-    auto to_bf16 = [](bf16x8 x) { return as_bf16x8(to_bf16_row<F>(__builtin_bit_cast(u32x4, x))); };
-
     const bf16_t *kb = k + tok_base(ts, bh, H);
     const bf16_t *vb = v + tok_base(ts, bh, H);
     const bf16_t *gb = dy + tok_base(ts, bh, H);
@@ -688,6 +589,119 @@ __device__ __forceinline__ void dkdv_body(
         for (int s = 0; s < KS; ++s)
             t[s] = as_bf16x8(row8_bf16<DR>(base + tok_off(ts, n), (PACK && rep) ? 0 : (D / 2) * hh + 8 * s));
     };
+    // The first token tile's rows and statistics are requested before the operand images are built.
+    int tile = gp.x * TW + (PAIR ? wave >> 1 : wave);
+    bf16x8 kt[KS], vt[KS], gt[KS], ktn[KS], vtn[KS], gtn[KS];
+    float lse_next = 0.f, delta_next = 0.f;
+    if (tile < tiles) {
+        load_cols(kb, tile, kt, true);
+        load_cols(vb, tile, vt, false);
+        load_cols(gb, tile, gt, ZPACK);
+        const size_t row0 = (size_t)min(tile * 32 + l32, N - 1);
+        lse_next = lb[row0];
+        delta_next = db[row0];
+    }
+    // ---- build the operand images ----
+    {
+        // DQ: the latents' rows of q and z and their lse_enc were staged in the waves' part of the LDS (stage_latents), from where
+        // every image takes its own elements; dz, eps: the rows of this (b,h), in global memory or merged into LDS.
+        const LatentStage<DR> st(img + MT * PER_TILE * 64, mend - m0);
+        const bf16_t *qh_ = DQ ? st.q : q + (size_t)h * ts.sq + (size_t)m0 * DR;
+        const float *zb = DQ ? st.z : z + ((size_t)bh * Mtot + m0) * DR;
+        const float *leb = DQ ? st.lse : lse_enc + (size_t)bh * Mtot + m0;
+        const float *dzb = dz + (size_t)m0 * DR;
+        const float *eb = eps + m0;
+        // Padding latents (at or beyond mend; mleft = real ones from m0 on): reads are clamped to the last
+        // real latent and every value that could reach dK or dV is zero -- q, Z, dZ, eps, u and the ones
+        // that pick -delta -- so that a = c = 0 and dS = 0 whatever P and R come out as.
+        const int mleft = mend - m0;
+        // an image a wave and pass: which one it is, is the same for all its lanes
+#pragma unroll 1
+        for (int im = wave; im < MT * PER_TILE; im += WV) {
+            const int t = im / PER_TILE, sid = im % PER_TILE;
+            const int m = 32 * t + l32, mc = min(m, mleft - 1);
+            const bool real = m < mleft;
+            u32x4 w;
+            if (sid == NA - 1) {
+                // correction operand: slots 0,1 = -lse_enc2 (hi + lo pair), slots 2,3 = 1, else zero
+                const float le2 = real ? leb[mc] * kLog2e : 0.f;
+                w[0] = lower ? split_pair<F>(-le2) : 0u;
+                w[1] = lower ? kOnePair<F> : 0u;
+                w[2] = 0u; w[3] = 0u;
+                // Slots 4-6 belong to the c product and slots 8,9 to the a product, whose operands are bf16
+                // whatever the storage type; the score products meet them with zeros in the token operand
+                // (and the a and c products meet slots 0-3 with zeros).  Finite 16-bit patterns of either type read as
+                // finite values of the other, so the foreign slots contribute exact zeros.
+                if constexpr (ONE) {   // slots 4,5 := 1 (they pick -w delta hi, lo; the latent's factor of the c chain is 1)
+                    w[2] = lower && real ? 0x3f803f80u : 0u;
+                }
+                if (!lower) {
+                    w[0] = split_bf16_pair(real ? -eb[mc] : 0.f);          // slots 8,9 := -eps (bf16: the a chain)
+                    if (!ONE && real) w[1] = 0x3f803f80u;                  // slots 10,11 := 1 (picks -delta, two exponentials)
+                }
+            } else if (sid < NA) {
+                const int kind = sid / KS, ks = sid % KS;          // 0 q' hi, 1 q' lo, 2 dZ, 3 Z hi, 4 Z lo (DQ only)
+                const int d0 = (D / 2) * hh + 8 * ks;
+                float x[8];
+                if (kind <= 1) {
+                    const u32x4 raw = row8_bf16<DR>(qh_ + (size_t)mc * DR, PACK ? 0 : d0);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { x[2 * i] = elem_lo<F>(raw[i]) * c2; x[2 * i + 1] = elem_hi<F>(raw[i]) * c2; }
+                } else if (kind == 2) {
+                    row8_f32<DR>(dzb + (size_t)mc * DR, d0, x);
+                } else {
+                    row8_f32<DR>(zb + (size_t)mc * DR, ZPACK ? 0 : d0, x);
+                }
+                const bool want_lo = kind == 1 || kind >= 4 || (!lower && ((PACK && kind == 0) || (ZPACK && kind == 3)));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    HiLo p;
+                    if (kind <= 1) p = split_elems<F>(x[2 * i], x[2 * i + 1]);   // q' feeds the score products: storage type
+                    else p = split_elems<false>(x[2 * i], x[2 * i + 1]);
+                    w[i] = real ? (want_lo ? p.lo : p.hi) : 0u;
+                    if constexpr (DR == 4 && !ZPACK) {   // slots 4-7 of the Z image := its lo part (dY repeated there)
+                        if (kind == 3 && i >= 2) {
+                            const HiLo l = split_elems<false>(x[2 * i - 4], x[2 * i - 3]);
+                            w[i] = real && lower ? l.lo : 0u;
+                        }
+                    }
+                }
+                if (PACK && !lower && kind == 2 && real) w[0] = split_bf16_pair(-eb[mc]);   // slots 8,9 := -eps
+                if (PACK && !ZPACK && !lower && kind == 3 && real) {                 // slots 8,9,10 := 1, 1, 0 / 1, 1
+                    w[0] = 0x3f803f80u;
+                    if constexpr (ONE) w[1] = 0u;
+                }
+            } else {
+                const int rsid = sid - NA;                          // (which, hv, s2)
+                const int which = rsid / (2 * HV), hv = (rsid / 2) % HV, s2 = rsid % 2;
+                const int dd = WIDE ? l32 : 16 * hv + (l32 & 15);
+                // beyond the real head dimension every row image is zero
+                const uint32_t keep = (WIDE || l32 < 16) && dd < DR ? 0xffffffffu : 0u;
+                const int dc = dd & (DR - 1);
+#pragma unroll
+                for (int i = 0; i < 8; i += 2) {
+                    const int ma = 32 * t + perm_index(s2, hh, i), mb = ma + 1;
+                    const int ca = min(ma, mleft - 1) * DR + dc, cb = min(mb, mleft - 1) * DR + dc;
+                    uint32_t x;
+                    if (which == 0) x = cvt_pk_bf16(dzb[ca], dzb[cb]);
+                    else if constexpr (F) x = cvt_pk_bf16(elem_value<F>(qh_[ca]), elem_value<F>(qh_[cb]));
+                    else x = (uint32_t)qh_[ca] | ((uint32_t)qh_[cb] << 16);
+                    w[i / 2] = x & keep & ((ma < mleft ? 0xffffu : 0u) | (mb < mleft ? 0xffff0000u : 0u));
+                }
+            }
+            img[im * 64 + lane] = w;
+        }
+    }
+    __syncthreads();
+
+    u32x4 w11;
+    w11[1] = 0u; w11[2] = 0u; w11[3] = 0u;
+    w11[0] = lower ? kOnePair<F> : 0u;
+    const bf16x8 ones_s = as_bf16x8(w11);        // the same in the type of the score products
+    w11[0] = lower ? 0u : 0x3f803f80u;
+    const bf16x8 ones_eps = as_bf16x8(w11);      // slots 8,9 = 1 (bf16): picks -eps out of the correction image
+    auto to_bf16 = [](bf16x8 x) { return as_bf16x8(to_bf16_row<F>(__builtin_bit_cast(u32x4, x))); };
+
     // V rows as the operand of the a product; PACK: slots 8,9 := 1 (the upper lane half loaded zeros)
     auto v_operand = [&](bf16x8 x) {
         u32x4 w = to_bf16_row<F>(__builtin_bit_cast(u32x4, x));
@@ -714,25 +728,14 @@ __device__ __forceinline__ void dkdv_body(
             for (int db = 0; db < DB; ++db) dqa[t][jb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int c16 = lane & 15, g16 = lane >> 4;
 
-    int tile = gp.x * TW + (PAIR ? wave >> 1 : wave);
     int round = 0;   // PAIR: token tiles so far
-    bf16x8 kt[KS], vt[KS], gt[KS], ktn[KS], vtn[KS], gtn[KS];
     if (tile < tiles) {
-        load_cols(kb, tile, kt, true);
-        load_cols(vb, tile, vt, false);
-        load_cols(gb, tile, gt, ZPACK);
 #pragma unroll
         for (int s = 0; s < KS; ++s) { vt[s] = v_operand(vt[s]); gt[s] = to_bf16(gt[s]); }
     }
     // The token statistics (lse_dec2, delta) are requested one tile ahead like the rows: a request made where its
     // value is needed would also wait for the rows requested just before it (loads complete in order), and every
     // token tile would begin with a full memory latency.
-    float lse_next = 0.f, delta_next = 0.f;
-    if (tile < tiles) {
-        const size_t row0 = (size_t)min(tile * 32 + l32, N - 1);
-        lse_next = lb[row0];
-        delta_next = db[row0];
-    }
     // (the first tile's rows and statistics have arrived before the loop starts: inside it, nothing waits for
     // anything but what the loop itself requested a tile earlier)
     float nld_cur = pinned(-lse_next * ld_mul), dl_cur = pinned(delta_next);
@@ -1017,39 +1020,41 @@ __device__ __forceinline__ void dkdv_body(
     }
 
     if constexpr (DQ) {
-        // The waves add their dQ partials in wave order (fixed, so the bits are reproducible) in a
-        // [32*MT][D] fp32 buffer that reuses the image memory, then the workgroup stores its slot.
+        // The waves' dQ partials are added in wave order (fixed, so the bits are reproducible) and the workgroup stores its slot:
+        // as many latent tiles at a time as fit the LDS of images and waves once for every wave (one to three rounds; one wave
+        // after the other adding to a single sum took 4 us at 128 latents and d = 32).
         float *red = reinterpret_cast<float *>(img);
-        constexpr int STEP = PAIR ? 2 : 1;   // (the two halves of the latents side by side)
-        for (int w = 0; w < WV; w += STEP) {
-            __syncthreads();   // first pass: every wave is done with the images
-            if (wave / STEP == w / STEP) {
-#pragma unroll
-                for (int t = 0; t < HT; ++t)
-#pragma unroll
-                    for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-                        for (int db = 0; db < DB; ++db) {
-                            float4 *cell = reinterpret_cast<float4 *>(red + (32 * (half * HT + t) + 16 * jb + c16) * D + 16 * db + 4 * g16);
-                            const f32x4 &q4 = dqa[t][jb][db];
-                            float4 x = make_float4(q4[0], q4[1], q4[2], q4[3]);
-                            if (w > 0) {
-                                const float4 o = *cell;
-                                x.x += o.x; x.y += o.y; x.z += o.z; x.w += o.w;
-                            }
-                            *cell = x;
-                        }
-            }
-        }
-        __syncthreads();
+        constexpr int kTileFloats = 32 * D;                      // of one wave
+        constexpr int kFit = (MT * PER_TILE * 1024 + WV * fused_wave_lds(D, MT) * 2) / (WV * kTileFloats * 4);
+        static_assert(kFit >= 1, "the images and the waves' tiles leave room for one latent tile of every wave");
+        constexpr int kRounds = (HT + kFit - 1) / kFit, TB = (HT + kRounds - 1) / kRounds;   // latent tiles (of a wave) a round
+        constexpr int STEP = PAIR ? 2 : 1;                       // (the two halves of the latents side by side)
         const int mleft = mend - m0;
         float *out = dq_part + (((size_t)bh * gridDim.x + gp.x) * Mtot + m0) * DR;
-        constexpr int PCS = DR / 4;                             // float4 pieces of a DR-element row
-        for (int i = tid; i < 32 * MT * PCS; i += 64 * WV) {   // latent i / PCS, columns 4 (i % PCS) ..
-            const int lat = i / PCS, pc = i % PCS;
-            if (lat < mleft)
-                *reinterpret_cast<float4 *>(out + (size_t)lat * DR + 4 * pc) =
-                    *reinterpret_cast<const float4 *>(red + (size_t)lat * D + 4 * pc);
+        constexpr int PCS = DR / 4;                              // float4 pieces of a DR-element row
+#pragma unroll
+        for (int t0 = 0; t0 < HT; t0 += TB) {
+            __syncthreads();   // every wave is done with the images, or with the round before
+#pragma unroll
+            for (int t = t0; t < t0 + TB && t < HT; ++t)
+#pragma unroll
+                for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) {
+                        const f32x4 &q4 = dqa[t][jb][db];
+                        *reinterpret_cast<float4 *>(red + (wave * TB + t - t0) * kTileFloats + (16 * jb + c16) * D + 16 * db + 4 * g16) =
+                            make_float4(q4[0], q4[1], q4[2], q4[3]);
+                    }
+            __syncthreads();
+            for (int i = tid; i < STEP * TB * 32 * PCS; i += 64 * WV) {
+                const int pc = i % PCS, r = i / PCS, hf = STEP == 1 ? 0 : r / (32 * TB), row = r - hf * 32 * TB;
+                const int lat = 32 * (hf * HT + t0) + row;
+                const float *src = red + (hf * TB * 32 + row) * D + 4 * pc;
+                float4 x = *reinterpret_cast<const float4 *>(src);
+#pragma unroll
+                for (int w = 1; w < WV / STEP; ++w) add4(x, *reinterpret_cast<const float4 *>(src + w * STEP * TB * kTileFloats));
+                if (t0 + row / 32 < HT && lat < mleft) *reinterpret_cast<float4 *>(out + (size_t)lat * DR + 4 * pc) = x;
+            }
         }
     }
 }
@@ -1074,6 +1079,12 @@ __global__ __launch_bounds__(64 * WV, 1) void bwd_dkdv_planned_kernel(FLARE_DKDV
     const GridPos gp = grid_pos_latents(ts, H, DR * 2);
     float *rows = reinterpret_cast<float *>(reinterpret_cast<char *>(img) + merge.lds);
     const float *dz_bh, *eps_bh;
+    if constexpr (DQ) {
+        const size_t row = (size_t)gp.y * Mtot + m0;
+        stage_latents<DR, MT>(img + MT * dkdv_images(DR, DQ, ZL) * 64, q + (size_t)(gp.y % H) * ts.sq + (size_t)m0 * DR, z + row * DR,
+                              lse_enc + row, mend - m0);
+        if (merge.parts == 0) __syncthreads();       // (merging has barriers of its own)
+    }
     // (a dQ kernel of its own runs behind this one and reads what workgroup 0 writes)
     if (merged_dz<DR>(merge, z, lse_enc, gp.y, Mtot, true, !DQ && gp.x == 0, rows, red, dz_bh, eps_bh))
         dkdv_body<DR, MT, DQ, true, F, ZL>(FLARE_DKDV_PASS);

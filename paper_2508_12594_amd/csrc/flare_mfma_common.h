@@ -51,12 +51,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 w) { return __builtin_bit_cast(bf16x8, w); }
-__device__ __forceinline__ uint32_t rne_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
-}
 // two fp32 -> packed bf16 (low half = a, high half = b), round to nearest even: one
 // v_cvt_pk_bf16_f32.  Left to the compiler (no inline asm) so that it keeps the wait state a
 // VALU read of a transcendental result needs.
@@ -69,6 +63,7 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b)
     v[1] = b;
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
+__device__ __forceinline__ uint32_t rne_bf16(float f) { return cvt_pk_bf16(f, 0.f); }   // in the low half, zero above it
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c)
 {
@@ -126,6 +121,14 @@ __device__ __forceinline__ uint32_t pack_elems(float a, float b)
     } else {
         return cvt_pk_bf16(a, b);
     }
+}
+// Two fp32 as packed hi and lo words of the storage type: the rounded values, and what the rounding left, rounded again.
+struct HiLo { uint32_t hi, lo; };
+template <bool F>
+__device__ __forceinline__ HiLo split_elems(float a, float b)
+{
+    const uint32_t hi = pack_elems<F>(a, b);
+    return HiLo{hi, pack_elems<F>(a - elem_lo<F>(hi), b - elem_hi<F>(hi))};
 }
 // Value of a stored dY element as the c product sees it: with fp16 storage the rows are rounded to
 // bf16 before they meet Z, and delta[n] = <dY_n, Y_n> must be formed from the same rounded values, or
@@ -281,7 +284,10 @@ __device__ __forceinline__ void row8_f32(const float *__restrict__ row, int e0, 
     for (int i = 0; i < 8; ++i) x[i] = 0.f;
     if (DR >= 16 || e0 == 0) {
 #pragma unroll
-        for (int i = 0; i < (DR >= 8 ? 8 : DR); ++i) x[i] = row[e0 + i];
+        for (int i = 0; i < (DR >= 8 ? 8 : DR); i += 4) {
+            const float4 t = *reinterpret_cast<const float4 *>(row + e0 + i);
+            x[i] = t.x; x[i + 1] = t.y; x[i + 2] = t.z; x[i + 3] = t.w;
+        }
     }
 }
 // Accumulator rows of one 16-wide column group: registers 0-3 hold columns 4*hh .. 4*hh+3, registers
@@ -313,11 +319,9 @@ __device__ __forceinline__ void load_q_operand(const bf16_t *__restrict__ q_row,
             u32x4 wh, wl;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float a = elem_lo<F>(w[i]) * c2, b = elem_hi<F>(w[i]) * c2;
-                const uint32_t ah = rne_elem<F>(a), bh = rne_elem<F>(b);
-                const float ar = a - elem_value<F>(ah), br = b - elem_value<F>(bh);
-                wh[i] = ah | (bh << 16);
-                wl[i] = rne_elem<F>(ar) | (rne_elem<F>(br) << 16);
+                const HiLo x = split_elems<F>(elem_lo<F>(w[i]) * c2, elem_hi<F>(w[i]) * c2);
+                wh[i] = x.hi;
+                wl[i] = x.lo;
             }
             hi[s] = as_bf16x8((PACKED && hh) ? wl : wh);
             lo[s] = as_bf16x8(wl);
@@ -347,17 +351,10 @@ __device__ __forceinline__ bf16x8 zero_operand()
 template <bool F>
 __device__ __forceinline__ uint32_t split_pair(float x)
 {
-    const uint32_t hi = rne_elem<F>(x);
-    return hi | (rne_elem<F>(x - elem_value<F>(hi)) << 16);
+    return pack_elems<F>(x, x - elem_lo<F>(pack_elems<F>(x, 0.f)));
 }
 // x as a hi + lo pair of bf16 values packed in one word (hi in the low half)
-__device__ __forceinline__ uint32_t split_bf16_pair(float x)
-{
-    const uint32_t hi = (__float_as_uint(x) + 0x7fffu + ((__float_as_uint(x) >> 16) & 1u)) >> 16;
-    const float r = x - __uint_as_float(hi << 16);
-    const uint32_t lo = (__float_as_uint(r) + 0x7fffu + ((__float_as_uint(r) >> 16) & 1u)) >> 16;
-    return hi | (lo << 16);
-}
+__device__ __forceinline__ uint32_t split_bf16_pair(float x) { return split_pair<false>(x); }
 // Replace contraction slot 0 (low half of word 0) of an operand; `keep` and `bits` are per-lane
 // constants so that only the lower lane half (which owns slot 0) is changed.
 __device__ __forceinline__ bf16x8 with_slot0(bf16x8 x, uint32_t keep, uint32_t bits)

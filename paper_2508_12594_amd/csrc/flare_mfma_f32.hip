@@ -664,7 +664,8 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
     bool one_exp = false;
     float *const merged = reinterpret_cast<float *>(smem + A.CT * L::TILE);
     if constexpr (MERGE && MODE == 0) {
-        merge_z_rows<DR>(A.mz, bh, M, 0, M, threadIdx.x, blockDim.x, merged, gp.x == 0);
+        auto put = [&](int m, int j, const float4 &x) { *reinterpret_cast<float4 *>(merged + (size_t)m * DR + 4 * j) = x; };
+        merge_z_rows<DR, 1>(A.mz, bh, M, 0, M, threadIdx.x, blockDim.x, put, gp.x == 0);
         __syncthreads();
         zr = merged;
     } else if constexpr (MERGE && MODE == 2) {

@@ -71,56 +71,60 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
     }
     const int mleft = Mtot - m0;   // real latents from m0 on (may exceed the 32*MT this kernel covers)
 
-    // Zaug^T operand: row l32 (< 16: column 16*hv + l32 of Z; 16: ones; else zero).  In registers, or --
-    // for the shapes whose registers would not allow two waves per SIMD otherwise (ZLDS = !PRE) --
-    // built once per workgroup in LDS (the four waves share one (b,h)) and read per latent tile.
+    // Zaug^T operand: row l32 (< 16: column 16*hv + l32 of Z; 16: ones; else zero).  The rows of Z are put into dynamic LDS once
+    // per workgroup (the four waves share one (b,h)) as rows of bf16, row = latent: D columns of Z, a column of ones, zeros
+    // to the next 16; the transposing LDS read hands them over as operands (as the encode's values).  They stay in registers, or --
+    // in the shapes whose registers would not allow two waves per SIMD otherwise (ZLDS = !PRE) -- are read per latent tile.
+    // (As fp32 rows whose columns every wave picked and rounded for itself, with the queries rounded in integer arithmetic,
+    // the setup took 20 us of the 49 of 32 x 8 heads, 4096 tokens, 128 latents, d = 32.)
     constexpr bool ZLDS = !PRE;
-    __shared__ __attribute__((aligned(16))) u32x4 zlds[ZLDS ? HV * 2 * MT * 64 : 1];
-    bf16x8 zt[ZLDS ? 1 : HV][ZLDS ? 1 : 2 * MT];
+    constexpr int RS = D + 16 + 8;               // uint16 per row (16-byte aligned; as the encode's value tile)
+    extern __shared__ __attribute__((aligned(16))) uint16_t z_rows[];   // [32 * MT][RS]
     {
-        const float *zb = z + ((size_t)bh * Mtot + m0) * DR;
-        if constexpr (MERGE) {   // few encode slots: every workgroup merges them for itself, into dynamic LDS
-            extern __shared__ __attribute__((aligned(16))) float z_rows[];
-            merge_z_rows<DR>(merge, bh, Mtot, 0, Mtot, threadIdx.x, 256, z_rows, gp.x == 0);   // (one also writes them)
-            __syncthreads();
-            zb = z_rows;
+        constexpr int L = DR / 4;
+        // row m, columns 4 j ... 4 j + 3; at d <= 8 also what stands in columns 8 ... 15: zeros, or (z_lo) what the rounding
+        // of Z to bf16 left over, so that the rows of Y behind delta carry Z as a hi + lo pair like the c chain does
+        auto put = [&](int m, int j, const float4 &x) {
+            uint16_t *row = z_rows + m * RS;
+            const HiLo a = split_elems<false>(x.x, x.y), b = split_elems<false>(x.z, x.w);
+            *reinterpret_cast<u32x2 *>(row + 4 * j) = u32x2{a.hi, b.hi};
+            if constexpr (DR <= 8) *reinterpret_cast<u32x2 *>(row + 8 + 4 * j) = z_lo ? u32x2{a.lo, b.lo} : u32x2{0u, 0u};
+            if constexpr (DR == 4) {
+                *reinterpret_cast<u32x2 *>(row + 4) = u32x2{0u, 0u};
+                *reinterpret_cast<u32x2 *>(row + 12) = u32x2{0u, 0u};
+            }
+            if (j == 0) {
+                *reinterpret_cast<u32x4 *>(row + D) = u32x4{0x3f80u, 0u, 0u, 0u};
+                *reinterpret_cast<u32x4 *>(row + D + 8) = u32x4{0u, 0u, 0u, 0u};
+            }
+        };
+        const int real = min(32 * MT, mleft);
+        if constexpr (MERGE) {   // few encode slots: every workgroup merges them for itself
+            constexpr int R = ZLDS || MT <= 2 || L * MT < 8 ? 1 : L * MT / 8 > 4 ? 4 : L * MT / 8;   // (all rows, as registers allow)
+            merge_z_rows<DR, R>(merge, bh, Mtot, 0, Mtot, threadIdx.x, 256, put, gp.x == 0);   // (one also writes them)
+        } else {
+            const float4 *zb = reinterpret_cast<const float4 *>(z + ((size_t)bh * Mtot + m0) * DR);
+            for (int i = threadIdx.x; i < real * L; i += 256) put(i / L, i % L, zb[i]);
         }
+        for (int i = real * (RS / 8) + (int)threadIdx.x; i < 32 * MT * (RS / 8); i += 256)   // padding latents
+            *reinterpret_cast<u32x4 *>(z_rows + 8 * i) = u32x4{0u, 0u, 0u, 0u};
+        __syncthreads();
+    }
+    const uint16_t *z_lane = z_rows + (4 * hh + (lane & 15) / 4) * RS + 4 * (lane & 3);   // (lane mapping: lds_read_tr16)
+    auto z_read = [&](int hv, int s) {
+        const uint16_t *src = z_lane + 16 * s * RS + ((lane & 16) ? D : 16 * hv);
+        const u32x2 a = lds_read_tr16(src), b = lds_read_tr16(src + 8 * RS);
+        return as_bf16x8(u32x4{a[0], a[1], b[0], b[1]});
+    };
+    bf16x8 zt[ZLDS ? 1 : HV][ZLDS ? 1 : 2 * MT];
+    if constexpr (!ZLDS) {
 #pragma unroll
         for (int hv = 0; hv < HV; ++hv)
 #pragma unroll
-            for (int s = 0; s < 2 * MT; ++s) {
-                if (ZLDS && (s & 3) != wave) continue;   // each wave builds a quarter of the images
-                u32x4 w;
-#pragma unroll
-                for (int i = 0; i < 8; i += 2) {
-                    float a, b;
-                    if (l32 < 16 && 16 * hv + l32 < DR) {
-                        const int la = 32 * (s / 2) + perm_index(s % 2, hh, i);
-                        const int lb = 32 * (s / 2) + perm_index(s % 2, hh, i + 1);
-                        a = la < mleft ? zb[(size_t)la * DR + 16 * hv + l32] : 0.f;
-                        b = lb < mleft ? zb[(size_t)lb * DR + 16 * hv + l32] : 0.f;
-                    } else if (DR <= 8 && z_lo && l32 >= 8 && l32 < 8 + DR) {
-                        // rows 8 .. 8 + d - 1 (free at d <= 8): what the rounding of Z to bf16 left over, so
-                        // that the rows of Y behind delta carry Z as a hi + lo pair like the c chain does
-                        const int la = 32 * (s / 2) + perm_index(s % 2, hh, i);
-                        const int lb = 32 * (s / 2) + perm_index(s % 2, hh, i + 1);
-                        a = la < mleft ? zb[(size_t)la * DR + l32 - 8] : 0.f;
-                        b = lb < mleft ? zb[(size_t)lb * DR + l32 - 8] : 0.f;
-                        a -= __uint_as_float(rne_bf16(a) << 16);
-                        b -= __uint_as_float(rne_bf16(b) << 16);
-                    } else {   // row 16: ones (for the real latents), the rest: zero
-                        a = (l32 == 16 && 32 * (s / 2) + perm_index(s % 2, hh, i) < mleft) ? 1.f : 0.f;
-                        b = (l32 == 16 && 32 * (s / 2) + perm_index(s % 2, hh, i + 1) < mleft) ? 1.f : 0.f;
-                    }
-                    w[i / 2] = rne_bf16(a) | (rne_bf16(b) << 16);
-                }
-                if constexpr (ZLDS) zlds[(hv * 2 * MT + s) * 64 + lane] = w;
-                else zt[hv][s] = as_bf16x8(w);
-            }
+            for (int s = 0; s < 2 * MT; ++s) zt[hv][s] = z_read(hv, s);
     }
-    if constexpr (ZLDS) __syncthreads();
     auto z_op = [&](int hv, int s) {
-        if constexpr (ZLDS) return as_bf16x8(zlds[(hv * 2 * MT + s) * 64 + lane]);
+        if constexpr (ZLDS) return z_read(hv, s);
         else return zt[hv][s];
     };
 
@@ -1349,7 +1353,7 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
                                 TokStride ts_y, const void *dy, float *lse_dec2, float *delta, float *run, int m0, int Mc,
                                 float scale, const MergeZ &merge, hipStream_t stream, int flags = 0)
 {
-    const size_t lds = merge.parts ? (size_t)s.M * s.d * 4 : 0;
+    const size_t lds = (size_t)Mc * (padded_dim(s.d) + 24) * 2;   // rows of Z
     const int BH = s.B * s.H;
     const int tiles = (s.N + 31) / 32;
     // Workgroups that fit a CU by the kernel's registers (d = 32 with more than 128 latents keeps Z in LDS).  Two are launched
@@ -1378,7 +1382,7 @@ static int launch_decode_family(const flare_shape &s, const void *q, const void 
             }                                                                                                      \
         }                                                                                                          \
         if constexpr (MODE != 2 || (MTT >= 5 && DD <= 16))                                                         \
-            decode_mfma_kernel<DD, MTT, PREE, MINB, MODE, FF, false><<<grid, 256, 0, stream>>>(FLARE_DEC_ARGS);    \
+            decode_mfma_kernel<DD, MTT, PREE, MINB, MODE, FF, false><<<grid, 256, lds, stream>>>(FLARE_DEC_ARGS);    \
     } while (0)
 #define FLARE_DEC(DD, MTT, PREE, MINB)                                                                          \
     do {                                                                                                        \

@@ -303,7 +303,7 @@ __global__ __launch_bounds__(256) void encode_merge_few_kernel(const MergeZ g, i
 {
     constexpr int ROWS = 256 / (D / 4);
     const int m0 = blockIdx.x * ROWS;
-    merge_z_rows<D>(g, blockIdx.y, M, m0, min(M, m0 + ROWS), threadIdx.x, 256, nullptr, true);
+    merge_z_rows<D, 1>(g, blockIdx.y, M, m0, min(M, m0 + ROWS), threadIdx.x, 256, [](int, int, const float4 &) {}, true);
 }
 
 // ---------------------------------------------------------------------------------------
