@@ -615,17 +615,19 @@ __device__ __forceinline__ void dkdv_body(
         // real latent and every value that could reach dK or dV is zero -- q, Z, dZ, eps, u and the ones
         // that pick -delta -- so that a = c = 0 and dS = 0 whatever P and R come out as.
         const int mleft = mend - m0;
+        // all ones where a < b (as a value: the results of many compares side by side take the scalar registers that the token loop
+        // needs, and every one spilled there costs it vector registers)
+        auto below = [](int a, int b) { return (uint32_t)((a - b) >> 31); };
         // an image a wave and pass: which one it is, is the same for all its lanes
 #pragma unroll 1
         for (int im = wave; im < MT * PER_TILE; im += WV) {
             const int t = im / PER_TILE, sid = im % PER_TILE;
             const int m = 32 * t + l32, mc = min(m, mleft - 1);
-            const bool real = m < mleft;
+            const uint32_t real = below(m, mleft);
             u32x4 w;
             if (sid == NA - 1) {
                 // correction operand: slots 0,1 = -lse_enc2 (hi + lo pair), slots 2,3 = 1, else zero
-                const float le2 = real ? leb[mc] * kLog2e : 0.f;
-                w[0] = lower ? split_pair<F>(-le2) : 0u;
+                w[0] = lower ? split_pair<F>(-(leb[mc] * kLog2e)) & real : 0u;
                 w[1] = lower ? kOnePair<F> : 0u;
                 w[2] = 0u; w[3] = 0u;
                 // Slots 4-6 belong to the c product and slots 8,9 to the a product, whose operands are bf16
@@ -633,11 +635,11 @@ __device__ __forceinline__ void dkdv_body(
                 // (and the a and c products meet slots 0-3 with zeros).  Finite 16-bit patterns of either type read as
                 // finite values of the other, so the foreign slots contribute exact zeros.
                 if constexpr (ONE) {   // slots 4,5 := 1 (they pick -w delta hi, lo; the latent's factor of the c chain is 1)
-                    w[2] = lower && real ? 0x3f803f80u : 0u;
+                    w[2] = lower ? 0x3f803f80u & real : 0u;
                 }
                 if (!lower) {
-                    w[0] = split_bf16_pair(real ? -eb[mc] : 0.f);          // slots 8,9 := -eps (bf16: the a chain)
-                    if (!ONE && real) w[1] = 0x3f803f80u;                  // slots 10,11 := 1 (picks -delta, two exponentials)
+                    w[0] = split_bf16_pair(-eb[mc]) & real;                 // slots 8,9 := -eps (bf16: the a chain)
+                    if (!ONE) w[1] = 0x3f803f80u & real;                    // slots 10,11 := 1 (picks -delta, two exponentials)
                 }
             } else if (sid < NA) {
                 const int kind = sid / KS, ks = sid % KS;          // 0 q' hi, 1 q' lo, 2 dZ, 3 Z hi, 4 Z lo (DQ only)
@@ -658,17 +660,17 @@ __device__ __forceinline__ void dkdv_body(
                     HiLo p;
                     if (kind <= 1) p = split_elems<F>(x[2 * i], x[2 * i + 1]);   // q' feeds the score products: storage type
                     else p = split_elems<false>(x[2 * i], x[2 * i + 1]);
-                    w[i] = real ? (want_lo ? p.lo : p.hi) : 0u;
+                    w[i] = (want_lo ? p.lo : p.hi) & real;
                     if constexpr (DR == 4 && !ZPACK) {   // slots 4-7 of the Z image := its lo part (dY repeated there)
                         if (kind == 3 && i >= 2) {
                             const HiLo l = split_elems<false>(x[2 * i - 4], x[2 * i - 3]);
-                            w[i] = real && lower ? l.lo : 0u;
+                            w[i] = lower ? l.lo & real : 0u;
                         }
                     }
                 }
-                if (PACK && !lower && kind == 2 && real) w[0] = split_bf16_pair(-eb[mc]);   // slots 8,9 := -eps
-                if (PACK && !ZPACK && !lower && kind == 3 && real) {                 // slots 8,9,10 := 1, 1, 0 / 1, 1
-                    w[0] = 0x3f803f80u;
+                if (PACK && !lower && kind == 2) w[0] = split_bf16_pair(-eb[mc]) & real;     // slots 8,9 := -eps
+                if (PACK && !ZPACK && !lower && kind == 3) {                         // slots 8,9,10 := 1, 1, 0 / 1, 1
+                    w[0] = 0x3f803f80u & real;
                     if constexpr (ONE) w[1] = 0u;
                 }
             } else {
@@ -686,7 +688,7 @@ __device__ __forceinline__ void dkdv_body(
                     if (which == 0) x = cvt_pk_bf16(dzb[ca], dzb[cb]);
                     else if constexpr (F) x = cvt_pk_bf16(elem_value<F>(qh_[ca]), elem_value<F>(qh_[cb]));
                     else x = (uint32_t)qh_[ca] | ((uint32_t)qh_[cb] << 16);
-                    w[i / 2] = x & keep & ((ma < mleft ? 0xffffu : 0u) | (mb < mleft ? 0xffff0000u : 0u));
+                    w[i / 2] = x & keep & ((below(ma, mleft) & 0xffffu) | (below(mb, mleft) << 16));
                 }
             }
             img[im * 64 + lane] = w;
@@ -1023,6 +1025,8 @@ __device__ __forceinline__ void dkdv_body(
         // The waves' dQ partials are added in wave order (fixed, so the bits are reproducible) and the workgroup stores its slot:
         // as many latent tiles at a time as fit the LDS of images and waves once for every wave (one to three rounds; one wave
         // after the other adding to a single sum took 4 us at 128 latents and d = 32).
+        // (the lane counted anew: what is kept from before the token loop costs that a register)
+        const int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
         float *red = reinterpret_cast<float *>(img);
         constexpr int kTileFloats = 32 * D;                      // of one wave
         constexpr int kFit = (MT * PER_TILE * 1024 + WV * fused_wave_lds(D, MT) * 2) / (WV * kTileFloats * 4);
@@ -1042,11 +1046,11 @@ __device__ __forceinline__ void dkdv_body(
 #pragma unroll
                     for (int db = 0; db < DB; ++db) {
                         const f32x4 &q4 = dqa[t][jb][db];
-                        *reinterpret_cast<float4 *>(red + (wave * TB + t - t0) * kTileFloats + (16 * jb + c16) * D + 16 * db + 4 * g16) =
+                        *reinterpret_cast<float4 *>(red + (wave * TB + t - t0) * kTileFloats + (16 * jb + (ln & 15)) * D + 16 * db + 4 * (ln >> 4)) =
                             make_float4(q4[0], q4[1], q4[2], q4[3]);
                     }
             __syncthreads();
-            for (int i = tid; i < STEP * TB * 32 * PCS; i += 64 * WV) {
+            for (int i = 64 * wave + ln; i < STEP * TB * 32 * PCS; i += 64 * WV) {
                 const int pc = i % PCS, r = i / PCS, hf = STEP == 1 ? 0 : r / (32 * TB), row = r - hf * 32 * TB;
                 const int lat = 32 * (hf * HT + t0) + row;
                 const float *src = red + (hf * TB * 32 + row) * D + 4 * pc;

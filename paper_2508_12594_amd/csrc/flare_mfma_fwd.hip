@@ -86,7 +86,8 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
         // of Z to bf16 left over, so that the rows of Y behind delta carry Z as a hi + lo pair like the c chain does
         auto put = [&](int m, int j, const float4 &x) {
             uint16_t *row = z_rows + m * RS;
-            const HiLo a = split_elems<false>(x.x, x.y), b = split_elems<false>(x.z, x.w);
+            // (the rounded quotients: contracted with the subtraction of their hi part, the lo part would not be that of z)
+            const HiLo a = split_elems<false>(pinned(x.x), pinned(x.y)), b = split_elems<false>(pinned(x.z), pinned(x.w));
             *reinterpret_cast<u32x2 *>(row + 4 * j) = u32x2{a.hi, b.hi};
             if constexpr (DR <= 8) *reinterpret_cast<u32x2 *>(row + 8 + 4 * j) = z_lo ? u32x2{a.lo, b.lo} : u32x2{0u, 0u};
             if constexpr (DR == 4) {
