@@ -173,7 +173,10 @@ int mfma32_dq_partial(const flare_shape &s, const float *q, const float *k, cons
                       const float *delta, float ld_mul, const int *plan, float *dq_part, float scale, hipStream_t stream);
 int mfma32_dkdv(const flare_shape &s, const float *q, const float *k, const float *v, const float *dy, const float *z,
                 const float *lse_enc, const float *lse_dec, const float *delta, float ld_mul, float *dk, float *dv,
-                float scale, const MergeDz &g, hipStream_t stream);
+                float *dq_part, float scale, const MergeDz &g, hipStream_t stream);
+// Does the dK/dV kernel also form the dQ partials (dq_part != NULL above)?  Its slots per (b,h) then (0: it does not).
+bool mfma32_dq_fused(const flare_shape &s);
+int mfma32_dq_blocks(const flare_shape &s);
 bool mfma32_inline(const flare_shape &s);   // do the decode and dK/dV kernels merge the slots?
 
 // ---- spectral analysis (Appendix C.1, Algorithm 1) ---------------------------------------------

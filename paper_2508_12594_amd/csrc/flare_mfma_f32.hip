@@ -208,9 +208,9 @@ __device__ __forceinline__ f32x16 value_step(const bf16x8 (&v)[F32Geo<DR>::NV], 
     return acc;
 }
 // acc[column of the value rows][lane's column] += 32 value rows (transposed) . the 32 x 32 tile w of weights, whose
-// accumulator layout is the operand's: k-step s2 takes registers 8 s2 ... 8 s2 + 7
-template <int DR>
-__device__ __forceinline__ f32x16 value_product(const uint16_t *rows, const TrLane &tl, const f32x16 &w, f32x16 acc)
+// accumulator layout is the operand's: k-step s2 takes registers 8 s2 ... 8 s2 + 7.  take(s2, planes) sees the weights' planes.
+template <int DR, typename Take>
+__device__ __forceinline__ f32x16 value_product(const uint16_t *rows, const TrLane &tl, const f32x16 &w, f32x16 acc, const Take &take)
 {
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
@@ -223,9 +223,15 @@ __device__ __forceinline__ f32x16 value_product(const uint16_t *rows, const TrLa
         split3(x, wp);
 #pragma unroll
         for (int j = 0; j < 3; ++j) p[j] = as_bf16x8(wp[j]);
+        take(s2, wp);
         acc = value_step<DR>(v, p, acc);
     }
     return acc;
+}
+template <int DR>
+__device__ __forceinline__ f32x16 value_product(const uint16_t *rows, const TrLane &tl, const f32x16 &w, f32x16 acc)
+{
+    return value_product<DR>(rows, tl, w, acc, [](int, const u32x4 (&)[3]) {});
 }
 // The planes' rows added up: out[i] is column out_col(i, hh) of the value rows.
 template <int DR>
@@ -628,6 +634,7 @@ struct TokenArgs {
     MergeZ mz;               // MODE 0
     MergeDz mdz;             // MODE 2
     float *out0, *out1;      // y, lse_dec | lse_dec2, delta | dk, dv
+    float *dq_part;          // MODE 2, DQ: slot x of (b,h) at [(b*h) * gridDim.x + x][M][d]
     TokStride ts;
     int H, N, M, CT;
     float c2, ld_mul;
@@ -639,13 +646,37 @@ struct TokenLds {   // in uint16 units, per latent tile
     static constexpr int Z = Q + 32 * QR, ZR = MODE == 2 ? Geo::RD : Geo::RT;
     static constexpr int D = Z + 32 * ZR;                                  // dZ (MODE 2)
     static constexpr int ST = D + (MODE == 2 ? 32 * Geo::RT : 0);          // per latent: bias of the scores, -eps, lse_enc
-    static constexpr int TILE = ST + 192;
+    static constexpr int TILE = ST + (MODE == 2 && DR <= 16 ? 256 : 192);   // (fused dQ: and eps)
 };
 
 constexpr int kTokenWaves = 8;
-template <int DR, int MODE, int T, bool MERGE>
+// Fused dQ (MODE 2, T == 1, d <= 16): per wave a tile of LDS for what reaches the dQ product transposed, one plane of dS at a
+// time ([token][latent]) and the planes of K ([token][d]; at d <= 8 two planes side by side) once a token tile, and the
+// parts of dK and dV that two waves of a pair exchange; in uint16 units.
+constexpr int kDqTiles = 4;                      // latent tiles whose dQ a wave keeps in registers
+constexpr int kDsRow = 36, kKRow = 16;           // rows of the two tiles
+constexpr int kDqLds = 3 * 32 * kKRow;
+static_assert(kDqLds >= 32 * kDsRow && kDqLds * 2 >= 64 * 8 * 4, "one region holds either, and the exchange");
+// f(wave, counter): see lds_post, lds_wait in the 16-bit dK/dV kernel
+__device__ __forceinline__ void pair_post(int *counter, int value, int lane)
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    if (lane == 0) __hip_atomic_store(counter, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void pair_wait(const int *counter, int value)
+{
+    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < value) {}
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
+// DQ (MODE 2): 0: dK and dV only; 1: also the dQ partials, a wave to a token tile (at most kDqTiles latent tiles); 2: the same
+// with two waves to a token tile, each with half of the latent tiles.
+template <int DR, int MODE, int T, bool MERGE, int DQ = 0>
 __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(const TokenArgs A)
 {
+    static_assert(DQ == 0 || (MODE == 2 && T == 1 && DR <= 16), "dQ comes out of the dK/dV pass");
     using Geo = F32Geo<DR>;
     using L = TokenLds<DR, MODE>;
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
@@ -662,7 +693,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
     // the planes
     const float *zr = A.z + (size_t)bh * M * DR, *dzr = nullptr, *epr = nullptr;
     bool one_exp = false;
-    float *const merged = reinterpret_cast<float *>(smem + A.CT * L::TILE);
+    float *const merged = reinterpret_cast<float *>(smem + A.CT * L::TILE + (DQ ? waves * kDqLds : 0));
     if constexpr (MERGE && MODE == 0) {
         auto put = [&](int m, int j, const float4 &x) { *reinterpret_cast<float4 *>(merged + (size_t)m * DR + 4 * j) = x; };
         merge_z_rows<DR, 1>(A.mz, bh, M, 0, M, threadIdx.x, blockDim.x, put, gp.x == 0);
@@ -705,7 +736,11 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
                 float *stat = reinterpret_cast<float *>(tile + L::ST);
                 if (a == 0) stat[row & 31] = mm < M ? 0.f : -1e30f;   // no weight for the padding latents
                 if constexpr (MODE == 2) {
-                    if (a == 1) stat[32 + (row & 31)] = mm < M ? -epr[mc] : 0.f;
+                    if (a == 1) {
+                        const float ep = mm < M ? epr[mc] : 0.f;
+                        stat[32 + (row & 31)] = -ep;
+                        if constexpr (DQ != 0) stat[96 + (row & 31)] = ep;
+                    }
                     if (a == 2) stat[64 + (row & 31)] = A.lse_enc[(size_t)bh * M + mc];
                 }
             }
@@ -720,6 +755,195 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
     const int batch = waves * T, batches = (tiles + batch - 1) / batch;
     auto tile_of = [&](int b, int t) { return b * batch + t * waves + wave; };
     auto tok_of = [&](int tile) { return min(tile * 32 + l32, A.N - 1); };
+    if constexpr (DQ != 0) {
+        // dK, dV and dQ of a token tile from one pass over the scores.  dS of a latent tile reaches the dQ product transposed
+        // (contraction over the tokens), one plane at a time through a wave-private LDS tile, and that product is
+        //     dQ^T[dd][m] += K^T[dd][n] dS^T[n][m]     with v_mfma_f32_16x16x32_bf16: 16 rows = d (d <= 8: two planes of K)
+        // A latent tile takes 8 registers of dQ, so a wave keeps at most four; with more, two waves share a token tile (PAIR),
+        // each with half of the latent tiles, and hand each other their parts of dK and dV at its end.  (A dQ kernel of its
+        // own forms the three score products again: 18 of its 26 matrix products a tile.)
+        // Every other wave takes V, dY, -eps and -delta, and so dS, with the opposite sign, for the reason at the head of the file.
+        constexpr bool PAIR = DQ == 2;
+        constexpr int NK = DR <= 8 ? 2 : 3;              // operands of K: planes (d <= 8: [k0 | k1], [k2 | 0])
+        __shared__ int posted[PAIR ? kTokenWaves : 1], taken[PAIR ? kTokenWaves : 1];
+        if (PAIR && threadIdx.x < kTokenWaves) posted[threadIdx.x] = taken[threadIdx.x] = 0;
+        if (PAIR) __syncthreads();
+        const int half = PAIR ? wave & 1 : 0, slot = PAIR ? wave >> 1 : wave, slots = PAIR ? waves >> 1 : waves;
+        const int mine = PAIR ? (MT + 1) >> 1 : MT, t0 = half * mine, nlt = min(mine, MT - t0);   // this wave's latent tiles
+        const int c16 = lane & 15, g16 = lane >> 4;
+        const bool neg = ((slot + gp.x) & 1) != 0;
+        const float sign = neg ? -1.f : 1.f;
+        const int eps_at = neg ? 96 : 32;                // of the latents' statistics: eps or -eps
+        uint16_t *const tb = smem + A.CT * L::TILE + wave * kDqLds;
+        f32x4 dqa[kDqTiles][2];
+#pragma unroll
+        for (int t = 0; t < kDqTiles; ++t) dqa[t][0] = dqa[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        int round = 0;
+        for (int tile = gp.x * slots + slot; tile < tiles; tile += gridDim.x * slots) {
+            const int n = min(tile * 32 + l32, A.N - 1);
+            const size_t off = base + tok_off(A.ts, n);
+            float kx[1][8], vx[1][8], gx[1][8];
+            load_row_half<DR>(A.k + off, hh, kx);
+            load_row_half<DR>(A.v + off, hh, vx);
+            load_row_half<DR>(A.dy + off, hh, gx);
+            const float ld_raw = A.lse_dec[rows + n], ndl = -sign * A.delta[rows + n];
+            bf16x8 kp[Geo::NP], vp[Geo::NP], gq[Geo::NP], k_op[NK];
+            reg_ops<DR, false>(kx, hh, kp);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                vx[0][i] *= sign;
+                gx[0][i] *= sign;
+            }
+            reg_ops<DR, false>(vx, hh, vp);
+            reg_ops<DR, false>(gx, hh, gq);
+            if (PAIR) pair_wait(taken + (wave ^ 1), round);   // (the other wave has what was left here at the last tile's end)
+            {   // the planes of K as rows of tokens (zero beyond the last one), read back transposed
+                const uint32_t live = tile * 32 + l32 < A.N ? 0xffffffffu : 0u;
+                auto put = [&](int at, bf16x8 p) {
+                    u32x4 w = __builtin_bit_cast(u32x4, p);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) w[i] &= live;
+                    *reinterpret_cast<u32x4 *>(tb + at + l32 * kKRow) = w;
+                };
+                if constexpr (DR <= 8) {   // kp: k0 | k0, k1 | k1, k0 | k2 of the two lane halves, the whole row in each
+                    put(8 * hh, hh ? kp[1] : kp[0]);
+                    put(32 * kKRow + 8 * (1 - hh), hh ? kp[2] : zero_operand());
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) put(j * 32 * kKRow + 8 * hh, kp[j]);
+                }
+                compiler_fence();
+#pragma unroll
+                for (int j = 0; j < NK; ++j) {
+                    const uint16_t *src = tb + j * 32 * kKRow + (8 * g16 + c16 / 4) * kKRow + 4 * (c16 % 4);
+                    const u32x2 a = lds_read_tr16(src), b = lds_read_tr16(src + 4 * kKRow);
+                    k_op[j] = as_bf16x8(u32x4{a[0], a[1], b[0], b[1]});
+                }
+                compiler_fence();
+            }
+            float ld;
+            const float w = exp2_neg_lse(ld_raw, A.ld_mul, kSpan32, ld);
+            f32x16 acc = splat16(0.f), acc2 = splat16(0.f);
+#pragma unroll
+            for (int lt = 0; lt < kDqTiles; ++lt) {
+                if (lt >= nlt) continue;
+                const uint16_t *im = smem + (t0 + lt) * L::TILE;
+                const float *stat = reinterpret_cast<const float *>(im + L::ST);
+                bf16x8 lat[Geo::NP];
+                row_ops<DR, true>(im + L::Q + l32 * L::QR, hh, lat);
+                f32x16 s = row_dot<DR, false>(lat, kp, tile_rows(stat, hh));
+                row_ops<DR, true>(im + L::D + l32 * Geo::RT, hh, lat);
+                f32x16 a = row_dot<DR, false>(lat, vp, tile_rows(stat + eps_at, hh));
+                row_ops<DR, true>(im + L::Z + l32 * L::ZR, hh, lat);
+                f32x16 c = row_dot<DR, false>(lat, gq, splat16(ndl));
+                if (one_exp) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        s[i] = fast_exp2(s[i]);
+                        a[i] = s[i] * fmaf(w, c[i], a[i]);
+                    }
+                } else {
+                    const f32x16 le = tile_rows(stat + 64, hh);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const float r = fast_exp2(s[i] - ld);
+                        s[i] = fast_exp2(fmaf(le[i], -kLog2e, s[i]));
+                        a[i] = fmaf(s[i], a[i], r * c[i]);
+                    }
+                }
+                acc2 = value_product<DR>(im + L::D, tl, s, acc2);
+                u32x4 ds[2][3];
+                acc = value_product<DR>(im + L::Q, tl, a, acc, [&](int s2, const u32x4 (&p)[3]) {
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) ds[s2][j] = p[j];
+                });
+#pragma unroll
+                for (int j = 2; j >= 0; --j) {           // small terms first
+                    // (this lane: token l32, latents 8 (r / 4) + 4 hh + r % 4 for r = 0 ... 15)
+                    uint16_t *row = tb + l32 * kDsRow + 4 * hh;
+#pragma unroll
+                    for (int s2 = 0; s2 < 2; ++s2) {
+                        *reinterpret_cast<u32x2 *>(row + 16 * s2) = u32x2{ds[s2][j][0], ds[s2][j][1]};
+                        *reinterpret_cast<u32x2 *>(row + 16 * s2 + 8) = u32x2{ds[s2][j][2], ds[s2][j][3]};
+                    }
+                    compiler_fence();
+#pragma unroll
+                    for (int jb = 0; jb < 2; ++jb) {
+                        const uint16_t *src = tb + (8 * g16 + c16 / 4) * kDsRow + 16 * jb + 4 * (c16 % 4);
+                        const u32x2 lo = lds_read_tr16(src), hi = lds_read_tr16(src + 4 * kDsRow);
+                        const bf16x8 b = as_bf16x8(u32x4{lo[0], lo[1], hi[0], hi[1]});
+                        if constexpr (DR <= 8) {
+                            if (j == 0) dqa[lt][jb] = mfma16(k_op[1], b, dqa[lt][jb]);
+                            dqa[lt][jb] = mfma16(k_op[0], b, dqa[lt][jb]);
+                        } else {
+                            if (j == 0) dqa[lt][jb] = mfma16(k_op[2], b, dqa[lt][jb]);
+                            if (j <= 1) dqa[lt][jb] = mfma16(k_op[1], b, dqa[lt][jb]);
+                            dqa[lt][jb] = mfma16(k_op[0], b, dqa[lt][jb]);
+                        }
+                    }
+                    compiler_fence();
+                }
+            }
+            float dkr[Geo::OUT], dvr[Geo::OUT];
+            fold_planes<DR>(acc, dkr);
+            fold_planes<DR>(acc2, dvr);
+            if constexpr (PAIR) {   // wave 0 of the pair finishes dK, wave 1 dV
+                float *give = reinterpret_cast<float *>(tb) + lane;
+#pragma unroll
+                for (int i = 0; i < Geo::OUT; ++i) give[64 * i] = half ? dkr[i] : dvr[i];
+                pair_post(posted + wave, ++round, lane);
+                pair_wait(posted + (wave ^ 1), round);
+                const float *get = reinterpret_cast<const float *>(tb + (1 - 2 * half) * kDqLds) + lane;
+#pragma unroll
+                for (int i = 0; i < Geo::OUT; ++i) {
+                    const float o = get[64 * i];
+                    if (half) dvr[i] += o;
+                    else dkr[i] += o;
+                }
+                pair_post(taken + wave, round, lane);
+            }
+            if (tile * 32 + l32 < A.N) {
+                // the rows of Q carry c2 = scale log2 e; dK wants scale
+#pragma unroll
+                for (int i = 0; i < Geo::OUT; ++i) dkr[i] *= sign * kLn2;
+                if (!PAIR || half == 0) store_quartets<DR>(A.out0 + off, hh, dkr);
+                if (!PAIR || half != 0) store_quartets<DR>(A.out1 + off, hh, dvr);
+            }
+        }
+        // the waves' dQ, added in wave order through the LDS of the planes
+        float *red = reinterpret_cast<float *>(smem);            // [wave][latent tile][32 latents][RD]
+        constexpr int RD = DR <= 8 ? 8 : 16;
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < kDqTiles; ++t) {
+            if (t >= mine) continue;
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb) {
+                f32x4 x = dqa[t][jb];
+                if constexpr (DR <= 8) {                        // the planes' rows
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[i] += __shfl_xor(x[i], 32);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] *= sign;
+                if (DR > 8 || lane < 32)
+                    *reinterpret_cast<float4 *>(red + ((wave * mine + t) * 32 + 16 * jb + c16) * RD + 4 * g16) =
+                        make_float4(x[0], x[1], x[2], x[3]);
+            }
+        }
+        __syncthreads();
+        float *out = A.dq_part + ((size_t)bh * gridDim.x + gp.x) * M * DR;
+        constexpr int PCS = DR / 4;
+        for (int i = threadIdx.x; i < M * PCS; i += blockDim.x) {
+            const int m = i / PCS, pc = i % PCS, hf = m / (32 * mine);          // (PAIR: which wave of a pair)
+            const float *src = red + (m - hf * 32 * mine) * RD + 4 * pc;
+            float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int v = 0; v < slots; ++v)
+                add4(x, *reinterpret_cast<const float4 *>(src + (PAIR ? 2 * v + hf : v) * mine * 32 * RD));
+            *reinterpret_cast<float4 *>(out + (size_t)m * DR + 4 * pc) = x;
+        }
+        return;
+    }
     float kx[Geo::KS][8];
     for (int b = gp.x; b < batches; b += gridDim.x) {
         f32x16 acc[T], acc2[MODE == 2 ? T : 1];
@@ -935,39 +1159,86 @@ int launch_latent(const flare_shape &s, const LatentArgs &a, int kid, hipStream_
     return check_launch();
 }
 
+// LDS for the planes of latents in the token-major kernels (the workgroup's votes and counters take a little of the 160 KiB).
+constexpr int kPlaneLds = 160 * 1024 - 512;
+
+// Grid of the token-major kernels.  Eight waves share a workgroup's planes; with less than half of the CUs busy that way, four
+// (1024 tokens, 4 heads: dK/dV 17 -> 15.5 us).  tokens: token tiles a workgroup of eight waves takes at a time, lds: bytes.
+struct TokenGrid { int waves, blocks; };
+inline TokenGrid token_grid(const flare_shape &s, bool dkdv, int tiles_per_wave, int waves_per_tile, size_t lds, int setup, int from)
+{
+    const int tiles = (s.N + 31) / 32, BH = s.B * s.H;
+    const int want = tiles * waves_per_tile;        // waves that a tile each would keep busy
+    TokenGrid g;
+    g.waves = (want + kTokenWaves - 1) / kTokenWaves * BH <= 128 ? kTokenWaves / 2 : kTokenWaves;
+    const int batches = (tiles + tiles_per_wave - 1) / tiles_per_wave, slots = g.waves / waves_per_tile;   // a wave's steps
+    // resident workgroups: as many as waves (dK/dV keeps two on a SIMD) and LDS allow
+    int cu = (dkdv ? kCuWaves / 2 : kCuWaves) / g.waves;
+    if (cu > (int)(kPlaneLds / lds)) cu = (int)(kPlaneLds / lds) > 1 ? (int)(kPlaneLds / lds) : 1;
+    // two rounds where one workgroup fits a CU: the second evens out what the first leaves (16 (b,h), 213277 tokens, 21
+    // latents: dK/dV 316 us in one round, 292 in two)
+    const int most = BH <= 512 ? (512 + BH - 1) / BH : 4;
+    g.blocks = round_blocks(BH, cu, batches, slots, setup, most, min(4 * most, (batches + slots - 1) / slots), 3, from);
+    return g;
+}
+
+// The dK/dV pass that also forms dQ: its LDS and grid.  A wave adds the dQ of its tiles one after the other in fp32, as the
+// latent-major kernels do over a chunk: at most 8192 tokens.
+inline bool dq_pair(const flare_shape &s) { return s.M > 32 * kDqTiles; }
+inline size_t dq_lds(const flare_shape &s)   // (with the merged rows, which lie there for few slots only: one grid either way)
+{
+    const int tile = s.d == 16 ? TokenLds<16, 2>::TILE : s.d == 8 ? TokenLds<8, 2>::TILE : TokenLds<4, 2>::TILE;
+    return (size_t)((s.M + 31) / 32) * tile * 2 + kTokenWaves * kDqLds * 2 + (size_t)s.M * (s.d + 1) * 4;
+}
+inline TokenGrid dq_grid(const flare_shape &s)
+{
+    const int tiles = (s.N + 31) / 32, per = dq_pair(s) ? 2 : 1;
+    const int longest = 8192 / 32 * (kTokenWaves / per);
+    return token_grid(s, true, 1, per, dq_lds(s), 2, (tiles + longest - 1) / longest);
+}
+
 template <int DR, int MODE>
 int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t stream)
 {
     using L = TokenLds<DR, MODE>;
-    constexpr int kLds = 160 * 1024 - 512;   // (the workgroup's votes take a little of the 160 KiB)
-    constexpr int CTMAX = kLds / (L::TILE * 2) < 8 ? kLds / (L::TILE * 2) : 8;
-    const int MT = (s.M + 31) / 32, tiles = (s.N + 31) / 32, BH = s.B * s.H;
+    constexpr int CTMAX = kPlaneLds / (L::TILE * 2) < 8 ? kPlaneLds / (L::TILE * 2) : 8;
+    const int MT = (s.M + 31) / 32;
     TokenArgs A = a;
     const bool fits = MT <= CTMAX;
     A.CT = fits ? MT : CTMAX;
     size_t lds = (size_t)A.CT * L::TILE * 2;
-    if (fits && (MODE == 0 ? A.mz.parts : A.mdz.parts) != 0) lds += (size_t)s.M * (s.d + 1) * 4;
     const bool merge = fits && (MODE == 0 ? A.mz.parts : A.mdz.parts) != 0;
-    // eight waves share a workgroup's planes; with less than half of the CUs busy that way, four (1024 tokens, 4 heads:
-    // dK/dV 17 -> 15.5 us)
-    const int waves = (tiles + kTokenWaves - 1) / kTokenWaves * BH <= 128 ? kTokenWaves / 2 : kTokenWaves;
-    const int batches = (tiles + (fits ? 1 : MODE == 2 ? 2 : 4) - 1) / (fits ? 1 : MODE == 2 ? 2 : 4);   // a wave's steps
-    // resident workgroups: as many as waves (dK/dV keeps two on a SIMD) and LDS allow
-    int cu = (MODE == 2 ? kCuWaves / 2 : kCuWaves) / waves;
-    if (cu > (int)(kLds / lds)) cu = (int)(kLds / lds) > 1 ? (int)(kLds / lds) : 1;
-    // two rounds where one workgroup fits a CU: the second evens out what the first leaves (16 (b,h), 213277 tokens, 21
-    // latents: dK/dV 316 us in one round, 292 in two)
-    const int most = BH <= 512 ? (512 + BH - 1) / BH : 4;
-    const dim3 grid(round_blocks(BH, cu, batches, waves, 1, most, min(4 * most, (batches + waves - 1) / waves), 3), BH);
+    const size_t merged = merge ? (size_t)s.M * (s.d + 1) * 4 : 0;
     LaunchTimer t(kid, stream);
-    if constexpr (MODE != 1) {
-        if (merge) {
-            token_pass_f32_kernel<DR, MODE, 1, true><<<grid, 64 * waves, lds, stream>>>(A);
+    if constexpr (MODE == 2 && DR <= 16) {
+        if (A.dq_part) {
+            const TokenGrid g = dq_grid(s);
+            const dim3 grid(g.blocks, s.B * s.H);
+            lds += g.waves * kDqLds * 2 + merged;
+#define FLARE_TOK_DQ(MG, DQ) token_pass_f32_kernel<DR, 2, 1, MG, DQ><<<grid, 64 * g.waves, lds, stream>>>(A)
+            if (dq_pair(s)) {
+                if (merge) FLARE_TOK_DQ(true, 2);
+                else FLARE_TOK_DQ(false, 2);
+            } else if (merge) {
+                FLARE_TOK_DQ(true, 1);
+            } else {
+                FLARE_TOK_DQ(false, 1);
+            }
+#undef FLARE_TOK_DQ
             return check_launch();
         }
     }
-    if (fits) token_pass_f32_kernel<DR, MODE, 1, false><<<grid, 64 * waves, lds, stream>>>(A);
-    else token_pass_f32_kernel<DR, MODE, MODE == 2 ? 2 : 4, false><<<grid, 64 * waves, lds, stream>>>(A);
+    lds += merged;
+    const TokenGrid g = token_grid(s, MODE == 2, fits ? 1 : MODE == 2 ? 2 : 4, 1, lds, 1, 1);
+    const dim3 grid(g.blocks, s.B * s.H);
+    if constexpr (MODE != 1) {
+        if (merge) {
+            token_pass_f32_kernel<DR, MODE, 1, true><<<grid, 64 * g.waves, lds, stream>>>(A);
+            return check_launch();
+        }
+    }
+    if (fits) token_pass_f32_kernel<DR, MODE, 1, false><<<grid, 64 * g.waves, lds, stream>>>(A);
+    else token_pass_f32_kernel<DR, MODE, MODE == 2 ? 2 : 4, false><<<grid, 64 * g.waves, lds, stream>>>(A);
     return check_launch();
 }
 
@@ -1068,14 +1339,22 @@ int mfma32_token_stats(const flare_shape &s, const float *q, const float *k, con
     a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e;
     FLARE_D(s, (launch_token<D, 1>(s, a, KID_BWD_TOKEN_STATS, stream)));
 }
+// dQ comes out of the dK/dV kernel where the planes of all latents lie in LDS beside the tiles of that product, and two waves a
+// SIMD have registers for it: d <= 16, at most 256 latents.  (FLARE_VARIANT_SEPARATE_DQ: a dQ kernel of its own, as elsewhere.)
+bool mfma32_dq_fused(const flare_shape &s)
+{
+    return s.d <= 16 && s.M <= 256 && (s.variant & FLARE_VARIANT_SEPARATE_DQ) == 0;
+}
+int mfma32_dq_blocks(const flare_shape &s) { return mfma32_dq_fused(s) ? dq_grid(s).blocks : 0; }
+
 int mfma32_dkdv(const flare_shape &s, const float *q, const float *k, const float *v, const float *dy, const float *z,
                 const float *lse_enc, const float *lse_dec, const float *delta, float ld_mul, float *dk, float *dv,
-                float scale, const MergeDz &g, hipStream_t stream)
+                float *dq_part, float scale, const MergeDz &g, hipStream_t stream)
 {
     TokenArgs a{};
     a.mdz = g;
     a.q = q; a.k = k; a.v = v; a.dy = dy; a.z = z; a.lse_enc = lse_enc;
-    a.lse_dec = lse_dec; a.delta = delta; a.ld_mul = ld_mul; a.out0 = dk; a.out1 = dv;
+    a.lse_dec = lse_dec; a.delta = delta; a.ld_mul = ld_mul; a.out0 = dk; a.out1 = dv; a.dq_part = dq_part;
     a.ts = tok_stride(s); a.H = s.H; a.N = s.N; a.M = s.M; a.c2 = scale * kLog2e;
     FLARE_D(s, (launch_token<D, 2>(s, a, KID_BWD_DKDV, stream)));
 }

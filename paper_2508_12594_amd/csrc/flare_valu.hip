@@ -754,7 +754,12 @@ inline bool dz_inline(const flare_shape &s)
 struct BwdSlots { int dz, dq; };
 inline BwdSlots bwd_slots(const flare_shape &s, const ValuPlan &plan)
 {
-    if (!mfma_supported(s)) return BwdSlots{plan.bwd.chunks, plan.bwd.chunks};
+    if (!mfma_supported(s)) {
+        flare_shape t = s;      // (what the caller is told to bring does not depend on the variant)
+        t.variant = 0;
+        const int blocks = s.dtype == FLARE_F32 ? mfma32_dq_blocks(t) : 0;
+        return BwdSlots{plan.bwd.chunks, plan.bwd.chunks > blocks ? plan.bwd.chunks : blocks};
+    }
     int dq = mfma_dq_fused(s) ? mfma_dkdv_blocks(s) : 0;
     // the dQ kernel's slots depend on the token order (dq_geom); what the caller is told to bring does not
     for (const flare_layout layout : {FLARE_BHND, FLARE_BNHD}) {
@@ -955,7 +960,7 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
     // A dQ kernel of its own runs before dK and dV are written, which may be over k, v or dy -- unless the dK/dV kernel
     // merges dZ for it.  Then it has to run behind that one, so dZ is merged first where the outputs lie over the inputs
     // (the same bits: merge_dz_row either way).
-    const bool dq_fused = mf && mfma_dq_fused(s);           // dQ comes out of the dK/dV kernel
+    const bool dq_fused = F32 ? mfma32_dq_fused(s) : mf && mfma_dq_fused(s);   // dQ comes out of the dK/dV kernel
     const size_t tok_bytes = (size_t)BH * s.N * D * sizeof(T);
     const bool in_place = overlap(dk, k, tok_bytes) || overlap(dk, v, tok_bytes) || overlap(dk, dy, tok_bytes) ||
                           overlap(dv, k, tok_bytes) || overlap(dv, v, tok_bytes) || overlap(dv, dy, tok_bytes);
@@ -978,9 +983,11 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
     // shared latents: one gradient for all heads, summed over (b, h) in that fixed order
     const int groups = s.shared_latents ? BH : s.B, outers = s.shared_latents ? 1 : s.H;
     if (mf) dq_parts = dq_fused ? mfma_dkdv_blocks(s) : mfma_dq_parts(s);
+    else if (dq_fused) dq_parts = mfma32_dq_blocks(s);
     auto dkdv = [&]() -> int {
         if constexpr (F32) {
-            return mfma32_dkdv(s, q, k, v, dy, z, lse_enc, ld, w.delta, ld_mul, dk, dv, scale, merge, stream);
+            return mfma32_dkdv(s, q, k, v, dy, z, lse_enc, ld, w.delta, ld_mul, dk, dv, dq_fused ? w.dq_part : nullptr, scale,
+                               merge, stream);
         } else if (mf) {
             const bool chunked = mfma_dkdv_acc_bytes(s) != 0;   // more than 256 latents: one pass per chunk
             int rc = FLARE_OK;

@@ -56,6 +56,33 @@ def test_latent_tiles(oracle, M, d, N):
     _check(oracle, "f16" if M % 3 == 0 else "bf16", 2, N, M, d, "bnhd" if M % 2 else "bhnd", saved=M % 5 != 0)
 
 
+# fp32 storage, dQ out of the dK/dV kernel (d <= 16, at most 256 latents): one wave to a token tile up to 128 latents, two from
+# 129 on (an odd number of tiles between them too), fewer tiles of tokens than waves, more than one round of them
+FUSED_F32 = [(1, 4, 40), (32, 16, 31), (33, 8, 65), (128, 16, 700), (129, 16, 700), (161, 8, 300), (255, 4, 257), (256, 8, 64),
+             (160, 16, 9000), (256, 16, 2049)]
+
+
+@pytest.mark.parametrize("M,d,N", FUSED_F32)
+def test_fused_dq_of_fp32_storage(oracle, M, d, N):
+    """Every way to the gradients meets the bar: dQ from the dK/dV kernel (one and two exponentials) and from its own."""
+    layout = "bnhd" if N % 2 else "bhnd"
+    print("[case] f32 fused dQ N=%d M=%d d=%d %s" % (N, M, d, layout), flush=True)
+    inp = synth.make_inputs(1, B=2, H=2, N=N, M=M, d=d, dtype="f32", with_dy=True, seed=5 + N + M + d)
+    scale, dev = inp["scale"], to_device(inp)
+    order = (lambda t: t.permute(0, 2, 1, 3).contiguous()) if layout == "bnhd" else (lambda t: t)
+    k, v, dy = (order(dev[n]) for n in ("k", "v", "dy"))
+    ld = torch.empty((2, 2, N), dtype=torch.float32, device="cuda")
+    y, z, lse = binding.forward(dev["q"], k, v, scale, lse_dec=ld, layout=layout)
+    refs = oracle.backward(inp["q"], inp["k"], inp["v"], inp["dy"], scale)
+    for variant in (0, binding.VARIANT_TWO_EXP, binding.VARIANT_SEPARATE_DQ):
+        dq, dk, dv = binding.backward(dev["q"], k, v, dy, z, lse, scale, y=y, lse_dec=ld, layout=layout, variant=variant)
+        again = binding.backward(dev["q"], k, v, dy, z, lse, scale, y=y, lse_dec=ld, layout=layout, variant=variant)
+        errs = [slice_relerr(to_host(g), r) for g, r in zip((dq, order(dk), order(dv)), refs)]
+        print("[case]    variant %d: dq %.2e dk %.2e dv %.2e" % ((variant,) + tuple(errs)), flush=True)
+        assert max(errs) <= tol_for(inp)
+        assert all(torch.equal(a, b) for a, b in zip((dq, dk, dv), again))
+
+
 @pytest.mark.parametrize("M,d,N", F32)
 def test_latent_tiles_of_fp32_storage(oracle, M, d, N):
     _check(oracle, "f32", 2, N, M, d, "bnhd" if M % 2 else "bhnd", saved=M % 3 != 0)
