@@ -560,6 +560,9 @@ __device__ __forceinline__ void dkdv_body(
     // comes from rows of Y formed with the same hi + lo pair (the token-statistics kernel at d <= 8), so
     // c - delta cancels where one latent dominates a token, down to a single latent.
     constexpr bool ZPACK = PACK && DQ;
+    // ... and with one exponential, where dS = P (a + w c) and a takes both corrections, -w delta comes in through slots 10, 11 of
+    // the dZ image (ones, against the hi + lo pair in the V operand) beside -eps: no correction product at all.
+    constexpr bool APACK = ZPACK && ONE;
     extern __shared__ __attribute__((aligned(16))) u32x4 img[];   // [MT][PER_TILE][64 lanes]
     __shared__ int posted[PAIR ? WV : 1], taken[PAIR ? WV : 1];   // PAIR: parts handed over / picked up so far
 
@@ -669,6 +672,7 @@ __device__ __forceinline__ void dkdv_body(
                     }
                 }
                 if (PACK && !lower && kind == 2) w[0] = split_bf16_pair(-eb[mc]) & real;     // slots 8,9 := -eps
+                if (APACK && !lower && kind == 2) w[1] = 0x3f803f80u & real;                 // slots 10,11 := 1 (pick -w delta)
                 if (PACK && !ZPACK && !lower && kind == 3) {                         // slots 8,9,10 := 1, 1, 0 / 1, 1
                     w[0] = 0x3f803f80u & real;
                     if constexpr (ONE) w[1] = 0u;
@@ -773,6 +777,11 @@ __device__ __forceinline__ void dkdv_body(
         wg[2] = (ONE && lower) ? ds_ : 0u;                   // one: slots 4,5,6 := -w delta hi, lo, hi
         wg[3] = (ONE && lower) ? (ds_ & 0xffffu) : 0u;
         const bf16x8 g_aug = as_bf16x8(wg);
+        if constexpr (APACK) {   // slots 10,11 of the V operand := -w delta hi, lo
+            u32x4 w = __builtin_bit_cast(u32x4, vt[0]);
+            w[1] = lower ? w[1] : ds_;
+            vt[0] = as_bf16x8(w);
+        }
         bf16x8 gc[KS];   // dY operand of the c product; PACK: slots 8,9,10 := -delta hi, lo, hi
 #pragma unroll
         for (int s = 0; s < KS; ++s) gc[s] = gt[s];
@@ -839,7 +848,7 @@ __device__ __forceinline__ void dkdv_body(
             if constexpr (!PIPE) scores(t, s1, s2);   // not enough registers at d = 32: no look-ahead
             f32x16 av = splat16(0.f), cv = splat16(0.f);
             if constexpr (ONE) {
-                if constexpr (!PACK || ZPACK) av = mfma(image(t, NA - 1), g_aug, av);
+                if constexpr (!PACK) av = mfma(image(t, NA - 1), g_aug, av);
             } else {
                 if constexpr (!PACK) av = mfma(image(t, NA - 1), ones_eps, av);
                 if constexpr (!PACK || ZPACK) cv = mfma(image(t, NA - 1), g_aug, cv);

@@ -750,12 +750,12 @@ __global__ __launch_bounds__(256, MINB) void encode_mfma_kernel(
 
     // The waves of a workgroup that share token tiles (one per latent group) read the same rows; nothing else keeps
     // them together, and once they are more tiles apart than the L2 holds, the later one fetches its rows a second
-    // time.  The dZ kernel therefore lines its waves up every kSyncTiles tiles (a wave passes the same number of
-    // barriers whatever its number of tiles: those its sweep does not reach follow after it).  Eight: 32 x 8 heads, 4096 tokens,
-    // 128 latents, d = 32, where every 32 comes to never, 52 -> 45 us (four and two the same); at four the million tokens
-    // of d = 16 take 300 us, 292 at 8 and 32.
+    // time.  The dZ kernel therefore lines its waves up every sync_tiles tiles (a wave passes the same number of
+    // barriers whatever its number of tiles: those its sweep does not reach follow after it): 32, which costs nothing measurable,
+    // or 8 in chunks that would hardly come to the 32nd (32 x 8 heads, 4096 tokens, 128 latents, d = 32, 32 tiles a wave: dZ
+    // 52 -> 45 us, the same at 4 and 2; but every 8 in long chunks, 10^6 tokens, 2048 latents, d = 8: 2296 -> 2390).
     constexpr bool SYNC = MODE == 1;
-    constexpr int kSyncTiles = 8;
+    const int cnt_max = (tiles + TG - 1) / TG, sync_tiles = cnt_max > 64 ? 32 : 8;
     // One sweep over this wave's token tiles.  PLAIN (encode only): the weights are 2^S2 as they come, with no
     // stabiliser (c = 0: no running maximum, no correction k-step, no rescaling) -- right whenever the row sums
     // end up in a range that shows that nothing overflowed and nothing that matters was flushed to zero, which
@@ -955,7 +955,7 @@ __global__ __launch_bounds__(256, MINB) void encode_mfma_kernel(
         };
         int j = 0;
         for (; j + 2 < cnt; j += 2) {
-            if (SYNC && j > 0 && (j & (kSyncTiles - 1)) == 0) __syncthreads();
+            if (SYNC && j > 0 && (j & (sync_tiles - 1)) == 0) __syncthreads();
             tile(j, PlainTag<false>{}, c_a, c_b, vr1, vr2, yr1, yr2, la, lb2);
             tile(j + 1, PlainTag<false>{}, c_b, c_a, vr2, vr1, yr2, yr1, lb2, la);
         }
@@ -968,8 +968,7 @@ __global__ __launch_bounds__(256, MINB) void encode_mfma_kernel(
     };
     if constexpr (SYNC) {
         // the barriers this wave's sweep does not reach (it has one tile fewer than the longest, or none at all)
-        const int cnt_max = (tiles + TG - 1) / TG;
-        const int mine = cnt >= 3 ? (cnt - 3) / kSyncTiles : 0, all = cnt_max >= 3 ? (cnt_max - 3) / kSyncTiles : 0;
+        const int mine = cnt >= 3 ? (cnt - 3) / sync_tiles : 0, all = cnt_max >= 3 ? (cnt_max - 3) / sync_tiles : 0;
         if (cnt > 0) sweep(PlainTag<false>{});
         for (int i = mine; i < all; ++i) __syncthreads();
     } else if (cnt > 0) {
