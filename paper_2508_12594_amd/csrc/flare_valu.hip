@@ -226,72 +226,83 @@ __global__ __launch_bounds__(kLatentBlock) void encode_partial_kernel(
     store_row<D>(o_part + slot * D, o);
 }
 
-// Merge of the partial slots of one (b*h, m): a workgroup takes 16 latents; the 16 threads of a
-// latent each fold the slots p = j, j+16, ... in order and a fixed xor-shuffle tree folds the 16
-// results, so the association order depends on the slot count only (bit-reproducible).
-// A slot with m = -inf is empty and contributes nothing.
+// Merges of many partial slots: a workgroup takes kMergeRows rows (latents) of one (b*h), its 256 threads sixteen groups of
+// slots: group g adds the slots g, g + 16, ... in order, four columns a lane, so that sixteen lanes read 256 contiguous bytes of
+// a slot, and a fixed tree adds the sixteen results (lanes 16 and 32 apart, then the four waves through LDS): the association
+// order depends on the slot count only (bit-reproducible).  These launches are bound by two or three memory latencies, so they
+// want many workgroups with few loads in a row each.  (With sixteen rows a workgroup, a thread holding whole rows that the
+// tree moved through sixty-four shuffles and more: 8 heads, 256 latents, 64 slots, d = 32: encode 11.7 us, dZ 13.7, dQ 9.9.)
+constexpr int kMergeGroups = 16;
+constexpr int merge_rows(int d) { return 64 / d; }          // rows of a workgroup: 256 bytes of a slot
+template <int D>
+struct MergeLane {
+    int m, j, g;      // row, lane's four columns 4 j ..., slot group
+    bool live;
+    __device__ __forceinline__ MergeLane(int block, int M)
+    {
+        constexpr int L = D / 4;
+        const int row = block * merge_rows(D) + (threadIdx.x & 15) / L;
+        live = row < M;
+        m = live ? row : M - 1;
+        j = (threadIdx.x & 15) % L;
+        g = threadIdx.x >> 4;
+    }
+};
+struct MergeSum { float m, l; float4 o; };      // stabiliser, sum of weights, weighted columns
+__device__ __forceinline__ MergeSum fold_pair(const MergeSum &a, const MergeSum &b)
+{
+    MergeSum r;
+    r.m = fmaxf(a.m, b.m);
+    const float wa = (a.m == -INFINITY) ? 0.f : fast_exp2(a.m - r.m);
+    const float wb = (b.m == -INFINITY) ? 0.f : fast_exp2(b.m - r.m);
+    r.l = a.l * wa + b.l * wb;
+    r.o = make_float4(a.o.x * wa + b.o.x * wb, a.o.y * wa + b.o.y * wb, a.o.z * wa + b.o.z * wb, a.o.w * wa + b.o.w * wb);
+    return r;
+}
+__device__ __forceinline__ float4 shfl_xor4(const float4 &x, int off)
+{
+    return make_float4(__shfl_xor(x.x, off), __shfl_xor(x.y, off), __shfl_xor(x.z, off), __shfl_xor(x.w, off));
+}
+
+// z and lse_enc of many encode slots.  A slot with m = -inf is empty and contributes nothing.
 template <int D>
 __global__ __launch_bounds__(256) void encode_merge_kernel(
     const float *__restrict__ m_part, const float *__restrict__ l_part, const float *__restrict__ o_part,
     float *__restrict__ z, float *__restrict__ lse_enc, int BH, int M, int parts, bool f32)
 {
-    const int j = threadIdx.x & 15;
-    const int m = blockIdx.x * 16 + (threadIdx.x >> 4);
-    const int bh = blockIdx.y;
-    const bool live = m < M;
-    const int mm = live ? m : M - 1;
-    float gm = -INFINITY, l = 0.f, o[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) o[i] = 0.f;
-    // four slots at a time: their loads are all issued before the first is folded (one memory latency per
-    // batch instead of two per slot); the folds keep the slot order
+    const MergeLane<D> at(blockIdx.x, M);
+    const int bh = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    MergeSum s{-INFINITY, 0.f, make_float4(0.f, 0.f, 0.f, 0.f)};
+    // four slots at a time: their loads are all issued before the first is folded (one memory latency per batch)
     constexpr int kBatch = 4;
-    for (int p0 = j; p0 < parts; p0 += 16 * kBatch) {
-        float mp[kBatch], lp[kBatch], oc[kBatch][D];
+    for (int p0 = at.g; p0 < parts; p0 += kMergeGroups * kBatch) {
+        MergeSum t[kBatch];
 #pragma unroll
         for (int b = 0; b < kBatch; ++b) {
-            const int p = p0 + 16 * b;
-            const size_t slot = ((size_t)bh * parts + min(p, parts - 1)) * M + mm;
-            mp[b] = p < parts ? m_part[slot] : -INFINITY;
-            lp[b] = l_part[slot];
-            load_row<D>(o_part + slot * D, oc[b]);
+            const int p = p0 + kMergeGroups * b;
+            const size_t slot = ((size_t)bh * parts + min(p, parts - 1)) * M + at.m;
+            t[b].m = p < parts ? m_part[slot] : -INFINITY;
+            t[b].l = l_part[slot];
+            t[b].o = *reinterpret_cast<const float4 *>(o_part + slot * D + 4 * at.j);
         }
 #pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            if (mp[b] == -INFINITY) continue;          // an empty slot (or none): contributes nothing
-            const float ng = fmaxf(gm, mp[b]);
-            const float wa = fast_exp2(gm - ng);          // gm = -inf on the first live slot: weight 0
-            const float wb = fast_exp2(mp[b] - ng);
-            l = l * wa + lp[b] * wb;
-#pragma unroll
-            for (int i = 0; i < D; ++i) o[i] = o[i] * wa + oc[b][i] * wb;
-            gm = ng;
-        }
+        for (int b = 0; b < kBatch; ++b)
+            if (t[b].m != -INFINITY) s = fold_pair(s, t[b]);
     }
 #pragma unroll
-    for (int off = 1; off < 16; off <<= 1) {
-        const float gm2 = __shfl_xor(gm, off);
-        const float l2 = __shfl_xor(l, off);
-        const float ng = fmaxf(gm, gm2);
-        const float wa = (gm == -INFINITY) ? 0.f : fast_exp2(gm - ng);
-        const float wb = (gm2 == -INFINITY) ? 0.f : fast_exp2(gm2 - ng);
-        // both lanes of a pair must form the same sum: order the operands by lane parity
-        const bool low = (j & off) == 0;
-        l = low ? (l * wa + l2 * wb) : (l2 * wb + l * wa);
-#pragma unroll
-        for (int i = 0; i < D; ++i) {
-            const float o2 = __shfl_xor(o[i], off);
-            o[i] = low ? (o[i] * wa + o2 * wb) : (o2 * wb + o[i] * wa);
-        }
-        gm = ng;
+    for (int off = 16; off < 64; off <<= 1) {
+        const MergeSum o{__shfl_xor(s.m, off), __shfl_xor(s.l, off), shfl_xor4(s.o, off)};
+        s = (lane & off) == 0 ? fold_pair(s, o) : fold_pair(o, s);      // both lanes of a pair form the same sum
     }
-    if (!live || j != 0) return;
-    const float inv = 1.f / l;
-#pragma unroll
-    for (int i = 0; i < D; ++i) o[i] *= inv;
-    const size_t idx = (size_t)bh * M + m;
-    store_row<D>(z + idx * D, o);
-    lse_enc[idx] = f32 ? lse_nat(gm, l) : (gm + log2f(l)) * kLn2;
+    __shared__ MergeSum part[4][16];
+    if (lane < 16) part[wave][lane] = s;
+    __syncthreads();
+    if (threadIdx.x >= 16 || !at.live) return;
+    s = fold_pair(fold_pair(part[0][lane], part[1][lane]), fold_pair(part[2][lane], part[3][lane]));
+    const float inv = 1.f / s.l;
+    const size_t idx = (size_t)bh * M + at.m;
+    *reinterpret_cast<float4 *>(z + idx * D + 4 * at.j) = make_float4(s.o.x * inv, s.o.y * inv, s.o.z * inv, s.o.w * inv);
+    if (at.j == 0) lse_enc[idx] = f32 ? lse_nat(s.m, s.l) : (s.m + log2f(s.l)) * kLn2;
 }
 
 // The same merge for few partial slots (flare_merge.h).  With 16 threads per latent striding over the slots most of them
@@ -482,46 +493,43 @@ __global__ __launch_bounds__(kLatentBlock) void dz_partial_kernel(
     store_row<D>(dz_part + (((size_t)bh * chunks + chunk) * M + m) * D, acc);
 }
 
-// Fixed-order sum of partial slots, shared by dZ and dQ.  A workgroup takes 16 rows (latents); the
-// 16 threads of a row each add the slots j, j+16, ... in order and a fixed xor-shuffle tree adds
-// the 16 results, so the association order depends on the slot count only.
-// Slot s of output row (outer, m) lives at  part[((s / inner) * stride_o + outer) * inner + s % inner][m]
-// with stride_o = outer count:  dZ: outer = b*h, one group of `inner` slots;  dQ: outer = h, the
-// slots of all batch items b (groups of `inner` partials each), i.e. the batch sum in b order.
+// Fixed-order sum of many partial slots, shared by dZ and dQ (see encode_merge_kernel): the sums are in the first sixteen threads.
+// Slot s of output row (outer, m) lives at  part[((s / inner) * n_outer + outer) * inner + s % inner][m]:
+// dZ: outer = b*h, one group of `inner` slots;  dQ: outer = h, the slots of all batch items b (groups of `inner` partials
+// each), i.e. the batch sum in b order.  One barrier inside.
 template <int D>
-__device__ __forceinline__ void sum_slots(const float *__restrict__ part, int outer, int n_outer, int groups,
-                                          int inner, int M, int m, int j, float (&acc)[D])
+__device__ __forceinline__ float4 sum_slots(const float *__restrict__ part, int outer, int n_outer, int groups, int inner, int M,
+                                            const MergeLane<D> &at)
 {
-#pragma unroll
-    for (int i = 0; i < D; ++i) acc[i] = 0.f;
-    const int total = groups * inner;
+    __shared__ float4 waves[4][16];
+    const int total = groups * inner, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     // four slots at a time: their loads are all issued before the first is added; the sums keep the slot order
     constexpr int kBatch = 4;
-    for (int s0 = j; s0 < total; s0 += 16 * kBatch) {
-        float t[kBatch][D];
+    for (int s0 = at.g; s0 < total; s0 += kMergeGroups * kBatch) {
+        float4 t[kBatch];
 #pragma unroll
         for (int b = 0; b < kBatch; ++b) {
-            const int s = min(s0 + 16 * b, total - 1);
+            const int s = min(s0 + kMergeGroups * b, total - 1);
             const size_t slot = ((size_t)(s / inner) * n_outer + outer) * inner + (s % inner);
-            load_row<D>(part + (slot * M + m) * D, t[b]);
+            t[b] = *reinterpret_cast<const float4 *>(part + (slot * M + at.m) * D + 4 * at.j);
         }
 #pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            if (s0 + 16 * b < total) {
-#pragma unroll
-                for (int i = 0; i < D; ++i) acc[i] += t[b][i];
-            }
-        }
+        for (int b = 0; b < kBatch; ++b)
+            if (s0 + kMergeGroups * b < total) add4(acc, t[b]);
     }
 #pragma unroll
-    for (int off = 1; off < 16; off <<= 1) {
-        const bool low = (j & off) == 0;
-#pragma unroll
-        for (int i = 0; i < D; ++i) {
-            const float o = __shfl_xor(acc[i], off);
-            acc[i] = low ? (acc[i] + o) : (o + acc[i]);
-        }
+    for (int off = 16; off < 64; off <<= 1) add4(acc, shfl_xor4(acc, off));
+    if (lane < 16) waves[wave][lane] = acc;
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        float4 a = waves[0][lane], b = waves[2][lane];
+        add4(a, waves[1][lane]);
+        add4(b, waves[3][lane]);
+        add4(a, b);
+        acc = a;
     }
+    return acc;
 }
 
 // dZ[b*h][m] = sum of its partial slots; eps[m] = <dZ_m, Z_m>.
@@ -531,9 +539,11 @@ __global__ __launch_bounds__(256) void dz_merge_kernel(
     float *__restrict__ dz, float *__restrict__ eps, int BH, int M, int parts, int round_bf16,
     const float *__restrict__ ld_range, const float *__restrict__ lse_enc, int *__restrict__ plan, float span)
 {
-    const int j = threadIdx.x & 15;
-    const int m = blockIdx.x * 16 + (threadIdx.x >> 4);
+    const MergeLane<D> at(blockIdx.x, M);
     const int bh = blockIdx.y;
+    const size_t idx = (size_t)bh * M + at.m;
+    DzRow r;
+    r.a = sum_slots<D>(dz_part, bh, BH, 1, parts, M, at);
     // matrix-core path: which variant of the next kernels runs for this (b,h) (every workgroup works it out for
     // itself: the one-exponential variant wants dZ scaled, see bwd_one_exp_ok); one more workgroup records it
     __shared__ float plan_red[64];
@@ -542,28 +552,14 @@ __global__ __launch_bounds__(256) void dz_merge_kernel(
         if (threadIdx.x == 0) plan[bh] = one_exp ? 1 : 0;
         return;
     }
-    const bool live = m < M;
-    float acc[D], zr[D];
-    sum_slots<D>(dz_part, bh, BH, 1, parts, M, live ? m : M - 1, j, acc);
-    if (!live || j != 0) return;
-    const size_t idx = (size_t)bh * M + m;
-    if (one_exp) {
-        const float em = round_bf16 ? exp2f(-lse_enc[idx] * 1.4426950408889634f) : expf(-lse_enc[idx]);   // as merge_dz_row
-#pragma unroll
-        for (int i = 0; i < D; ++i) acc[i] *= em;
-    }
-    if (round_bf16) {
-        // The matrix-core kernels take dZ as a bf16 operand.  Rounding it here, before eps is formed,
-        // keeps a[m][n] = <dZ_m, V_n - Z_m> an exact expression in the rounded dZ (eps and the products
-        // see the same values), instead of leaving <V_n, rounding error> uncancelled in every score.
-#pragma unroll
-        for (int i = 0; i < D; ++i) {
-            acc[i] = bf16_rounded(acc[i]);
-        }
-    }
-    load_row<D>(z + idx * D, zr);
-    store_row<D>(dz + idx * D, acc);
-    eps[idx] = dot<D>(acc, zr);
+    if (threadIdx.x >= 16) return;
+    r.z = *reinterpret_cast<const float4 *>(z + idx * D + 4 * at.j);
+    r.lse_enc = lse_enc[idx];
+    float e;
+    const float4 a = finish_dz_row<D>(r, at.j, one_exp, round_bf16 != 0, e);
+    if (!at.live) return;
+    *reinterpret_cast<float4 *>(dz + idx * D + 4 * at.j) = a;
+    if (at.j == 0) eps[idx] = e;
 }
 
 // Few slots: see encode_merge_few_kernel.
@@ -669,16 +665,11 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void dq_reduce_kernel(
     const float *__restrict__ dq_part, T *__restrict__ dq, int B, int H, int M, int parts, float scale)
 {
-    const int j = threadIdx.x & 15;
-    const int m = blockIdx.x * 16 + (threadIdx.x >> 4);
+    const MergeLane<D> at(blockIdx.x, M);
     const int h = blockIdx.y;
-    const bool live = m < M;
-    float acc[D];
-    sum_slots<D>(dq_part, h, H, B, parts, M, live ? m : M - 1, j, acc);
-    if (!live || j != 0) return;
-#pragma unroll
-    for (int i = 0; i < D; ++i) acc[i] *= scale;
-    store_row<D>(dq + ((size_t)h * M + m) * D, acc);
+    const float4 a = sum_slots<D>(dq_part, h, H, B, parts, M, at);
+    if (threadIdx.x < 16 && at.live)
+        store_four(dq + ((size_t)h * M + at.m) * D + 4 * at.j, make_float4(a.x * scale, a.y * scale, a.z * scale, a.w * scale));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -974,7 +965,7 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
                 w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, planned ? w.plan : nullptr,
                 span);
         else
-            dz_merge_kernel<D><<<dim3((s.M + 15) / 16 + (planned ? 1 : 0), BH), 256, 0, stream>>>(
+            dz_merge_kernel<D><<<dim3((s.M + merge_rows(D) - 1) / merge_rows(D) + (planned ? 1 : 0), BH), 256, 0, stream>>>(
                 w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, planned ? w.plan : nullptr,
                 span);
     }
@@ -1029,8 +1020,8 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
             dq_reduce_few_kernel<O, D><<<dim3((s.M + kFewRows - 1) / kFewRows, outers), 256, 0, stream>>>(
                 w.dq_part, out, groups, outers, s.M, dq_parts, scale);
         else
-            dq_reduce_kernel<O, D><<<dim3((s.M + 15) / 16, outers), 256, 0, stream>>>(w.dq_part, out, groups, outers, s.M,
-                                                                                     dq_parts, scale);
+            dq_reduce_kernel<O, D><<<dim3((s.M + merge_rows(D) - 1) / merge_rows(D), outers), 256, 0, stream>>>(
+                w.dq_part, out, groups, outers, s.M, dq_parts, scale);
     };
     if (dq_cast) reduce_dq(static_cast<T *>(dq));
     else reduce_dq(static_cast<float *>(dq));
@@ -1089,7 +1080,7 @@ int launch_encode_merge(const flare_shape &s, const float *m_part, const float *
                         float *z, float *lse_enc, int parts, hipStream_t stream)
 {
     const int BH = s.B * s.H;
-    const dim3 blocks((s.M + 15) / 16, BH);
+    const dim3 blocks((s.M + merge_rows(s.d) - 1) / merge_rows(s.d), BH);
     LaunchTimer t(KID_ENCODE_MERGE, stream);
     if (parts <= kFewSlots || merge_inline(s, parts)) {   // (the same bits wherever a shape's slots are merged)
         const MergeZ g{m_part, l_part, o_part, z, lse_enc, parts, s.dtype == FLARE_F32};
