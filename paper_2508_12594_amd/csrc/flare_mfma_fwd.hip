@@ -62,6 +62,22 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
     const bool flip = c2 < 0.f;
     const float ac2 = PRE ? c2 : fabsf(c2);
 
+    const bf16_t *kb = k + tok_base(ts, bh, H);
+    const int tiles = (N + 31) / 32;
+    const int stride = gridDim.x * 4;
+    int tile = gp.x * 4 + wave;
+    bf16x8 kt[KS], ktn[KS];
+    auto request_keys = [&](int t, bf16x8 (&kk)[KS]) {
+        const int nld = min(t * 32 + l32, N - 1);
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            kk[s] = as_bf16x8(row8_bf16<DR>(kb + tok_off(ts, nld), PACK ? 0 : (D / 2) * hh + 8 * s));
+    };
+    // The keys of the wave's first tile are requested before the latents' operands are made.  (Not where Z stays in LDS: five
+    // registers more would cost that variant its third wave per SIMD.)
+    constexpr bool EARLY_K = PRE;
+    if (EARLY_K && tile < tiles) request_keys(tile, kt);
+
     bf16x8 qh[MT][KS], ql[MT][KS];
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
@@ -129,12 +145,7 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
         else return zt[hv][s];
     };
 
-    const bf16_t *kb = k + tok_base(ts, bh, H);
     bf16_t *yb = y + tok_base(ts_y, bh, H);
-    const int tiles = (N + 31) / 32;
-    const int stride = gridDim.x * 4;
-    int tile = gp.x * 4 + wave;
-    bf16x8 kt[KS], ktn[KS];
     // hi part of the scores of latent tile t against the keys kk, without a stabiliser
     auto qk_hi = [&](int t, const bf16x8 (&kk)[KS]) {
         f32x16 r = splat16(0.f);
@@ -164,23 +175,14 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
     float mx = 0.f;
     f32x16 s_cur0 = splat16(0.f);
     if (tile < tiles) {
-        const int nld = min(tile * 32 + l32, N - 1);
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-            kt[s] = as_bf16x8(row8_bf16<DR>(kb + tok_off(ts, nld), PACK ? 0 : (D / 2) * hh + 8 * s));
+        if (!EARLY_K) request_keys(tile, kt);
         const f32x16 hi = qk_hi(0, kt);
         mx = tile_max(hi);
         s_cur0 = first_scores(hi, mx, kt);
     }
     for (; tile < tiles; tile += stride) {
         const int n = tile * 32 + l32;
-        {   // prefetch the keys of this wave's next tile (the last tile is simply loaded again)
-            const int tn = (tile + stride < tiles) ? tile + stride : tile;
-            const int nld = min(tn * 32 + l32, N - 1);
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                ktn[s] = as_bf16x8(row8_bf16<DR>(kb + tok_off(ts, nld), PACK ? 0 : (D / 2) * hh + 8 * s));
-        }
+        request_keys(tile + stride < tiles ? tile + stride : tile, ktn);   // of this wave's next tile (the last one is simply loaded again)
         // MODE 1: this lane's quartets of the tile's dY rows, used after the sweep (for delta).  Requested here, a
         // whole tile before their use -- except at d = 32, where their eight registers would cost the kernel its
         // third wave per SIMD: there they are requested where they are used.
@@ -554,16 +556,6 @@ __global__ __launch_bounds__(256, MINB) void encode_mfma_kernel(
 
     const int lat0 = 32 * NB * (G * (int)blockIdx.z + g);   // a workgroup owns NB*G tiles of latents
     bf16x8 qh[NB][KS], ql[NB][KS];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {   // padding latents (at or beyond M): zero queries, nothing stored
-        const int m = lat0 + 32 * b + l32;
-        load_q_operand<DR, true, F, PACK>(q + (size_t)h * ts.sq + (size_t)min(m, M - 1) * DR, hh, c2, false, qh[b],
-                                          ql[b]);
-        if (m >= M) {
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) { qh[b][ks] = zero_operand(); ql[b][ks] = zero_operand(); }
-        }
-    }
     u32x4 wzero;
     wzero[0] = 0u; wzero[1] = 0u; wzero[2] = 0u; wzero[3] = 0u;
     bf16x8 caug[MODE == 0 ? NB : 1];             // query side of the stabiliser k-step: slot 0 := -c
@@ -748,6 +740,28 @@ __global__ __launch_bounds__(256, MINB) void encode_mfma_kernel(
         if (do_delta && j < cnt && g == 0 && (lane & 1) == 0 && n < n1) delta_out[(size_t)bh * N + n] = part;
     };
 
+    // the rows of the wave's first tile, requested before the latents' operands are made
+    bf16x8 k_first[KS];
+    u32x4 v_first[LOADS], y_first[LOADS];
+    float lse_first = 0.f;
+    auto request_first = [&]() {
+        load_k(0, k_first);
+        load_v(0, v_first);
+        if constexpr (MODE == 1) lse_first = load_lse(0);
+        if (do_delta) load_y(0, y_first);
+    };
+    if (cnt > 0) request_first();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {   // padding latents (at or beyond M): zero queries, nothing stored
+        const int m = lat0 + 32 * b + l32;
+        load_q_operand<DR, true, F, PACK>(q + (size_t)h * ts.sq + (size_t)min(m, M - 1) * DR, hh, c2, false, qh[b],
+                                          ql[b]);
+        if (m >= M) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) { qh[b][ks] = zero_operand(); ql[b][ks] = zero_operand(); }
+        }
+    }
+
     // The waves of a workgroup that share token tiles (one per latent group) read the same rows; nothing else keeps
     // them together, and once they are more tiles apart than the L2 holds, the later one fetches its rows a second
     // time.  The dZ kernel therefore lines its waves up every sync_tiles tiles (a wave passes the same number of
@@ -782,18 +796,17 @@ __global__ __launch_bounds__(256, MINB) void encode_mfma_kernel(
         // prologue: tile 0 fully staged, tile 1's values in flight
         // -lse_dec2 of the current tile's token and of the next tile's; the values are requested two tiles ahead
         // (la, lb2 alternate like the row registers), so that nothing waits for a request of the same tile
-        float nl = -load_lse(0) * ld_mul, nln = 0.f;
+        float nl = -lse_first * ld_mul, nln = 0.f;
         float la = load_lse(1), lb2 = 0.f;
-        load_k(0, kt);
         load_k(1, ktn);
-        load_v(0, vr1);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) kt[s] = k_first[s];
         if (do_delta) {
-            load_y(0, yr1);
-            put_delta(0, vr1, yr1);
+            put_delta(0, v_first, y_first);
             load_y(1, yr1);
         }
         compiler_fence();
-        write_vt(vr1, vt);
+        write_vt(v_first, vt);
         compiler_fence();
         read_va(vt, va);
         load_v(1, vr1);
@@ -984,7 +997,10 @@ __global__ __launch_bounds__(256, MINB) void encode_mfma_kernel(
                 const uint32_t e = (__float_as_uint(den) >> 23) & 0xffu;
                 redo |= hh == 0 && lat0 + 32 * b + l32 < M && (e < 127u - 80u || e > 127u + 100u);
             }
-            if (__any(redo)) sweep(PlainTag<false>{});
+            if (__any(redo)) {
+                request_first();
+                sweep(PlainTag<false>{});
+            }
         } else {
             sweep(PlainTag<false>{});
         }
