@@ -249,15 +249,18 @@ __device__ __forceinline__ float4 merge_dz_row(const float *__restrict__ part, c
 }
 // What a consuming workgroup needs of one (b,h): the variant, and rows of dZ and eps: merged into `lds` (M * D, then M
 // floats; with `write` they and the plan also go to global memory, for a later kernel) or in global memory.  Ends with
-// a barrier when it merges.  red: 64 floats of LDS.
-template <int D>
+// a barrier when it merges.  red: 64 floats of LDS.  meanwhile(): called once, after the slots were requested.
+template <int D, typename Meanwhile>
 __device__ __forceinline__ bool merged_dz(const MergeDz &g, const float *z, const float *lse_enc, int bh, int M,
                                           bool round_bf16, bool write, float *lds, float *red, const float *&dz,
-                                          const float *&eps)
+                                          const float *&eps, const Meanwhile &meanwhile)
 {
     dz = g.dz + (size_t)bh * M * D;
     eps = g.eps + (size_t)bh * M;
-    if (g.parts == 0) return g.plan[bh] != 0;
+    if (g.parts == 0) {
+        meanwhile();
+        return g.plan[bh] != 0;
+    }
     constexpr int L = D / 4;
     // R rows a thread go together, all of their slots requested before the variant is decided (its test waits for memory too)
     constexpr int R = D == 32 ? 2 : 1;
@@ -269,6 +272,7 @@ __device__ __forceinline__ bool merged_dz(const MergeDz &g, const float *z, cons
             r[i] = load_dz_row<D>(g.part, z, lse_enc, bh, M, g.parts, min(m0 + i * rows + (int)threadIdx.x / L, M - 1), j);
     };
     load(0);
+    meanwhile();
     const bool one = bwd_one_exp_ok(g.ld_range, lse_enc, bh, g.parts, M, g.span, red);
     for (int m0 = 0; m0 < M; m0 += R * rows) {       // whole rows of lanes stay together (shuffles)
         if (m0 > 0) load(m0);

@@ -481,16 +481,37 @@ struct LatentStage {
     }
     static constexpr int kBytes = DR * 6 + 4;   // per latent
 };
+// (requested and put away apart, so that what is merged meanwhile waits for memory at the same time)
 template <int DR, int MT>
-__device__ __forceinline__ void stage_latents(void *at, const bf16_t *q, const float *z, const float *lse_enc, int M)
-{
+struct LatentPieces {
     static_assert(LatentStage<DR>::kBytes * 32 * MT <= WV * fused_wave_lds(padded_dim(DR), MT) * 2, "as long as the waves' tiles");
-    const LatentStage<DR> st(at, M);
-    const int tid = threadIdx.x, nt = 64 * WV;
-    for (int i = tid; i < M * DR / 4; i += nt) reinterpret_cast<float4 *>(st.z)[i] = reinterpret_cast<const float4 *>(z)[i];
-    for (int i = tid; i < M * DR / 4; i += nt) reinterpret_cast<u32x2 *>(st.q)[i] = reinterpret_cast<const u32x2 *>(q)[i];
-    for (int i = tid; i < M; i += nt) st.lse[i] = lse_enc[i];
-}
+    static constexpr int NT = 64 * WV, P = (32 * MT * DR / 4 + NT - 1) / NT;   // pieces of four columns a thread
+    float4 z[P];
+    u32x2 q[P];
+    float lse;
+    __device__ __forceinline__ void request(const bf16_t *qr, const float *zr, const float *lr, int M)
+    {
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const int at = min((int)threadIdx.x + i * NT, M * DR / 4 - 1);
+            z[i] = reinterpret_cast<const float4 *>(zr)[at];
+            q[i] = reinterpret_cast<const u32x2 *>(qr)[at];
+        }
+        lse = lr[min((int)threadIdx.x, M - 1)];
+    }
+    __device__ __forceinline__ void put(void *where, int M) const
+    {
+        const LatentStage<DR> st(where, M);
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const int at = (int)threadIdx.x + i * NT;
+            if (at >= M * DR / 4) continue;
+            reinterpret_cast<float4 *>(st.z)[at] = z[i];
+            reinterpret_cast<u32x2 *>(st.q)[at] = q[i];
+        }
+        if ((int)threadIdx.x < M) st.lse[threadIdx.x] = lse;
+    }
+};
 
 template <int DR, int MT, bool DQ, bool ONE, bool F, bool ZL = false>
 __device__ __forceinline__ void dkdv_body(
@@ -606,7 +627,7 @@ __device__ __forceinline__ void dkdv_body(
     }
     // ---- build the operand images ----
     {
-        // DQ: the latents' rows of q and z and their lse_enc were staged in the waves' part of the LDS (stage_latents), from where
+        // DQ: the latents' rows of q and z and their lse_enc were staged in the waves' part of the LDS (LatentPieces), from where
         // every image takes its own elements; dz, eps: the rows of this (b,h), in global memory or merged into LDS.
         const LatentStage<DR> st(img + MT * PER_TILE * 64, mend - m0);
         const bf16_t *qh_ = DQ ? st.q : q + (size_t)h * ts.sq + (size_t)m0 * DR;
@@ -621,61 +642,76 @@ __device__ __forceinline__ void dkdv_body(
         // all ones where a < b (as a value: the results of many compares side by side take the scalar registers that the token loop
         // needs, and every one spilled there costs it vector registers)
         auto below = [](int a, int b) { return (uint32_t)((a - b) >> 31); };
-        // an image a wave and pass: which one it is, is the same for all its lanes
+        // A wave makes the images of one kind for GT latent tiles at a time: which kind it is, is the same for all its lanes, and the
+        // tiles' reads wait together.  (All tiles together: kinds do not divide evenly over the waves, and at eight tiles 200 scalar
+        // registers spilled.  An image at a time, 2 x 8 heads, 7225 tokens, 100 latents, d = 16: 19.9 us the kernel, 18.2 so.)
+        constexpr int GT = MT < 2 ? 1 : 2, GROUPS = (MT + GT - 1) / GT;
 #pragma unroll 1
-        for (int im = wave; im < MT * PER_TILE; im += WV) {
-            const int t = im / PER_TILE, sid = im % PER_TILE;
-            const int m = 32 * t + l32, mc = min(m, mleft - 1);
-            const uint32_t real = below(m, mleft);
-            u32x4 w;
+        for (int u = wave; u < PER_TILE * GROUPS; u += WV) {
+            const int sid = u / GROUPS, t0 = u % GROUPS * GT;
+            u32x4 im[GT];
             if (sid == NA - 1) {
                 // correction operand: slots 0,1 = -lse_enc2 (hi + lo pair), slots 2,3 = 1, else zero
-                w[0] = lower ? split_pair<F>(-(leb[mc] * kLog2e)) & real : 0u;
-                w[1] = lower ? kOnePair<F> : 0u;
-                w[2] = 0u; w[3] = 0u;
                 // Slots 4-6 belong to the c product and slots 8,9 to the a product, whose operands are bf16
                 // whatever the storage type; the score products meet them with zeros in the token operand
                 // (and the a and c products meet slots 0-3 with zeros).  Finite 16-bit patterns of either type read as
                 // finite values of the other, so the foreign slots contribute exact zeros.
-                if constexpr (ONE) {   // slots 4,5 := 1 (they pick -w delta hi, lo; the latent's factor of the c chain is 1)
-                    w[2] = lower ? 0x3f803f80u & real : 0u;
-                }
-                if (!lower) {
-                    w[0] = split_bf16_pair(-eb[mc]) & real;                 // slots 8,9 := -eps (bf16: the a chain)
-                    if (!ONE) w[1] = 0x3f803f80u & real;                    // slots 10,11 := 1 (picks -delta, two exponentials)
+#pragma unroll
+                for (int t = 0; t < GT; ++t) {
+                    const int m = 32 * (t0 + t) + l32, mc = min(m, mleft - 1);
+                    const uint32_t real = below(m, mleft);
+                    u32x4 &w = im[t];
+                    w[0] = lower ? split_pair<F>(-(leb[mc] * kLog2e)) & real
+                                 : split_bf16_pair(-eb[mc]) & real;             // slots 8,9 := -eps (bf16: the a chain)
+                    w[1] = lower ? kOnePair<F> : ONE ? 0u : 0x3f803f80u & real;   // slots 10,11 := 1 (picks -delta, two exponentials)
+                    // one exponential: slots 4,5 := 1 (they pick -w delta hi, lo; the latent's factor of the c chain is 1)
+                    w[2] = ONE && lower ? 0x3f803f80u & real : 0u;
+                    w[3] = 0u;
                 }
             } else if (sid < NA) {
                 const int kind = sid / KS, ks = sid % KS;          // 0 q' hi, 1 q' lo, 2 dZ, 3 Z hi, 4 Z lo (DQ only)
                 const int d0 = (D / 2) * hh + 8 * ks;
-                float x[8];
-                if (kind <= 1) {
-                    const u32x4 raw = row8_bf16<DR>(qh_ + (size_t)mc * DR, PACK ? 0 : d0);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) { x[2 * i] = elem_lo<F>(raw[i]) * c2; x[2 * i + 1] = elem_hi<F>(raw[i]) * c2; }
-                } else if (kind == 2) {
-                    row8_f32<DR>(dzb + (size_t)mc * DR, d0, x);
-                } else {
-                    row8_f32<DR>(zb + (size_t)mc * DR, ZPACK ? 0 : d0, x);
-                }
                 const bool want_lo = kind == 1 || kind >= 4 || (!lower && ((PACK && kind == 0) || (ZPACK && kind == 3)));
+                const uint32_t take_lo = want_lo ? 0xffffffffu : 0u;
+                if (kind <= 1) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    HiLo p;
-                    if (kind <= 1) p = split_elems<F>(x[2 * i], x[2 * i + 1]);   // q' feeds the score products: storage type
-                    else p = split_elems<false>(x[2 * i], x[2 * i + 1]);
-                    w[i] = (want_lo ? p.lo : p.hi) & real;
-                    if constexpr (DR == 4 && !ZPACK) {   // slots 4-7 of the Z image := its lo part (dY repeated there)
-                        if (kind == 3 && i >= 2) {
-                            const HiLo l = split_elems<false>(x[2 * i - 4], x[2 * i - 3]);
-                            w[i] = lower ? l.lo & real : 0u;
+                    for (int t = 0; t < GT; ++t) {
+                        const int m = 32 * (t0 + t) + l32;
+                        const uint32_t real = below(m, mleft);
+                        const u32x4 raw = row8_bf16<DR>(qh_ + (size_t)min(m, mleft - 1) * DR, PACK ? 0 : d0);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {              // q' feeds the score products: storage type
+                            const HiLo p = split_elems<F>(elem_lo<F>(raw[i]) * c2, elem_hi<F>(raw[i]) * c2);
+                            im[t][i] = ((p.lo & take_lo) | (p.hi & ~take_lo)) & real;
                         }
                     }
-                }
-                if (PACK && !lower && kind == 2) w[0] = split_bf16_pair(-eb[mc]) & real;     // slots 8,9 := -eps
-                if (APACK && !lower && kind == 2) w[1] = 0x3f803f80u & real;                 // slots 10,11 := 1 (pick -w delta)
-                if (PACK && !ZPACK && !lower && kind == 3) {                         // slots 8,9,10 := 1, 1, 0 / 1, 1
-                    w[0] = 0x3f803f80u & real;
-                    if constexpr (ONE) w[1] = 0u;
+                } else {
+                    const float *src = kind == 2 ? dzb : zb;
+                    const int e0 = ZPACK && kind >= 3 ? 0 : d0;
+#pragma unroll
+                    for (int t = 0; t < GT; ++t) {
+                        const int m = 32 * (t0 + t) + l32, mc = min(m, mleft - 1);
+                        const uint32_t real = below(m, mleft);
+                        float x[8];
+                        row8_f32<DR>(src + (size_t)mc * DR, e0, x);
+                        u32x4 &w = im[t];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const HiLo p = split_elems<false>(x[2 * i], x[2 * i + 1]);
+                            w[i] = ((p.lo & take_lo) | (p.hi & ~take_lo)) & real;
+                            if constexpr (DR == 4 && !ZPACK) {   // slots 4-7 of the Z image := its lo part (dY repeated there)
+                                if (kind == 3 && i >= 2) w[i] = lower ? split_elems<false>(x[2 * i - 4], x[2 * i - 3]).lo & real : 0u;
+                            }
+                        }
+                        if (PACK && !lower && kind == 2) {
+                            w[0] = split_bf16_pair(-eb[mc]) & real;                    // slots 8,9 := -eps
+                            if constexpr (APACK) w[1] = 0x3f803f80u & real;            // slots 10,11 := 1 (pick -w delta)
+                        }
+                        if (PACK && !ZPACK && !lower && kind == 3) {                   // slots 8,9,10 := 1, 1, 0 / 1, 1
+                            w[0] = 0x3f803f80u & real;
+                            if constexpr (ONE) w[1] = 0u;
+                        }
+                    }
                 }
             } else {
                 const int rsid = sid - NA;                          // (which, hv, s2)
@@ -685,17 +721,22 @@ __device__ __forceinline__ void dkdv_body(
                 const uint32_t keep = (WIDE || l32 < 16) && dd < DR ? 0xffffffffu : 0u;
                 const int dc = dd & (DR - 1);
 #pragma unroll
-                for (int i = 0; i < 8; i += 2) {
-                    const int ma = 32 * t + perm_index(s2, hh, i), mb = ma + 1;
-                    const int ca = min(ma, mleft - 1) * DR + dc, cb = min(mb, mleft - 1) * DR + dc;
-                    uint32_t x;
-                    if (which == 0) x = cvt_pk_bf16(dzb[ca], dzb[cb]);
-                    else if constexpr (F) x = cvt_pk_bf16(elem_value<F>(qh_[ca]), elem_value<F>(qh_[cb]));
-                    else x = (uint32_t)qh_[ca] | ((uint32_t)qh_[cb] << 16);
-                    w[i / 2] = x & keep & ((below(ma, mleft) & 0xffffu) | (below(mb, mleft) << 16));
+                for (int t = 0; t < GT; ++t) {
+#pragma unroll
+                    for (int i = 0; i < 8; i += 2) {
+                        const int ma = 32 * (t0 + t) + perm_index(s2, hh, i), mb = ma + 1;
+                        const int ca = min(ma, mleft - 1) * DR + dc, cb = min(mb, mleft - 1) * DR + dc;
+                        uint32_t x;
+                        if (which == 0) x = cvt_pk_bf16(dzb[ca], dzb[cb]);
+                        else if constexpr (F) x = cvt_pk_bf16(elem_value<F>(qh_[ca]), elem_value<F>(qh_[cb]));
+                        else x = (uint32_t)qh_[ca] | ((uint32_t)qh_[cb] << 16);
+                        im[t][i / 2] = x & keep & ((below(ma, mleft) & 0xffffu) | (below(mb, mleft) << 16));
+                    }
                 }
             }
-            img[im * 64 + lane] = w;
+#pragma unroll
+            for (int t = 0; t < GT; ++t)
+                if (t0 + t < MT) img[((t0 + t) * PER_TILE + sid) * 64 + lane] = im[t];
         }
     }
     __syncthreads();
@@ -1092,14 +1133,18 @@ __global__ __launch_bounds__(64 * WV, 1) void bwd_dkdv_planned_kernel(FLARE_DKDV
     const GridPos gp = grid_pos_latents(ts, H, DR * 2);
     float *rows = reinterpret_cast<float *>(reinterpret_cast<char *>(img) + merge.lds);
     const float *dz_bh, *eps_bh;
+    LatentPieces<DR, DQ ? MT : 0> pieces;
     if constexpr (DQ) {
         const size_t row = (size_t)gp.y * Mtot + m0;
-        stage_latents<DR, MT>(img + MT * dkdv_images(DR, DQ, ZL) * 64, q + (size_t)(gp.y % H) * ts.sq + (size_t)m0 * DR, z + row * DR,
-                              lse_enc + row, mend - m0);
-        if (merge.parts == 0) __syncthreads();       // (merging has barriers of its own)
+        pieces.request(q + (size_t)(gp.y % H) * ts.sq + (size_t)m0 * DR, z + row * DR, lse_enc + row, mend - m0);
     }
+    auto put = [&]() {
+        if constexpr (DQ) pieces.put(img + MT * dkdv_images(DR, DQ, ZL) * 64, mend - m0);
+    };
     // (a dQ kernel of its own runs behind this one and reads what workgroup 0 writes)
-    if (merged_dz<DR>(merge, z, lse_enc, gp.y, Mtot, true, !DQ && gp.x == 0, rows, red, dz_bh, eps_bh))
+    const bool one = merged_dz<DR>(merge, z, lse_enc, gp.y, Mtot, true, !DQ && gp.x == 0, rows, red, dz_bh, eps_bh, put);
+    if (DQ && merge.parts == 0) __syncthreads();     // (merging has barriers of its own)
+    if (one)
         dkdv_body<DR, MT, DQ, true, F, ZL>(FLARE_DKDV_PASS);
     else
         dkdv_body<DR, MT, DQ, false, F, ZL>(FLARE_DKDV_PASS);
