@@ -123,15 +123,15 @@ int flare_workspace_bytes(const flare_shape *shape, size_t *fwd_bytes, size_t *b
 {
     const int rc = check_shape(shape);
     if (rc != FLARE_OK) return rc;
-    const ValuPlan p = valu_plan(*shape);
     if (fwd_bytes) {
-        *fwd_bytes = p.fwd_bytes;
         if (mfma_supported(*shape)) {   // the encode's partials are dead when the decode starts: one region
             *fwd_bytes = mfma_fwd_bytes(*shape);
             if (mfma_tok_run_bytes(*shape) > *fwd_bytes) *fwd_bytes = mfma_tok_run_bytes(*shape);
+        } else {
+            *fwd_bytes = valu_plan(*shape).fwd_bytes;
         }
     }
-    if (bwd_bytes) *bwd_bytes = p.bwd_bytes;
+    if (bwd_bytes) *bwd_bytes = valu_bwd_bytes(*shape);
     return FLARE_OK;
 }
 

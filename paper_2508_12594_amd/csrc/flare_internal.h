@@ -81,9 +81,9 @@ struct ValuPlan {
     Split enc;          // split used by the encode partials
     Split bwd;          // split used by the dZ and dQ partials
     size_t fwd_bytes;   // workspace for encode
-    size_t bwd_bytes;   // workspace for backward
 };
 ValuPlan valu_plan(const flare_shape &s);
+size_t valu_bwd_bytes(const flare_shape &s);   // workspace for backward
 
 // Carves the encode workspace for sp.chunks partial slots per (b,h); returns its size in bytes.
 // Any of the output pointers may be NULL (then ws is not touched).

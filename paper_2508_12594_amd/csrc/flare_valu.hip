@@ -1122,9 +1122,10 @@ ValuPlan valu_plan(const flare_shape &s)
     if (s.dtype == FLARE_F32) p.enc = mfma32_split(s);
     p.bwd = p.enc;
     p.fwd_bytes = valu_fwd_layout(s, p.enc, nullptr, nullptr, nullptr, nullptr);
-    p.bwd_bytes = bwd_layout(s, p, nullptr, nullptr);
     return p;
 }
+// (apart from the plan, which every forward call makes two or three times over: the slots of dZ and dQ take the counts of four kernels)
+size_t valu_bwd_bytes(const flare_shape &s) { return bwd_layout(s, valu_plan(s), nullptr, nullptr); }
 
 int valu_encode(const flare_shape &s, const void *q, const void *k, const void *v, float *z, float *lse_enc,
                 float scale, void *ws, hipStream_t stream)
