@@ -681,7 +681,7 @@ __device__ __forceinline__ void dkdv_body(
                         const u32x4 raw = row8_bf16<DR>(qh_ + (size_t)min(m, mleft - 1) * DR, PACK ? 0 : d0);
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {              // q' feeds the score products: storage type
-                            const HiLo p = split_elems<F>(elem_lo<F>(raw[i]) * c2, elem_hi<F>(raw[i]) * c2);
+                            const HiLo p = split_scaled<F>(raw[i], c2);
                             im[t][i] = ((p.lo & take_lo) | (p.hi & ~take_lo)) & real;
                         }
                     }
