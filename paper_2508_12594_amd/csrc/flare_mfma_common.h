@@ -377,13 +377,15 @@ __device__ __forceinline__ float pinned(float x)
     asm volatile("" : "+v"(x));
     return x;
 }
-// Two stored elements times c, as fp32 rounds the products, in hi and lo words of the storage type.  (Pinned: contracted with the
-// subtraction of its hi part, a product would leave the lo part of the unrounded one there, and the gradients would hang on what
-// the compiler makes of the code around: 4 x 8 heads, 16384 tokens, 64 latents, d = 16: they moved by 4e-5.)
+// Two stored elements times c, as fp32 rounds the products, in hi and lo words of the storage type.  (Not contracted: with the
+// subtraction of its hi part in one multiply-add, a product would leave the lo part of the unrounded one there, and the gradients
+// would hang on what the compiler makes of the code around: 4 x 8 heads, 16384 tokens, 64 latents, d = 16: they moved by 4e-5.)
 template <bool F>
 __device__ __forceinline__ HiLo split_scaled(uint32_t w, float c)
 {
-    return split_elems<F>(pinned(elem_lo<F>(w) * c), pinned(elem_hi<F>(w) * c));
+#pragma clang fp contract(off)
+    const float a = elem_lo<F>(w) * c, b = elem_hi<F>(w) * c;
+    return split_elems<F>(a, b);
 }
 
 // More than 256 latents per head are taken in chunks of at most 256: the latent-major kernels get one more grid
