@@ -145,6 +145,13 @@ __device__ __forceinline__ float dy_hi(uint32_t w)
     if constexpr (F) return __uint_as_float(rne_bf16(elem_hi<true>(w)) << 16);
     else return elem_hi<false>(w);
 }
+// Both of a word, as two bf16 of one
+template <bool F>
+__device__ __forceinline__ uint32_t dy_pair(uint32_t w)
+{
+    if constexpr (F) return cvt_pk_bf16(elem_lo<true>(w), elem_hi<true>(w));
+    else return w;
+}
 // 1.0 in the storage type, and twice in one word
 template <bool F> constexpr uint32_t kOne = F ? 0x3c00u : 0x3f80u;
 template <bool F> constexpr uint32_t kOnePair = F ? 0x3c003c00u : 0x3f803f80u;

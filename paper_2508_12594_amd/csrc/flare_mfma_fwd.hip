@@ -401,19 +401,21 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
             float part = 0.f;
 #pragma unroll
             for (int hv = 0; hv < HV; ++hv) {
-                const u32x2 g0 = gq[hv][0], g1 = gq[hv][1];
+                // (pairs converted together: each half by itself took the kernel of d = 32, 64 latents, fp16, from 162 to 170 registers
+                // and its third wave per SIMD, which the launch counts on)
+                const u32x2 g0{dy_pair<F>(gq[hv][0][0]), dy_pair<F>(gq[hv][0][1])}, g1{dy_pair<F>(gq[hv][1][0]), dy_pair<F>(gq[hv][1][1])};
                 if constexpr (DR <= 8) {   // rows 8 + j: the lo part of column j (zero unless z_lo), same lane
 #pragma unroll
                     for (int i = 0; i < 4; ++i) acc[hv][i] += acc[hv][4 + i];
                 }
-                part = fmaf(acc[hv][0] * inv, dy_lo<F>(g0[0]), part);
-                part = fmaf(acc[hv][1] * inv, dy_hi<F>(g0[0]), part);
-                part = fmaf(acc[hv][2] * inv, dy_lo<F>(g0[1]), part);
-                part = fmaf(acc[hv][3] * inv, dy_hi<F>(g0[1]), part);
-                part = fmaf(acc[hv][4] * inv, dy_lo<F>(g1[0]), part);
-                part = fmaf(acc[hv][5] * inv, dy_hi<F>(g1[0]), part);
-                part = fmaf(acc[hv][6] * inv, dy_lo<F>(g1[1]), part);
-                part = fmaf(acc[hv][7] * inv, dy_hi<F>(g1[1]), part);
+                part = fmaf(acc[hv][0] * inv, elem_lo<false>(g0[0]), part);
+                part = fmaf(acc[hv][1] * inv, elem_hi<false>(g0[0]), part);
+                part = fmaf(acc[hv][2] * inv, elem_lo<false>(g0[1]), part);
+                part = fmaf(acc[hv][3] * inv, elem_hi<false>(g0[1]), part);
+                part = fmaf(acc[hv][4] * inv, elem_lo<false>(g1[0]), part);
+                part = fmaf(acc[hv][5] * inv, elem_hi<false>(g1[0]), part);
+                part = fmaf(acc[hv][6] * inv, elem_lo<false>(g1[1]), part);
+                part = fmaf(acc[hv][7] * inv, elem_hi<false>(g1[1]), part);
             }
             part += __shfl_xor(part, 32);
             // the stabiliser that was actually subtracted

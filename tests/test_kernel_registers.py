@@ -60,3 +60,12 @@ def test_dkdv_registers_at_32_columns(kernels, latent_tiles):
     """With two exponentials every value spilled is written and read again in each token tile: 26 to 39 of them made the
     kernel take half as long again (a few that are read once a tile do not show)."""
     assert spilled(kernels, 32, latent_tiles) <= 4
+
+
+@pytest.mark.parametrize("latent_tiles,waves", [(1, 4), (2, 3)])
+def test_wide_head_decode_keeps_its_waves(kernels, latent_tiles, waves):
+    """The launch counts on so many workgroups of four waves on a CU (512 registers a lane and SIMD, given in eights)."""
+    pat = re.compile(r"decode_mfma_kernelILi32ELi%dELb1E" % latent_tiles)
+    counts = {n: k[".vgpr_count"] for n, k in kernels.items() if pat.search(n)}
+    assert len(counts) >= 6, "no such kernels in the library"      # (two storage types, merging or not, token statistics)
+    assert all(-(-c // 8) * 8 * waves <= 512 for c in counts.values()), counts
