@@ -60,7 +60,7 @@ __device__ __forceinline__ void merge_z_row(const MergeZ &g, int bh, int M, int 
     size_t s0[R];                                         // slot p of row r: s0[r] + p * M
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        s0[r] = (size_t)bh * g.parts * M + min(m0 + r * step, m1 - 1);
+        s0[r] = (size_t)bh * g.parts * M + (R == 1 ? m0 : min(m0 + r * step, m1 - 1));
         gm[r] = -INFINITY;
         l[r] = 0.f;
         o[r] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -101,7 +101,7 @@ __device__ __forceinline__ void merge_z_row(const MergeZ &g, int bh, int M, int 
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int m = m0 + r * step;
-        if (m >= m1) continue;
+        if (R > 1 && m >= m1) continue;
         const float inv = 1.f / l[r];
         const size_t idx = (size_t)bh * M + m;
         const float4 x = make_float4(o[r].x * inv, o[r].y * inv, o[r].z * inv, o[r].w * inv);

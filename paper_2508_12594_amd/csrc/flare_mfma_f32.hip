@@ -631,8 +631,12 @@ __global__ __launch_bounds__(512, 2) void latent_pass_f32_kernel(const LatentArg
 // ============================================================================================
 struct TokenArgs {
     const float *q, *k, *v, *dy, *z, *lse_enc, *lse_dec, *delta;
-    MergeZ mz;               // MODE 0
-    MergeDz mdz;             // MODE 2
+    // One or the other: with both, and the sizes that every kernel finds behind its arguments, they took a fifth line of 64 bytes, and
+    // forwards of a few hundred tokens 2 to 4 % more (4 heads, 300 tokens, 64 latents, d = 8: 9.25 -> 9.6 us; 9.3 like this).
+    union {
+        MergeZ mz;           // MODE 0
+        MergeDz mdz;         // MODE 2
+    };
     float *out0, *out1;      // y, lse_dec | lse_dec2, delta | dk, dv
     float *dq_part;          // MODE 2, DQ: slot x of (b,h) at [(b*h) * gridDim.x + x][M][d]
     TokStride ts;
@@ -1207,7 +1211,7 @@ int launch_token(const flare_shape &s, const TokenArgs &a, int kid, hipStream_t 
     const bool fits = MT <= CTMAX;
     A.CT = fits ? MT : CTMAX;
     size_t lds = (size_t)A.CT * L::TILE * 2;
-    const bool merge = fits && (MODE == 0 ? A.mz.parts : A.mdz.parts) != 0;
+    const bool merge = fits && (MODE == 0 ? A.mz.parts : MODE == 2 ? A.mdz.parts : 0) != 0;
     const size_t merged = merge ? (size_t)s.M * (s.d + 1) * 4 : 0;
     LaunchTimer t(kid, stream);
     if constexpr (MODE == 2 && DR <= 16) {

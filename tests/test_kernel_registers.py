@@ -69,3 +69,15 @@ def test_wide_head_decode_keeps_its_waves(kernels, latent_tiles, waves):
     counts = {n: k[".vgpr_count"] for n, k in kernels.items() if pat.search(n)}
     assert len(counts) >= 6, "no such kernels in the library"      # (two storage types, merging or not, token statistics)
     assert all(-(-c // 8) * 8 * waves <= 512 for c in counts.values()), counts
+
+
+def test_arguments_of_the_fp32_token_kernels_in_four_lines(kernels):
+    """Short forwards wait for every 64-byte line of arguments; what a kernel reads behind its own is the workgroup's size."""
+    ends = {}
+    for n, k in kernels.items():
+        if "token_pass_f32_kernel" in n:
+            used = [a for a in k[".args"] if not a[".value_kind"].startswith("hidden_") or "block_count" in a[".value_kind"] or
+                    "group_size" in a[".value_kind"]]
+            ends[n] = max(a[".offset"] + a[".size"] for a in used)
+    assert len(ends) >= 40, "no such kernels in the library"
+    assert max(ends.values()) <= 256, ends
