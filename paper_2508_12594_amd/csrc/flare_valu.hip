@@ -542,19 +542,24 @@ __global__ __launch_bounds__(256) void dz_merge_kernel(
     const MergeLane<D> at(blockIdx.x, M);
     const int bh = blockIdx.y;
     const size_t idx = (size_t)bh * M + at.m;
-    DzRow r;
-    r.a = sum_slots<D>(dz_part, bh, BH, 1, parts, M, at);
     // matrix-core path: which variant of the next kernels runs for this (b,h) (every workgroup works it out for
     // itself: the one-exponential variant wants dZ scaled, see bwd_one_exp_ok); one more workgroup records it
+    const bool record = plan != nullptr && blockIdx.x == gridDim.x - 1;
+    DzRow r{};
+    if (!record) {
+        if (threadIdx.x < 16) {                      // (with the slots: one memory latency)
+            r.z = *reinterpret_cast<const float4 *>(z + idx * D + 4 * at.j);
+            r.lse_enc = lse_enc[idx];
+        }
+        r.a = sum_slots<D>(dz_part, bh, BH, 1, parts, M, at);
+    }
     __shared__ float plan_red[64];
     const bool one_exp = plan != nullptr && bwd_one_exp_ok(ld_range, lse_enc, bh, parts, M, span, plan_red);
-    if (plan != nullptr && blockIdx.x == gridDim.x - 1) {
+    if (record) {
         if (threadIdx.x == 0) plan[bh] = one_exp ? 1 : 0;
         return;
     }
     if (threadIdx.x >= 16) return;
-    r.z = *reinterpret_cast<const float4 *>(z + idx * D + 4 * at.j);
-    r.lse_enc = lse_enc[idx];
     float e;
     const float4 a = finish_dz_row<D>(r, at.j, one_exp, round_bf16 != 0, e);
     if (!at.live) return;
