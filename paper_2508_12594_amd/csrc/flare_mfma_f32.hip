@@ -705,7 +705,8 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
         zr = merged;
     } else if constexpr (MERGE && MODE == 2) {
         __shared__ float red[64];
-        one_exp = merged_dz<DR>(A.mdz, A.z, A.lse_enc, bh, M, false, gp.x == 0, merged, red, dzr, epr, []() {});
+        // (one workgroup also writes the rows, for a dQ kernel behind this one)
+        one_exp = merged_dz<DR>(A.mdz, A.z, A.lse_enc, bh, M, false, DQ == 0 && gp.x == 0, merged, red, dzr, epr, []() {});
     } else if constexpr (MODE == 2) {
         dzr = A.mdz.dz + (size_t)bh * M * DR;
         epr = A.mdz.eps + (size_t)bh * M;
