@@ -451,19 +451,6 @@ constexpr int fused_wave_lds(int d, int mt) { return ds_tile_lds(d, mt) + 32 * k
 constexpr int dkdv_a_images(int dr, bool dq, bool zl) { return (dq && !pack_dim(dr) && zl ? 5 : 4) * (padded_dim(dr) / 16) + 1; }
 constexpr int dkdv_images(int dr, bool dq, bool zl) { return dkdv_a_images(dr, dq, zl) + 4; }
 
-// One wave tells another of its workgroup how far it is: what its lanes have written to LDS and read from it until here comes
-// before the counter, and what the waiting wave does there after it.
-__device__ __forceinline__ void lds_post(int *counter, int value, int lane)
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    if (lane == 0) __hip_atomic_store(counter, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void lds_wait(const int *counter, int value)
-{
-    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < value) {}
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 constexpr int WV = 8;           // waves per workgroup (one workgroup per CU)
 
 // The latents' rows of z and q and their lse_enc in LDS while the operand images are built from them: in the part that the

@@ -371,6 +371,20 @@ __device__ __forceinline__ bf16x8 with_slot0(bf16x8 x, uint32_t keep, uint32_t b
     return as_bf16x8(w);
 }
 __device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory"); }
+// One wave tells another of its workgroup how far it is: what its lanes have written to LDS and read from it until here comes
+// before the counter, and what the waiting wave does there after it.  (LDS only.  Where the waves of a pair read the same token rows
+// and one then writes dK, the other dV, perhaps over them, the reads come first all the same: each wave has put dS of its latent tiles
+// into LDS before it posts, and that is made of its rows of k, v and dy.)
+__device__ __forceinline__ void lds_post(int *counter, int value, int lane)
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    if (lane == 0) __hip_atomic_store(counter, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_wait(const int *counter, int value)
+{
+    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < value) {}
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 // The value as of this point of the program: an opaque statement takes and returns it, so that whatever produces
 // it (a load's arrival, a conversion) is complete here and not wherever its first real use ends up.
 __device__ __forceinline__ bf16x8 pinned(bf16x8 x)

@@ -661,17 +661,6 @@ constexpr int kDqTiles = 4;                      // latent tiles whose dQ a wave
 constexpr int kDsRow = 36, kKRow = 16;           // rows of the two tiles
 constexpr int kDqLds = 3 * 32 * kKRow;
 static_assert(kDqLds >= 32 * kDsRow && kDqLds * 2 >= 64 * 8 * 4, "one region holds either, and the exchange");
-// f(wave, counter): see lds_post, lds_wait in the 16-bit dK/dV kernel
-__device__ __forceinline__ void pair_post(int *counter, int value, int lane)
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    if (lane == 0) __hip_atomic_store(counter, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void pair_wait(const int *counter, int value)
-{
-    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < value) {}
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
@@ -801,7 +790,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
             }
             reg_ops<DR, false>(vx, hh, vp);
             reg_ops<DR, false>(gx, hh, gq);
-            if (PAIR) pair_wait(taken + (wave ^ 1), round);   // (the other wave has what was left here at the last tile's end)
+            if (PAIR) lds_wait(taken + (wave ^ 1), round);   // (the other wave has what was left here at the last tile's end)
             {   // the planes of K as rows of tokens (zero beyond the last one), read back transposed
                 const uint32_t live = tile * 32 + l32 < A.N ? 0xffffffffu : 0u;
                 auto put = [&](int at, bf16x8 p) {
@@ -896,8 +885,8 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
                 float *give = reinterpret_cast<float *>(tb) + lane;
 #pragma unroll
                 for (int i = 0; i < Geo::OUT; ++i) give[64 * i] = half ? dkr[i] : dvr[i];
-                pair_post(posted + wave, ++round, lane);
-                pair_wait(posted + (wave ^ 1), round);
+                lds_post(posted + wave, ++round, lane);
+                lds_wait(posted + (wave ^ 1), round);
                 const float *get = reinterpret_cast<const float *>(tb + (1 - 2 * half) * kDqLds) + lane;
 #pragma unroll
                 for (int i = 0; i < Geo::OUT; ++i) {
@@ -905,7 +894,7 @@ __global__ __launch_bounds__(64 * kTokenWaves, 2) void token_pass_f32_kernel(con
                     if (half) dvr[i] += o;
                     else dkr[i] += o;
                 }
-                pair_post(taken + wave, round, lane);
+                lds_post(taken + wave, round, lane);
             }
             if (tile * 32 + l32 < A.N) {
                 // the rows of Q carry c2 = scale log2 e; dK wants scale
