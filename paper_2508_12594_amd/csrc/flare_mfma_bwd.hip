@@ -1184,7 +1184,7 @@ int mfma_dq_partial(const flare_shape &s, const void *q, const void *k, const vo
 }
 
 // dK and dV of the backward.  One workgroup of 8 waves per (b,h) slice and block of token tiles;
-// the operand images need (4 or 6)*KS + 1 + 4*HV KiB of LDS per latent tile.
+// the operand images need dkdv_images KiB of LDS per latent tile.
 // Workgroups per (b,h) (= dQ partial slots per (b,h) when it also forms dQ)
 int mfma_dkdv_blocks(const flare_shape &s)
 {
@@ -1227,14 +1227,12 @@ int mfma_dkdv(const flare_shape &s, const void *q, const void *k, const void *v,
     const int mend = min(s.M, m0 + lat_eff(s.M));
     int MT = lat_eff(s.M) / 32;
     const int pd = padded_dim(s.d);
-    const int KS = pd / 16, HV = (pd == 32) ? 1 : pd / 16;   // d = 32: one 32-row block of row images
     // dQ from this kernel at d = 16 with fewer tokens than latents: one more image, the lo term of Z (see the kernel)
     const bool zlo = fuse && s.d == 16 && s.N < s.M;
     // The forms that only few-token shapes and measurements take, and d = 4, exist for 1, 2, 4 and 8 tiles (and 7 at d = 32).
     if (zlo || s.d == 4 || (!fuse && !(s.d == 32 && MT == 7))) MT = MT <= 2 ? MT : MT <= 4 ? 4 : 8;
     if (fuse && dkdv_pair(s.d, MT)) MT += MT % 2;   // halved between two waves
-    const int na = (zlo ? 5 : 4) * KS + 1;
-    size_t lds = (size_t)MT * (na + 4 * HV) * 1024 + (fuse ? WV * fused_wave_lds(pd, MT) * 2 : 0);
+    size_t lds = (size_t)MT * dkdv_images(s.d, fuse, zlo) * 1024 + (fuse ? WV * fused_wave_lds(pd, MT) * 2 : 0);
     MergeDz merge = merge_in;
     merge.lds = (unsigned)lds;
     if (merge.parts) lds += (size_t)s.M * (s.d + 1) * 4;
