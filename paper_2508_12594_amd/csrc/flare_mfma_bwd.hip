@@ -558,7 +558,7 @@ __device__ __forceinline__ void dkdv_body(
     constexpr bool PIPE = (D == 16);            // look one latent tile ahead where registers allow
     // d <= 8: the upper half of the padded contraction carries what otherwise needs products of its own.
     // Images: q' hi | lo in one (keys repeated in both lane halves), slots 8,9 of the dZ image = -eps
-    // (against ones in the V operand), slots 8-10 of the Z image = u, u, u lo or 1, 1 (against -delta in
+    // (against ones in the V operand), slots 8,9 of the Z image = 1, 1 (against -delta in
     // the dY operand).  The q' lo image and the a / c parts of the correction image are then unused.
     constexpr bool PACK = pack_dim(DR);
     // PACK with DQ: the upper half of the Z image carries the lo term of Z instead (dY rows repeated in both
@@ -639,7 +639,7 @@ __device__ __forceinline__ void dkdv_body(
             u32x4 im[GT];
             if (sid == NA - 1) {
                 // correction operand: slots 0,1 = -lse_enc2 (hi + lo pair), slots 2,3 = 1, else zero
-                // Slots 4-6 belong to the c product and slots 8,9 to the a product, whose operands are bf16
+                // Slots 4,5 and 8-11 belong to the a and c products, whose operands are bf16
                 // whatever the storage type; the score products meet them with zeros in the token operand
                 // (and the a and c products meet slots 0-3 with zeros).  Finite 16-bit patterns of either type read as
                 // finite values of the other, so the foreign slots contribute exact zeros.
@@ -694,10 +694,7 @@ __device__ __forceinline__ void dkdv_body(
                             w[0] = split_bf16_pair(-eb[mc]) & real;                    // slots 8,9 := -eps
                             if constexpr (APACK) w[1] = 0x3f803f80u & real;            // slots 10,11 := 1 (pick -w delta)
                         }
-                        if (PACK && !ZPACK && !lower && kind == 3) {                   // slots 8,9,10 := 1, 1, 0 / 1, 1
-                            w[0] = 0x3f803f80u & real;
-                            if constexpr (ONE) w[1] = 0u;
-                        }
+                        if (PACK && !ZPACK && !lower && kind == 3) w[0] = 0x3f803f80u & real;   // slots 8,9 := 1 (pick -delta)
                     }
                 }
             } else {
@@ -795,28 +792,28 @@ __device__ __forceinline__ void dkdv_body(
         const bf16x8 kt_a = ones_s, kt_b = as_bf16x8(wb);    // slots 0,1 := 1 picks -lse_enc2
         // Token side of the correction k-step(s).  Two exponentials: g_aug picks -delta for the c chain
         // (slots 10,11 against the image's ones) and ones_eps picks -eps for the a chain.  One exponential:
-        // dS = P (a + w c), and w[n] is this lane's scalar, so ONE product serves both chains: slots 8,9 = 1
-        // pick -eps and slots 4,5,6 = -w delta (hi, lo, hi) meet u (hi, hi, lo); the a chain starts from
-        // it and the c chain from zero.
+        // dS = P (a + w c), and w[n] is this lane's scalar, so one product carries both corrections: slots 8,9 = 1
+        // pick -eps and slots 4,5 = -w delta (hi, lo) meet ones; the a chain starts from it and the c chain from
+        // zero.  (d <= 8: the operands' free slots carry them, see PACK, ZPACK and APACK.)
         u32x4 wg;
         const uint32_t ds_ = split_bf16_pair(ONE ? -dl * wn : -dl);
         wg[0] = (ONE && !lower && !PACK) ? 0x3f803f80u : 0u;
         wg[1] = (!ONE && !lower) ? ds_ : 0u;                 // two exponentials: slots 10,11 := -delta (hi, lo)
-        wg[2] = (ONE && lower) ? ds_ : 0u;                   // one: slots 4,5,6 := -w delta hi, lo, hi
-        wg[3] = (ONE && lower) ? (ds_ & 0xffffu) : 0u;
+        wg[2] = (ONE && lower) ? ds_ : 0u;                   // one: slots 4,5 := -w delta (hi, lo)
+        wg[3] = 0u;
         const bf16x8 g_aug = as_bf16x8(wg);
         if constexpr (APACK) {   // slots 10,11 of the V operand := -w delta hi, lo
             u32x4 w = __builtin_bit_cast(u32x4, vt[0]);
             w[1] = lower ? w[1] : ds_;
             vt[0] = as_bf16x8(w);
         }
-        bf16x8 gc[KS];   // dY operand of the c product; PACK: slots 8,9,10 := -delta hi, lo, hi
+        bf16x8 gc[KS];   // dY operand of the c product; PACK without dQ: slots 8,9 := -delta (hi, lo)
 #pragma unroll
         for (int s = 0; s < KS; ++s) gc[s] = gt[s];
         if constexpr (PACK && !ZPACK) {
             u32x4 w = __builtin_bit_cast(u32x4, gt[0]);
             const uint32_t dp_ = split_bf16_pair(-dl);   // here c keeps its own correction: -delta unscaled
-            if (!lower) { w[0] = dp_; w[1] = ONE ? (dp_ & 0xffffu) : 0u; }
+            if (!lower) { w[0] = dp_; w[1] = 0u; }
             if (DR == 4 && lower) { w[2] = w[0]; w[3] = w[1]; }   // against the lo part of Z in slots 4-7
             gc[0] = as_bf16x8(w);
         }
