@@ -57,9 +57,9 @@ def test_latent_tiles(oracle, M, d, N):
 
 
 # fp32 storage, dQ out of the dK/dV kernel (d <= 16, at most 256 latents): one wave to a token tile up to 128 latents, two from
-# 129 on (an odd number of tiles between them too), fewer tiles of tokens than waves, more than one round of them
+# 129 on (an odd number of tiles between them too), fewer tiles of tokens than waves, one round of them and eight
 FUSED_F32 = [(1, 4, 40), (32, 16, 31), (33, 8, 65), (128, 16, 700), (129, 16, 700), (161, 8, 300), (255, 4, 257), (256, 8, 64),
-             (160, 16, 9000), (256, 16, 2049)]
+             (160, 16, 9000), (256, 16, 2049), (200, 8, 60000)]
 
 
 @pytest.mark.parametrize("M,d,N", FUSED_F32)

@@ -650,11 +650,14 @@ def test_stream_that_is_not_torchs():
         assert torch.equal(a, b)
 
 
-# dQ from a kernel of its own (fp32, d = 32, the fp32 kernels of many latents) behind dZ merged by a kernel and by dK/dV, with
-# latents in chunks; and dQ out of the dK/dV kernel
+# dQ from a kernel of its own (fp32 of d = 32 or more than 256 latents, chunks of latents at d = 32 over few tokens) behind dZ merged by a
+# kernel and by dK/dV; and dQ out of the dK/dV kernel, fp32 of up to 128 latents by one wave to a token tile, of 129 to 256 by two,
+# of which one writes dK and the other dV over rows that both read (one tile and several to a pair, an odd number of latent tiles)
 IN_PLACE = [(500, 48, 16, "f32"), (12, 48, 16, "f32"), (2049, 48, 16, "f32"), (20000, 300, 8, "f32"), (500, 48, 32, "bf16"),
             (40000, 64, 32, "f16"), (700, 300, 32, "bf16"), (1500, 256, 32, "bf16"), (300, 2100, 8, "bf16"),
-            (12, 48, 16, "f16"), (500, 48, 16, "bf16"), (700, 300, 16, "f16")]
+            (12, 48, 16, "f16"), (500, 48, 16, "bf16"), (700, 300, 16, "f16"),
+            (500, 48, 32, "f32"), (2049, 128, 32, "f32"), (700, 300, 16, "f32"), (2049, 200, 16, "f32"), (60000, 256, 16, "f32"),
+            (777, 150, 8, "f32"), (300, 129, 4, "f32")]
 
 
 @pytest.mark.parametrize("layout", ["bhnd", "bnhd"])
