@@ -89,17 +89,36 @@ def test_backward_workspace_holds_the_slots_that_are_written(lib, B, H, N, M, d,
 
 def test_backward_workspace_serves_the_variants(lib):
     """The size for a shape as it comes is enough for the same shape with a dQ kernel of its own."""
-    for d in (4, 8, 16, 32):
-        for M in (33, 129, 200, 256, 300, 450, 2048):
-            for N in (16, 300, 5000, 100000):
-                for B, H in ((1, 1), (1, 8), (3, 8), (14, 4), (64, 32)):
-                    size = []
-                    for variant in (0, binding.VARIANT_SEPARATE_DQ, binding.VARIANT_TWO_EXP):
-                        b = ctypes.c_size_t(0)
-                        shp = binding.FlareShape(B, H, N, M, d, binding.FLARE_BF16, 0, 0, 0, variant)
-                        assert lib.flare_workspace_bytes(ctypes.byref(shp), None, ctypes.byref(b)) == 0
-                        size.append(b.value)
-                    assert max(size) == size[0]
+    for dtype in (binding.FLARE_BF16, binding.FLARE_F32):
+        for d in (4, 8, 16, 32):
+            for M in (33, 128, 129, 200, 256, 257, 300, 450, 2048):
+                for N in (16, 300, 5000, 100000):
+                    for B, H in ((1, 1), (1, 8), (3, 8), (14, 4), (64, 32)):
+                        size = []
+                        for variant in (0, binding.VARIANT_SEPARATE_DQ, binding.VARIANT_TWO_EXP):
+                            b = ctypes.c_size_t(0)
+                            shp = binding.FlareShape(B, H, N, M, d, dtype, 0, 0, 0, variant)
+                            assert lib.flare_workspace_bytes(ctypes.byref(shp), None, ctypes.byref(b)) == 0
+                            size.append(b.value)
+                        assert max(size) == size[0]
+
+
+@pytest.mark.parametrize("B,H,N", [(64, 32, 1000000), (300, 100, 200000), (16, 16, 3000000), (1, 8, 100000), (1, 1, 16)])
+def test_fused_fp32_dq_is_summed_over_few_enough_tokens(lib, B, H, N):
+    """Where dQ comes out of the fp32 dK/dV kernel a wave adds up its token tiles one after the other: at most 8192 tokens, however many
+    (b,h) fill the chip with few workgroups each; and the workspace holds a slot for each of those workgroups."""
+    blocks_of = lib["_ZN5flare16mfma32_dq_blocksERK11flare_shape"]
+    tiles = -(-N // 32)
+    for d in (4, 8, 16):
+        for M in (33, 128, 129, 256):
+            shp, b = binding.FlareShape(B, H, N, M, d, binding.FLARE_F32), ctypes.c_size_t(0)
+            blocks = blocks_of(ctypes.byref(shp))
+            waves = 8 if M <= 128 else 4                    # token tiles a workgroup of eight waves works on at a time
+            assert blocks >= 1 and -(-tiles // (blocks * waves)) * 32 <= 8192, (M, d)
+            assert lib.flare_workspace_bytes(ctypes.byref(shp), None, ctypes.byref(b)) == 0
+            assert b.value >= 4 * B * H * (2 * N + (blocks + 1) * M * d), (M, d)
+    shp = binding.FlareShape(B, H, N, 200, 16, binding.FLARE_F32, 0, 0, 0, binding.VARIANT_SEPARATE_DQ)
+    assert blocks_of(ctypes.byref(shp)) == 0                # (a dQ kernel of its own)
 
 
 def test_workspace_bytes_do_not_depend_on_the_layout(lib):
