@@ -71,6 +71,17 @@ def test_wide_head_decode_keeps_its_waves(kernels, latent_tiles, waves):
     assert all(-(-c // 8) * 8 * waves <= 512 for c in counts.values()), counts
 
 
+@pytest.mark.parametrize("head", [4, 8, 16])
+@pytest.mark.parametrize("form", [1, 2])
+def test_fp32_kernel_that_forms_dq_too_spills_nothing(kernels, head, form):
+    """dQ of four latent tiles lies in registers beside everything else (253 of 256 at 16 columns), two waves to a SIMD; a value
+    spilled would be written and read again in every token tile."""
+    pat = re.compile(r"token_pass_f32_kernelILi%dELi2ELi1ELb[01]ELi%dE" % (head, form))
+    found = {n: (k[".vgpr_spill_count"], k[".vgpr_count"]) for n, k in kernels.items() if pat.search(n)}
+    assert len(found) == 2, "no such kernels in the library"         # (merging dZ or not)
+    assert all(spills == 0 and count <= 256 for spills, count in found.values()), found
+
+
 def test_arguments_of_the_fp32_token_kernels_in_four_lines(kernels):
     """Short forwards wait for every 64-byte line of arguments; what a kernel reads behind its own is the workgroup's size."""
     ends = {}
