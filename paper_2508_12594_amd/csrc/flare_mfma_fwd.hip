@@ -122,7 +122,17 @@ __global__ __launch_bounds__(256, MINB) void decode_mfma_kernel(
             merge_z_rows<DR, R>(merge, bh, Mtot, 0, Mtot, threadIdx.x, 256, put, gp.x == 0);   // (one also writes them)
         } else {
             const float4 *zb = reinterpret_cast<const float4 *>(z + ((size_t)bh * Mtot + m0) * DR);
-            for (int i = threadIdx.x; i < real * L; i += 256) put(i / L, i % L, zb[i]);
+            // (all requested before the first is used: one after the other, up to eight memory latencies, they took this launch 3 us.  8 heads,
+            // 99747 tokens, 2048 latents, d = 32, eight launches: 488 -> 461 us; 30000 tokens, 512 latents 56 -> 47.5)
+            constexpr int P = (32 * MT * L + 255) / 256;
+            float4 x[P];
+#pragma unroll
+            for (int i = 0; i < P; ++i) x[i] = zb[min((int)threadIdx.x + 256 * i, real * L - 1)];
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                const int at = threadIdx.x + 256 * i;
+                if (at < real * L) put(at / L, at % L, x[i]);
+            }
         }
         for (int i = real * (RS / 8) + (int)threadIdx.x; i < 32 * MT * (RS / 8); i += 256)   // padding latents
             *reinterpret_cast<u32x4 *>(z_rows + 8 * i) = u32x4{0u, 0u, 0u, 0u};
