@@ -19,6 +19,8 @@ TILES += [(M, d, 1100) for M in (257, 300, 420, 545) for d in (4, 8, 16, 32)] + 
 SLOTS = [("bf16", 16 * 1024, 64, 16), ("f16", 16 * 1024 + 1, 64, 16), ("bf16", 16 * 1024 + 1, 64, 8),
          ("bf16", 511, 64, 16), ("bf16", 512, 64, 16), ("f16", 1025, 60, 16), ("bf16", 5000, 33, 8), ("bf16", 140, 256, 32),
          ("bf16", 8 * 1024 + 1, 96, 32), ("f32", 2048, 48, 16), ("f32", 2049, 48, 16), ("f32", 1900, 40, 32)]
+# many slots, merged by workgroups of 64 / d latents: one, 3, 8, 9, 17 and 33 of them (neighbours go to one XCD)
+SLOTS += [("bf16", 20000, 2, 16), ("f16", 20000, 33, 4), ("bf16", 20000, 16, 32), ("f32", 20000, 65, 8), ("bf16", 40000, 65, 16), ("f32", 5000, 65, 32)]
 
 # fp32: remainders of a tile, the last number of latents whose planes fit in LDS together and the first that runs in
 # chunks (d = 8, 16, 32: 256; a token batch is then 1024 tokens in the decode, 512 in dK/dV), more than 2048 latents
