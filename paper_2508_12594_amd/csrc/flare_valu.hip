@@ -238,6 +238,7 @@ template <int D>
 struct MergeLane {
     int m, j, g;      // row, lane's four columns 4 j ..., slot group
     bool live;
+    MergeLane() = default;
     __device__ __forceinline__ MergeLane(int block, int M)
     {
         constexpr int L = D / 4;
@@ -500,62 +501,79 @@ __global__ __launch_bounds__(kLatentBlock) void dz_partial_kernel(
 // Fixed-order sum of many partial slots, shared by dZ and dQ (see encode_merge_kernel): the sums are in the first sixteen threads.
 // Slot s of output row (outer, m) lives at  part[((s / inner) * n_outer + outer) * inner + s % inner][m]:
 // dZ: outer = b*h, one group of `inner` slots;  dQ: outer = h, the slots of all batch items b (groups of `inner` partials
-// each), i.e. the batch sum in b order.  One barrier inside.
-template <int D>
-__device__ __forceinline__ float4 sum_slots(const float *__restrict__ part, int outer, int n_outer, int groups, int inner, int M,
-                                            const MergeLane<D> &at)
+// each), i.e. the batch sum in b order.  One barrier inside.  R: row blocks of the workgroup, summed side by side.
+template <int D, int R>
+__device__ __forceinline__ void sum_slots(const float *__restrict__ part, int outer, int n_outer, int groups, int inner, int M,
+                                          const MergeLane<D> (&at)[R], float4 (&acc)[R])
 {
-    __shared__ float4 waves[4][16];
+    __shared__ float4 waves[R][4][16];
     const int total = groups * inner, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = make_float4(0.f, 0.f, 0.f, 0.f);
     // four slots at a time: their loads are all issued before the first is added; the sums keep the slot order
     constexpr int kBatch = 4;
-    for (int s0 = at.g; s0 < total; s0 += kMergeGroups * kBatch) {
-        float4 t[kBatch];
+    for (int s0 = at[0].g; s0 < total; s0 += kMergeGroups * kBatch) {
+        float4 t[R][kBatch];
 #pragma unroll
         for (int b = 0; b < kBatch; ++b) {
             const int s = min(s0 + kMergeGroups * b, total - 1);
             const size_t slot = ((size_t)(s / inner) * n_outer + outer) * inner + (s % inner);
-            t[b] = *reinterpret_cast<const float4 *>(part + (slot * M + at.m) * D + 4 * at.j);
+#pragma unroll
+            for (int r = 0; r < R; ++r) t[r][b] = *reinterpret_cast<const float4 *>(part + (slot * M + at[r].m) * D + 4 * at[r].j);
         }
 #pragma unroll
         for (int b = 0; b < kBatch; ++b)
-            if (s0 + kMergeGroups * b < total) add4(acc, t[b]);
+            if (s0 + kMergeGroups * b < total)
+#pragma unroll
+                for (int r = 0; r < R; ++r) add4(acc[r], t[r][b]);
     }
 #pragma unroll
-    for (int off = 16; off < 64; off <<= 1) add4(acc, shfl_xor4(acc, off));
-    if (lane < 16) waves[wave][lane] = acc;
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int off = 16; off < 64; off <<= 1) add4(acc[r], shfl_xor4(acc[r], off));
+        if (lane < 16) waves[r][wave][lane] = acc[r];
+    }
     __syncthreads();
     if (threadIdx.x < 16) {
-        float4 a = waves[0][lane], b = waves[2][lane];
-        add4(a, waves[1][lane]);
-        add4(b, waves[3][lane]);
-        add4(a, b);
-        acc = a;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float4 a = waves[r][0][lane], b = waves[r][2][lane];
+            add4(a, waves[r][1][lane]);
+            add4(b, waves[r][3][lane]);
+            add4(a, b);
+            acc[r] = a;
+        }
     }
-    return acc;
 }
 
-// dZ[b*h][m] = sum of its partial slots; eps[m] = <dZ_m, Z_m>.
-template <int D>
+// dZ[b*h][m] = sum of its partial slots; eps[m] = <dZ_m, Z_m>.  R row blocks a workgroup.
+template <int D, int R>
 __global__ __launch_bounds__(256) void dz_merge_kernel(
     const float *__restrict__ dz_part, const float *__restrict__ z,
     float *__restrict__ dz, float *__restrict__ eps, int BH, int M, int parts, int round_bf16,
     const float *__restrict__ ld_range, const float *__restrict__ lse_enc, int *__restrict__ plan, float span)
 {
-    const MergeLane<D> at(blockIdx.x, M);
+    MergeLane<D> at[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) at[r] = MergeLane<D>(blockIdx.x * R + r, M);
     const int bh = blockIdx.y;
-    const size_t idx = (size_t)bh * M + at.m;
     // matrix-core path: which variant of the next kernels runs for this (b,h) (every workgroup works it out for
     // itself: the one-exponential variant wants dZ scaled, see bwd_one_exp_ok); one more workgroup records it
     const bool record = plan != nullptr && blockIdx.x == gridDim.x - 1;
-    DzRow r{};
+    DzRow row[R]{};
     if (!record) {
         if (threadIdx.x < 16) {                      // (with the slots: one memory latency)
-            r.z = *reinterpret_cast<const float4 *>(z + idx * D + 4 * at.j);
-            r.lse_enc = lse_enc[idx];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const size_t idx = (size_t)bh * M + at[r].m;
+                row[r].z = *reinterpret_cast<const float4 *>(z + idx * D + 4 * at[r].j);
+                row[r].lse_enc = lse_enc[idx];
+            }
         }
-        r.a = sum_slots<D>(dz_part, bh, BH, 1, parts, M, at);
+        float4 acc[R];
+        sum_slots<D, R>(dz_part, bh, BH, 1, parts, M, at, acc);
+#pragma unroll
+        for (int r = 0; r < R; ++r) row[r].a = acc[r];
     }
     __shared__ float plan_red[64];
     const bool one_exp = plan != nullptr && bwd_one_exp_ok(ld_range, lse_enc, bh, parts, M, span, plan_red);
@@ -564,11 +582,15 @@ __global__ __launch_bounds__(256) void dz_merge_kernel(
         return;
     }
     if (threadIdx.x >= 16) return;
-    float e;
-    const float4 a = finish_dz_row<D>(r, at.j, one_exp, round_bf16 != 0, e);
-    if (!at.live) return;
-    *reinterpret_cast<float4 *>(dz + idx * D + 4 * at.j) = a;
-    if (at.j == 0) eps[idx] = e;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const size_t idx = (size_t)bh * M + at[r].m;
+        float e;
+        const float4 a = finish_dz_row<D>(row[r], at[r].j, one_exp, round_bf16 != 0, e);
+        if (!at[r].live) continue;
+        *reinterpret_cast<float4 *>(dz + idx * D + 4 * at[r].j) = a;
+        if (at[r].j == 0) eps[idx] = e;
+    }
 }
 
 // Few slots: see encode_merge_few_kernel.
@@ -674,11 +696,13 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void dq_reduce_kernel(
     const float *__restrict__ dq_part, T *__restrict__ dq, int B, int H, int M, int parts, float scale)
 {
-    const MergeLane<D> at(blockIdx.x, M);
+    const MergeLane<D> at[1] = {MergeLane<D>(blockIdx.x, M)};
     const int h = blockIdx.y;
-    const float4 a = sum_slots<D>(dq_part, h, H, B, parts, M, at);
-    if (threadIdx.x < 16 && at.live)
-        store_four(dq + ((size_t)h * M + at.m) * D + 4 * at.j, make_float4(a.x * scale, a.y * scale, a.z * scale, a.w * scale));
+    float4 sum[1];
+    sum_slots<D, 1>(dq_part, h, H, B, parts, M, at, sum);
+    const float4 &a = sum[0];
+    if (threadIdx.x < 16 && at[0].live)
+        store_four(dq + ((size_t)h * M + at[0].m) * D + 4 * at[0].j, make_float4(a.x * scale, a.y * scale, a.z * scale, a.w * scale));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -973,10 +997,16 @@ int backward_impl(const flare_shape &s, const T *q, const T *k, const T *v, cons
             dz_merge_few_kernel<D><<<dim3((s.M + kFewRows - 1) / kFewRows + (planned ? 1 : 0), BH), 256, 0, stream>>>(
                 w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, planned ? w.plan : nullptr,
                 span);
-        else
-            dz_merge_kernel<D><<<dim3((s.M + merge_rows(D) - 1) / merge_rows(D) + (planned ? 1 : 0), BH), 256, 0, stream>>>(
-                w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc, planned ? w.plan : nullptr,
-                span);
+        else {
+            // Two row blocks a workgroup where one each makes 2048 workgroups or more: each tests all of lse_enc for the variant, 8 KB of
+            // L2 at 2048 latents beside 16 KB of slots.  (8 heads, 12000 tokens, 2000 latents, d = 16: 15.2 us by one, 11.7 by two, 12.8 by
+            // four; d = 32 26.2, 20.2, 21.8; but 512 latents, d = 16 7.4, 7.9, 8.6.)
+            const int blocks = (s.M + merge_rows(D) - 1) / merge_rows(D), two = (long long)blocks * BH >= 2048;
+            const dim3 grid((two ? (blocks + 1) / 2 : blocks) + (planned ? 1 : 0), BH);
+            auto kern = two ? dz_merge_kernel<D, 2> : dz_merge_kernel<D, 1>;
+            kern<<<grid, 256, 0, stream>>>(w.part, z, w.dz, w.eps, BH, s.M, dz_parts, mf ? 1 : 0, w.ld_range, lse_enc,
+                                           planned ? w.plan : nullptr, span);
+        }
     }
     if (check_launch() != FLARE_OK) return FLARE_ELAUNCH;
     int dq_parts = plan.bwd.chunks;

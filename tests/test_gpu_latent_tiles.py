@@ -33,6 +33,8 @@ HEADS = [("bf16", 3, 8, 5100, 72, 8), ("f16", 7, 4, 5300, 64, 16), ("bf16", 5, 4
          ("bf16", 17, 16, 1111, 33, 16), ("f32", 20, 16, 390, 40, 16)]
 # more than one round of workgroups: 9 x 16 in every kernel; fp32 chunks of at most 8192 tokens, more than fill the chip
 HEADS += [("bf16", 9, 16, 2600, 40, 16), ("f16", 9, 16, 1900, 130, 32), ("f32", 9, 16, 2100, 33, 16), ("f32", 2, 16, 132000, 33, 8)]
+# dZ merged by workgroups of two row blocks (2048 of one or more), the last with one
+HEADS += [("bf16", 1, 8, 9000, 1025, 16), ("f32", 1, 8, 5000, 513, 32)]
 
 
 def _check(oracle, dtype, H, N, M, d, layout, saved, B=1):
