@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("cfg,over", [(2, dict(B=2, N=3000)), (5, dict(N=2000)), (1, dict(N=700)),
-                                      (4, dict(N=2500, M=300))])
+                                      (1, dict(N=900, M=200, d=16)), (4, dict(N=2500, M=300))])
 def test_step_in_a_hip_graph(cfg, over):
     import torch
     print("[case] graph capture cfg%d %s" % (cfg, over), flush=True)

@@ -55,6 +55,12 @@ def test_dkdv_registers_at_16_columns(kernels, latent_tiles, most):
     assert spilled(kernels, 16, latent_tiles) <= most
 
 
+@pytest.mark.parametrize("head,latent_tiles,most", [(4, 1, 0), (4, 2, 0), (4, 4, 0), (4, 8, 5)] + [(8, t, 0) for t in range(1, 7)] +
+                         [(8, 7, 2), (8, 8, 9)])
+def test_dkdv_registers_at_4_and_8_columns(kernels, head, latent_tiles, most):
+    assert spilled(kernels, head, latent_tiles) <= most
+
+
 @pytest.mark.parametrize("latent_tiles", [1, 2, 3, 4, 6, 8])
 def test_dkdv_registers_at_32_columns(kernels, latent_tiles):
     """With two exponentials every value spilled is written and read again in each token tile: 26 to 39 of them made the
